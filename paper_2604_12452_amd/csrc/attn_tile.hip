@@ -1,0 +1,517 @@
+// Tiled attention kernel on the matrix cores for the shapes that have no kernel of their own: fp32, heads narrower or wider
+// than the two layer widths, any scale.  Prefill over the condensed context (section 4.3, Eq. 10; per-query partition of
+// appendix A.2) and, with dense = 1, plain causal attention (section 3, Eq. 5).
+//
+// What these shapes need is parallelism and reuse, not the last MFMA: one wavefront per query row, every key element a
+// scalar load of its own, took 128 us for 0.36 GFLOP in fp32 (L = 1024, 4 heads, 128 + 32) and 1.44 ms for 5.3 GFLOP in bf16
+// (L = 2500, 16 heads over 4 KV heads, 64 / 64).  This kernel takes 15.6 us (launch and memory latency: three tiles per wavefront)
+// and 32 us (vector ALU: softmax and the splitting of the probabilities).  Here
+//   * a workgroup owns 16 QB query rows of one condensed set, numbered (token, head of the set): the heads of a set see the
+//     same keys, so the rows of a workgroup span few tokens;
+//   * its wavefronts split the KEY tiles among them, each with a softmax (running maximum) of its own, and are merged through
+//     LDS at the end: small problems, where a row sees a few hundred entries, still fill the chip, and nothing in the loop
+//     waits for another wavefront;
+//   * a tile (16 NB entries) travels memory -> registers -> the wavefront's own LDS area one tile ahead of its use, as
+//     16-byte pieces; rows are an odd number of 16-byte pieces apart, which spreads the key reads (16 rows, one piece
+//     each) and the value reads (rows 4 apart) over all banks;
+//   * products are computed transposed as in the other kernels: S^T[key, row] = K Q^T and O^T[dv, row] += V^T P^T with 16x16
+//     MFMAs, a lane's accumulator registers being one row's logits and, as they are, the operand of the second product.
+//
+// Precision is that of fp32 arithmetic throughout.  fp32 data uses the fp32 matrix instructions.  16-bit data is exact as an
+// operand; the fp32 probabilities are not, so the second product takes them in parts that add up to them: bf16 three parts
+// of 8 bits (the whole 24-bit significand), fp16 two of 11 (scaled by 2^15, so that the smaller part stays a normal number).
+//
+// The matrix product multiplies entries a row does not see by a zero probability; an infinity or a NaN in such an entry
+// would reach the row.  So if any result of the workgroup is not finite its rows are redone one by one (attn_row.h), each
+// touching only the entries it sees.
+#include "attn_row.h"
+#include "mla_tile16.h"
+
+namespace lca {
+namespace {
+
+using attn_row::RowParams;
+using tile16::bf16x4;
+using tile16::bf16x8;
+using tile16::f16x4;
+using tile16::f16x8;
+using tile16::floatx4;
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+
+constexpr int MAX_WAVES = 4;
+constexpr int RSRC_WORD3 = 0x00020000;   // raw buffer of dwords, gfx9 layout
+constexpr size_t LDS_LIMIT = 64 * 1024;
+
+// Per element type: columns of one fragment chunk (a 16-byte piece per lane, four lanes deep), and the two products.
+template <typename T> struct Mma;
+template <typename E8, typename E4, typename E, int NPARTS> struct Mma16 {
+    static constexpr int EPC = 8, CHUNK = 32, PARTS = NPARTS;
+    // LDS row behind S^T row m of a block of 16, and the entry that accumulator register r of lane group q4 stands for: the
+    // transpose reads of the value operand take rows 4 apart
+    __device__ static int row_of_m(int m) { return 4 * (m & 3) + (m >> 2); }
+    __device__ static int entry(int r, int q4) { return 4 * r + q4; }
+    __device__ static floatx4 score(const uintx4 &k, const uintx4 &q, floatx4 c)
+    {
+        return tile16::mfma_16x16x32(__builtin_bit_cast(E8, k), __builtin_bit_cast(E8, q), c);
+    }
+    template <int NB> struct Parts { E4 v[NPARTS][NB]; };
+    template <int NB> struct Frag { E4 v[NB]; };
+    // `base`: the tile's first value row; V^T fragment of value columns 16 t .. 16 t + 15
+    template <int NB> __device__ static Frag<NB> value(const char *base, int rs, int t, int col, int q4)
+    {
+        typedef __attribute__((address_space(3))) E4 *lds_ptr;
+        Frag<NB> f;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            f.v[b] = tile16::lds_read_tr16((lds_ptr)(base + (16 * b + 4 * (col >> 2) + q4) * rs + 8 * (col & 3) + 32 * t));
+        return f;
+    }
+    template <int NB> __device__ static floatx4 accumulate(const Frag<NB> &v, const Parts<NB> &p, int part, floatx4 c)
+    {
+        if constexpr (NB == 2) {
+            return tile16::mfma_16x16x32(__builtin_shufflevector(v.v[0], v.v[1], 0, 1, 2, 3, 4, 5, 6, 7),
+                                         __builtin_shufflevector(p.v[part][0], p.v[part][1], 0, 1, 2, 3, 4, 5, 6, 7), c);
+        } else {
+            return tile16::mfma_16x16x16(v.v[0], p.v[part][0], c);
+        }
+    }
+};
+template <> struct Mma<uint16_t> : Mma16<bf16x8, bf16x4, __bf16, 3> {
+    static constexpr float REF_SHIFT = 0.f;
+    // p = its leading 8 bits + the next 8 + the last 8 (cut off, not rounded: a subtraction each and one byte
+    // permutation per pair)
+    template <int NB> __device__ static void split(const float (&p)[NB][4], Parts<NB> &o)
+    {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            unsigned x[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x[r] = __float_as_uint(p[b][r]);
+#pragma unroll
+            for (int i = 0; i < PARTS; ++i) {
+                typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+                o.v[i][b] = __builtin_bit_cast(bf16x4, uintx2{__builtin_amdgcn_perm(x[1], x[0], 0x07060302u), __builtin_amdgcn_perm(x[3], x[2], 0x07060302u)});
+                if (i + 1 < PARTS) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) x[r] = __float_as_uint(__uint_as_float(x[r]) - __uint_as_float(x[r] & 0xffff0000u));
+                }
+            }
+        }
+    }
+    __device__ static void store4(uint16_t *p, const floatx4 &v)
+    {
+        *reinterpret_cast<bf16x4 *>(p) = bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
+    }
+};
+template <> struct Mma<f16_t> : Mma16<f16x8, f16x4, _Float16, 2> {
+    static constexpr float REF_SHIFT = 15.f;       // probabilities are kept times 2^15 (the sum of a row alike, so it cancels)
+    // p = its leading 11 bits + the next 11, both rounded
+    template <int NB> __device__ static void split(const float (&p)[NB][4], Parts<NB> &o)
+    {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const _Float16 hi = (_Float16)p[b][r];
+                o.v[0][b][r] = hi;
+                o.v[1][b][r] = (_Float16)(p[b][r] - (float)hi);
+            }
+    }
+    __device__ static void store4(f16_t *p, const floatx4 &v)
+    {
+        *reinterpret_cast<f16x4 *>(p) = f16x4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+    }
+};
+template <> struct Mma<float> {
+    static constexpr int EPC = 4, CHUNK = 16, PARTS = 1;
+    static constexpr float REF_SHIFT = 0.f;
+    __device__ static int row_of_m(int m) { return m; }
+    __device__ static int entry(int r, int q4) { return 4 * q4 + r; }
+    __device__ static floatx4 score(const uintx4 &k, const uintx4 &q, floatx4 c)
+    {
+        const floatx4 a = __builtin_bit_cast(floatx4, k), b = __builtin_bit_cast(floatx4, q);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[i], c, 0, 0, 0);
+        return c;
+    }
+    template <int NB> struct Parts { float v[NB][4]; };
+    template <int NB> __device__ static void split(const float (&p)[NB][4], Parts<NB> &o)
+    {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o.v[b][r] = p[b][r];
+    }
+    template <int NB> struct Frag { float v[NB][4]; };
+    template <int NB> __device__ static Frag<NB> value(const char *base, int rs, int t, int col, int q4)
+    {
+        Frag<NB> f;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) f.v[b][r] = *reinterpret_cast<const float *>(base + (16 * b + 4 * q4 + r) * rs + 4 * (16 * t + col));
+        return f;
+    }
+    template <int NB> __device__ static floatx4 accumulate(const Frag<NB> &v, const Parts<NB> &p, int, floatx4 c)
+    {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) c = __builtin_amdgcn_mfma_f32_16x16x4f32(v.v[b][r], p.v[b][r], c, 0, 0, 0);
+        return c;
+    }
+    __device__ static void store4(float *p, const floatx4 &v) { *reinterpret_cast<floatx4 *>(p) = v; }
+};
+
+// Byte layout of one wavefront's LDS area, the same on both sides of the launch.
+template <typename T, int NDT, int NKC, int QB, int NB> struct Layout {
+    int rsk, rsv, v_off, sel_off, cp, nc;      // row strides, start of the value rows, of the selected part in a key row; 16-byte pieces per row
+    int stage, area;                           // bytes of a tile; of the area (the merge and the row-by-row path use it too)
+    __host__ __device__ Layout(int d_pool, int d_sel, int mla)
+    {
+        constexpr int ELT = (int)sizeof(T), MERGE = 16 * QB * (16 * NDT + 4) * 4;
+        cp = d_pool * ELT / 16;
+        nc = cp + d_sel * ELT / 16;
+        rsk = NKC * 64 + 16;                                    // an odd number of 16-byte pieces
+        rsv = mla ? rsk : (d_pool * ELT + 63) / 64 * 64 + 16;
+        v_off = mla ? 0 : 16 * NB * rsk;
+        sel_off = mla ? cp * 16 : 0;
+        stage = 16 * NB * (rsk + (mla ? 0 : rsv)) + NDT * 16 * ELT;      // (value reads of a partial last column block may pass the last row's end)
+        const int row = ((mla ? d_pool + d_sel : d_sel) + attn_row::WAVE) * 4;
+        area = stage > MERGE ? stage : MERGE;
+        area = area > row ? area : row;
+        area = (area + 63) / 64 * 64;
+    }
+};
+
+// Largest / sum over the four lanes (l, l ^ 16, l ^ 32, l ^ 48) that hold one query row, by swapping rows of sixteen lanes
+// between two copies (no LDS traffic).
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float row_max4(float x)
+{
+    const uintx2 a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const uintx2 b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float row_sum4(float x)
+{
+    x += __shfl_xor(x, 16, 64);
+    return x + __shfl_xor(x, 32, 64);
+}
+
+// NDT: value columns / 16, NKC: key columns / Mma::CHUNK (both upper bounds; what lies past the real widths is zero keys and
+// results nobody stores), QB: blocks of 16 query rows, NB: blocks of 16 entries per tile, NIT: 16-byte pieces of a
+// row / 16 (upper bound).
+template <typename T, int NDT, int NKC, int QB, int NB, int NIT>
+__global__ __launch_bounds__(64 * MAX_WAVES) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 && NDT <= 4 ? 3 : sizeof(T) == 2 && NDT <= 16 ? 2 : 1, 8)))
+void attn_tile_kernel(const RowParams<T> kp, int n_blocks)
+{
+    typedef Mma<T> M;
+    extern __shared__ __attribute__((aligned(64))) char smem[];
+    constexpr int TK = 16 * NB, ROWS = 16 * QB, MROW = 16 * NDT + 4;
+    const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, q4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_waves = blockDim.x >> 6;
+    const Layout<T, NDT, NKC, QB, NB> lay(kp.d_pool, kp.d_sel, kp.mla);
+    char *const area = smem + wave * lay.area;
+
+    // which rows: the latest (heaviest) first
+    const int hps = kp.H / kp.S, L = kp.L, g = kp.g;
+    const int blk = n_blocks - 1 - (int)(blockIdx.x % n_blocks), bs = blockIdx.x / n_blocks, s = bs % kp.S, b = bs / kp.S;
+    const int n_rows = L * hps, r0 = blk * ROWS, r_last = min(r0 + ROWS, n_rows) - 1;
+    auto visible = [&](int t) { return (kp.dense || t + 1 <= kp.w) ? 0 : (t + 1 - kp.w) / g; };
+    const int t_first = r0 / hps, t_last = r_last / hps;
+    const int mt_first = visible(t_first), n_rep = visible(t_last), raw0 = mt_first * g;
+    const int rep_tiles = (n_rep + TK - 1) / TK, n_tiles = rep_tiles + (t_last + 1 - raw0 + TK - 1) / TK;
+    const int d_qk = kp.mla ? kp.d_pool + kp.d_sel : kp.d_sel;
+    const float c = kp.scale * 1.4426950408889634f, bias2 = kp.rep_bias * 1.4426950408889634f;
+
+    int t_row[QB], mt_row[QB];
+    size_t q_row[QB];                    // row index of the query in Q, O and lse: (b L + t) H + h
+    bool live[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const int r = r0 + 16 * qb + col, rc = min(r, n_rows - 1), t = rc / hps;
+        live[qb] = r < n_rows;
+        t_row[qb] = t;
+        mt_row[qb] = visible(t);
+        q_row[qb] = ((size_t)b * L + t) * kp.H + s * hps + (rc - t * hps);
+    }
+
+    // the pieces of one tile in registers: lane = (row of four, piece of sixteen).  Loads go through buffer descriptors: the
+    // address of a load is a scalar plus an offset that the lane keeps, and rows past a segment's end read as zeros (hidden
+    // below).  With 64-bit addresses per load a third of the loop's issue time was integer multiplication.
+    const int sub = lane & 15, rr = lane >> 4, p = kp.mla ? 0 : s;
+    constexpr int ELT = (int)sizeof(T);
+    const int pool_bytes = kp.d_pool * ELT, sel_bytes = kp.d_sel * ELT;
+    const T *const rep_p = kp.pool_rep + ((size_t)b * kp.S + s) * kp.m * kp.d_pool, *const rep_s = kp.sel_rep + ((size_t)b * kp.S + s) * kp.m * kp.d_sel;
+    const T *const raw_p = kp.POOL + ((size_t)b * L * kp.P + p) * kp.d_pool, *const raw_s = kp.SEL + ((size_t)b * L * kp.P + p) * kp.d_sel;
+    uintx4 held[4 * NB][NIT];
+    auto load_tile = [&](int tile) {
+        const bool is_rep = tile < rep_tiles;
+        const unsigned e0 = is_rep ? tile * TK : raw0 + (tile - rep_tiles) * TK, step = is_rep ? 1 : kp.P, last = is_rep ? n_rep - 1 : t_last;
+        const unsigned ps = step * pool_bytes, ss = step * sel_bytes;           // bytes between rows of the segment
+        const __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc((void *)(is_rep ? rep_p : raw_p), (short)0, last * ps + pool_bytes, RSRC_WORD3);
+        const __amdgpu_buffer_rsrc_t srs = __builtin_amdgcn_make_buffer_rsrc((void *)(is_rep ? rep_s : raw_s), (short)0, last * ss + sel_bytes, RSRC_WORD3);
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            const int x = sub + 16 * it;
+            if (x < lay.cp) {
+                const int voff = rr * ps + x * 16;
+#pragma unroll
+                for (int i = 0; i < 4 * NB; ++i) held[i][it] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(prs, voff, (e0 + 4 * i) * ps, 0));
+                asm volatile("; pooled part");       // (keeps the two branches apart: merged into one load, the descriptor would be a per-lane choice)
+            } else if (x < lay.nc) {
+                const int voff = rr * ss + (x - lay.cp) * 16;
+#pragma unroll
+                for (int i = 0; i < 4 * NB; ++i) held[i][it] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(srs, voff, (e0 + 4 * i) * ss, 0));
+                asm volatile("; selected part");
+            }
+        }
+    };
+    auto store_tile = [&]() {
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            const int x = sub + 16 * it;
+            const bool is_pool = x < lay.cp;
+            char *const dst = area + (is_pool ? lay.v_off + x * 16 : lay.sel_off + (x - lay.cp) * 16);
+            const int rs = is_pool ? lay.rsv : lay.rsk;
+            if (x < lay.nc) {
+#pragma unroll
+                for (int i = 0; i < 4 * NB; ++i) *reinterpret_cast<uintx4 *>(dst + (4 * i + rr) * rs) = held[i][it];
+            }
+        }
+    };
+
+    if (wave < n_tiles) load_tile(wave);
+    // queries as fragments: lane (col = row, q4) holds columns CHUNK kc + EPC q4 .. + EPC - 1; zero past the width
+    uintx4 qf[QB][NKC];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+        for (int kc = 0; kc < NKC; ++kc) {
+            const int x = M::CHUNK * kc + M::EPC * q4;
+            qf[qb][kc] = x < d_qk ? *reinterpret_cast<const uintx4 *>(kp.Q + q_row[qb] * d_qk + x) : uintx4{0, 0, 0, 0};
+        }
+    // the key columns past the width stay zero for the whole kernel (tiles are written over the real columns only)
+    for (int x = lane * 16; x < lay.stage; x += 64 * 16) *reinterpret_cast<uintx4 *>(area + x) = uintx4{0, 0, 0, 0};
+
+    floatx4 acc[QB][NDT];
+    float m_run[QB], l_run[QB];          // running maximum of the row (base 2); this lane's share of its sum
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        m_run[qb] = -INFINITY;
+        l_run[qb] = 0.f;
+#pragma unroll
+        for (int t = 0; t < NDT; ++t) acc[qb][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+
+    const char *const key = area + M::row_of_m(col) * lay.rsk + 16 * q4;
+    for (int tile = wave; tile < n_tiles; tile += n_waves) {
+        store_tile();
+        if (tile + n_waves < n_tiles) load_tile(tile + n_waves);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+        const bool is_rep = tile < rep_tiles;
+        const int e0 = is_rep ? tile * TK : raw0 + (tile - rep_tiles) * TK;
+        floatx4 sc[NB][QB];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) sc[nb][qb] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kc = 0; kc < NKC; ++kc) {
+                const uintx4 kf = *reinterpret_cast<const uintx4 *>(key + 16 * nb * lay.rsk + 64 * kc);
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) sc[nb][qb] = M::score(kf, qf[qb][kc], sc[nb][qb]);
+            }
+        }
+        typename M::template Parts<NB> pb[QB];
+        // every row of the workgroup sees the whole tile (its first row the fewest representatives, its last the fewest raw tokens at the front)
+        const bool full = is_rep ? e0 + TK <= mt_first : e0 >= n_rep * g && e0 + TK <= t_first + 1;
+        const float bias = is_rep ? bias2 : 0.f;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            float lg[NB][4];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) lg[nb][r] = fmaf(sc[nb][qb][r], c, bias);
+            if (!full) {                 // entries [lo, hi) of the tile's kind are visible to this lane's row
+                const int lo = is_rep ? 0 : mt_row[qb] * g, hi = is_rep ? mt_row[qb] : t_row[qb] + 1;
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int e = e0 + 16 * nb + M::entry(r, q4);
+                        lg[nb][r] = e >= lo && e < hi ? lg[nb][r] : -INFINITY;
+                    }
+            }
+            float mx = lg[0][0];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int r = nb == 0; r < 4; ++r) mx = fmaxf(mx, lg[nb][r]);
+            const float m_new = fmaxf(m_run[qb], row_max4(mx));
+            if (__builtin_amdgcn_ballot_w64(m_new > m_run[qb]) != 0) {
+                const float corr = __builtin_amdgcn_exp2f(m_run[qb] - (m_new == -INFINITY ? 0.f : m_new));
+                l_run[qb] *= corr;
+#pragma unroll
+                for (int t = 0; t < NDT; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[qb][t][r] *= corr;
+                m_run[qb] = m_new;
+            }
+            const float ref = (m_run[qb] == -INFINITY ? 0.f : m_run[qb]) - M::REF_SHIFT;
+            float pv[NB][4];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    pv[nb][r] = __builtin_amdgcn_exp2f(lg[nb][r] - ref);
+                    l_run[qb] += pv[nb][r];
+                }
+            M::template split<NB>(pv, pb[qb]);
+        }
+        // O^T += V^T P^T, four value tiles at a time
+        const char *const vals = area + lay.v_off;
+#pragma unroll
+        for (int t0 = 0; t0 < NDT; t0 += 4) {
+            typename M::template Frag<NB> vf[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) vf[t] = M::template value<NB>(vals, lay.rsv, t0 + t, col, q4);
+#pragma unroll
+            for (int part = 0; part < M::PARTS; ++part)
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) acc[qb][t0 + t] = M::template accumulate<NB>(vf[t], pb[qb], part, acc[qb][t0 + t]);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // this tile's reads are done before the next one is written
+        __builtin_amdgcn_wave_barrier();
+    }
+
+    // merge the wavefronts: the upper half hands its results to the lower half until one is left
+    float l_tot[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) l_tot[qb] = row_sum4(l_run[qb]);
+    float *const ml = reinterpret_cast<float *>(smem + n_waves * lay.area);     // [wave][row] (maximum, sum)
+    for (int half = n_waves >> 1; half > 0; half >>= 1) {
+        __syncthreads();
+        if (wave >= half && wave < 2 * half) {
+            float *const o = reinterpret_cast<float *>(smem + (wave - half) * lay.area);
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                if (q4 == 0) {
+                    ml[((wave - half) * ROWS + 16 * qb + col) * 2] = m_run[qb];
+                    ml[((wave - half) * ROWS + 16 * qb + col) * 2 + 1] = l_tot[qb];
+                }
+#pragma unroll
+                for (int t = 0; t < NDT; ++t) *reinterpret_cast<floatx4 *>(o + (16 * qb + col) * MROW + 16 * t + 4 * q4) = acc[qb][t];
+            }
+        }
+        __syncthreads();
+        if (wave < half) {
+            const float *const o = reinterpret_cast<const float *>(smem + wave * lay.area);
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                const float mo = ml[(wave * ROWS + 16 * qb + col) * 2], lo = ml[(wave * ROWS + 16 * qb + col) * 2 + 1];
+                const float m_new = fmaxf(m_run[qb], mo), m_eff = m_new == -INFINITY ? 0.f : m_new;
+                const float ca = __builtin_amdgcn_exp2f(m_run[qb] - m_eff), cb = __builtin_amdgcn_exp2f(mo - m_eff);
+                l_tot[qb] = l_tot[qb] * ca + lo * cb;
+                m_run[qb] = m_new;
+#pragma unroll
+                for (int t = 0; t < NDT; ++t) {
+                    const floatx4 v = *reinterpret_cast<const floatx4 *>(o + (16 * qb + col) * MROW + 16 * t + 4 * q4);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[qb][t][r] = acc[qb][t][r] * ca + v[r] * cb;
+                }
+            }
+        }
+    }
+
+    bool bad = false;
+    if (wave == 0) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            const float inv = 1.f / l_tot[qb];
+            float chk = 0.f;
+#pragma unroll
+            for (int t = 0; t < NDT; ++t) {
+                const int x = 16 * t + 4 * q4;                 // this lane's four value columns
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[qb][t][r] *= inv;
+                if (live[qb] && x < kp.d_pool) {
+                    M::store4(kp.O + q_row[qb] * kp.d_pool + x, acc[qb][t]);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) chk = fmaf(acc[qb][t][r], 0.f, chk);      // zero, or NaN if a value is not finite
+                }
+            }
+            if (kp.lse != nullptr && live[qb] && q4 == 0) kp.lse[q_row[qb]] = (m_run[qb] - M::REF_SHIFT + log2f(l_tot[qb])) * 0.6931471805599453f;
+            bad |= live[qb] && !(chk == 0.f);
+        }
+    }
+    if (__syncthreads_or(bad)) {                               // rare: a row met an infinity or a NaN, perhaps one it does not see
+        float *const q_s = reinterpret_cast<float *>(area), *const p_s = q_s + d_qk;
+        for (int r = wave; r <= r_last - r0; r += n_waves) {
+            const int t = (r0 + r) / hps;
+            attn_row::attend_row<T, NDT / 4>(kp, ((long)b * L + t) * kp.H + s * hps + (r0 + r - t * hps), q_s, p_s, lane);
+        }
+    }
+}
+
+template <typename T, int NDT, int NKC, int QB, int NB, int NIT>
+hipError_t run(const AttnArgs &a, hipStream_t st)
+{
+    const Dims &d = a.d;
+    const Layout<T, NDT, NKC, QB, NB> lay(d.d_pool, d.d_sel, d.mode == LCA_MODE_MLA);
+    int waves = MAX_WAVES;
+    while (waves > 1 && (size_t)waves * lay.area + waves * 16 * QB * 8 > LDS_LIMIT) waves /= 2;
+    const long blocks = ((long)d.L * (d.H / d.S) + 16 * QB - 1) / (16 * QB);
+    attn_tile_kernel<T, NDT, NKC, QB, NB, NIT><<<(unsigned)(blocks * d.S * d.B), 64 * waves, (size_t)waves * lay.area + waves * 16 * QB * 8, st>>>(
+        attn_row::row_params<T>(a), (int)blocks);
+    return hipGetLastError();
+}
+
+// The smallest instantiation that holds the widths.  At up to 64 value columns two blocks of query rows per wavefront (half the
+// tile traffic and half the key and value reads per row) once that still leaves every CU four workgroups: 34 us against 41 us
+// with one block at L = 2500, 93 against 116 us at B = 2, L = 4000 (16 heads, 64 / 64).  At 128 columns the second block's
+// registers cost the second wavefront of a SIMD: 151 us against 146 us in fp32 at L = 4096, 8 heads, so one.
+template <typename T> bool fits(const Dims &d, int ndt, int nkc, int nit)
+{
+    // (rows travel as 32-bit byte offsets inside one sequence)
+    const int widest = d.d_pool > d.d_sel ? d.d_pool : d.d_sel;
+    if ((long long)(d.L + 64) * d.P * widest * (long long)sizeof(T) >= (1ll << 32)) return false;
+    return d.d_pool <= 16 * ndt && d.d_qk <= nkc * Mma<T>::CHUNK && (d.d_pool + d.d_sel) <= nit * 16 * Mma<T>::EPC;
+}
+template <typename T> hipError_t dispatch(const AttnArgs &a, hipStream_t st, bool &done)
+{
+    const Dims &d = a.d;
+    const long rows = (long)d.L * (d.H / d.S);
+    const bool wide = (rows + 31) / 32 * d.S * d.B >= 1024;
+    done = true;
+    if constexpr (sizeof(T) == 2) {
+        if (fits<T>(d, 4, 2, 1)) return wide ? run<T, 4, 2, 2, 2, 1>(a, st) : run<T, 4, 2, 1, 2, 1>(a, st);
+        if (fits<T>(d, 8, 4, 2)) return run<T, 8, 4, 1, 2, 2>(a, st);
+        if (fits<T>(d, 16, 10, 3)) return run<T, 16, 10, 1, 1, 3>(a, st);
+        if (fits<T>(d, 32, 18, 5)) return run<T, 32, 18, 1, 1, 5>(a, st);
+    } else {
+        if (fits<T>(d, 4, 4, 2)) return wide ? run<T, 4, 4, 2, 1, 2>(a, st) : run<T, 4, 4, 1, 1, 2>(a, st);
+        if (fits<T>(d, 8, 10, 4)) return run<T, 8, 10, 1, 1, 4>(a, st);
+        if (fits<T>(d, 16, 18, 5)) return run<T, 16, 18, 1, 1, 5>(a, st);
+        if (fits<T>(d, 32, 36, 9)) return run<T, 32, 36, 1, 1, 9>(a, st);
+    }
+    done = false;
+    return hipSuccess;
+}
+
+}  // namespace
+
+hipError_t launch_attn_tile(const AttnArgs &a, hipStream_t st, bool &done)
+{
+    if (a.d.dtype == LCA_BF16) return dispatch<uint16_t>(a, st, done);
+    if (a.d.dtype == LCA_F16) return dispatch<f16_t>(a, st, done);
+    return dispatch<float>(a, st, done);
+}
+
+}  // namespace lca

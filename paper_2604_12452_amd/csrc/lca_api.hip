@@ -103,12 +103,13 @@ lca_status hip_status(hipError_t e, const char *what)
 #define LCA_LAUNCH(call, what) ((void)hipGetLastError(), hip_status((call), (what)))
 
 // The two matrix-core kernels take their widths in a 16-bit type with a positive scale (their fixed-reference softmax
-// orders logits by the raw products); every other descriptor, a zero or negative scale included, runs the general kernel.
 lca_status run_attn(const lca::AttnArgs &a, hipStream_t st, const char *what)
 {
     if (lca::attn_mla_supported(a.d)) return LCA_LAUNCH(lca::launch_attn_mla(a, st), what);
     if (lca::attn_gqa64_supported(a.d)) return LCA_LAUNCH(lca::launch_attn_gqa64(a, st), what);
-    return LCA_LAUNCH(lca::launch_attn_simple(a, st), what);
+    bool done = false;
+    const lca_status status = LCA_LAUNCH(lca::launch_attn_tile(a, st, done), what);
+    return done ? status : LCA_LAUNCH(lca::launch_attn_simple(a, st), what);
 }
 
 // ---- lca_condense_noalloc: the summary query lives in a device array of the library's own ----
