@@ -5,7 +5,7 @@
 //                          per-lane partial dots + a reduce-scatter butterfly, online softmax over
 //                          sub-blocks of <= 8 rows, pooling in-lane, anchor by (score, index) max.
 //                          HBM-bound: every C^KV / K^R byte is read once, as 16-byte coalesced loads.
-//   condense_generic_kernel  any sizes, scalar loads; fallback for shapes without an instantiation.
+//   condense_any_kernel    any sizes and reduce strategies.
 //
 // gfx950 only (wave64).
 #include "lca_internal.h"
@@ -82,39 +82,41 @@ template <> struct Elt<float> {
 
 // ---------------------------------------------------------------------------------------------
 // Summary query: qbar[b,s,x] = mean over t in [L-n_q, L), h in set s of Q[b,t,h,x].
-// One workgroup of 16 wavefronts per (b, s, 64 chunks of 16 bytes): wavefront v takes the (t, h) pairs
-// v, v+16, v+32, ... (row addresses are wave-uniform, kept in scalar registers and stepped without
-// divisions), each lane keeps up to 16 independent 16-byte loads in flight -- the 256 pairs of 16 queries x
-// 16 heads are one round trip to memory --, and the partial sums are merged in a fixed order through LDS
-// (deterministic), one output value per thread.
+// One workgroup of 16 wavefronts per (b, s, 16 chunks of 16 bytes): a load covers 256 bytes of four (t, h) rows, so the 64
+// row slots of the workgroup take the 256 rows of 16 queries x 16 heads in four loads per lane, all in flight at once; the
+// partial sums are merged in a fixed order (deterministic), the four rows of a wavefront by exchanges, the wavefronts through
+// LDS.  Bound by the memory round trip: the lca_condense call of 29 groups at 512 + 64 took
+// 11.2 us with 64 chunks per workgroup and one row per load, and takes 8.4 us.
 // ---------------------------------------------------------------------------------------------
 constexpr int SQ_WAVES = 16;
-constexpr int SQ_DEPTH = 16;
+constexpr int SQ_DEPTH = 8;
+constexpr int SQ_CHUNKS = 16;
+constexpr int SQ_SLOTS = SQ_WAVES * (WAVE / SQ_CHUNKS);
 template <typename T>
 __global__ __launch_bounds__(SQ_WAVES *WAVE) void summary_query_kernel(const T *__restrict__ Q, float *__restrict__ qbar, int L, int H, int S,
                                                                        int d_qk, int n_q)
 {
     constexpr int EPC = Elt<T>::EPC;
-    __shared__ float part[SQ_WAVES][WAVE][EPC + 1];
+    __shared__ float part[SQ_WAVES][SQ_CHUNKS][EPC + 1];
     const int n_chunks = d_qk / EPC;
-    const int xblocks = (n_chunks + WAVE - 1) / WAVE;
+    const int xblocks = (n_chunks + SQ_CHUNKS - 1) / SQ_CHUNKS;
     const int bs = blockIdx.x / xblocks, xb = blockIdx.x % xblocks;
     const int b = bs / S, s = bs % S, hps = H / S;
-    const int lane = threadIdx.x & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    const int chunk = xb * WAVE + lane;
+    const int sub = threadIdx.x % SQ_CHUNKS, slot = threadIdx.x / SQ_CHUNKS, wave = threadIdx.x / WAVE;
+    const int chunk = xb * SQ_CHUNKS + sub;
     const int n = n_q * hps;                       // (t, h) pairs, pair u -> t = L - n_q + u / hps, h = s*hps + u % hps
     float acc[EPC];
 #pragma unroll
     for (int e = 0; e < EPC; ++e) acc[e] = 0.f;
     if (chunk < n_chunks) {
-        const int step_t = SQ_WAVES / hps, step_h = SQ_WAVES % hps;
-        int ut = wave / hps, uh = wave % hps;       // pair u = wave + 16 j  ->  (u / hps, u % hps), stepped with carry
+        const int step_t = SQ_SLOTS / hps, step_h = SQ_SLOTS % hps;
+        int ut = slot / hps, uh = slot % hps;       // pair u = slot + 64 j  ->  (u / hps, u % hps), stepped with carry
         const T *const base = Q + ((size_t)b * L + (L - n_q)) * H * d_qk + (size_t)s * hps * d_qk + chunk * EPC;
-        for (int u0 = wave; u0 < n; u0 += SQ_WAVES * SQ_DEPTH) {
+        for (int u0 = slot; u0 < n; u0 += SQ_SLOTS * SQ_DEPTH) {
             uint4 v[SQ_DEPTH];
 #pragma unroll
             for (int i = 0; i < SQ_DEPTH; ++i) {
-                const int u = u0 + i * SQ_WAVES;
+                const int u = u0 + i * SQ_SLOTS;
                 v[i] = u < n ? *reinterpret_cast<const uint4 *>(base + ((size_t)ut * H + uh) * d_qk) : make_uint4(0, 0, 0, 0);
                 ut += step_t; uh += step_h;
                 if (uh >= hps) { uh -= hps; ++ut; }
@@ -129,11 +131,17 @@ __global__ __launch_bounds__(SQ_WAVES *WAVE) void summary_query_kernel(const T *
         }
     }
 #pragma unroll
-    for (int e = 0; e < EPC; ++e) part[wave][lane][e] = acc[e];
+    for (int mask = SQ_CHUNKS; mask < WAVE; mask <<= 1)
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) acc[e] += __shfl_xor(acc[e], mask, WAVE);
+    if ((threadIdx.x & (WAVE - 1)) < SQ_CHUNKS) {
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) part[wave][sub][e] = acc[e];
+    }
     __syncthreads();
     // thread x sums the 16 partial values of component x % EPC of chunk x / EPC (wavefront order: the same sum on every run)
-    const int ol = threadIdx.x / EPC, oe = threadIdx.x % EPC, ochunk = xb * WAVE + ol;
-    if (ol < WAVE && ochunk < n_chunks) {
+    const int ol = threadIdx.x / EPC, oe = threadIdx.x % EPC, ochunk = xb * SQ_CHUNKS + ol;
+    if (ol < SQ_CHUNKS && ochunk < n_chunks) {
         float t = 0.f;
 #pragma unroll
         for (int wv = 0; wv < SQ_WAVES; ++wv) t += part[wv][ol][oe];
@@ -338,108 +346,238 @@ void condense_reg_kernel(const T *__restrict__ POOL, const T *__restrict__ SEL, 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Generic condensation: one wave per (b, s, j), run-time sizes, g <= 64; any reduce strategy for either
-// component (the ablation grid of section 5.4, Table 5).
+// Condensation at any widths (16-byte multiples, up to 1024 columns), any group size up to 64, any reduce strategy for either
+// component (the ablation grid of section 5.4, Table 5): one wavefront per (sequence, set, group).
+//
+// A component's rows are read as 16-byte pieces, `lpr` lanes per row (the power of two that holds the row's pieces) and
+// 64 / lpr rows per load; what a wavefront can hold in registers (HELD) is requested at once and used for scores, norms and
+// pooling alike, the rest is read again when its turn comes (from the caches).  Bound by the latency of that round trip
+// at small sizes and by memory at large ones.  The call at B = 1, L = 2500, four KV heads, 64 / 64: 18.0 -> 9.7 us; at L = 16384,
+// 512 + 64, g = 24: 111 -> 33 us (scalar loads and a reduction per row before).  With the summary query computed inside by every
+// workgroup, one launch instead of two, the first took 8.2 us, but fp32 128 + 32 took longer (8.4 against 8.2 us) and 512 + 64
+// nearly twice as long; not kept.
 // ---------------------------------------------------------------------------------------------
-// Lane r holds v_r (r < g); returns, in every lane, the row with the largest v (lowest row on ties).
-__device__ __forceinline__ int wave_argmax(float v, int lane, float *vmax_out)
+// Lane r holds v_r (r < g <= 2 top, top a power of two); returns, in every lane, the row with the largest v (lowest row on ties).
+__device__ __forceinline__ int wave_argmax(float v, int lane, int top, float *vmax_out)
 {
     float bmax = v;
     int brow = lane;
-    for (int mask = 32; mask >= 1; mask >>= 1) {
+    for (int mask = top; mask >= 1; mask >>= 1) {
         const float os = __shfl_xor(bmax, mask, WAVE);
         const int orow = __shfl_xor(brow, mask, WAVE);
         if (os > bmax || (os == bmax && orow < brow)) { bmax = os; brow = orow; }
     }
-    if (vmax_out) *vmax_out = bmax;
-    return brow;
+    if (vmax_out) *vmax_out = readlane_f(bmax, 0);
+    return __builtin_amdgcn_readfirstlane(brow);
 }
 
-// One component of the representative: rows base + (j*g + r)*row_stride, r < g, `width` wide, into out.
-//   WEIGHTED / MEAN: sum of w_r x_r with lane r holding w_r;  MAXSEL / MAXPOOL: row `pick`, copied bit for bit.
-template <typename T>
-__device__ __forceinline__ void reduce_component(int strategy, const T *base, size_t row_stride, int j, int g, int width, float w_mine, int pick,
-                                                 T *out, int lane)
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+template <typename T> __device__ __forceinline__ void unpack4(const uintx4 &c, float *f) { Elt<T>::unpack(make_uint4(c[0], c[1], c[2], c[3]), f); }
+template <typename T> __device__ __forceinline__ uintx4 pack4(const float *f)
 {
-    if (strategy == LCA_REDUCE_MAXSEL || strategy == LCA_REDUCE_MAXPOOL) {
-        const T *src = base + (size_t)(j * g + pick) * row_stride;
-        for (int x = lane; x < width; x += WAVE) out[x] = src[x];
-        return;
+    const uint4 u = Elt<T>::pack(f);
+    return uintx4{u.x, u.y, u.z, u.w};
+}
+
+// The rows of one component of a group, spread over a wavefront.
+template <typename T, int N> struct Rows {
+    const T *base;           // row 0 of the group
+    size_t stride;           // elements between rows
+    int chunks, g;           // 16-byte pieces per row, rows
+    int shift;               // log2 of the lanes per row
+    int row0, c0;            // this lane's first row and piece
+    bool held_all;           // one piece per lane and row, all of them in `held`
+    uintx4 held[N];
+
+    __device__ __forceinline__ void init(const T *b, size_t st, int ch, int gg, int lane)
+    {
+        base = b; stride = st; chunks = ch; g = gg;
+        shift = ch <= 1 ? 0 : min(6, 32 - __builtin_clz(ch - 1));
+        row0 = lane >> shift; c0 = lane & ((1 << shift) - 1);
+        held_all = ch <= WAVE && ((gg + (WAVE >> shift) - 1) >> (6 - shift)) <= N;
     }
-    for (int x0 = 0; x0 < width; x0 += WAVE) {      // every lane takes part in the broadcasts
-        const int x = x0 + lane;
-        float acc = 0.f;
-        for (int r = 0; r < g; ++r) {
-            const float wr = __shfl(w_mine, r, WAVE);
-            if (x < width) acc = fmaf(wr, Elt<T>::ld(base + (size_t)(j * g + r) * row_stride + x), acc);
+    __device__ __forceinline__ int rows_per_load() const { return WAVE >> shift; }
+    __device__ __forceinline__ uintx4 fetch(int row, int c) const
+    {
+        return row < g && c < chunks ? *reinterpret_cast<const uintx4 *>(base + row * stride + c * Elt<T>::EPC) : uintx4{0, 0, 0, 0};
+    }
+    __device__ __forceinline__ void request()
+    {
+        if (!held_all) return;
+#pragma unroll
+        for (int i = 0; i < N; ++i) held[i] = i * rows_per_load() < g ? fetch(row0 + i * rows_per_load(), c0) : uintx4{0, 0, 0, 0};
+    }
+    // out[row] = per-row sums over the columns of term(element values, first column), plus `add`[row] if there is one
+    template <class F> __device__ __forceinline__ void row_sums(F term, float *out, const float *add) const
+    {
+        float f[Elt<T>::EPC];
+        if (held_all) {                          // (the exchanges of four loads' rows overlap)
+            static_assert(N % 4 == 0, "batches of four");
+#pragma unroll
+            for (int i0 = 0; i0 < N; i0 += 4) {
+                if (i0 * rows_per_load() >= g) break;
+                float a[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    unpack4<T>(held[i0 + i], f);
+                    a[i] = c0 < chunks ? term(f, c0 * Elt<T>::EPC) : 0.f;
+                }
+#pragma unroll 1
+                for (int mask = (1 << shift) >> 1; mask >= 1; mask >>= 1)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) a[i] += __shfl_xor(a[i], mask, WAVE);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int row = row0 + (i0 + i) * rows_per_load();
+                    if (c0 == 0 && row < g) out[row] = add != nullptr ? add[row] + a[i] : a[i];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            return;
         }
-        if (x < width) Elt<T>::st(out + x, acc);
-    }
-}
-
-// Lane r gets the squared Euclidean norm of row r of the group (for MAXPOOL).
-template <typename T>
-__device__ __forceinline__ float row_norms(const T *base, size_t row_stride, int j, int g, int width, int lane)
-{
-    float mine = -INFINITY;
-    for (int r = 0; r < g; ++r) {
-        float a = 0.f;
-        for (int x = lane; x < width; x += WAVE) {
-            const float v = Elt<T>::ld(base + (size_t)(j * g + r) * row_stride + x);
-            a = fmaf(v, v, a);
+        for (int r = 0; r < g; r += rows_per_load()) {
+            const int row = r + row0;
+            float a = 0.f;
+            for (int c = c0; c < chunks; c += WAVE) {
+                unpack4<T>(fetch(row, c), f);
+                a += term(f, c * Elt<T>::EPC);
+            }
+            for (int mask = (1 << shift) >> 1; mask >= 1; mask >>= 1) a += __shfl_xor(a, mask, WAVE);
+            if (c0 == 0 && row < g) out[row] = add != nullptr ? add[row] + a : a;
         }
-        for (int mask = 32; mask >= 1; mask >>= 1) a += __shfl_xor(a, mask, WAVE);
-        if (lane == r) mine = a;
     }
-    return mine;
-}
+    // out = sum of weight[row] * row
+    __device__ __forceinline__ void weighted_sum(const float *weight, T *out) const
+    {
+        constexpr int EPC = Elt<T>::EPC;
+        auto finish = [&](float (&acc)[EPC], int c) {
+#pragma unroll 1
+            for (int mask = 1 << shift; mask < WAVE; mask <<= 1)
+#pragma unroll
+                for (int e = 0; e < EPC; ++e) acc[e] += __shfl_xor(acc[e], mask, WAVE);
+            if (row0 == 0 && c < chunks) *reinterpret_cast<uintx4 *>(out + c * EPC) = pack4<T>(acc);
+        };
+        float f[EPC], acc[EPC];
+        if (held_all) {
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) acc[e] = 0.f;
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int row = row0 + i * rows_per_load();
+                if (i * rows_per_load() < g) {
+                    const float w = row < g ? weight[row] : 0.f;
+                    unpack4<T>(held[i], f);
+#pragma unroll
+                    for (int e = 0; e < EPC; ++e) acc[e] = row < g ? fmaf(w, f[e], acc[e]) : acc[e];
+                }
+            }
+            finish(acc, c0);
+            return;
+        }
+        for (int cb = 0; cb < chunks; cb += WAVE) {
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) acc[e] = 0.f;
+#pragma unroll 4
+            for (int r = 0; r < g; r += rows_per_load()) {
+                const int row = r + row0;
+                const float w = row < g ? weight[row] : 0.f;
+                unpack4<T>(fetch(row, cb + c0), f);
+#pragma unroll
+                for (int e = 0; e < EPC; ++e) acc[e] = row < g ? fmaf(w, f[e], acc[e]) : acc[e];
+            }
+            finish(acc, cb + c0);
+        }
+    }
+    __device__ __forceinline__ void copy_row(int row, T *out, int lane) const      // bit for bit
+    {
+        for (int c = lane; c < chunks; c += WAVE)
+            *reinterpret_cast<uintx4 *>(out + c * Elt<T>::EPC) = *reinterpret_cast<const uintx4 *>(base + row * stride + c * Elt<T>::EPC);
+    }
+};
+
+constexpr int ANY_WAVES = 4;         // wavefronts (groups) per workgroup
+struct AnyParams {
+    const void *POOL, *SEL;
+    const float *qbar;               // [B, S, d_qk]
+    void *pool_rep, *sel_rep;
+    int32_t *anchor;
+    float *alpha_dbg;
+    int L, S, m, g, d_pool, d_sel, mla, pool_reduce, sel_reduce;
+    float scale;
+};
 
 template <typename T>
-__global__ __launch_bounds__(256) void condense_generic_kernel(const T *__restrict__ POOL, const T *__restrict__ SEL,
-                                                               const float *__restrict__ qbar, T *__restrict__ pool_rep,
-                                                               T *__restrict__ sel_rep, int32_t *__restrict__ anchor,
-                                                               float *__restrict__ alpha_dbg, int B, int L, int S, int m, int g,
-                                                               int d_pool, int d_sel, int mla, float scale, int pool_reduce, int sel_reduce)
+__global__ __launch_bounds__(ANY_WAVES *WAVE) void condense_any_kernel(const AnyParams kp)
 {
-    const int lane = threadIdx.x & (WAVE - 1);
-    const long unit = (long)blockIdx.x * (blockDim.x / WAVE) + (threadIdx.x / WAVE);
-    if (unit >= (long)B * S * m) return;
-    const int j = (int)(unit % m), s = (int)((unit / m) % S), b = (int)(unit / ((long)m * S));
-    const int P = mla ? 1 : S, p = mla ? 0 : s, d_qk = mla ? d_pool + d_sel : d_sel;
-    const float *qb = qbar + ((size_t)b * S + s) * d_qk;
-    const T *pool_base = POOL + ((size_t)b * L * P + p) * d_pool;
-    const T *sel_base = SEL + ((size_t)b * L * P + p) * d_sel;
-    const size_t pool_stride = (size_t)P * d_pool, sel_stride = (size_t)P * d_sel;
+    constexpr int EPC = Elt<T>::EPC;
+    __shared__ float per_row[ANY_WAVES][2][WAVE];          // per wavefront and row of its group: score, then weight; norm
+    const int lane = threadIdx.x & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int g = kp.g, m = kp.m, S = kp.S, mla = kp.mla, d_pool = kp.d_pool, d_sel = kp.d_sel;
+    const int d_qk = mla ? d_pool + d_sel : d_sel;
+    const int blocks = (m + ANY_WAVES - 1) / ANY_WAVES;    // workgroups per (sequence, set)
+    const int bs = blockIdx.x / blocks, s = bs % S, b = bs / S, j = (int)(blockIdx.x % blocks) * ANY_WAVES + wave;
+    if (j >= m) return;
+    const int P = mla ? 1 : S, p = mla ? 0 : s;
+    const T *const pool_base = (const T *)kp.POOL + (((size_t)b * kp.L + (size_t)j * g) * P + p) * d_pool;
+    const T *const sel_base = (const T *)kp.SEL + (((size_t)b * kp.L + (size_t)j * g) * P + p) * d_sel;
+    Rows<T, 16> pool;
+    Rows<T, 4> sel;
+    pool.init(pool_base, (size_t)P * d_pool, d_pool / EPC, g, lane);
+    sel.init(sel_base, (size_t)P * d_sel, d_sel / EPC, g, lane);
+    pool.request();
+    sel.request();
+    const float *const qb = kp.qbar + (size_t)bs * d_qk;
 
-    float my_score = -INFINITY;            // lane r holds the score of row r
-    for (int r = 0; r < g; ++r) {
-        const T *pr = pool_base + (size_t)(j * g + r) * pool_stride;
-        const T *sr = sel_base + (size_t)(j * g + r) * sel_stride;
+    float *const row_val = per_row[wave][0], *const row_norm = per_row[wave][1];
+    const size_t unit = (size_t)bs * m + j;
+    auto dot = [&](const float *q) {
+        return [q](const float *f, int col) {
+            float a = 0.f;
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) a = fmaf(f[e], q[col + e], a);
+            return a;
+        };
+    };
+    auto square = [](const float *f, int) {
         float a = 0.f;
-        if (mla)
-            for (int x = lane; x < d_pool; x += WAVE) a = fmaf(Elt<T>::ld(pr + x), qb[x], a);
-        const int qoff = mla ? d_pool : 0;
-        for (int x = lane; x < d_sel; x += WAVE) a = fmaf(Elt<T>::ld(sr + x), qb[qoff + x], a);
-        for (int mask = 32; mask >= 1; mask >>= 1) a += __shfl_xor(a, mask, WAVE);
-        if (lane == r) my_score = scale * a;
-    }
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) a = fmaf(f[e], f[e], a);
+        return a;
+    };
+    if (mla) pool.row_sums(dot(qb), row_val, nullptr);
+    __builtin_amdgcn_wave_barrier();
+    sel.row_sums(dot(qb + (mla ? d_pool : 0)), row_val, mla ? row_val : nullptr);
+    __builtin_amdgcn_wave_barrier();
+    const float my_score = lane < g ? kp.scale * row_val[lane] : -INFINITY;      // lane r holds the score of row r
     float bmax;
-    const int brow = wave_argmax(my_score, lane, &bmax);
+    const int top = g <= 1 ? 0 : 1 << (31 - __builtin_clz(g - 1));               // lanes 0 .. 2 top - 1 hold the rows
+    const int brow = wave_argmax(my_score, lane, top, &bmax);
     const float pmine = lane < g ? __expf(my_score - bmax) : 0.f;
     float z = pmine;
-    for (int mask = 32; mask >= 1; mask >>= 1) z += __shfl_xor(z, mask, WAVE);
-    const float alpha = pmine / z;
-    const float mean_w = lane < g ? 1.f / (float)g : 0.f;
+    for (int mask = top; mask >= 1; mask >>= 1) z += __shfl_xor(z, mask, WAVE);
+    const float alpha = pmine / readlane_f(z, 0);
 
-    int pick_pool = brow, pick_sel = brow;
-    if (pool_reduce == LCA_REDUCE_MAXPOOL) pick_pool = wave_argmax(row_norms(pool_base, pool_stride, j, g, d_pool, lane), lane, nullptr);
-    if (sel_reduce == LCA_REDUCE_MAXPOOL) pick_sel = wave_argmax(row_norms(sel_base, sel_stride, j, g, d_sel, lane), lane, nullptr);
-    reduce_component(pool_reduce, pool_base, pool_stride, j, g, d_pool, pool_reduce == LCA_REDUCE_MEAN ? mean_w : alpha, pick_pool,
-                     pool_rep + (size_t)unit * d_pool, lane);
-    reduce_component(sel_reduce, sel_base, sel_stride, j, g, d_sel, sel_reduce == LCA_REDUCE_MEAN ? mean_w : alpha, pick_sel,
-                     sel_rep + (size_t)unit * d_sel, lane);
-    if (lane == 0) anchor[unit] = j * g + brow;
-    if (alpha_dbg != nullptr && lane < g) alpha_dbg[(size_t)unit * g + lane] = alpha;
+    // one component: a weighted sum of the group's rows, or one of them
+    auto reduce = [&](auto &rows, int strategy, T *out) {
+        int pick = brow;
+        if (strategy == LCA_REDUCE_MAXPOOL) {
+            rows.row_sums(square, row_norm, nullptr);
+            __builtin_amdgcn_wave_barrier();
+            pick = wave_argmax(lane < g ? row_norm[lane] : -INFINITY, lane, top, nullptr);
+        }
+        if (strategy == LCA_REDUCE_MAXSEL || strategy == LCA_REDUCE_MAXPOOL) {
+            rows.copy_row(pick, out, lane);
+            return;
+        }
+        __builtin_amdgcn_wave_barrier();
+        row_val[lane] = lane >= g ? 0.f : strategy == LCA_REDUCE_MEAN ? 1.f / (float)g : alpha;
+        __builtin_amdgcn_wave_barrier();
+        rows.weighted_sum(row_val, out);
+    };
+    reduce(pool, kp.pool_reduce, (T *)kp.pool_rep + unit * d_pool);
+    reduce(sel, kp.sel_reduce, (T *)kp.sel_rep + unit * d_sel);
+    if (lane == 0) kp.anchor[unit] = j * g + brow;
+    if (kp.alpha_dbg != nullptr && lane < g) kp.alpha_dbg[unit * g + lane] = alpha;
 }
 
 template <typename T, int DP, int DS, int G, bool MLA>
@@ -461,14 +599,13 @@ hipError_t run_reg(const CondenseArgs &a, hipStream_t st)
 }
 
 template <typename T>
-hipError_t run_generic(const CondenseArgs &a, hipStream_t st)
+hipError_t run_any(const CondenseArgs &a, hipStream_t st)
 {
     const Dims &d = a.d;
-    const long units = (long)d.B * d.S * d.m;
-    const int blocks = (int)((units + 3) / 4);
-    condense_generic_kernel<T><<<blocks, 256, 0, st>>>((const T *)a.POOL, (const T *)a.SEL, a.qbar, (T *)a.pool_rep, (T *)a.sel_rep,
-                                                       a.anchor, a.alpha_dbg, d.B, d.L, d.S, d.m, d.g, d.d_pool, d.d_sel,
-                                                       d.mode == LCA_MODE_MLA, d.scale, d.pool_reduce, d.sel_reduce);
+    const AnyParams kp{a.POOL, a.SEL, a.qbar, a.pool_rep, a.sel_rep, a.anchor, a.alpha_dbg, d.L, d.S, d.m, d.g,
+                       d.d_pool, d.d_sel, d.mode == LCA_MODE_MLA, d.pool_reduce, d.sel_reduce, d.scale};
+    const unsigned blocks = (d.m + ANY_WAVES - 1) / ANY_WAVES;
+    condense_any_kernel<T><<<blocks * d.S * d.B, ANY_WAVES * WAVE, 0, st>>>(kp);
     return hipGetLastError();
 }
 
@@ -492,13 +629,13 @@ bool try_reg(const CondenseArgs &a, hipStream_t st, hipError_t &err)
 hipError_t launch_summary_query(const Dims &d, const void *Q, int L, float *qbar, hipStream_t st)
 {
     if (d.dtype == LCA_BF16) {
-        const int sq_blocks = d.B * d.S * ((d.d_qk / 8 + WAVE - 1) / WAVE);
+        const int sq_blocks = d.B * d.S * ((d.d_qk / 8 + SQ_CHUNKS - 1) / SQ_CHUNKS);
         summary_query_kernel<uint16_t><<<sq_blocks, SQ_WAVES * WAVE, 0, st>>>((const uint16_t *)Q, qbar, L, d.H, d.S, d.d_qk, d.n_q);
     } else if (d.dtype == LCA_F16) {
-        const int sq_blocks = d.B * d.S * ((d.d_qk / 8 + WAVE - 1) / WAVE);
+        const int sq_blocks = d.B * d.S * ((d.d_qk / 8 + SQ_CHUNKS - 1) / SQ_CHUNKS);
         summary_query_kernel<f16_t><<<sq_blocks, SQ_WAVES * WAVE, 0, st>>>((const f16_t *)Q, qbar, L, d.H, d.S, d.d_qk, d.n_q);
     } else {
-        const int sq_blocks = d.B * d.S * ((d.d_qk / 4 + WAVE - 1) / WAVE);
+        const int sq_blocks = d.B * d.S * ((d.d_qk / 4 + SQ_CHUNKS - 1) / SQ_CHUNKS);
         summary_query_kernel<float><<<sq_blocks, SQ_WAVES * WAVE, 0, st>>>((const float *)Q, qbar, L, d.H, d.S, d.d_qk, d.n_q);
     }
     return hipGetLastError();
@@ -507,26 +644,27 @@ hipError_t launch_summary_query(const Dims &d, const void *Q, int L, float *qbar
 hipError_t launch_condense(const CondenseArgs &a, hipStream_t st)
 {
     const Dims &d = a.d;
+    if (d.m == 0) return hipSuccess;        // nothing to condense, and nobody to read a summary query
+    auto any = [&]() {
+        return d.dtype == LCA_BF16 ? run_any<uint16_t>(a, st) : d.dtype == LCA_F16 ? run_any<f16_t>(a, st) : run_any<float>(a, st);
+    };
     // 1. summary query (Algorithm 1, first step)
     hipError_t err = launch_summary_query(d, a.Q, d.L, a.qbar, st);
-    if (err != hipSuccess || d.m == 0) return err;
+    if (err != hipSuccess) return err;
     // MLA widths, several sets, groups of whole 16-row tiles: scores and pooling on the matrix cores.  (Measured at 128K, g = 16,
     // this kernel / the register kernel below, summary query included: 52 / 40 us with one set, 52 / 51 with two, 55 / 72 with
     // four, 60 / 111 with eight, 72 / 190 with sixteen.)
     if (condense_mla_mfma_supported(d) && d.S >= 3) return launch_condense_mla_mfma(a, st);
     // 2. groups
     const bool mla = d.mode == LCA_MODE_MLA;
-    // the register kernels implement the method's own strategies (weighted pooling, max selection); the ablation's others run generic
-    auto generic = [&]() {
-        return d.dtype == LCA_BF16 ? run_generic<uint16_t>(a, st) : d.dtype == LCA_F16 ? run_generic<f16_t>(a, st) : run_generic<float>(a, st);
-    };
-    if (d.pool_reduce != LCA_REDUCE_WEIGHTED || d.sel_reduce != LCA_REDUCE_MAXSEL) return generic();
+    // the register kernels implement the method's own strategies (weighted pooling, max selection); the ablation's others run any-width
+    if (d.pool_reduce != LCA_REDUCE_WEIGHTED || d.sel_reduce != LCA_REDUCE_MAXSEL) return any();
     if (d.dtype == LCA_F16 && mla && d.d_pool == 512 && d.d_sel == 64 && try_reg<f16_t, 512, 64, true>(a, st, err)) return err;
     if (d.dtype == LCA_F16 && !mla && d.d_pool == 128 && d.d_sel == 128 && try_reg<f16_t, 128, 128, false>(a, st, err)) return err;
     if (d.dtype == LCA_BF16 && mla && d.d_pool == 512 && d.d_sel == 64 && try_reg<uint16_t, 512, 64, true>(a, st, err)) return err;
     if (d.dtype == LCA_BF16 && !mla && d.d_pool == 128 && d.d_sel == 128 && try_reg<uint16_t, 128, 128, false>(a, st, err)) return err;
     if (d.dtype == LCA_F32 && mla && d.d_pool == 128 && d.d_sel == 32 && try_reg<float, 128, 32, true>(a, st, err)) return err;
-    return generic();
+    return any();
 }
 
 }  // namespace lca
