@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes
 import os
 from dataclasses import dataclass
+from functools import lru_cache
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "liblca.so")
@@ -89,17 +90,22 @@ class Desc:
     def kv_heads(self) -> int:
         return 1 if self.mode == MODE_MLA else self.S
 
+    def _key(self):
+        return (self.B, self.L, self.H, self.S, self.d_pool, self.d_sel, self.g, self.w, self.n_q, self.mode, self.dtype, self.scale,
+                self.rep_logit_bias, self.pool_reduce, self.sel_reduce)
+
     def c(self) -> _CDesc:
         return _CDesc(self.B, self.L, self.H, self.S, self.d_pool, self.d_sel, self.g, self.w, self.n_q, self.mode,
                       self.dtype, float(self.scale), float(self.rep_logit_bias), self.pool_reduce, self.sel_reduce)
 
 
 _lib = None
+_raw_stream = None      # torch's own "address of the current stream" call, where there is one (a Stream object costs ten times as much)
 
 
 def load() -> ctypes.CDLL:
     """Load liblca.so; raises if it has not been built (``python -m paper_2604_12452_amd.build``)."""
-    global _lib
+    global _lib, _raw_stream
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise FileNotFoundError(f"{LIB_PATH} is missing: build it with `python -m paper_2604_12452_amd.build`; "
@@ -109,28 +115,41 @@ def load() -> ctypes.CDLL:
         # runtimes in one process, and the one that initialises second finds no device (every launch then fails with
         # "no ROCm-capable device is detected").  The tensors this binding takes are torch's, so torch goes first.
         try:
-            import torch  # noqa: F401
+            import torch
+            _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+            _KNOWN_DTYPES.update({BF16: (torch.bfloat16, torch.int16, torch.uint16), F32: (torch.float32,), F16: (torch.float16,)})
         except ImportError:
             pass
         lib = ctypes.CDLL(LIB_PATH)
         for name in EXPORTS:
             getattr(lib, name).restype = ctypes.c_int
         lib.lca_last_error.restype = ctypes.c_char_p
+        # (with the argument types declared, addresses and sizes are passed as plain integers: converting seven or ten of them
+        # into ctypes objects was a fifth of a call's time on the host)
+        p, n, i = ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int32
+        for name, args in {
+            "lca_workspace_size": [p, p], "lca_cache_bytes": [p, p, p], "lca_condensed_rows": [p, p, p],
+            "lca_condense": [p] * 8 + [p, n, p], "lca_condense_noalloc": [p] * 8 + [p],
+            "lca_prefill_attn": [p] * 8 + [p, n, p], "lca_prefill_attn_up": [p] * 9 + [p, n, p], "dense_mla_attn": [p] * 6 + [p, n, p],
+            "lca_decode_attn": [p] * 7 + [p, n, p], "lca_decode_attn_cached": [p] * 8 + [p, n, p],
+            "lca_cache_update": [p] * 8 + [p, n, p], "lca_quantize_cache": [p, p, i] + [p] * 6, "lca_decode_attn_q8": [p] * 9 + [p, n, p],
+            "lca_deviation_stats": [p] * 6 + [p, n, p], "lca_probe_hbm_read": [p, n, p, p], "lca_probe_mfma_bf16": [i, i, p, p, p],
+            "lca_last_error": [],
+        }.items():
+            getattr(lib, name).argtypes = args
         _lib = lib
     return _lib
 
 
 def _ptr(t):
     """Device address of a tensor (or None / int passthrough)."""
-    if t is None:
-        return ctypes.c_void_p(0)
-    if isinstance(t, int):
-        return ctypes.c_void_p(t)
+    if t is None or isinstance(t, int):
+        return t
     if not t.is_contiguous():
         raise ValueError("liblca needs contiguous tensors")
     if not t.is_cuda:
         raise ValueError(f"a tensor of shape {tuple(t.shape)} is not a device tensor: liblca takes device pointers")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _nbytes(t) -> int:
@@ -140,10 +159,10 @@ def _nbytes(t) -> int:
 def _stream(stream):
     if stream is None:
         import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        return torch.cuda.current_stream().cuda_stream if _raw_stream is None else _raw_stream(torch.cuda.current_device())
     if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
 def _check(status: int):
@@ -155,6 +174,7 @@ def _check(status: int):
 # size and element type the header documents for it before anything is launched: a kernel reading or writing past a
 # buffer is a GPU memory fault, not an exception.  Only sizes and types are compared (marshalling), no values.
 _ELT_NAMES = {BF16: ("torch.bfloat16", "torch.int16", "torch.uint16"), F32: ("torch.float32",), F16: ("torch.float16",)}
+_KNOWN_DTYPES = {}              # the same as dtype objects, filled in when torch is imported (comparing these is cheaper than names)
 _KIND_NAMES = {"i32": ("torch.int32",), "f32": ("torch.float32",), "u8": ("torch.uint8",)}
 
 
@@ -165,6 +185,8 @@ def _fit(desc: Desc, t, name: str, elems: int, kind: str = "elt", optional: bool
             return
         raise ValueError(f"{name} is required")
     if isinstance(t, int):          # a raw device address: the caller vouches for it
+        return
+    if kind == "elt" and t.dtype in _KNOWN_DTYPES.get(desc.dtype, ()) and t.numel() >= elems:
         return
     names = _ELT_NAMES[desc.dtype] if kind == "elt" else _KIND_NAMES[kind]
     if str(t.dtype) not in names:
@@ -197,12 +219,19 @@ def workspace_size(desc: Desc) -> int:
     return int(n.value)
 
 
+@lru_cache(maxsize=256, typed=True)
+def _plan(*key):
+    """(C descriptor, m, k) of a descriptor's field values: what every call needs and only the values determine.  The C structure is
+    shared by later calls with equal values and only ever read."""
+    cd = Desc(*key).c()
+    m, k = ctypes.c_int32(0), ctypes.c_int32(0)
+    _check(load().lca_condensed_rows(ctypes.byref(cd), ctypes.byref(m), ctypes.byref(k)))
+    return cd, int(m.value), int(k.value)
+
+
 def condensed_rows(desc: Desc):
     """(m, k) of section 4.2's partition for this descriptor, from the library."""
-    m, k = ctypes.c_int32(0), ctypes.c_int32(0)
-    cd = desc.c()
-    _check(load().lca_condensed_rows(ctypes.byref(cd), ctypes.byref(m), ctypes.byref(k)))
-    return int(m.value), int(k.value)
+    return _plan(*desc._key())[1:]
 
 
 def cache_bytes(desc: Desc):
@@ -213,20 +242,18 @@ def cache_bytes(desc: Desc):
 
 
 def condense(desc: Desc, Q, POOL, SEL, pool_rep, sel_rep, anchor_idx, alpha_dbg, workspace, stream=None):
-    cd = desc.c()
-    m, _ = condensed_rows(desc)
+    cd, m, _ = _plan(*desc._key())
     _fit_inputs(desc, Q, POOL, SEL)
     _fit_reps(desc, pool_rep, sel_rep, m)
     _fit(desc, anchor_idx, "anchor_idx", desc.B * desc.S * m, "i32")
     _fit(desc, alpha_dbg, "alpha_dbg", desc.B * desc.S * m * desc.g, "f32", optional=True)
     _check(load().lca_condense(ctypes.byref(cd), _ptr(Q), _ptr(POOL), _ptr(SEL), _ptr(pool_rep), _ptr(sel_rep),
-                               _ptr(anchor_idx), _ptr(alpha_dbg), _ptr(workspace), ctypes.c_size_t(_nbytes(workspace)),
+                               _ptr(anchor_idx), _ptr(alpha_dbg), _ptr(workspace), _nbytes(workspace),
                                _stream(stream)))
 
 
 def condense_noalloc(desc: Desc, Q, POOL, SEL, pool_rep, sel_rep, anchor_idx, alpha_dbg, stream=None):
-    cd = desc.c()
-    m, _ = condensed_rows(desc)
+    cd, m, _ = _plan(*desc._key())
     _fit_inputs(desc, Q, POOL, SEL)
     _fit_reps(desc, pool_rep, sel_rep, m)
     _fit(desc, anchor_idx, "anchor_idx", desc.B * desc.S * m, "i32")
@@ -236,38 +263,38 @@ def condense_noalloc(desc: Desc, Q, POOL, SEL, pool_rep, sel_rep, anchor_idx, al
 
 
 def prefill_attn(desc: Desc, Q, POOL, SEL, pool_rep, sel_rep, O, lse, workspace, stream=None):
-    cd = desc.c()
+    cd, m, _ = _plan(*desc._key())
     _fit_inputs(desc, Q, POOL, SEL)
-    _fit_reps(desc, pool_rep, sel_rep, condensed_rows(desc)[0])
+    _fit_reps(desc, pool_rep, sel_rep, m)
     _fit(desc, O, "O", desc.B * desc.L * desc.H * desc.d_pool)
     _fit(desc, lse, "lse", desc.B * desc.L * desc.H, "f32", optional=True)
     _check(load().lca_prefill_attn(ctypes.byref(cd), _ptr(Q), _ptr(POOL), _ptr(SEL), _ptr(pool_rep), _ptr(sel_rep),
-                                   _ptr(O), _ptr(lse), _ptr(workspace), ctypes.c_size_t(_nbytes(workspace)),
+                                   _ptr(O), _ptr(lse), _ptr(workspace), _nbytes(workspace),
                                    _stream(stream)))
 
 
 def prefill_attn_up(desc: Desc, Q, POOL, SEL, pool_rep, sel_rep, W_up, O_up, lse, workspace, stream=None):
-    cd = desc.c()
+    cd, m, _ = _plan(*desc._key())
     _fit_inputs(desc, Q, POOL, SEL)
-    _fit_reps(desc, pool_rep, sel_rep, condensed_rows(desc)[0])
+    _fit_reps(desc, pool_rep, sel_rep, m)
     _fit(desc, W_up, "W_up", desc.H * 128 * desc.d_pool)
     _fit(desc, O_up, "O_up", desc.B * desc.L * desc.H * 128)
     _fit(desc, lse, "lse", desc.B * desc.L * desc.H, "f32", optional=True)
     _check(load().lca_prefill_attn_up(ctypes.byref(cd), _ptr(Q), _ptr(POOL), _ptr(SEL), _ptr(pool_rep), _ptr(sel_rep), _ptr(W_up),
-                                      _ptr(O_up), _ptr(lse), _ptr(workspace), ctypes.c_size_t(_nbytes(workspace)), _stream(stream)))
+                                      _ptr(O_up), _ptr(lse), _ptr(workspace), _nbytes(workspace), _stream(stream)))
 
 
 def dense_attn(desc: Desc, Q, POOL, SEL, O, lse, workspace, stream=None):
-    cd = desc.c()
     _fit_inputs(desc, Q, POOL, SEL)
     _fit(desc, O, "O", desc.B * desc.L * desc.H * desc.d_pool)
     _fit(desc, lse, "lse", desc.B * desc.L * desc.H, "f32", optional=True)
+    cd = _plan(*desc._key())[0]
     _check(load().dense_mla_attn(ctypes.byref(cd), _ptr(Q), _ptr(POOL), _ptr(SEL), _ptr(O), _ptr(lse), _ptr(workspace),
-                                 ctypes.c_size_t(_nbytes(workspace)), _stream(stream)))
+                                 _nbytes(workspace), _stream(stream)))
 
 
 def _fit_decode(desc: Desc, layout, q, pool_rep, sel_rep, pool_tail, sel_tail, O, rep_kind="elt", scales=None):
-    m, k = condensed_rows(desc)
+    cd, m, k = _plan(*desc._key())
     m_cap, k_cap = (layout.m_cap, layout.k_cap) if layout is not None else (m, k)
     _fit(desc, q, "q", desc.B * desc.H * desc.d_qk)
     _fit(desc, pool_rep, "pool_rep", desc.B * desc.S * m_cap * desc.d_pool if m > 0 else 0, rep_kind)
@@ -276,64 +303,63 @@ def _fit_decode(desc: Desc, layout, q, pool_rep, sel_rep, pool_tail, sel_tail, O
         _fit(desc, scales, "scales", desc.B * desc.S * m_cap * 2 if m > 0 else 0, "f32")
     _fit_tails(desc, pool_tail, sel_tail, k_cap)
     _fit(desc, O, "O", desc.B * desc.H * desc.d_pool)
+    return cd
 
 
 def decode_attn(desc: Desc, q, pool_rep, sel_rep, pool_tail, sel_tail, O, workspace, stream=None):
-    cd = desc.c()
-    _fit_decode(desc, None, q, pool_rep, sel_rep, pool_tail, sel_tail, O)
+    cd = _fit_decode(desc, None, q, pool_rep, sel_rep, pool_tail, sel_tail, O)
     _check(load().lca_decode_attn(ctypes.byref(cd), _ptr(q), _ptr(pool_rep), _ptr(sel_rep), _ptr(pool_tail),
-                                  _ptr(sel_tail), _ptr(O), _ptr(workspace), ctypes.c_size_t(_nbytes(workspace)),
+                                  _ptr(sel_tail), _ptr(O), _ptr(workspace), _nbytes(workspace),
                                   _stream(stream)))
 
 
 def decode_attn_cached(desc: Desc, layout: CacheLayout, q, pool_rep, sel_rep, pool_tail, sel_tail, O, workspace, stream=None):
-    cd, cl = desc.c(), layout.c()
-    _fit_decode(desc, layout, q, pool_rep, sel_rep, pool_tail, sel_tail, O)
+    cl = layout.c()
+    cd = _fit_decode(desc, layout, q, pool_rep, sel_rep, pool_tail, sel_tail, O)
     _check(load().lca_decode_attn_cached(ctypes.byref(cd), ctypes.byref(cl), _ptr(q), _ptr(pool_rep), _ptr(sel_rep), _ptr(pool_tail),
-                                         _ptr(sel_tail), _ptr(O), _ptr(workspace), ctypes.c_size_t(_nbytes(workspace)), _stream(stream)))
+                                         _ptr(sel_tail), _ptr(O), _ptr(workspace), _nbytes(workspace), _stream(stream)))
 
 
 def cache_update(desc: Desc, layout: CacheLayout, q_recent, pool_tail, sel_tail, pool_rep, sel_rep, anchor_idx, workspace, stream=None):
-    cd, cl = desc.c(), layout.c()
+    cl = layout.c()
     _fit(desc, q_recent, "q_recent", desc.B * (desc.n_q or desc.g) * desc.H * desc.d_qk)
     _fit_tails(desc, pool_tail, sel_tail, layout.k_cap)
     _fit_reps(desc, pool_rep, sel_rep, layout.m_cap)
     _fit(desc, anchor_idx, "anchor_idx", desc.B * desc.S * layout.m_cap, "i32", optional=True)
+    cd = _plan(*desc._key())[0]
     _check(load().lca_cache_update(ctypes.byref(cd), ctypes.byref(cl), _ptr(q_recent), _ptr(pool_tail), _ptr(sel_tail), _ptr(pool_rep),
-                                   _ptr(sel_rep), _ptr(anchor_idx), _ptr(workspace), ctypes.c_size_t(_nbytes(workspace)), _stream(stream)))
+                                   _ptr(sel_rep), _ptr(anchor_idx), _ptr(workspace), _nbytes(workspace), _stream(stream)))
 
 
 def quantize_cache(desc: Desc, layout, pool_rep, sel_rep, pool_q8, sel_q8, scales, first_row=0, stream=None):
-    cd = desc.c()
+    cd, m, _ = _plan(*desc._key())
     cl = layout.c() if layout is not None else None
-    m, _ = condensed_rows(desc)
     rows = layout.m_cap if layout is not None else m
     if 0 <= first_row < m:          # (otherwise the library rejects first_row or has nothing to do, and reads nothing)
         _fit_reps(desc, pool_rep, sel_rep, rows)
         _fit(desc, pool_q8, "pool_q8", desc.B * desc.S * rows * desc.d_pool, "u8")
         _fit(desc, sel_q8, "sel_q8", desc.B * desc.S * rows * desc.d_sel, "u8")
         _fit(desc, scales, "scales", desc.B * desc.S * rows * 2, "f32")
-    _check(load().lca_quantize_cache(ctypes.byref(cd), ctypes.byref(cl) if cl is not None else None, ctypes.c_int32(first_row), _ptr(pool_rep), _ptr(sel_rep),
+    _check(load().lca_quantize_cache(ctypes.byref(cd), ctypes.byref(cl) if cl is not None else None, first_row, _ptr(pool_rep), _ptr(sel_rep),
                                      _ptr(pool_q8), _ptr(sel_q8), _ptr(scales), _stream(stream)))
 
 
 def decode_attn_q8(desc: Desc, layout, q, pool_q8, sel_q8, scales, pool_tail, sel_tail, O, workspace, stream=None):
-    cd = desc.c()
     cl = layout.c() if layout is not None else None
-    _fit_decode(desc, layout, q, pool_q8, sel_q8, pool_tail, sel_tail, O, rep_kind="u8", scales=scales)
+    cd = _fit_decode(desc, layout, q, pool_q8, sel_q8, pool_tail, sel_tail, O, rep_kind="u8", scales=scales)
     _check(load().lca_decode_attn_q8(ctypes.byref(cd), ctypes.byref(cl) if cl is not None else None, _ptr(q), _ptr(pool_q8), _ptr(sel_q8),
                                      _ptr(scales), _ptr(pool_tail), _ptr(sel_tail), _ptr(O), _ptr(workspace),
-                                     ctypes.c_size_t(_nbytes(workspace)), _stream(stream)))
+                                     _nbytes(workspace), _stream(stream)))
 
 
 def deviation_stats(desc: Desc, POOL, SEL, pool_rep, sel_rep, stats, workspace, stream=None):
-    cd = desc.c()
     _fit(desc, POOL, "POOL", desc.B * desc.L * desc.kv_heads * desc.d_pool)
     _fit(desc, SEL, "SEL", desc.B * desc.L * desc.kv_heads * desc.d_sel)
     _fit_reps(desc, pool_rep, sel_rep, condensed_rows(desc)[0])
     _fit(desc, stats, "stats", desc.B * desc.S * 6, "f32")
+    cd = _plan(*desc._key())[0]
     _check(load().lca_deviation_stats(ctypes.byref(cd), _ptr(POOL), _ptr(SEL), _ptr(pool_rep), _ptr(sel_rep), _ptr(stats), _ptr(workspace),
-                                      ctypes.c_size_t(_nbytes(workspace)), _stream(stream)))
+                                      _nbytes(workspace), _stream(stream)))
 
 
 # ---------------------------------------------------------------------------------------------
@@ -365,7 +391,7 @@ def probe_hbm_read(buf, wg_sums, stream=None):
     """Stream `buf` out of HBM once (measurement aid); `wg_sums` (PROBE_WORDS int32 / uint32) receives per-workgroup word sums."""
     if _nbytes(wg_sums) < PROBE_WORDS * 4 or wg_sums.element_size() != 4:
         raise ValueError(f"wg_sums must hold {PROBE_WORDS} 32-bit words")
-    _check(load().lca_probe_hbm_read(_ptr(buf), ctypes.c_size_t(_nbytes(buf)), _ptr(wg_sums), _stream(stream)))
+    _check(load().lca_probe_hbm_read(_ptr(buf), _nbytes(buf), _ptr(wg_sums), _stream(stream)))
 
 
 def probe_mfma_bf16(iters: int, out, pattern: int = 0, stream=None) -> int:
@@ -374,5 +400,5 @@ def probe_mfma_bf16(iters: int, out, pattern: int = 0, stream=None) -> int:
     if _nbytes(out) < PROBE_MFMA_FLOATS * 4 or str(out.dtype) != "torch.float32":
         raise ValueError(f"out must hold {PROBE_MFMA_FLOATS} float32")
     waves = ctypes.c_int32(0)
-    _check(load().lca_probe_mfma_bf16(ctypes.c_int32(iters), ctypes.c_int32(pattern), _ptr(out), ctypes.byref(waves), _stream(stream)))
+    _check(load().lca_probe_mfma_bf16(iters, pattern, _ptr(out), ctypes.byref(waves), _stream(stream)))
     return int(waves.value)
