@@ -229,17 +229,19 @@ __global__ __launch_bounds__(WAVE *NWAVE) void decode_split_kernel(const T *__re
 }
 
 // One workgroup per (b, set, head-in-set): blockIdx.x = (b*S + s)*HPS + h.  The weights of the splits,
-// exp(max_sp - max) / sum, are computed once into LDS; then every thread owns two adjacent columns and sums
-// the splits' rows with 8-byte loads, eight of them in flight.  DP is even; rows start 8 bytes into a
-// (DP + 2)-float record, so 8 bytes is the alignment there is.
+// exp(max_sp - max) / sum, are computed once into LDS; then thread (group, column pair) sums every GROUPS-th run of eight
+// splits' rows with 8-byte loads, eight of them in flight, and the groups' sums are added in order through LDS.  DP is even;
+// rows start 8 bytes into a (DP + 2)-float record, so 8 bytes is the alignment there is.  GROUPS = 4 where there are more
+// than sixteen splits: one group takes a round trip to memory per eight of them (B = 1, L = 131072 at 512 + 64, 72 splits:
+// the step 17.7 -> 17.0 us).
 constexpr int MERGE_THREADS = 256;
-template <typename T>
-__global__ __launch_bounds__(MERGE_THREADS) void decode_merge_kernel(const float *__restrict__ part, T *__restrict__ O, int HPS, int DP, int splits)
+template <typename T, int GROUPS>
+__global__ __launch_bounds__(MERGE_THREADS *GROUPS) void decode_merge_kernel(const float *__restrict__ part, T *__restrict__ O, int HPS, int DP, int splits)
 {
-    extern __shared__ float wgt[];                        // [splits]
-    __shared__ float red[MERGE_THREADS / WAVE];
+    extern __shared__ float wgt[];                        // [splits], then [GROUPS - 1][DP] partial sums
+    __shared__ float red[MERGE_THREADS * GROUPS / WAVE];
     const size_t bs = blockIdx.x / HPS;
-    const int h = blockIdx.x % HPS, tid = threadIdx.x;
+    const int h = blockIdx.x % HPS, tid = threadIdx.x, group = tid / MERGE_THREADS;
     const float *base = part + (bs * splits * HPS + h) * (size_t)(DP + 2);
     const size_t stride = (size_t)HPS * (DP + 2);
     auto block_reduce = [&](float v, bool is_max) {
@@ -251,39 +253,59 @@ __global__ __launch_bounds__(MERGE_THREADS) void decode_merge_kernel(const float
         if ((tid & (WAVE - 1)) == 0) red[tid / WAVE] = v;
         __syncthreads();
         float r = red[0];
-        for (int i = 1; i < MERGE_THREADS / WAVE; ++i) r = is_max ? fmaxf(r, red[i]) : r + red[i];
+        for (int i = 1; i < MERGE_THREADS * GROUPS / WAVE; ++i) r = is_max ? fmaxf(r, red[i]) : r + red[i];
         return r;
     };
     float mx = -INFINITY;
-    for (int sp = tid; sp < splits; sp += MERGE_THREADS) mx = fmaxf(mx, base[sp * stride]);
+    for (int sp = tid; sp < splits; sp += MERGE_THREADS * GROUPS) mx = fmaxf(mx, base[sp * stride]);
     mx = block_reduce(mx, true);
     float l = 0.f;
-    for (int sp = tid; sp < splits; sp += MERGE_THREADS) {
+    for (int sp = tid; sp < splits; sp += MERGE_THREADS * GROUPS) {
         const float e = __expf(base[sp * stride] - mx);
         wgt[sp] = e;
         l += base[sp * stride + 1] * e;
     }
     l = block_reduce(l, false);                           // (its barriers also publish wgt[])
     const float inv = 1.f / l;
-    for (int x = 2 * tid; x < DP; x += 2 * MERGE_THREADS) {
+    float *const psum = wgt + splits;
+    for (int x0 = 0; x0 < DP; x0 += 2 * MERGE_THREADS) {
+        const int x = x0 + 2 * (tid % MERGE_THREADS);
         float a0 = 0.f, a1 = 0.f;
         const float *col = base + 2 + x;
-        int sp = 0;
-        for (; sp + 8 <= splits; sp += 8) {
-            float2 v[8];
+        if (x < DP) {
+            int sp = 8 * group;
+            for (; sp + 8 <= splits; sp += 8 * GROUPS) {
+                float2 v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float2 *>(col + (sp + u) * stride);
+                for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float2 *>(col + (sp + u) * stride);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) { a0 = fmaf(v[u].x, wgt[sp + u], a0); a1 = fmaf(v[u].y, wgt[sp + u], a1); }
+                for (int u = 0; u < 8; ++u) { a0 = fmaf(v[u].x, wgt[sp + u], a0); a1 = fmaf(v[u].y, wgt[sp + u], a1); }
+            }
+            for (int i = sp; i < splits && i < sp + 8; ++i) {        // (the last run, shorter than eight, is one group's)
+                const float2 v = *reinterpret_cast<const float2 *>(col + i * stride);
+                a0 = fmaf(v.x, wgt[i], a0);
+                a1 = fmaf(v.y, wgt[i], a1);
+            }
         }
-        for (; sp < splits; ++sp) {
-            const float2 v = *reinterpret_cast<const float2 *>(col + sp * stride);
-            a0 = fmaf(v.x, wgt[sp], a0);
-            a1 = fmaf(v.y, wgt[sp], a1);
+        if (GROUPS > 1) {
+            if (group > 0 && x < DP) { psum[(group - 1) * DP + x] = a0; psum[(group - 1) * DP + x + 1] = a1; }
+            __syncthreads();
+            if (group == 0 && x < DP)
+                for (int i = 0; i < GROUPS - 1; ++i) { a0 += psum[i * DP + x]; a1 += psum[i * DP + x + 1]; }
         }
-        DElt<T>::st(O + (size_t)blockIdx.x * DP + x, a0 * inv);
-        DElt<T>::st(O + (size_t)blockIdx.x * DP + x + 1, a1 * inv);
+        if (group == 0 && x < DP) {
+            DElt<T>::st(O + (size_t)blockIdx.x * DP + x, a0 * inv);
+            DElt<T>::st(O + (size_t)blockIdx.x * DP + x + 1, a1 * inv);
+        }
     }
+}
+template <typename T> void launch_merge(const DecodeArgs &a, int splits, hipStream_t st)
+{
+    const Dims &d = a.d;
+    if (splits > 16)
+        decode_merge_kernel<T, 4><<<d.B * d.H, MERGE_THREADS * 4, (splits + 3 * d.d_pool) * sizeof(float), st>>>(a.part, (T *)a.O, d.H / d.S, d.d_pool, splits);
+    else
+        decode_merge_kernel<T, 1><<<d.B * d.H, MERGE_THREADS, splits * sizeof(float), st>>>(a.part, (T *)a.O, d.H / d.S, d.d_pool, splits);
 }
 
 template <typename T, int DP, int DS, bool MLA, int HPS>
@@ -295,7 +317,7 @@ hipError_t run(const DecodeArgs &a, hipStream_t st)
         d.k, a.splits, d.scale, d.rep_logit_bias, a.m_cap, a.k_cap, a.k_start);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    decode_merge_kernel<T><<<d.B * d.H, MERGE_THREADS, a.splits * sizeof(float), st>>>(a.part, (T *)a.O, HPS, DP, a.splits);
+    launch_merge<T>(a, a.splits, st);
     return hipGetLastError();
 }
 
@@ -329,7 +351,16 @@ int decode_splits(const Dims &d)
 size_t decode_workspace_bytes(const Dims &d)
 {
     if (!decode_supported(d)) return 0;
-    return (size_t)d.B * d.S * decode_splits(d) * (d.H / d.S) * (d.d_pool + 2) * sizeof(float);
+    int records = decode_splits(d);
+    if (decode_mla_supported(d) || decode_gqa_mfma_supported(d)) {
+        // One result per workgroup of four wavefronts.  The size asked for is that of four results for every four wavefronts of four
+        // tiles each, at most 4 * 256 in all (rounded up per pair): never less than the workgroups of the rule in use need.
+        const int bn = decode_mla_supported(d) ? 16 : 32, tiles = (d.m + bn - 1) / bn + (d.k + bn - 1) / bn;
+        const int target = (256 + d.B * d.S - 1) / (d.B * d.S), most = (tiles + 15) / 16;
+        const int wgs = target < most ? target : most;
+        records = 4 * (wgs < 1 ? 1 : wgs);
+    }
+    return (size_t)d.B * d.S * records * (d.H / d.S) * (d.d_pool + 2) * sizeof(float);
 }
 
 hipError_t launch_decode(const DecodeArgs &a, hipStream_t st)
@@ -340,9 +371,9 @@ hipError_t launch_decode(const DecodeArgs &a, hipStream_t st)
         const int wgs = a.splits / 4;    // one partial result per workgroup of four wavefronts
         if (wgs == 1) return hipSuccess; // ... unless a workgroup had a (sequence, set) to itself: then it wrote O
         if (a.d.dtype == LCA_F16)
-            decode_merge_kernel<f16_t><<<a.d.B * a.d.H, MERGE_THREADS, wgs * sizeof(float), st>>>(a.part, (f16_t *)a.O, a.d.H / a.d.S, a.d.d_pool, wgs);
+            launch_merge<f16_t>(a, wgs, st);
         else
-            decode_merge_kernel<uint16_t><<<a.d.B * a.d.H, MERGE_THREADS, wgs * sizeof(float), st>>>(a.part, (uint16_t *)a.O, a.d.H / a.d.S, a.d.d_pool, wgs);
+            launch_merge<uint16_t>(a, wgs, st);
         return hipGetLastError();
     }
     if (decode_gqa_mfma_supported(a.d)) {     // matrix-core kernel at the GQA widths, then the common merge
@@ -351,9 +382,9 @@ hipError_t launch_decode(const DecodeArgs &a, hipStream_t st)
         const int wgs = a.splits / 4;
         if (wgs == 1) return hipSuccess; // a workgroup had a (sequence, KV head) to itself and wrote O
         if (a.d.dtype == LCA_F16)
-            decode_merge_kernel<f16_t><<<a.d.B * a.d.H, MERGE_THREADS, wgs * sizeof(float), st>>>(a.part, (f16_t *)a.O, a.d.H / a.d.S, a.d.d_pool, wgs);
+            launch_merge<f16_t>(a, wgs, st);
         else
-            decode_merge_kernel<uint16_t><<<a.d.B * a.d.H, MERGE_THREADS, wgs * sizeof(float), st>>>(a.part, (uint16_t *)a.O, a.d.H / a.d.S, a.d.d_pool, wgs);
+            launch_merge<uint16_t>(a, wgs, st);
         return hipGetLastError();
     }
     const bool f16 = a.d.dtype == LCA_F16;

@@ -379,14 +379,23 @@ bool decode_mla_supported(const Dims &d)
     return (d.dtype == LCA_BF16 || d.dtype == LCA_F16) && d.mode == LCA_MODE_MLA && d.d_pool == DP && d.d_sel == DS && hps <= 16 && d.scale > 0.f;
 }
 
-// partial results per (sequence, set): a multiple of 4 (one per wavefront), enough workgroups to fill the chip,
-// at least four tiles per wavefront where the cache is long enough
+// Wavefronts per (sequence, set), a multiple of 4 (a workgroup's, which leave one partial result): four tiles for each, where
+// the cache is long enough to fill the chip that way, never more workgroups than CUs (a second round costs as much as the
+// first).  A short or lonely cache is bound by the chain of tiles a wavefront works through: two tiles for each while the
+// workgroups stay below 160, one while they stay below 200 and the merge has few results to add (16 of 33 KB).  Measured
+// (step with merge, 16 heads; four / two / one tile each): B = 1, L = 700 15.9 / 14.6 / 13.3 us; B = 1, L = 4001 16.7 / 14.4 / 14.4;
+// B = 1, L = 16384 15.4 / 14.1 / 15.8; B = 8, L = 1500 17.4 / 15.2 / 15.5; B = 32, L = 700 17.5 / 18.2 / 19.3 (192, 256 workgroups);
+// B = 150, L = 20000 103 us with two workgroups per sequence (300 on 256 CUs), 77 us with one.
 int decode_mla_parts(const Dims &d)
 {
     const int tiles = (d.m + BN - 1) / BN + (d.k + BN - 1) / BN;      // (an upper bound when the two kinds share tiles)
-    int wgs = (256 + d.B * d.S - 1) / (d.B * d.S);
-    const int max_wgs = (tiles + 15) / 16;
-    if (wgs > max_wgs) wgs = max_wgs;
+    const long pairs = (long)d.B * d.S;
+    auto wgs_for = [&](int per_wave) { return (tiles + 4 * per_wave - 1) / (4 * per_wave); };
+    int wgs = wgs_for(4);
+    if (wgs_for(1) <= 16 && pairs * wgs_for(1) <= 200) wgs = wgs_for(1);
+    else if (pairs * wgs_for(2) <= 160) wgs = wgs_for(2);
+    const long most = pairs >= 256 ? 1 : 256 / pairs;
+    if (wgs > most) wgs = (int)most;
     if (wgs < 1) wgs = 1;
     return 4 * wgs;
 }

@@ -1,0 +1,44 @@
+"""How a decode step is split over workgroups: one, two and four tiles per wavefront, caches whose pairs (sequence, set) fill the chip
+alone, more partial results than the merge's one-group form takes, and fewer tiles than wavefronts."""
+import numpy as np
+import pytest
+
+from paper_2604_12452_amd import inputs
+from tests import helpers as hp
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,mode,B,L,H,S,g,w", [
+    ("bf16", inputs.MODE_MLA, 1, 37, 16, 1, 4, 20),              # fewer tiles than wavefronts of one workgroup
+    ("bf16", inputs.MODE_MLA, 1, 1024, 16, 1, 16, 1024),         # 16 workgroups: one tile each, the merge's one-group form at its limit
+    ("f16", inputs.MODE_MLA, 2, 2200, 16, 1, 1, 100),            # 35 workgroups each, two tiles per wavefront, the last one ragged
+    ("bf16", inputs.MODE_MLA, 1, 16400, 16, 1, 2, 16),           # 64 workgroups
+    ("bf16", inputs.MODE_MLA, 20, 1500, 4, 1, 1, 30),            # 12 workgroups per sequence at most, four tiles each
+    ("bf16", inputs.MODE_MLA, 130, 300, 2, 1, 2, 30),            # more than half as many sequences as CUs: one workgroup each
+    ("bf16", inputs.MODE_GQA, 1, 6100, 28, 4, 1, 40),            # 48 workgroups per KV head
+    ("f16", inputs.MODE_GQA, 3, 2900, 14, 2, 2, 33),
+    ("bf16", inputs.MODE_GQA, 33, 400, 8, 4, 2, 64),             # 132 pairs
+])
+def test_decode_step_splits(oracle, dtype, mode, B, L, H, S, g, w):
+    import torch
+    from paper_2604_12452_amd import lca
+    d_pool, d_sel = (512, 64) if mode == inputs.MODE_MLA else (128, 128)
+    wl = inputs.Workload("splits", B=B, L=L, H=H, S=S, d_pool=d_pool, d_sel=d_sel, g=g, w=w, dtype=dtype, mode=mode)
+    print(f"[case] {wl}", flush=True)
+    desc = hp.lca_desc(wl)
+    rng = np.random.default_rng(31 + L)
+    P, dq = desc.kv_heads, desc.d_qk
+    def draw(*shape, std=1.0):
+        return inputs.to_storage(rng.standard_normal(shape, dtype=np.float32) * np.float32(std), dtype)
+    host = dict(q=draw(B, H, dq, std=dq ** -0.5), pool_rep=draw(B, S, desc.m, d_pool), sel_rep=draw(B, S, desc.m, d_sel),
+                pool_tail=draw(B, P, desc.k, d_pool), sel_tail=draw(B, P, desc.k, d_sel))
+    dev = {n: hp.to_dev(x, dtype) for n, x in host.items()}
+    O = torch.full((B, H, d_pool), float("nan"), dtype=lca.torch_dtype(desc), device="cuda")
+    ws = torch.full((lca.workspace_size(desc),), 0xFF, dtype=torch.uint8, device="cuda")      # NaN patterns: nothing may be read before it is written
+    lca.decode_attn(desc, dev["q"], dev["pool_rep"], dev["sel_rep"], dev["pool_tail"], dev["sel_tail"], O, ws)
+    torch.cuda.synchronize()
+    ref = oracle.decode_attn(hp.oracle_desc(oracle, wl), *(inputs.to_f64(host[n], dtype) for n in ("q", "pool_rep", "sel_rep", "pool_tail", "sel_tail")))
+    err = hp.vec_rel_err(hp.from_dev(O, dtype), ref)
+    print(f"  decode err {err:.2e}", flush=True)
+    assert err <= hp.TOL[dtype]
