@@ -4,105 +4,53 @@
 // the selected component copied from the arg-max token (Eq. 8; lowest index on ties).
 //
 // The summary query comes from the condensation's own summary_query_kernel (the g recent queries are a
-// sequence of length n_q to it).  Then one workgroup of four wavefronts per (sequence, set): the wavefronts
-// split the g rows for the scores, the threads split the columns for the pooled row.  g rows of at most 2 KB
-// each — the step is bound by launch latency, not by bandwidth, and runs once every g decode steps.  Any
-// widths, both element types, both modes.
-#include "lca_internal.h"
+// sequence of length n_q to it).  Then one wavefront per (sequence, set) does what the any-width condensation does with a
+// group (group_rows.h), its rows being rows of the ring.  g rows of at most 2 KB each — the step is bound by launch latency and
+// one round trip to memory, not by bandwidth, and runs once every g decode steps; one wavefront per workgroup, so that
+// the few there are sit on CUs of their own.  The call: 16.5 -> 13.6 us at
+// one sequence and 22.2 -> 14.8 us at 32 (512 + 64, 16 heads), 11.1 -> 9.0 us at five (28 heads over 4 KV heads), scalar loads before.
+#include "group_rows.h"
 
 namespace lca {
 namespace {
 
-template <typename T> struct Elt;
-template <> struct Elt<uint16_t> {
-    __device__ static float ld(const uint16_t *p) { return __uint_as_float((unsigned)*p << 16); }
-    __device__ static void st(uint16_t *p, float v)
-    {
-        unsigned u = __float_as_uint(v);
-        if ((u & 0x7fffffffu) > 0x7f800000u) { *p = (uint16_t)((u >> 16) | 0x40); return; }   // NaN stays NaN
-        u += 0x7fffu + ((u >> 16) & 1u);                                                        // round to nearest even
-        *p = (uint16_t)(u >> 16);
-    }
-};
-template <> struct Elt<f16_t> {
-    __device__ static float ld(const f16_t *p) { return f16_bits_to_float(p->bits); }
-    __device__ static void st(f16_t *p, float v) { p->bits = float_to_f16_bits(v); }
-};
-template <> struct Elt<float> {
-    __device__ static float ld(const float *p) { return *p; }
-    __device__ static void st(float *p, float v) { *p = v; }
+using namespace group_rows;
+
+struct UpdParams {
+    const float *qbar;
+    const void *pool_tail, *sel_tail;
+    void *pool_rep, *sel_rep;
+    int32_t *anchor;
+    int S, d_pool, d_sel, g, m, mla, m_cap, k_cap, k_start;
+    float scale;
 };
 
-__device__ __forceinline__ float wave_sum(float x)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
-}
-
-constexpr int UPD_THREADS = 256;
-
-// dynamic LDS: qbar[d_qk] then score[g]
 template <typename T>
-__global__ __launch_bounds__(UPD_THREADS) void cache_update_kernel(const float *__restrict__ qbar_g, const T *__restrict__ pool_tail,
-                                                                   const T *__restrict__ sel_tail, T *__restrict__ pool_rep,
-                                                                   T *__restrict__ sel_rep, int32_t *__restrict__ anchor, int S, int P, int d_pool,
-                                                                   int d_sel, int d_qk, int g, int m, int mla, float scale, int m_cap, int k_cap,
-                                                                   int k_start)
+__global__ __launch_bounds__(WAVE) void cache_update_kernel(const UpdParams kp)
 {
-    extern __shared__ float lds[];
-    float *qbar = lds, *score = lds + d_qk;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, s = blockIdx.x, b = blockIdx.y;
-    const int p = mla ? 0 : s;
-    for (int col = tid; col < d_qk; col += UPD_THREADS) qbar[col] = qbar_g[((size_t)b * S + s) * d_qk + col];
-    __syncthreads();
-
-    auto ring_row = [&](int i) { const int r = k_start + i; return r >= k_cap ? r - k_cap : r; };
-    const T *ptail = pool_tail + ((size_t)b * P + p) * k_cap * d_pool;
-    const T *stail = sel_tail + ((size_t)b * P + p) * k_cap * d_sel;
-
-    // scores of the g oldest tail tokens: key = [pooled ; selected] (MLA, absorbed form) or the selected component (GQA)
-    for (int i = wave; i < g; i += UPD_THREADS / 64) {
-        const int r = ring_row(i);
-        float a = 0.f;
-        if (mla)
-            for (int col = lane; col < d_pool; col += 64) a += qbar[col] * Elt<T>::ld(ptail + (size_t)r * d_pool + col);
-        for (int col = lane; col < d_sel; col += 64) a += qbar[(mla ? d_pool : 0) + col] * Elt<T>::ld(stail + (size_t)r * d_sel + col);
-        a = wave_sum(a) * scale;
-        if (lane == 0) score[i] = a;
-    }
-    __syncthreads();
-
-    // group softmax and arg-max (every thread redundantly: g <= 64 values)
-    float mx = -INFINITY;
-    int best = 0;
-    for (int i = 0; i < g; ++i)
-        if (score[i] > mx) { mx = score[i]; best = i; }
-    float z = 0.f;
-    for (int i = 0; i < g; ++i) z += __expf(score[i] - mx);
-    const float inv_z = 1.f / z;
-
-    // pooled component: softmax-weighted sum; selected component: the arg-max token's, copied
-    T *prep = pool_rep + (((size_t)b * S + s) * m_cap + (m - 1)) * d_pool;
-    T *srep = sel_rep + (((size_t)b * S + s) * m_cap + (m - 1)) * d_sel;
-    for (int col = tid; col < d_pool; col += UPD_THREADS) {
-        float a = 0.f;
-        for (int i = 0; i < g; ++i) a += __expf(score[i] - mx) * inv_z * Elt<T>::ld(ptail + (size_t)ring_row(i) * d_pool + col);
-        Elt<T>::st(prep + col, a);
-    }
-    const int rb = ring_row(best);
-    for (int col = tid; col < d_sel; col += UPD_THREADS) srep[col] = stail[(size_t)rb * d_sel + col];
-    if (anchor != nullptr && tid == 0) anchor[((size_t)b * S + s) * m_cap + (m - 1)] = (m - 1) * g + best;
+    constexpr int EPC = Elt<T>::EPC;
+    __shared__ float per_row[2][WAVE];
+    const int lane = threadIdx.x, bs = blockIdx.x, d_pool = kp.d_pool, d_sel = kp.d_sel, mla = kp.mla;
+    const size_t src = mla ? bs / kp.S : bs;                 // (sequence, KV head) whose ring is read
+    Rows<T, 16> pool;
+    Rows<T, 4> sel;
+    pool.init((const T *)kp.pool_tail + src * kp.k_cap * d_pool, d_pool, d_pool / EPC, kp.g, lane, kp.k_start, kp.k_cap);
+    sel.init((const T *)kp.sel_tail + src * kp.k_cap * d_sel, d_sel, d_sel / EPC, kp.g, lane, kp.k_start, kp.k_cap);
+    pool.request();
+    sel.request();
+    const size_t unit = (size_t)bs * kp.m_cap + (kp.m - 1);
+    condense_group<T>(pool, sel, kp.qbar + (size_t)bs * (mla ? d_pool + d_sel : d_sel), mla, d_pool, kp.g, kp.scale, LCA_REDUCE_WEIGHTED,
+                      LCA_REDUCE_MAXSEL, (T *)kp.pool_rep + unit * d_pool, (T *)kp.sel_rep + unit * d_sel,
+                      kp.anchor != nullptr ? kp.anchor + unit : nullptr, (kp.m - 1) * kp.g, nullptr, per_row[0], per_row[1], lane);
 }
 
 template <typename T>
 hipError_t run(const UpdateArgs &a, hipStream_t st)
 {
     const Dims &d = a.d;
-    const size_t lds_bytes = (size_t)(d.d_qk + d.g) * sizeof(float);
-    cache_update_kernel<T><<<dim3(d.S, d.B), UPD_THREADS, lds_bytes, st>>>(
-        a.qbar, (const T *)a.pool_tail, (const T *)a.sel_tail, (T *)a.pool_rep, (T *)a.sel_rep, a.anchor, d.S, d.P, d.d_pool, d.d_sel, d.d_qk, d.g,
-        d.m, d.mode == LCA_MODE_MLA ? 1 : 0, d.scale, a.m_cap, a.k_cap, a.k_start);
+    const UpdParams kp{a.qbar, a.pool_tail, a.sel_tail, a.pool_rep, a.sel_rep, a.anchor, d.S, d.d_pool, d.d_sel, d.g, d.m,
+                       d.mode == LCA_MODE_MLA ? 1 : 0, a.m_cap, a.k_cap, a.k_start, d.scale};
+    cache_update_kernel<T><<<d.B * d.S, WAVE, 0, st>>>(kp);
     return hipGetLastError();
 }
 

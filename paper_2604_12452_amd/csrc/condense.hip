@@ -8,77 +8,12 @@
 //   condense_any_kernel    any sizes and reduce strategies.
 //
 // gfx950 only (wave64).
-#include "lca_internal.h"
+#include "group_rows.h"
 
 namespace lca {
 namespace {
 
-constexpr int WAVE = 64;
-
-__device__ __forceinline__ float bf16_bits_to_float(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
-__device__ __forceinline__ uint16_t float_to_bf16_bits(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);   // round to nearest even (inputs are finite)
-    return (uint16_t)(u >> 16);
-}
-
-template <typename T> struct Elt;
-template <> struct Elt<uint16_t> {      // bf16 bit patterns
-    static constexpr int EPC = 8;        // elements per 16-byte chunk
-    __device__ static float ld(const uint16_t *p) { return bf16_bits_to_float(*p); }
-    __device__ static void st(uint16_t *p, float v) { *p = float_to_bf16_bits(v); }
-    __device__ static void unpack(const uint4 &c, float *f)
-    {
-        const uint32_t w[4] = {c.x, c.y, c.z, c.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            f[2 * i] = __uint_as_float(w[i] << 16);
-            f[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
-        }
-    }
-    __device__ static uint4 pack(const float *f)
-    {
-        uint32_t w[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = (uint32_t)float_to_bf16_bits(f[2 * i]) | ((uint32_t)float_to_bf16_bits(f[2 * i + 1]) << 16);
-        return make_uint4(w[0], w[1], w[2], w[3]);
-    }
-};
-template <> struct Elt<f16_t> {         // fp16 bit patterns
-    static constexpr int EPC = 8;
-    __device__ static float ld(const f16_t *p) { return f16_bits_to_float(p->bits); }
-    __device__ static void st(f16_t *p, float v) { p->bits = float_to_f16_bits(v); }
-    __device__ static void unpack(const uint4 &c, float *f)
-    {
-        const uint32_t w[4] = {c.x, c.y, c.z, c.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            f[2 * i] = f16_bits_to_float((uint16_t)w[i]);
-            f[2 * i + 1] = f16_bits_to_float((uint16_t)(w[i] >> 16));
-        }
-    }
-    __device__ static uint4 pack(const float *f)
-    {
-        uint32_t w[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = (uint32_t)float_to_f16_bits(f[2 * i]) | ((uint32_t)float_to_f16_bits(f[2 * i + 1]) << 16);
-        return make_uint4(w[0], w[1], w[2], w[3]);
-    }
-};
-template <> struct Elt<float> {
-    static constexpr int EPC = 4;
-    __device__ static float ld(const float *p) { return *p; }
-    __device__ static void st(float *p, float v) { *p = v; }
-    __device__ static void unpack(const uint4 &c, float *f)
-    {
-        f[0] = __uint_as_float(c.x); f[1] = __uint_as_float(c.y); f[2] = __uint_as_float(c.z); f[3] = __uint_as_float(c.w);
-    }
-    __device__ static uint4 pack(const float *f)
-    {
-        return make_uint4(__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3]));
-    }
-};
+using namespace group_rows;
 
 // ---------------------------------------------------------------------------------------------
 // Summary query: qbar[b,s,x] = mean over t in [L-n_q, L), h in set s of Q[b,t,h,x].
@@ -152,11 +87,6 @@ __global__ __launch_bounds__(SQ_WAVES *WAVE) void summary_query_kernel(const T *
 // ---------------------------------------------------------------------------------------------
 // wave helpers
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ float readlane_f(float v, int lane)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
-}
-
 // Sum R per-lane partial values across the wave so that lane l ends with the total of value
 // (l >> (6 - log2 R)).  log2(R) halving exchanges, then an all-reduce over the remaining lane bits.
 template <int R>
@@ -357,144 +287,6 @@ void condense_reg_kernel(const T *__restrict__ POOL, const T *__restrict__ SEL, 
 // workgroup, one launch instead of two, the first took 8.2 us, but fp32 128 + 32 took longer (8.4 against 8.2 us) and 512 + 64
 // nearly twice as long; not kept.
 // ---------------------------------------------------------------------------------------------
-// Lane r holds v_r (r < g <= 2 top, top a power of two); returns, in every lane, the row with the largest v (lowest row on ties).
-__device__ __forceinline__ int wave_argmax(float v, int lane, int top, float *vmax_out)
-{
-    float bmax = v;
-    int brow = lane;
-    for (int mask = top; mask >= 1; mask >>= 1) {
-        const float os = __shfl_xor(bmax, mask, WAVE);
-        const int orow = __shfl_xor(brow, mask, WAVE);
-        if (os > bmax || (os == bmax && orow < brow)) { bmax = os; brow = orow; }
-    }
-    if (vmax_out) *vmax_out = readlane_f(bmax, 0);
-    return __builtin_amdgcn_readfirstlane(brow);
-}
-
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-template <typename T> __device__ __forceinline__ void unpack4(const uintx4 &c, float *f) { Elt<T>::unpack(make_uint4(c[0], c[1], c[2], c[3]), f); }
-template <typename T> __device__ __forceinline__ uintx4 pack4(const float *f)
-{
-    const uint4 u = Elt<T>::pack(f);
-    return uintx4{u.x, u.y, u.z, u.w};
-}
-
-// The rows of one component of a group, spread over a wavefront.
-template <typename T, int N> struct Rows {
-    const T *base;           // row 0 of the group
-    size_t stride;           // elements between rows
-    int chunks, g;           // 16-byte pieces per row, rows
-    int shift;               // log2 of the lanes per row
-    int row0, c0;            // this lane's first row and piece
-    bool held_all;           // one piece per lane and row, all of them in `held`
-    uintx4 held[N];
-
-    __device__ __forceinline__ void init(const T *b, size_t st, int ch, int gg, int lane)
-    {
-        base = b; stride = st; chunks = ch; g = gg;
-        shift = ch <= 1 ? 0 : min(6, 32 - __builtin_clz(ch - 1));
-        row0 = lane >> shift; c0 = lane & ((1 << shift) - 1);
-        held_all = ch <= WAVE && ((gg + (WAVE >> shift) - 1) >> (6 - shift)) <= N;
-    }
-    __device__ __forceinline__ int rows_per_load() const { return WAVE >> shift; }
-    __device__ __forceinline__ uintx4 fetch(int row, int c) const
-    {
-        return row < g && c < chunks ? *reinterpret_cast<const uintx4 *>(base + row * stride + c * Elt<T>::EPC) : uintx4{0, 0, 0, 0};
-    }
-    __device__ __forceinline__ void request()
-    {
-        if (!held_all) return;
-#pragma unroll
-        for (int i = 0; i < N; ++i) held[i] = i * rows_per_load() < g ? fetch(row0 + i * rows_per_load(), c0) : uintx4{0, 0, 0, 0};
-    }
-    // out[row] = per-row sums over the columns of term(element values, first column), plus `add`[row] if there is one
-    template <class F> __device__ __forceinline__ void row_sums(F term, float *out, const float *add) const
-    {
-        float f[Elt<T>::EPC];
-        if (held_all) {                          // (the exchanges of four loads' rows overlap)
-            static_assert(N % 4 == 0, "batches of four");
-#pragma unroll
-            for (int i0 = 0; i0 < N; i0 += 4) {
-                if (i0 * rows_per_load() >= g) break;
-                float a[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    unpack4<T>(held[i0 + i], f);
-                    a[i] = c0 < chunks ? term(f, c0 * Elt<T>::EPC) : 0.f;
-                }
-#pragma unroll 1
-                for (int mask = (1 << shift) >> 1; mask >= 1; mask >>= 1)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) a[i] += __shfl_xor(a[i], mask, WAVE);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int row = row0 + (i0 + i) * rows_per_load();
-                    if (c0 == 0 && row < g) out[row] = add != nullptr ? add[row] + a[i] : a[i];
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            return;
-        }
-        for (int r = 0; r < g; r += rows_per_load()) {
-            const int row = r + row0;
-            float a = 0.f;
-            for (int c = c0; c < chunks; c += WAVE) {
-                unpack4<T>(fetch(row, c), f);
-                a += term(f, c * Elt<T>::EPC);
-            }
-            for (int mask = (1 << shift) >> 1; mask >= 1; mask >>= 1) a += __shfl_xor(a, mask, WAVE);
-            if (c0 == 0 && row < g) out[row] = add != nullptr ? add[row] + a : a;
-        }
-    }
-    // out = sum of weight[row] * row
-    __device__ __forceinline__ void weighted_sum(const float *weight, T *out) const
-    {
-        constexpr int EPC = Elt<T>::EPC;
-        auto finish = [&](float (&acc)[EPC], int c) {
-#pragma unroll 1
-            for (int mask = 1 << shift; mask < WAVE; mask <<= 1)
-#pragma unroll
-                for (int e = 0; e < EPC; ++e) acc[e] += __shfl_xor(acc[e], mask, WAVE);
-            if (row0 == 0 && c < chunks) *reinterpret_cast<uintx4 *>(out + c * EPC) = pack4<T>(acc);
-        };
-        float f[EPC], acc[EPC];
-        if (held_all) {
-#pragma unroll
-            for (int e = 0; e < EPC; ++e) acc[e] = 0.f;
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const int row = row0 + i * rows_per_load();
-                if (i * rows_per_load() < g) {
-                    const float w = row < g ? weight[row] : 0.f;
-                    unpack4<T>(held[i], f);
-#pragma unroll
-                    for (int e = 0; e < EPC; ++e) acc[e] = row < g ? fmaf(w, f[e], acc[e]) : acc[e];
-                }
-            }
-            finish(acc, c0);
-            return;
-        }
-        for (int cb = 0; cb < chunks; cb += WAVE) {
-#pragma unroll
-            for (int e = 0; e < EPC; ++e) acc[e] = 0.f;
-#pragma unroll 4
-            for (int r = 0; r < g; r += rows_per_load()) {
-                const int row = r + row0;
-                const float w = row < g ? weight[row] : 0.f;
-                unpack4<T>(fetch(row, cb + c0), f);
-#pragma unroll
-                for (int e = 0; e < EPC; ++e) acc[e] = row < g ? fmaf(w, f[e], acc[e]) : acc[e];
-            }
-            finish(acc, cb + c0);
-        }
-    }
-    __device__ __forceinline__ void copy_row(int row, T *out, int lane) const      // bit for bit
-    {
-        for (int c = lane; c < chunks; c += WAVE)
-            *reinterpret_cast<uintx4 *>(out + c * Elt<T>::EPC) = *reinterpret_cast<const uintx4 *>(base + row * stride + c * Elt<T>::EPC);
-    }
-};
-
 constexpr int ANY_WAVES = 4;         // wavefronts (groups) per workgroup
 struct AnyParams {
     const void *POOL, *SEL;
@@ -528,56 +320,10 @@ __global__ __launch_bounds__(ANY_WAVES *WAVE) void condense_any_kernel(const Any
     sel.request();
     const float *const qb = kp.qbar + (size_t)bs * d_qk;
 
-    float *const row_val = per_row[wave][0], *const row_norm = per_row[wave][1];
     const size_t unit = (size_t)bs * m + j;
-    auto dot = [&](const float *q) {
-        return [q](const float *f, int col) {
-            float a = 0.f;
-#pragma unroll
-            for (int e = 0; e < EPC; ++e) a = fmaf(f[e], q[col + e], a);
-            return a;
-        };
-    };
-    auto square = [](const float *f, int) {
-        float a = 0.f;
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) a = fmaf(f[e], f[e], a);
-        return a;
-    };
-    if (mla) pool.row_sums(dot(qb), row_val, nullptr);
-    __builtin_amdgcn_wave_barrier();
-    sel.row_sums(dot(qb + (mla ? d_pool : 0)), row_val, mla ? row_val : nullptr);
-    __builtin_amdgcn_wave_barrier();
-    const float my_score = lane < g ? kp.scale * row_val[lane] : -INFINITY;      // lane r holds the score of row r
-    float bmax;
-    const int top = g <= 1 ? 0 : 1 << (31 - __builtin_clz(g - 1));               // lanes 0 .. 2 top - 1 hold the rows
-    const int brow = wave_argmax(my_score, lane, top, &bmax);
-    const float pmine = lane < g ? __expf(my_score - bmax) : 0.f;
-    float z = pmine;
-    for (int mask = top; mask >= 1; mask >>= 1) z += __shfl_xor(z, mask, WAVE);
-    const float alpha = pmine / readlane_f(z, 0);
-
-    // one component: a weighted sum of the group's rows, or one of them
-    auto reduce = [&](auto &rows, int strategy, T *out) {
-        int pick = brow;
-        if (strategy == LCA_REDUCE_MAXPOOL) {
-            rows.row_sums(square, row_norm, nullptr);
-            __builtin_amdgcn_wave_barrier();
-            pick = wave_argmax(lane < g ? row_norm[lane] : -INFINITY, lane, top, nullptr);
-        }
-        if (strategy == LCA_REDUCE_MAXSEL || strategy == LCA_REDUCE_MAXPOOL) {
-            rows.copy_row(pick, out, lane);
-            return;
-        }
-        __builtin_amdgcn_wave_barrier();
-        row_val[lane] = lane >= g ? 0.f : strategy == LCA_REDUCE_MEAN ? 1.f / (float)g : alpha;
-        __builtin_amdgcn_wave_barrier();
-        rows.weighted_sum(row_val, out);
-    };
-    reduce(pool, kp.pool_reduce, (T *)kp.pool_rep + unit * d_pool);
-    reduce(sel, kp.sel_reduce, (T *)kp.sel_rep + unit * d_sel);
-    if (lane == 0) kp.anchor[unit] = j * g + brow;
-    if (kp.alpha_dbg != nullptr && lane < g) kp.alpha_dbg[unit * g + lane] = alpha;
+    condense_group<T>(pool, sel, qb, mla, d_pool, g, kp.scale, kp.pool_reduce, kp.sel_reduce, (T *)kp.pool_rep + unit * d_pool,
+                      (T *)kp.sel_rep + unit * d_sel, kp.anchor + unit, j * g, kp.alpha_dbg != nullptr ? kp.alpha_dbg + unit * g : nullptr,
+                      per_row[wave][0], per_row[wave][1], lane);
 }
 
 template <typename T, int DP, int DS, int G, bool MLA>
