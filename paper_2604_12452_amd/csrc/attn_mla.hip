@@ -2,7 +2,7 @@
 // condensed context (section 4.3, Eq. 10; per-query partition of appendix A.2) and, with dense = 1,
 // plain causal attention in absorbed form (section 3, Eq. 5).
 //
-// One workgroup = 4 wavefronts = 128 query rows of one (sequence, head); each wavefront owns 32 rows
+// One workgroup = 4 wavefronts = 128 (query row, head) pairs of one sequence; each wavefront owns 32 rows of a head
 // and the whole 512-wide output, one wavefront per SIMD with the full 512-register budget:
 //   Q^T fragments   144 VGPRs (held for a whole work item)
 //   O^T accumulator 256 AGPRs (16 tiles of 32 value columns x 32 queries)
@@ -58,7 +58,7 @@ typedef __attribute__((address_space(3))) const char *lds_cptr;
 #define LCA_FENCE() __builtin_amdgcn_sched_barrier(0)
 
 constexpr int DP = 512, DS = 64, DQK = 576, DV = 512;
-constexpr int BM = 128;                 // query rows per workgroup
+constexpr int BM = 128;                 // (query row, head) pairs per workgroup
 constexpr int BN = 32;                  // entries per key tile
 constexpr int NSTAGE = 4;
 constexpr int RSB = 1040;               // LDS row stride of the latent part in bytes: 1024 + 16
@@ -87,6 +87,7 @@ struct MlaParams {
     float *lse;
     const uint16_t *W_up;   // UP variant: value up-projection W^UV in fragment order (pack_up_kernel), and O is [B, L, H, DU]
     int B, L, H, S, g, w, m, dense, n_qb;
+    int hw_log2;            // log2 of the heads of a work item (4, 2 or 1): its wavefronts are that many heads x 4 / heads groups of 32 rows
     float scale_log2, bias_log2;
 };
 
@@ -318,9 +319,10 @@ __device__ __forceinline__ void pv_tail(const PvFrags &f, const Pb &pb, floatx16
     LCA_FENCE();
 }
 
-// Everything one workgroup needs to know about one work item = 128 query rows of one (sequence, head).
+// Everything one wavefront needs to know about one work item = 128 (row, head) pairs of one sequence: BM / heads query rows of
+// each of its heads, which share a condensed set.
 struct Blk {
-    int b, h, t0, t_last;                    // sequence, head, first / last query row
+    int b, h, t0, t_last, t_w0;              // sequence, this wavefront's head, first / last query row of the item, first of the wavefront
     int t_row, mt_row, raw_lo_row;           // per lane: query row, representatives it sees, first raw token it sees
     int raw_lo_blk, mt_blk_hi;               // first raw token / representatives any row of the block sees
     int n_rep_tiles, n_tiles;
@@ -328,15 +330,17 @@ struct Blk {
     Seg rep_pool, rep_sel, raw_pool, raw_sel;     // the two segments: visible representatives, raw tokens 0 .. t_last of the sequence
 };
 
-__device__ __forceinline__ Blk make_blk(const MlaParams &kp, int b, int h, int qb, int wave, int n)
+__device__ __forceinline__ Blk make_blk(const MlaParams &kp, int b, int hg, int qb, int wave, int n)
 {
     Blk k;
     const int L = kp.L, g = kp.g, w = kp.w;
     auto groups_visible = [&](int t) { return (kp.dense || t + 1 <= w) ? 0 : (t + 1 - w) / g; };
+    const int rows = BM >> kp.hw_log2, h = (hg << kp.hw_log2) + (wave & ((1 << kp.hw_log2) - 1));
     k.b = b; k.h = h;
-    k.t0 = qb * BM;
-    k.t_last = min(k.t0 + BM, L) - 1;
-    const int t_wfirst = k.t0 + wave * 32, t_wlast = t_wfirst + 31;
+    k.t0 = qb * rows;
+    k.t_last = min(k.t0 + rows, L) - 1;
+    const int t_wfirst = k.t0 + (wave >> kp.hw_log2) * 32, t_wlast = t_wfirst + 31;
+    k.t_w0 = t_wfirst;
     k.t_row = t_wfirst + n;
     k.mt_row = groups_visible(k.t_row);
     k.raw_lo_row = k.mt_row * g;
@@ -471,10 +475,9 @@ __device__ __forceinline__ void issue_first_copies(const Blk &k, int wave, unsig
 // registers into fragments through a private 4 KB LDS buffer, one column block (four k-steps) at a time.
 __device__ __forceinline__ void load_q(const MlaParams &kp, const Blk &k, int wave, int lane, bf16x8 (&qf)[NKS])
 {
-    const int t_wfirst = k.t0 + wave * 32;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int t = min(t_wfirst + 8 * q + (lane >> 3), kp.L - 1);
+        const int t = min(k.t_w0 + 8 * q + (lane >> 3), kp.L - 1);
         const uint16_t *qp = kp.Q + (((size_t)k.b * kp.L + t) * kp.H + k.h) * DQK + (lane & 7) * 8;
 #pragma unroll
         for (int c = 0; c < NKS / 4; ++c) qf[4 * c + q] = *reinterpret_cast<const bf16x8 *>(qp + c * 64);
@@ -534,9 +537,9 @@ __device__ __forceinline__ float row_max(const floatx16 &sv, float c, float bias
 
 
 // Persistent kernel: one workgroup per CU walks a list of work items.  Workgroup w lives on XCD w%8 (round-
-// robin placement) and is slot w/8 of that XCD; the XCD's item list is (query blocks 2x, 2x+1, 2x+16, 2x+17, ...
-// of the heaviest-first order) x (all heads), so that at any time the slots of an XCD work on the heads of two
-// neighbouring query blocks, which see nearly the same keys, and share their K/V tiles in that XCD's L2.  The next item's queries and first
+// robin placement) and is slot w/8 of that XCD; the heaviest-first list of query blocks is dealt out to the XCDs in runs of 256
+// rows, back and forth, and an XCD's item list is (its blocks) x (all heads), so that at any time the slots of an XCD
+// work on the heads of 256 neighbouring rows, which see nearly the same keys, and share their K/V tiles in that XCD's L2.  The next item's queries and first
 // tiles are requested before the current item's output is written, so the transition costs no round trip.
 //
 // Iteration tl of the tile loop, after its barrier: the held-back last MFMAs of the O^T update of tile tl-1
@@ -610,14 +613,16 @@ __global__ __launch_bounds__(256) void attn_mla_kernel(const MlaParams kp)
     const unsigned lds0 = lds_address(&stages[0][0]);
 
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, n_slots = gridDim.x >> 3;
-    const int n_units = kp.n_qb * kp.B;                       // (query block, sequence) pairs, heaviest first
-    const int items_per_xcd = ((n_units + 15) / 16) * 2 * H;  // some may fall past n_units
-    auto item = [&](int kidx, int &b, int &h, int &qb) {      // false when the item does not exist
-        h = kidx % H;
-        const int j = kidx / H, ord = (j >> 1) * 16 + 2 * xcd + (j & 1);     // an XCD works on two neighbouring query blocks at a time
+    const int n_units = kp.n_qb * kp.B, n_hg = H >> kp.hw_log2;             // (query block, sequence) pairs, heaviest first; head groups
+    const int run = kp.hw_log2 + 1;                                         // log2 of the query blocks an XCD works on at a time (256 rows)
+    const int items_per_xcd = (((n_units - 1) >> (run + 3)) + 1) * (n_hg << run);   // some may fall past n_units
+    auto item = [&](int kidx, int &b, int &hg, int &qb) {     // false when the item does not exist
+        hg = kidx % n_hg;
+        const int j = kidx / n_hg, round = j >> run, pos = (xcd << run) + (j & ((1 << run) - 1)), last = (8 << run) - 1;
+        const int ord = (round << (run + 3)) + ((round & 1) ? last - pos : pos);     // every other round the other way: an even load
         b = ord % kp.B;
         qb = kp.n_qb - 1 - ord / kp.B;
-        return kidx < items_per_xcd && ord < n_units;
+        return ord < n_units;
     };
 
     // per-lane LDS byte offsets
@@ -633,7 +638,7 @@ __global__ __launch_bounds__(256) void attn_mla_kernel(const MlaParams kp)
     const float c = kp.scale_log2;
 
     int kidx = slot, ib, ih, iqb;
-    while (kidx < items_per_xcd && !item(kidx, ib, ih, iqb)) kidx += n_slots;   // items past n_units only sit at the list's end
+    while (kidx < items_per_xcd && !item(kidx, ib, ih, iqb)) kidx += n_slots;   // (items past n_units: in the last round)
     if (kidx >= items_per_xcd) return;
     Blk cur = make_blk(kp, ib, ih, iqb, wave, n);
 
@@ -761,9 +766,10 @@ __global__ __launch_bounds__(256) void attn_mla_kernel(const MlaParams kp)
 
         // request the next item's first tiles (stages 0..2) and queries before writing this item's output
         int nb, nh, nqb;
-        kidx += n_slots;
-        const bool has_next = item(kidx, nb, nh, nqb);
-        const int out_b = cur.b, out_h = cur.h, out_t0 = cur.t0;
+        do kidx += n_slots;
+        while (kidx < items_per_xcd && !item(kidx, nb, nh, nqb));
+        const bool has_next = kidx < items_per_xcd;
+        const int out_b = cur.b, out_h = cur.h, out_t0 = cur.t_w0;
         const float l_tot = st.l_run + __shfl_xor(st.l_run, 32, 64);
         const float inv = 1.f / l_tot;
         floatx16 up[UP ? DU / 32 : 1];
@@ -790,7 +796,7 @@ __global__ __launch_bounds__(256) void attn_mla_kernel(const MlaParams kp)
         constexpr int ORS = 128 * 2 + 16;                    // staging row stride (bytes)
         static_assert(4 * 32 * ORS <= STAGE_BYTES, "output staging must fit in one tile stage");
         char *obuf = &stages[3][0] + wave * 32 * ORS;
-        const int t_wfirst = out_t0 + wave * 32;
+        const int t_wfirst = out_t0;
         // The stores go through a buffer descriptor of this wavefront's rows of this head (row r at r*H*1 KB): scalar
         // offsets instead of 64-bit address arithmetic per store, and rows past the end of the sequence fall outside
         // the descriptor's range and are dropped.
@@ -859,11 +865,18 @@ hipError_t launch_attn_mla(const AttnArgs &a, hipStream_t st)
     kp.pool_rep = (const uint16_t *)a.pool_rep; kp.sel_rep = (const uint16_t *)a.sel_rep;
     kp.O = (uint16_t *)a.O; kp.lse = a.lse;
     kp.B = d.B; kp.L = d.L; kp.H = d.H; kp.S = d.S; kp.g = d.g; kp.w = d.w; kp.m = d.m; kp.dense = a.dense;
-    kp.n_qb = (d.L + BM - 1) / BM;
+    // Four heads x 32 rows share their key tiles where four heads share a set: 1024 + 32 tokens of window instead of 1024 + 128 are
+    // three tiles less per item (of 40 at 8K), and the boundary tiles are the same for every wavefront.  Measured with one head x 128
+    // rows / four heads x 32 rows (16 heads, one set, g = 16, w = 1024): L = 1500 76.0 / 71.2 us, 2500 104 / 75.8, 8192 338 / 300,
+    // 32768 1915 / 1767, 131072 17.72 / 17.22 ms; with the up-projection, where four heads read four matrices, L = 20000 1082 / 993.
+    const int hps = d.H / d.S;
+    kp.hw_log2 = hps % 4 == 0 ? 2 : hps % 2 == 0 ? 1 : 0;
+    const int rows = BM >> kp.hw_log2;
+    kp.n_qb = (d.L + rows - 1) / rows;
     kp.scale_log2 = d.scale * 1.4426950408889634f;
     kp.bias_log2 = d.rep_logit_bias * 1.4426950408889634f;
     // persistent grid: one workgroup per CU (a workgroup takes all of a CU's LDS and registers)
-    const long items = (((long)kp.n_qb * d.B + 15) / 16) * 16 * d.H;
+    const long run = 16l << kp.hw_log2, items = ((long)kp.n_qb * d.B + run - 1) / run * run * (d.H >> kp.hw_log2);
     const long cus = persistent_grid();
     long grid = items < cus ? items : cus;
     grid = (grid + 7) / 8 * 8;

@@ -1,0 +1,20 @@
+"""Work items of the MLA prefill kernel: four, two or one heads x 32, 64 or 128 rows, dealt out to the XCDs in runs of 256 rows,
+every other round the other way."""
+import pytest
+
+from paper_2604_12452_amd import inputs
+from tests.test_gpu_parity import _full_parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("L,g,w,H,S,B,dtype", [
+    (97, 8, 20, 12, 1, 2, "bf16"),        # three groups of four heads, four query blocks, the last of one row
+    (259, 16, 33, 6, 1, 1, "f16"),        # three groups of two heads x 64 rows
+    (260, 8, 16, 8, 2, 3, "bf16"),        # four heads per set, two sets
+    (133, 4, 9, 5, 1, 1, "bf16"),         # an odd number of heads: one head x 128 rows
+    (2100, 64, 20, 64, 1, 1, "bf16"),     # a second, reversed round with work for one XCD only; several items per slot and round
+])
+def test_mla_work_items(oracle, L, g, w, H, S, B, dtype):
+    wl = inputs.Workload("items", B=B, L=L, H=H, S=S, d_pool=512, d_sel=64, g=g, w=w, dtype=dtype, seed=70 + L)
+    _full_parity(oracle, wl, dense=L < 1000)
