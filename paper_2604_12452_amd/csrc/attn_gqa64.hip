@@ -10,10 +10,10 @@
 // must be cheap: a wavefront owns 64 query rows of ONE query head (two blocks of 32), and every key fragment and
 // every value fragment it reads from LDS feeds two MFMAs.
 //
-// Workgroup = 4 wavefronts = the four query heads of one KV head (of one group of four) x the same 64 query rows:
-// they see exactly the same keys and share every key/value tile.  (With 2 or 1 heads per KV head the wavefronts
-// are 2 heads x 2 groups of 64 rows, or 4 groups of 64 rows of one head.)  Tiles of 64 entries (K and V rows of 256 B)
-// are copied by direct-to-LDS loads into four 32 KB stages, three tiles ahead.  Rows sit at a 256-byte stride
+// Workgroup = 4 wavefronts = four (64 query rows, head) blocks of one KV head that share every key/value tile, numbered row block
+// by row block: with a multiple of four heads per KV head four heads x the same rows, with seven at most 128 rows apart
+// (items of one head x 256 rows took 162 us instead of 138 at L = 5003, 28 heads over 4 KV heads, fp16, 1396 instead of 1280 at
+// L = 40000, 70 instead of 63 at L = 6000, 12 heads over 4, bf16).  Tiles of 64 entries (K and V rows of 256 B) are copied by direct-to-LDS loads into four 32 KB stages, three tiles ahead.  Rows sit at a 256-byte stride
 // with their 16-byte chunks XOR-swizzled by row (at the source address of the copy), which keeps both read
 // patterns bank-conflict-free:
 //   S^T[key, query] = K Q^T      16-byte key reads, lane = S^T row m reads LDS row pi(m)
@@ -85,9 +85,9 @@ struct G64Params {
     uint16_t *O;
     float *lse;
     int B, L, H, S, g, w, m, dense;
-    int hw, hgs;        // query heads per work item (4, 2 or 1, a divisor of H/S: the wavefronts are hw heads x 4/hw groups of 64 rows); head groups per KV head
-    int n_qb, n_units;  // query blocks (of 256/hw rows) per sequence; KV-sharing units = B * S * hgs
-    unsigned g_magic, units_magic, hgs_magic, s_magic;     // for divisions by g, n_units, hgs and S (udiv_small)
+    int hps;            // query heads per KV head
+    int n_it, n_units;  // work items per (sequence, KV head); (sequence, KV head) pairs
+    unsigned g_magic, units_magic, hps_magic, s_magic;     // for divisions by g, n_units, hps and S (udiv_small)
     float scale_log2, bias_log2;
 };
 
@@ -120,7 +120,9 @@ __device__ __forceinline__ void dma_1k(unsigned voff, const int4v &rs, unsigned 
                  : : "v"(voff), "s"(rs), "s"(m0_base), "s"(soff), "n"(M0_ADD) : "scc", "memory");
 }
 
-// Everything one wavefront needs to know about one work item = 256/hw query rows of the hw heads of one head group.
+// Everything one wavefront needs to know about one work item.  The (64 rows, head) blocks of a KV head are numbered row block by
+// row block, the heads of a row block next to each other, and an item is four of them in a row, one per wavefront: whatever the
+// number of heads, the item's rows span no more of the sequence than they must (a window of 1024 tokens is 1024 + span entries).
 struct Blk {
     int b, h, t0, t_last, t_w0;              // sequence, this wavefront's query head, first / last query row of the item, first of the wavefront
     int t_row[2], mt_row[2], raw_lo_row[2];  // per lane and row block: query row, representatives it sees, first raw token it sees
@@ -131,19 +133,19 @@ struct Blk {
     unsigned rep_stride, raw_stride;         // bytes between rows of a segment
 };
 
-__device__ __forceinline__ Blk make_blk(const G64Params &kp, int unit, int qb, int wave, int n)
+__device__ __forceinline__ Blk make_blk(const G64Params &kp, int unit, int it, int wave, int n)
 {
     Blk k;
-    const int L = kp.L, g = kp.g, w = kp.w, hps = kp.H / kp.S;
+    const int L = kp.L, g = kp.g, w = kp.w, hps = kp.hps;
     auto groups_visible = [&](int t) { return (kp.dense || t + 1 <= w) ? 0 : (int)udiv_small(t + 1 - w, g, kp.g_magic); };
-    const int uq = udiv_small(unit, kp.hgs, kp.hgs_magic), hg = unit - uq * kp.hgs;
-    k.b = udiv_small(uq, kp.S, kp.s_magic);
-    const int s = uq - k.b * kp.S;
-    const int hi = wave & (kp.hw - 1), rg = wave / kp.hw, rows = BMW * (NW / kp.hw);     // hw is 1, 2 or 4
-    k.h = s * hps + hg * kp.hw + hi;
-    k.t0 = qb * rows;
-    k.t_last = min(k.t0 + rows, L) - 1;
-    k.t_w0 = k.t0 + rg * BMW;
+    auto row_block = [&](int u) { return (int)udiv_small(u, hps, kp.hps_magic); };
+    k.b = udiv_small(unit, kp.S, kp.s_magic);
+    const int s = unit - k.b * kp.S;
+    const int u = NW * it + wave, rb_w = row_block(u);
+    k.h = s * hps + (u - rb_w * hps);
+    k.t0 = row_block(NW * it) * BMW;
+    k.t_last = min(row_block(NW * it + NW - 1) * BMW + BMW, L) - 1;
+    k.t_w0 = rb_w * BMW;                     // (past the end of the sequence for a wavefront without a block)
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
         k.t_row[rb] = k.t_w0 + 32 * rb + n;
@@ -346,9 +348,9 @@ __device__ __forceinline__ void q_to_fragments(char *buf, int lane, bf16x8 (&qf)
 }
 
 // Persistent kernel: one workgroup per CU walks a list of work items.  Workgroup w lives on XCD w%8 (round-robin
-// placement) and is slot w/8 of that XCD.  Items are numbered (query block, heaviest first) x (unit = sequence x KV
-// head x head group) and item i belongs to XCD i%8: with a multiple of eight units every unit keeps to one XCD, whose
-// L2 then holds that KV head's representatives and the sliding raw window.
+// placement) and is slot w/8 of that XCD.  Items are numbered (latest rows, the heaviest, first) x (sequence, KV head) and item i
+// belongs to XCD i%8: with a multiple of eight pairs every one keeps to one XCD, whose L2 then holds that KV head's
+// representatives and the sliding raw window; with four it keeps to two.
 template <bool F16>
 __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params kp)
 {
@@ -361,12 +363,12 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
     const float c = kp.scale_log2;
 
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, n_slots = gridDim.x >> 3;
-    const int n_items = kp.n_qb * kp.n_units;
-    auto item = [&](int kidx, int &unit, int &qb) {           // item kidx of this XCD; false past the end
+    const int n_items = kp.n_it * kp.n_units;
+    auto item = [&](int kidx, int &unit, int &it) {           // item kidx of this XCD; false past the end
         const int i = kidx * 8 + xcd;
         const int iq = udiv_small(i, kp.n_units, kp.units_magic);
         unit = i - iq * kp.n_units;
-        qb = kp.n_qb - 1 - iq;
+        it = kp.n_it - 1 - iq;
         return i < n_items;
     };
 
@@ -731,19 +733,18 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
 
 }  // namespace
 
-// Query heads that share one work item (and with it every K/V tile read): the largest of 4, 2, 1 that divides the heads
-// per KV head; the heads of a KV head then form hps / that many groups (7 heads per KV head: seven groups of one).
-static int heads_per_item(int hps) { return hps % NW == 0 ? NW : hps % 2 == 0 ? 2 : 1; }
+// work items per (sequence, KV head): four (64 rows, head) blocks each
+static long items_per_unit(const Dims &d) { return (((long)d.L + BMW - 1) / BMW * (d.H / d.S) + NW - 1) / NW; }
 
 bool attn_gqa64_supported(const Dims &d)
 {
-    const int hps = d.H / d.S;
     // segment sizes and row offsets travel as 32-bit byte counts
-    // ... and item indices are divided with udiv_small
-    const int hw = heads_per_item(hps), rows = BMW * (NW / hw);
-    const long n_units = (long)d.B * d.S * (hps / hw), n_items = ((long)d.L + rows - 1) / rows * n_units;
+    // ... and item and block indices are divided with udiv_small
+    const int hps = d.H / d.S;
+    const long n_units = (long)d.B * d.S, n_it = items_per_unit(d), n_items = n_it * n_units;
     return (d.dtype == LCA_BF16 || d.dtype == LCA_F16) && d.mode == LCA_MODE_GQA && d.d_pool == D && d.d_sel == D && d.scale > 0.f &&
-           (long)(d.L + 4 * BN) * d.S * RB < (1l << 32) && (n_items + 8 * GRID) * n_units < (1l << 32) && (long)d.L * d.g < (1l << 31);
+           (long)(d.L + 4 * BN) * d.S * RB < (1l << 32) && (n_items + 8 * GRID) * n_units < (1l << 32) && (n_it + 1) * NW * hps < (1l << 32) &&
+           (long)d.L * d.g < (1l << 31);
 }
 
 hipError_t launch_attn_gqa64(const AttnArgs &a, hipStream_t st)
@@ -754,18 +755,15 @@ hipError_t launch_attn_gqa64(const AttnArgs &a, hipStream_t st)
     kp.k_rep = (const uint16_t *)a.sel_rep; kp.v_rep = (const uint16_t *)a.pool_rep;
     kp.O = (uint16_t *)a.O; kp.lse = a.lse;
     kp.B = d.B; kp.L = d.L; kp.H = d.H; kp.S = d.S; kp.g = d.g; kp.w = d.w; kp.m = d.m; kp.dense = a.dense;
-    const int hps = d.H / d.S;
-    kp.hw = heads_per_item(hps);
-    kp.hgs = hps / kp.hw;
-    const int rows = BMW * (NW / kp.hw);
-    kp.n_qb = (d.L + rows - 1) / rows;
-    kp.n_units = d.B * d.S * kp.hgs;
+    kp.hps = d.H / d.S;
+    kp.n_it = (int)items_per_unit(d);
+    kp.n_units = d.B * d.S;
     auto magic = [](int dv) { return dv > 1 ? (unsigned)((1ull << 32) / (unsigned)dv + 1) : 0u; };
-    kp.g_magic = magic(d.g); kp.units_magic = magic(kp.n_units); kp.hgs_magic = magic(kp.hgs); kp.s_magic = magic(d.S);
+    kp.g_magic = magic(d.g); kp.units_magic = magic(kp.n_units); kp.hps_magic = magic(kp.hps); kp.s_magic = magic(d.S);
     kp.scale_log2 = d.scale * 1.4426950408889634f;
     kp.bias_log2 = d.rep_logit_bias * 1.4426950408889634f;
     // persistent grid: one workgroup per CU (a workgroup takes 128 KB of LDS and most of the registers)
-    const long items = (long)kp.n_qb * kp.n_units;
+    const long items = (long)kp.n_it * kp.n_units;
     const long cus = persistent_grid();     // <= GRID
     long grid = items < cus ? items : cus;
     grid = (grid + 7) / 8 * 8;
