@@ -78,6 +78,7 @@ constexpr float L_LIMIT = 0x1p90f;      // a row sum beyond this (or not finite)
 // binades at the bottom.
 constexpr float P_LIMIT_F16 = 65000.f;
 constexpr float REF_SHIFT_F16 = 4.f;
+constexpr int FEW_REPS = 16;            // fp16: with fewer visible representatives an item starts with its raw tokens (make_blk)
 constexpr int RSRC_WORD3 = 0x00020000;  // raw buffer of dwords, gfx9 layout
 
 struct G64Params {
@@ -127,12 +128,13 @@ struct Blk {
     int b, h, t0, t_last, t_w0;              // sequence, this wavefront's query head, first / last query row of the item, first of the wavefront
     int t_row[2], mt_row[2], raw_lo_row[2];  // per lane and row block: query row, representatives it sees, first raw token it sees
     int raw_lo_blk, mt_blk_hi;               // first raw token / representatives any row of the block sees
-    int n_rep_tiles, n_tiles;
-    int rep_full_end, raw_full_lo, raw_full_hi;   // tiles every row of this wavefront sees completely (no masking)
+    int flip, n_first, n_tiles;              // 0: the representatives' tiles come first; -1: the raw tokens'; tiles of the first kind, of both
+    int rep_full_lo, rep_full_hi, raw_full_lo, raw_full_hi;   // tiles every row of this wavefront sees completely (no masking)
     Seg rep_k, rep_v, raw_k, raw_v;
     unsigned rep_stride, raw_stride;         // bytes between rows of a segment
 };
 
+template <bool F16>
 __device__ __forceinline__ Blk make_blk(const G64Params &kp, int unit, int it, int wave, int n)
 {
     Blk k;
@@ -154,12 +156,23 @@ __device__ __forceinline__ Blk make_blk(const G64Params &kp, int unit, int it, i
     }
     const int mt_w_lo = groups_visible(k.t_w0), mt_w_hi = groups_visible(k.t_w0 + BMW - 1);
     k.mt_blk_hi = groups_visible(k.t_last);
-    k.raw_lo_blk = groups_visible(k.t0) * g;
-    k.n_rep_tiles = (k.mt_blk_hi + BN - 1) / BN;
-    k.n_tiles = k.n_rep_tiles + (k.t_last + 1 - k.raw_lo_blk + BN - 1) / BN;
-    k.rep_full_end = mt_w_lo / BN;
-    k.raw_full_lo = k.n_rep_tiles + (mt_w_hi * g - k.raw_lo_blk + BN - 1) / BN;
-    k.raw_full_hi = k.n_rep_tiles + max(0, (k.t_w0 + 1 - k.raw_lo_blk) / BN);
+    const int mt_blk_lo = groups_visible(k.t0);
+    k.raw_lo_blk = mt_blk_lo * g;
+    // fp16: a row's reference is the largest of the first entries it sees, and later logits may rise by 20 binades over it before
+    // the item has to be repeated.  While the first representatives are a handful they are a poor sample (a row may see
+    // one): such items start with the raw tokens (a window of 32 or more), of which every row sees at least
+    // min(g, 32) in its first half tile.  Repeats
+    // cost L = 1100, 32 heads over 8 KV heads, 85 us instead of 34, L = 5003 136 instead of 110 (28 over 4: 138, now 97).  Starting
+    // every item with the raw tokens is no better: neighbouring tokens are alike, and 16 of them are a poor sample too (139 us).
+    const int n_rep = (k.mt_blk_hi + BN - 1) / BN, n_raw = (k.t_last + 1 - k.raw_lo_blk + BN - 1) / BN;
+    k.flip = F16 && w >= 32 ? lt_mask(mt_blk_lo, FEW_REPS) : 0;
+    const int rep0 = k.flip ? n_raw : 0, raw0 = k.flip ? 0 : n_rep;
+    k.n_first = k.flip ? n_raw : n_rep;
+    k.n_tiles = n_rep + n_raw;
+    k.rep_full_lo = rep0;
+    k.rep_full_hi = rep0 + mt_w_lo / BN;
+    k.raw_full_lo = raw0 + (mt_w_hi * g - k.raw_lo_blk + BN - 1) / BN;
+    k.raw_full_hi = raw0 + min(n_raw, max(0, (k.t_w0 + 1 - k.raw_lo_blk) / BN));
     // segments: representatives [B,S,m,128] (row stride 256 B), raw tokens [B,L,S,128] (row stride S*256 B)
     k.rep_stride = RB;
     k.raw_stride = kp.S * RB;
@@ -182,12 +195,12 @@ struct CopyCtl {
 __device__ __forceinline__ CopyCtl make_copy(const Blk &k, int tc, int sd, int wave, unsigned lds0)
 {
     CopyCtl c;
-    const int is_rep = lt_mask(tc, k.n_rep_tiles);
+    const int first = lt_mask(tc, k.n_first), is_rep = first ^ k.flip;
     const Seg &ks = is_rep ? k.rep_k : k.raw_k, &vs = is_rep ? k.rep_v : k.raw_v;
     c.k_rs = int4v{(int)ks.lo, (int)ks.hi, (int)ks.bytes, RSRC_WORD3};
     c.v_rs = int4v{(int)vs.lo, (int)vs.hi, (int)vs.bytes, RSRC_WORD3};
     c.stride = is_rep ? k.rep_stride : k.raw_stride;
-    const unsigned row0 = (is_rep ? tc * BN : k.raw_lo_blk + (tc - k.n_rep_tiles) * BN) + 4 * wave;
+    const unsigned row0 = (first ? tc : tc - k.n_first) * BN + (is_rep ? 0 : k.raw_lo_blk) + 4 * wave;
     c.soff[0] = row0 * c.stride;
     c.soff[1] = c.soff[0] + 16 * c.stride;
     c.soff[2] = c.soff[1] + 16 * c.stride;
@@ -203,7 +216,7 @@ template <int STEP>
 __device__ __forceinline__ void copy_step(CopyCtl &c, CopySel &t, const Blk &k, int tc, int wave, unsigned lds0)
 {
     if constexpr (STEP == 0) {
-        t.is_rep = lt_mask(tc, k.n_rep_tiles);
+        t.is_rep = lt_mask(tc, k.n_first) ^ k.flip;
         t.k0 = t.is_rep ? k.rep_k.lo : k.raw_k.lo;
         t.k1 = t.is_rep ? k.rep_k.hi : k.raw_k.hi;
         t.k2 = t.is_rep ? k.rep_k.bytes : k.raw_k.bytes;
@@ -215,7 +228,7 @@ __device__ __forceinline__ void copy_step(CopyCtl &c, CopySel &t, const Blk &k, 
         c.stride = t.is_rep ? k.rep_stride : k.raw_stride;
         LCA_PIN_S(t.v0); LCA_PIN_S(t.v1); LCA_PIN_S(t.v2); LCA_PIN_S(c.stride);
     } else if constexpr (STEP == 2) {
-        const unsigned row0 = (t.is_rep ? tc * BN : k.raw_lo_blk + (tc - k.n_rep_tiles) * BN) + 4 * wave;
+        const unsigned row0 = (tc < k.n_first ? tc : tc - k.n_first) * BN + (t.is_rep ? 0 : k.raw_lo_blk) + 4 * wave;
         c.soff[0] = row0 * c.stride;
         c.m0 = lds0 + (tc & (NSTAGE - 1)) * STAGE_BYTES + 4 * wave * RB;
         LCA_PIN_S(c.soff[0]); LCA_PIN_S(c.m0);
@@ -391,7 +404,7 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
 
     int kidx = slot, iu, iqb;
     if (!item(kidx, iu, iqb)) return;
-    Blk cur = make_blk(kp, iu, iqb, wave, n);
+    Blk cur = make_blk<F16>(kp, iu, iqb, wave, n);
 
     bf16x8 qf[2][NKS];
     floatx16 acc[2][NDV];
@@ -482,9 +495,10 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
             struct TileInfo { int is_rep, full, e0; float bias; };
             auto tile_info = [&](int tl) {
                 TileInfo ti;
-                ti.is_rep = lt_mask(tl, cur.n_rep_tiles);
-                ti.full = lt_mask(tl, cur.rep_full_end) | (~lt_mask(tl, cur.raw_full_lo) & lt_mask(tl, cur.raw_full_hi));
-                ti.e0 = ti.is_rep ? tl * BN : cur.raw_lo_blk + (tl - cur.n_rep_tiles) * BN;
+                const int first = lt_mask(tl, cur.n_first);
+                ti.is_rep = first ^ cur.flip;
+                ti.full = (~lt_mask(tl, cur.rep_full_lo) & lt_mask(tl, cur.rep_full_hi)) | (~lt_mask(tl, cur.raw_full_lo) & lt_mask(tl, cur.raw_full_hi));
+                ti.e0 = (first ? tl : tl - cur.n_first) * BN + (ti.is_rep ? 0 : cur.raw_lo_blk);
                 ti.bias = ti.is_rep ? kp.bias_log2 : 0.f;
                 return ti;
             };
@@ -685,7 +699,7 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
         const __amdgpu_buffer_rsrc_t o_rs = __builtin_amdgcn_make_buffer_rsrc(
             (void *)(kp.O + (((size_t)out_b * L + out_t0) * H + out_h) * D), (short)0, rows_valid > 0 ? ((rows_valid - 1) * H * D + D) * 2 : 0, RSRC_WORD3);
         if (has_next) {
-            cur = make_blk(kp, nu, nqb, wave, n);
+            cur = make_blk<F16>(kp, nu, nqb, wave, n);
             issue_first_copies(cur);
             load_q(kp, cur, lane, qf);
         }

@@ -1,4 +1,4 @@
-"""Work items of the MLA prefill kernel: four, two or one heads x 32, 64 or 128 rows, dealt out to the XCDs in runs of 256 rows,
+"""Work items of the prefill kernels.  MLA: four, two or one heads x 32, 64 or 128 rows, dealt out to the XCDs in runs of 256 rows,
 every other round the other way."""
 import pytest
 
@@ -18,3 +18,11 @@ pytestmark = pytest.mark.gpu
 def test_mla_work_items(oracle, L, g, w, H, S, B, dtype):
     wl = inputs.Workload("items", B=B, L=L, H=H, S=S, d_pool=512, d_sel=64, g=g, w=w, dtype=dtype, seed=70 + L)
     _full_parity(oracle, wl, dense=L < 1000)
+
+
+@pytest.mark.parametrize("L,g,w,H,S", [(620, 8, 64, 8, 2), (390, 16, 32, 7, 1), (300, 4, 31, 4, 1)])
+def test_gqa_fp16_items_on_both_sides_of_the_segment_order(oracle, L, g, w, H, S):
+    """fp16 items whose rows see fewer than 16 representatives start with the raw tokens, later ones with the representatives (a
+    window below 32 keeps the representatives first)."""
+    wl = inputs.Workload("order", B=1, L=L, H=H, S=S, d_pool=128, d_sel=128, g=g, w=w, dtype="f16", mode=inputs.MODE_GQA, theta=500000.0, seed=90 + L)
+    _full_parity(oracle, wl)
