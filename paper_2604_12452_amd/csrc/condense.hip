@@ -17,71 +17,20 @@ using namespace group_rows;
 
 // ---------------------------------------------------------------------------------------------
 // Summary query: qbar[b,s,x] = mean over t in [L-n_q, L), h in set s of Q[b,t,h,x].
-// One workgroup of 16 wavefronts per (b, s, 16 chunks of 16 bytes): a load covers 256 bytes of four (t, h) rows, so the 64
-// row slots of the workgroup take the 256 rows of 16 queries x 16 heads in four loads per lane, all in flight at once; the
-// partial sums are merged in a fixed order (deterministic), the four rows of a wavefront by exchanges, the wavefronts through
-// LDS.  Bound by the memory round trip: the lca_condense call of 29 groups at 512 + 64 took
-// 11.2 us with 64 chunks per workgroup and one row per load, and takes 8.4 us.
+// One workgroup per (b, s, 16 chunks of 16 bytes), see summary_columns.  Bound by the memory round trip: the lca_condense call of
+// 29 groups at 512 + 64 took 11.2 us with 64 chunks per workgroup and one row per load, and takes 8.4 us.
 // ---------------------------------------------------------------------------------------------
 constexpr int SQ_WAVES = 16;
-constexpr int SQ_DEPTH = 8;
-constexpr int SQ_CHUNKS = 16;
-constexpr int SQ_SLOTS = SQ_WAVES * (WAVE / SQ_CHUNKS);
 template <typename T>
 __global__ __launch_bounds__(SQ_WAVES *WAVE) void summary_query_kernel(const T *__restrict__ Q, float *__restrict__ qbar, int L, int H, int S,
                                                                        int d_qk, int n_q)
 {
-    constexpr int EPC = Elt<T>::EPC;
-    __shared__ float part[SQ_WAVES][SQ_CHUNKS][EPC + 1];
-    const int n_chunks = d_qk / EPC;
+    __shared__ SummaryPart<T, SQ_WAVES> part;
+    const int n_chunks = d_qk / Elt<T>::EPC;
     const int xblocks = (n_chunks + SQ_CHUNKS - 1) / SQ_CHUNKS;
     const int bs = blockIdx.x / xblocks, xb = blockIdx.x % xblocks;
     const int b = bs / S, s = bs % S, hps = H / S;
-    const int sub = threadIdx.x % SQ_CHUNKS, slot = threadIdx.x / SQ_CHUNKS, wave = threadIdx.x / WAVE;
-    const int chunk = xb * SQ_CHUNKS + sub;
-    const int n = n_q * hps;                       // (t, h) pairs, pair u -> t = L - n_q + u / hps, h = s*hps + u % hps
-    float acc[EPC];
-#pragma unroll
-    for (int e = 0; e < EPC; ++e) acc[e] = 0.f;
-    if (chunk < n_chunks) {
-        const int step_t = SQ_SLOTS / hps, step_h = SQ_SLOTS % hps;
-        int ut = slot / hps, uh = slot % hps;       // pair u = slot + 64 j  ->  (u / hps, u % hps), stepped with carry
-        const T *const base = Q + ((size_t)b * L + (L - n_q)) * H * d_qk + (size_t)s * hps * d_qk + chunk * EPC;
-        for (int u0 = slot; u0 < n; u0 += SQ_SLOTS * SQ_DEPTH) {
-            uint4 v[SQ_DEPTH];
-#pragma unroll
-            for (int i = 0; i < SQ_DEPTH; ++i) {
-                const int u = u0 + i * SQ_SLOTS;
-                v[i] = u < n ? *reinterpret_cast<const uint4 *>(base + ((size_t)ut * H + uh) * d_qk) : make_uint4(0, 0, 0, 0);
-                ut += step_t; uh += step_h;
-                if (uh >= hps) { uh -= hps; ++ut; }
-            }
-#pragma unroll
-            for (int i = 0; i < SQ_DEPTH; ++i) {
-                float f[EPC];
-                Elt<T>::unpack(v[i], f);
-#pragma unroll
-                for (int e = 0; e < EPC; ++e) acc[e] += f[e];
-            }
-        }
-    }
-#pragma unroll
-    for (int mask = SQ_CHUNKS; mask < WAVE; mask <<= 1)
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) acc[e] += __shfl_xor(acc[e], mask, WAVE);
-    if ((threadIdx.x & (WAVE - 1)) < SQ_CHUNKS) {
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) part[wave][sub][e] = acc[e];
-    }
-    __syncthreads();
-    // thread x sums the 16 partial values of component x % EPC of chunk x / EPC (wavefront order: the same sum on every run)
-    const int ol = threadIdx.x / EPC, oe = threadIdx.x % EPC, ochunk = xb * SQ_CHUNKS + ol;
-    if (ol < SQ_CHUNKS && ochunk < n_chunks) {
-        float t = 0.f;
-#pragma unroll
-        for (int wv = 0; wv < SQ_WAVES; ++wv) t += part[wv][ol][oe];
-        qbar[(size_t)bs * d_qk + ochunk * EPC + oe] = t / (float)n;
-    }
+    summary_columns<SQ_WAVES>(Q + (((size_t)b * L + (L - n_q)) * H + (size_t)s * hps) * d_qk, H, hps, d_qk, n_q, xb, part, qbar + (size_t)bs * d_qk);
 }
 
 // ---------------------------------------------------------------------------------------------

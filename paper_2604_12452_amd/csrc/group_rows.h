@@ -214,6 +214,67 @@ template <typename T, int N> struct Rows {
     }
 };
 
+// Summary query: the mean of n_q hps query rows, hps neighbouring heads of each of n_q tokens.
+// WAVES wavefronts take 16 chunks of 16 bytes (SQ_CHUNKS, block xb of them): a load covers 256 bytes of four rows, so the 64 row
+// slots of 16 wavefronts take the 256 rows of 16 queries x 16 heads in four loads per lane, all in flight at once; the partial
+// sums are merged in a fixed order (deterministic), the four rows of a wavefront by exchanges, the wavefronts through LDS.
+constexpr int SQ_DEPTH = 8;
+constexpr int SQ_CHUNKS = 16;
+template <typename T, int WAVES> using SummaryPart = float[WAVES][SQ_CHUNKS][Elt<T>::EPC + 1];
+// `rows`: the first token's first head; tokens are H rows apart.  `out`: the d_qk sums' means (memory or LDS).
+template <int WAVES, typename T>
+__device__ __forceinline__ void summary_columns(const T *rows, int H, int hps, int d_qk, int n_q, int xb, SummaryPart<T, WAVES> &part, float *out)
+{
+    constexpr int EPC = Elt<T>::EPC, SQ_SLOTS = WAVES * (WAVE / SQ_CHUNKS);
+    static_assert(WAVES * WAVE >= SQ_CHUNKS * EPC, "a thread per component");
+    const int n_chunks = d_qk / EPC;
+    const int sub = threadIdx.x % SQ_CHUNKS, slot = threadIdx.x / SQ_CHUNKS, wave = threadIdx.x / WAVE;
+    const int chunk = xb * SQ_CHUNKS + sub;
+    const int n = n_q * hps;                       // row u is head u % hps of token u / hps
+    float acc[EPC];
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) acc[e] = 0.f;
+    if (chunk < n_chunks) {
+        const int step_t = SQ_SLOTS / hps, step_h = SQ_SLOTS % hps;
+        int ut = slot / hps, uh = slot % hps;       // pair u = slot + 64 j  ->  (u / hps, u % hps), stepped with carry
+        const T *const base = rows + chunk * EPC;
+        for (int u0 = slot; u0 < n; u0 += SQ_SLOTS * SQ_DEPTH) {
+            uint4 v[SQ_DEPTH];
+#pragma unroll
+            for (int i = 0; i < SQ_DEPTH; ++i) {
+                const int u = u0 + i * SQ_SLOTS;
+                v[i] = u < n ? *reinterpret_cast<const uint4 *>(base + ((size_t)ut * H + uh) * d_qk) : make_uint4(0, 0, 0, 0);
+                ut += step_t; uh += step_h;
+                if (uh >= hps) { uh -= hps; ++ut; }
+            }
+#pragma unroll
+            for (int i = 0; i < SQ_DEPTH; ++i) {
+                float f[EPC];
+                Elt<T>::unpack(v[i], f);
+#pragma unroll
+                for (int e = 0; e < EPC; ++e) acc[e] += f[e];
+            }
+        }
+    }
+#pragma unroll
+    for (int mask = SQ_CHUNKS; mask < WAVE; mask <<= 1)
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) acc[e] += __shfl_xor(acc[e], mask, WAVE);
+    if ((threadIdx.x & (WAVE - 1)) < SQ_CHUNKS) {
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) part[wave][sub][e] = acc[e];
+    }
+    __syncthreads();
+    // thread x sums the wavefronts' partial values of component x % EPC of chunk x / EPC (wavefront order: the same sum on every run)
+    const int ol = threadIdx.x / EPC, oe = threadIdx.x % EPC, ochunk = xb * SQ_CHUNKS + ol;
+    if (ol < SQ_CHUNKS && ochunk < n_chunks) {
+        float t = 0.f;
+#pragma unroll
+        for (int wv = 0; wv < WAVES; ++wv) t += part[wv][ol][oe];
+        out[ochunk * EPC + oe] = t / (float)n;
+    }
+}
+
 // One group by one wavefront: scores against the summary query `qb` (Eq. 6), both components reduced (Eq. 7, Eq. 8 or an ablation's
 // strategy), the anchor's token index (first_token + row) and, if asked for, the weights.  row_val, row_norm: 64 floats of LDS each,
 // the wavefront's own.
