@@ -229,17 +229,16 @@ __global__ __launch_bounds__(WAVE *NWAVE) void decode_split_kernel(const T *__re
 }
 
 // One workgroup per (b, set, head-in-set): blockIdx.x = (b*S + s)*HPS + h.  The weights of the splits,
-// exp(max_sp - max) / sum, are computed once into LDS; then thread (group, column pair) sums every GROUPS-th run of eight
+// exp(max_sp - max) / sum, are computed once into LDS; then thread (group, column pair) sums every MERGE_GROUPS-th run of eight
 // splits' rows with 8-byte loads, eight of them in flight, and the groups' sums are added in order through LDS.  DP is even;
-// rows start 8 bytes into a (DP + 2)-float record, so 8 bytes is the alignment there is.  GROUPS = 4 where there are more
-// than sixteen splits: one group takes a round trip to memory per eight of them (B = 1, L = 131072 at 512 + 64, 72 splits:
-// the step 17.7 -> 17.0 us).
-constexpr int MERGE_THREADS = 256;
-template <typename T, int GROUPS>
-__global__ __launch_bounds__(MERGE_THREADS *GROUPS) void decode_merge_kernel(const float *__restrict__ part, T *__restrict__ O, int HPS, int DP, int splits)
+// rows start 8 bytes into a (DP + 2)-float record, so 8 bytes is the alignment there is.  For more than 64 splits (one or two
+// lonely caches); fewer go to decode_merge_few_kernel.
+constexpr int MERGE_THREADS = 256, MERGE_GROUPS = 4;
+template <typename T>
+__global__ __launch_bounds__(MERGE_THREADS *MERGE_GROUPS) void decode_merge_kernel(const float *__restrict__ part, T *__restrict__ O, int HPS, int DP, int splits)
 {
-    extern __shared__ float wgt[];                        // [splits], then [GROUPS - 1][DP] partial sums
-    __shared__ float red[MERGE_THREADS * GROUPS / WAVE];
+    extern __shared__ float wgt[];                        // [splits], then [MERGE_GROUPS - 1][DP] partial sums
+    __shared__ float red[MERGE_THREADS * MERGE_GROUPS / WAVE];
     const size_t bs = blockIdx.x / HPS;
     const int h = blockIdx.x % HPS, tid = threadIdx.x, group = tid / MERGE_THREADS;
     const float *base = part + (bs * splits * HPS + h) * (size_t)(DP + 2);
@@ -253,14 +252,14 @@ __global__ __launch_bounds__(MERGE_THREADS *GROUPS) void decode_merge_kernel(con
         if ((tid & (WAVE - 1)) == 0) red[tid / WAVE] = v;
         __syncthreads();
         float r = red[0];
-        for (int i = 1; i < MERGE_THREADS * GROUPS / WAVE; ++i) r = is_max ? fmaxf(r, red[i]) : r + red[i];
+        for (int i = 1; i < MERGE_THREADS * MERGE_GROUPS / WAVE; ++i) r = is_max ? fmaxf(r, red[i]) : r + red[i];
         return r;
     };
     float mx = -INFINITY;
-    for (int sp = tid; sp < splits; sp += MERGE_THREADS * GROUPS) mx = fmaxf(mx, base[sp * stride]);
+    for (int sp = tid; sp < splits; sp += MERGE_THREADS * MERGE_GROUPS) mx = fmaxf(mx, base[sp * stride]);
     mx = block_reduce(mx, true);
     float l = 0.f;
-    for (int sp = tid; sp < splits; sp += MERGE_THREADS * GROUPS) {
+    for (int sp = tid; sp < splits; sp += MERGE_THREADS * MERGE_GROUPS) {
         const float e = __expf(base[sp * stride] - mx);
         wgt[sp] = e;
         l += base[sp * stride + 1] * e;
@@ -274,7 +273,7 @@ __global__ __launch_bounds__(MERGE_THREADS *GROUPS) void decode_merge_kernel(con
         const float *col = base + 2 + x;
         if (x < DP) {
             int sp = 8 * group;
-            for (; sp + 8 <= splits; sp += 8 * GROUPS) {
+            for (; sp + 8 <= splits; sp += 8 * MERGE_GROUPS) {
                 float2 v[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float2 *>(col + (sp + u) * stride);
@@ -287,25 +286,81 @@ __global__ __launch_bounds__(MERGE_THREADS *GROUPS) void decode_merge_kernel(con
                 a1 = fmaf(v.y, wgt[i], a1);
             }
         }
-        if (GROUPS > 1) {
-            if (group > 0 && x < DP) { psum[(group - 1) * DP + x] = a0; psum[(group - 1) * DP + x + 1] = a1; }
-            __syncthreads();
-            if (group == 0 && x < DP)
-                for (int i = 0; i < GROUPS - 1; ++i) { a0 += psum[i * DP + x]; a1 += psum[i * DP + x + 1]; }
-        }
+        if (group > 0 && x < DP) { psum[(group - 1) * DP + x] = a0; psum[(group - 1) * DP + x + 1] = a1; }
+        __syncthreads();
+        if (group == 0 && x < DP)
+            for (int i = 0; i < MERGE_GROUPS - 1; ++i) { a0 += psum[i * DP + x]; a1 += psum[i * DP + x + 1]; }
         if (group == 0 && x < DP) {
             DElt<T>::st(O + (size_t)blockIdx.x * DP + x, a0 * inv);
             DElt<T>::st(O + (size_t)blockIdx.x * DP + x + 1, a1 * inv);
         }
     }
 }
+// The same for up to 64 splits and 512 columns, in one round trip to memory: lane l of every wavefront reads the maximum and the sum
+// of split l and finds the weights by itself, and the up to SPAN rows that a thread adds up are requested before that.
+// GROUPS groups of wavefronts take SPAN splits each.  Bound by launch latency and that round trip: with the
+// reductions over LDS barriers and the rows requested after them the kernel took 4.0 us of a step of 13.9 (one sequence, 512 + 64).
+// Eight rows per thread where that is enough, so that short steps request no more than there is; four groups above sixteen
+// splits.  Together with the merge inside the split kernels (all reads in flight, nothing rescaled before it is written), the
+// step before / now, back to back in a graph: 512 + 64, 16 heads, B = 1, L = 700 13.2 / 11.2 us, 4001 13.9 / 12.1, 131072 16.3 / 15.6;
+// B = 8, 4001 16.0 / 14.1; B = 32, 131072 66.4 / 65.1; 28 heads over 4 KV heads, B = 5, L = 16016 9.7 / 8.5; 32 over 8, B = 1,
+// L = 65536 10.6 / 9.0.
+template <typename T, int GROUPS, int SPAN>
+__global__ __launch_bounds__(MERGE_THREADS *GROUPS) void decode_merge_few_kernel(const float *__restrict__ part, T *__restrict__ O, int HPS, int DP, int splits)
+{
+    __shared__ float2 psum[GROUPS > 1 ? GROUPS - 1 : 1][MERGE_THREADS];
+    const size_t bs = blockIdx.x / HPS;
+    const int h = blockIdx.x % HPS, lane = threadIdx.x & (WAVE - 1), per_group = blockDim.x / GROUPS;
+    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x / per_group), x = 2 * (threadIdx.x % per_group);
+    const float *base = part + (bs * splits * HPS + h) * (size_t)(DP + 2);
+    const size_t stride = (size_t)HPS * (DP + 2);
+    const float2 ml = lane < splits ? *reinterpret_cast<const float2 *>(base + lane * stride) : float2{-INFINITY, 0.f};
+    const int sp0 = group * SPAN;
+    float2 v[SPAN];
+#pragma unroll
+    for (int u = 0; u < SPAN; ++u)
+        v[u] = sp0 + u < splits && x < DP ? *reinterpret_cast<const float2 *>(base + 2 + x + (sp0 + u) * stride) : float2{0.f, 0.f};
+    float mx = ml.x;
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, WAVE));
+    const float e = lane < splits ? __expf(ml.x - mx) : 0.f;
+    float l = lane < splits ? ml.y * e : 0.f;
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) l += __shfl_xor(l, o, WAVE);
+    float2 sum = float2{0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < SPAN; ++u)
+        if (sp0 + u < splits) {
+            const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(e), sp0 + u));
+            sum.x = fmaf(v[u].x, w, sum.x);
+            sum.y = fmaf(v[u].y, w, sum.y);
+        }
+    if constexpr (GROUPS > 1) {
+        if (group > 0) psum[group - 1][x / 2] = sum;
+        __syncthreads();
+        if (group > 0) return;
+#pragma unroll
+        for (int i = 0; i < GROUPS - 1; ++i) { sum.x += psum[i][x / 2].x; sum.y += psum[i][x / 2].y; }
+    }
+    const float inv = 1.f / l;
+    if (x < DP) {
+        DElt<T>::st(O + (size_t)blockIdx.x * DP + x, sum.x * inv);
+        DElt<T>::st(O + (size_t)blockIdx.x * DP + x + 1, sum.y * inv);
+    }
+}
 template <typename T> void launch_merge(const DecodeArgs &a, int splits, hipStream_t st)
 {
     const Dims &d = a.d;
-    if (splits > 16)
-        decode_merge_kernel<T, 4><<<d.B * d.H, MERGE_THREADS * 4, (splits + 3 * d.d_pool) * sizeof(float), st>>>(a.part, (T *)a.O, d.H / d.S, d.d_pool, splits);
-    else
-        decode_merge_kernel<T, 1><<<d.B * d.H, MERGE_THREADS, splits * sizeof(float), st>>>(a.part, (T *)a.O, d.H / d.S, d.d_pool, splits);
+    const unsigned grid = d.B * d.H;
+    const int hps = d.H / d.S;
+    if (splits <= WAVE && d.d_pool <= 2 * MERGE_THREADS) {
+        const int threads = (d.d_pool / 2 + WAVE - 1) / WAVE * WAVE;       // two columns each
+        if (splits <= 8) decode_merge_few_kernel<T, 1, 8><<<grid, threads, 0, st>>>(a.part, (T *)a.O, hps, d.d_pool, splits);
+        else if (splits <= 16) decode_merge_few_kernel<T, 1, 16><<<grid, threads, 0, st>>>(a.part, (T *)a.O, hps, d.d_pool, splits);
+        else decode_merge_few_kernel<T, 4, 16><<<grid, threads * 4, 0, st>>>(a.part, (T *)a.O, hps, d.d_pool, splits);
+    } else {
+        decode_merge_kernel<T><<<grid, MERGE_THREADS * MERGE_GROUPS, (splits + (MERGE_GROUPS - 1) * d.d_pool) * sizeof(float), st>>>(a.part, (T *)a.O, hps, d.d_pool, splits);
+    }
 }
 
 template <typename T, int DP, int DS, bool MLA, int HPS>

@@ -43,8 +43,8 @@ constexpr int TILE_BYTES = 2 * BN * RB;         // 16 KB
 constexpr int NKS = D / 32;                     // 4 k-steps of S^T
 constexpr int NDT = D / 16;                     // 8 value tiles
 constexpr int COPIES = 2 * BN / 4;              // direct-to-LDS loads per tile (four rows each): 16
-constexpr int MROW = D + 4;                     // floats per head of a wavefront's rescaled output in LDS (merge at the end)
-static_assert(16 * MROW * 4 <= 2 * TILE_BYTES, "the rescaled output of 16 heads fits a wavefront's tile buffers");
+constexpr int MROW = D + 4;                     // floats per head of a wavefront's output in LDS (merge at the end)
+static_assert(16 * MROW * 4 <= 2 * TILE_BYTES, "the output of 16 heads fits a wavefront's tile buffers");
 constexpr float NEG_BIG = -1.0e30f;
 constexpr float LN2 = 0.6931471805599453f;
 constexpr float SUM_LIMIT = 0x1p100f;
@@ -98,7 +98,6 @@ __global__ __launch_bounds__(256, 1) void decode_gqa_mfma_kernel(const DgParams 
     typedef E ex4 __attribute__((ext_vector_type(4)));
     __shared__ __attribute__((aligned(1024))) char bufs[4][2][TILE_BYTES];
     __shared__ float wave_ml[4][16][2];                                     // (reference, sum) per wavefront and head
-    __shared__ float l_heads[16];                                           // merged sum per head
 
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, q4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -311,48 +310,58 @@ __global__ __launch_bounds__(256, 1) void decode_gqa_mfma_kernel(const DgParams 
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                      // the last tile's reads are done before the buffers are reused
 
     // The four wavefronts' results (reference, sum, unnormalised output per head) are merged here, through LDS, so that
-    // one partial result per workgroup goes to memory: each wavefront publishes its references and sums, rescales its
-    // accumulators to the common reference into its own (now idle) tile buffers, and then adds up a quarter of the
-    // value columns over the four wavefronts' buffers.
+    // one partial result per workgroup goes to memory: each wavefront publishes its references and sums and leaves its
+    // accumulators as they are in its own (now idle) tile buffers; then wavefront w adds up heads w, w + 4, .. over the four
+    // wavefronts' buffers, scaled to the common reference on the way, and writes them: as this workgroup's partial result
+    // (natural-log units), or -- when the workgroup has the whole (sequence, KV head) to itself -- normalised, as the final
+    // output.  All of a wavefront's reads are in flight together.
     const bool any = t_lo < t_hi;
+    {
+        float *mine = reinterpret_cast<float *>(buf0) + col * MROW + 4 * q4;   // [head][MROW] floats
+#pragma unroll
+        for (int t = 0; t < NDT; ++t) *reinterpret_cast<floatx4 *>(mine + 16 * t) = acc[t];
+    }
     if (q4 == 0) {
         wave_ml[wave][col][0] = any ? m_ref : -INFINITY;
         wave_ml[wave][col][1] = any ? l_tot : 0.f;
     }
     __syncthreads();
-    float m_all = -INFINITY;
+    float m_all = -INFINITY, l_all = 0.f, factor[4];                        // of head `col`
 #pragma unroll
     for (int w = 0; w < 4; ++w) m_all = fmaxf(m_all, wave_ml[w][col][0]);
-    float l_all = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
         const float mw = wave_ml[w][col][0];
-        l_all += mw == -INFINITY ? 0.f : wave_ml[w][col][1] * __builtin_amdgcn_exp2f(mw - m_all);
+        factor[w] = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - m_all);
+        l_all += wave_ml[w][col][1] * factor[w];
     }
-    {
-        const float f = any ? __builtin_amdgcn_exp2f(m_ref - m_all) : 0.f;
-        float *mine = reinterpret_cast<float *>(buf0) + col * MROW + 4 * q4;   // [head][MROW] floats
-#pragma unroll
-        for (int t = 0; t < NDT; ++t) {
-            floatx4 v = acc[t];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = any ? v[r] * f : 0.f;
-            *reinterpret_cast<floatx4 *>(mine + 16 * t) = v;
-        }
-    }
-    if (wave == 0 && q4 == 0) l_heads[col] = l_all;
-    __syncthreads();
-    // wavefront w adds up value columns [32 w, 32 w + 32) of every head (lane l: head l >> 5 + 2 j in step j, column
-    // 32 w + (l & 31)) and writes them: as this workgroup's partial result (natural-log units), or -- when the workgroup
-    // has the whole (sequence, KV head) to itself -- normalised, as the final output
+    const float inv = 1.f / l_all;
     float *dst0 = kp.part + ((size_t)bs * wg_per_bs + blockIdx.x % wg_per_bs) * kp.hps * (D + 2);
-    for (int h = lane >> 5; h < kp.hps; h += 2) {
-        const int x = 32 * wave + (lane & 31);
-        float sum = 0.f;
+    auto of_head = [](float v, int h) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), h)); };   // (lane h: head h)
+    float2 v[4][4];
 #pragma unroll
-        for (int w = 0; w < 4; ++w) sum += reinterpret_cast<const float *>(bufs[w][0])[h * MROW + x];
-        if (kp.O != nullptr) reinterpret_cast<E *>(kp.O)[((size_t)bs * kp.hps + h) * D + x] = (E)(sum / l_heads[h]);
-        else dst0[(size_t)h * (D + 2) + 2 + x] = sum;
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            if (wave + 4 * i < kp.hps) v[i][w] = *reinterpret_cast<const float2 *>(reinterpret_cast<const float *>(bufs[w][0]) + (wave + 4 * i) * MROW + 2 * lane);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int h = wave + 4 * i;
+        if (h >= kp.hps) break;
+        float2 sum = float2{0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float f = of_head(factor[w], h);
+            sum.x = fmaf(v[i][w].x, f, sum.x);
+            sum.y = fmaf(v[i][w].y, f, sum.y);
+        }
+        if (kp.O != nullptr) {
+            typedef E ex2 __attribute__((ext_vector_type(2)));
+            const float n = of_head(inv, h);
+            *reinterpret_cast<ex2 *>(reinterpret_cast<E *>(kp.O) + ((size_t)bs * kp.hps + h) * D + 2 * lane) = ex2{(E)(sum.x * n), (E)(sum.y * n)};
+        } else {
+            *reinterpret_cast<float2 *>(dst0 + (size_t)h * (D + 2) + 2 + 2 * lane) = sum;
+        }
     }
     if (kp.O != nullptr) return;
     if (wave == 0 && q4 == 0 && col < kp.hps) {

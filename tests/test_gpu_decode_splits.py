@@ -16,6 +16,10 @@ pytestmark = pytest.mark.gpu
     ("bf16", inputs.MODE_MLA, 1, 16400, 16, 1, 2, 16),           # 64 workgroups
     ("bf16", inputs.MODE_MLA, 20, 1500, 4, 1, 1, 30),            # 12 workgroups per sequence at most, four tiles each
     ("bf16", inputs.MODE_MLA, 130, 300, 2, 1, 2, 30),            # more than half as many sequences as CUs: one workgroup each
+    ("bf16", inputs.MODE_MLA, 1, 512, 16, 1, 16, 512),           # 8 and 9 partial results: on both sides of eight rows per thread
+    ("f16", inputs.MODE_MLA, 1, 520, 7, 1, 16, 1024),
+    ("bf16", inputs.MODE_MLA, 1, 2100, 16, 1, 16, 4096),         # 17: the first with four groups
+    ("bf16", inputs.MODE_MLA, 1, 8300, 16, 1, 16, 9000),         # 65: more than a wavefront has lanes
     ("bf16", inputs.MODE_GQA, 1, 6100, 28, 4, 1, 40),            # 48 workgroups per KV head
     ("f16", inputs.MODE_GQA, 3, 2900, 14, 2, 2, 33),
     ("bf16", inputs.MODE_GQA, 33, 400, 8, 4, 2, 64),             # 132 pairs
