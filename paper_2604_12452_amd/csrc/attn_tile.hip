@@ -5,7 +5,7 @@
 // What these shapes need is parallelism and reuse, not the last MFMA: one wavefront per query row, every key element a
 // scalar load of its own, took 128 us for 0.36 GFLOP in fp32 (L = 1024, 4 heads, 128 + 32) and 1.44 ms for 5.3 GFLOP in bf16
 // (L = 2500, 16 heads over 4 KV heads, 64 / 64).  This kernel takes 15.6 us (launch and memory latency: three tiles per wavefront)
-// and 32 us (vector ALU: softmax and the splitting of the probabilities).  Here
+// and 32 us (request rate of the tile loads and vector ALU: softmax, the splitting of the probabilities).  Here
 //   * a workgroup owns 16 QB query rows of one condensed set, numbered (token, head of the set): the heads of a set see the
 //     same keys, so the rows of a workgroup span few tokens;
 //   * its wavefronts split the KEY tiles among them, each with a softmax (running maximum) of its own, and are merged through
@@ -238,7 +238,9 @@ void attn_tile_kernel(const RowParams<T> kp, int n_blocks)
         q_row[qb] = ((size_t)b * L + t) * kp.H + s * hps + (rc - t * hps);
     }
 
-    // the pieces of one tile in registers: lane = (row of four, piece of sixteen).  Loads go through buffer descriptors: the
+    // the pieces of one tile in registers: lane = (row of four, piece of sixteen of both components), or, where either component
+    // has at most eight (NIT == 1), lane = (row of eight, piece of eight) for one component after the other: with both in one row of
+    // lanes each needs a load of its own all the same (its descriptor), half of whose lanes are idle: 64 / 64, 16 heads, L = 2500 34 -> 32 us.  Loads go through buffer descriptors: the
     // address of a load is a scalar plus an offset that the lane keeps, and rows past a segment's end read as zeros (hidden
     // below).  With 64-bit addresses per load a third of the loop's issue time was integer multiplication.
     const int sub = lane & 15, rr = lane >> 4, p = kp.mla ? 0 : s;
@@ -246,6 +248,8 @@ void attn_tile_kernel(const RowParams<T> kp, int n_blocks)
     const int pool_bytes = kp.d_pool * ELT, sel_bytes = kp.d_sel * ELT;
     const T *const rep_p = kp.pool_rep + ((size_t)b * kp.S + s) * kp.m * kp.d_pool, *const rep_s = kp.sel_rep + ((size_t)b * kp.S + s) * kp.m * kp.d_sel;
     const T *const raw_p = kp.POOL + ((size_t)b * L * kp.P + p) * kp.d_pool, *const raw_s = kp.SEL + ((size_t)b * L * kp.P + p) * kp.d_sel;
+    static_assert(NIT > 1 || (16 * NDT <= 8 * M::EPC && NKC * M::CHUNK <= 8 * M::EPC), "at most eight pieces per component");
+    const int r8 = lane >> 3, x8 = lane & 7, ncs = lay.nc - lay.cp;
     uintx4 held[4 * NB][NIT];
     auto load_tile = [&](int tile) {
         const bool is_rep = tile < rep_tiles;
@@ -253,6 +257,19 @@ void attn_tile_kernel(const RowParams<T> kp, int n_blocks)
         const unsigned ps = step * pool_bytes, ss = step * sel_bytes;           // bytes between rows of the segment
         const __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc((void *)(is_rep ? rep_p : raw_p), (short)0, last * ps + pool_bytes, RSRC_WORD3);
         const __amdgpu_buffer_rsrc_t srs = __builtin_amdgcn_make_buffer_rsrc((void *)(is_rep ? rep_s : raw_s), (short)0, last * ss + sel_bytes, RSRC_WORD3);
+        if constexpr (NIT == 1) {
+            if (x8 < lay.cp) {
+                const int voff = r8 * ps + x8 * 16;
+#pragma unroll
+                for (int i = 0; i < 2 * NB; ++i) held[i][0] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(prs, voff, (e0 + 8 * i) * ps, 0));
+            }
+            if (x8 < ncs) {
+                const int voff = r8 * ss + x8 * 16;
+#pragma unroll
+                for (int i = 0; i < 2 * NB; ++i) held[2 * NB + i][0] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(srs, voff, (e0 + 8 * i) * ss, 0));
+            }
+            return;
+        }
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
             const int x = sub + 16 * it;
@@ -270,6 +287,18 @@ void attn_tile_kernel(const RowParams<T> kp, int n_blocks)
         }
     };
     auto store_tile = [&]() {
+        if constexpr (NIT == 1) {
+            char *const vdst = area + lay.v_off + x8 * 16 + r8 * lay.rsv, *const kdst = area + lay.sel_off + x8 * 16 + r8 * lay.rsk;
+            if (x8 < lay.cp) {
+#pragma unroll
+                for (int i = 0; i < 2 * NB; ++i) *reinterpret_cast<uintx4 *>(vdst + 8 * i * lay.rsv) = held[i][0];
+            }
+            if (x8 < ncs) {
+#pragma unroll
+                for (int i = 0; i < 2 * NB; ++i) *reinterpret_cast<uintx4 *>(kdst + 8 * i * lay.rsk) = held[2 * NB + i][0];
+            }
+            return;
+        }
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
             const int x = sub + 16 * it;
