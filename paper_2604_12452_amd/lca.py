@@ -11,6 +11,7 @@ import ctypes
 import os
 from dataclasses import dataclass
 from functools import lru_cache
+from operator import index
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "liblca.so")
@@ -91,8 +92,10 @@ class Desc:
         return 1 if self.mode == MODE_MLA else self.S
 
     def _key(self):
-        return (self.B, self.L, self.H, self.S, self.d_pool, self.d_sel, self.g, self.w, self.n_q, self.mode, self.dtype, self.scale,
-                self.rep_logit_bias, self.pool_reduce, self.sel_reduce)
+        """The fields as plain numbers: one that holds a tensor or an array scalar is read now, not remembered by its identity."""
+        return (index(self.B), index(self.L), index(self.H), index(self.S), index(self.d_pool), index(self.d_sel), index(self.g), index(self.w),
+                index(self.n_q), index(self.mode), index(self.dtype), float(self.scale), float(self.rep_logit_bias), index(self.pool_reduce),
+                index(self.sel_reduce))
 
     def c(self) -> _CDesc:
         return _CDesc(self.B, self.L, self.H, self.S, self.d_pool, self.d_sel, self.g, self.w, self.n_q, self.mode,

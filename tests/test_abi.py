@@ -66,6 +66,26 @@ def test_condensed_rows_follow_the_partition_of_section_4_2(lib):
     assert lib.lca_condensed_rows(ctypes.byref(cd), None, None) == lca.ERR_INVALID_ARG
 
 
+def test_descriptor_fields_are_read_on_every_call(lib):
+    """What the binding keeps per descriptor is kept by the fields' values: a field that holds a tensor or an array scalar is
+    read again on the next call, and need not be hashable."""
+    import numpy as np
+    import torch
+    t = torch.tensor(0.5)
+    d = _desc(scale=t)
+    assert d.m == 448
+    t.fill_(float("nan"))
+    with pytest.raises(lca.LcaError) as e:
+        lca.condensed_rows(d)
+    assert e.value.status == lca.ERR_INVALID_ARG
+    tokens = torch.tensor(8192)
+    d = _desc(L=tokens)
+    assert lca.condensed_rows(d) == (448, 1024)
+    tokens += 17
+    assert lca.condensed_rows(d) == (449, 1025)
+    assert lca.condensed_rows(_desc(scale=np.array(0.25), rep_logit_bias=np.float32(0.5), g=np.int64(16))) == (448, 1024)
+
+
 def test_binding_rejects_tensors_that_do_not_fit_the_descriptor(lib):
     """The binding compares every tensor with the size and element type the header documents before the library is
     called: a mismatch raises ValueError and nothing is launched (CPU tensors here; a tensor of the right size and type
