@@ -120,7 +120,8 @@ def load() -> ctypes.CDLL:
         try:
             import torch
             _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-            _KNOWN_DTYPES.update({BF16: (torch.bfloat16, torch.int16, torch.uint16), F32: (torch.float32,), F16: (torch.float16,)})
+            u16 = getattr(torch, "uint16", None)          # (not every torch has it)
+            _KNOWN_DTYPES.update({BF16: (torch.bfloat16, torch.int16) + ((u16,) if u16 else ()), F32: (torch.float32,), F16: (torch.float16,)})
         except ImportError:
             pass
         lib = ctypes.CDLL(LIB_PATH)

@@ -3,6 +3,8 @@ host-side validation rejects bad arguments before anything is launched."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -84,6 +86,14 @@ def test_descriptor_fields_are_read_on_every_call(lib):
     tokens += 17
     assert lca.condensed_rows(d) == (449, 1025)
     assert lca.condensed_rows(_desc(scale=np.array(0.25), rep_logit_bias=np.float32(0.5), g=np.int64(16))) == (448, 1024)
+
+
+def test_binding_loads_with_a_torch_that_lacks_unsigned_16_bit_integers(lib):
+    """torch.uint16 is one of three types that carry bf16 bit patterns; a torch without it still carries the other two."""
+    code = ("import torch; del torch.uint16; from paper_2604_12452_amd import lca; lca.load(); "
+            "assert lca._KNOWN_DTYPES[lca.BF16] == (torch.bfloat16, torch.int16)")
+    p = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0, p.stderr[-2000:]
 
 
 def test_binding_rejects_tensors_that_do_not_fit_the_descriptor(lib):
