@@ -18,8 +18,11 @@
 //     MFMAs, a lane's accumulator registers being one row's logits and, as they are, the operand of the second product.
 //
 // Precision is that of fp32 arithmetic throughout.  fp32 data uses the fp32 matrix instructions.  16-bit data is exact as an
-// operand; the fp32 probabilities are not, so the second product takes them in parts that add up to them: bf16 three parts
-// of 8 bits (the whole 24-bit significand), fp16 two of 11 (scaled by 2^15, so that the smaller part stays a normal number).
+// operand; the fp32 probabilities are not, so the second product takes them in three parts that add up to all their 24 bits: bf16
+// 8 + 8 + 8, fp16 11 + 11 + 2.  (fp16 parts are of 2^15 p: whole down to p = 2^-16, below that cut off at 2^-40, the last bit
+// of 2^-16.  Two fp16 parts, and the 2^15 put into the exponential's argument, whose last bit that costs four binades, left an error of
+// 2^-21.4 of p where it is 2^-24 now, as in bf16 and fp32; the attention at B = 1, L = 2500, 16 heads over 4 KV heads, 64 / 64: 27.7 us so, 29.5 us
+// with all the bits.)
 //
 // The matrix product multiplies entries a row does not see by a zero probability; an infinity or a NaN in such an entry
 // would reach the row.  So if any result of the workgroup is not finite its rows are redone one by one (attn_row.h), each
@@ -77,7 +80,7 @@ template <typename E8, typename E4, typename E, int NPARTS> struct Mma16 {
     }
 };
 template <> struct Mma<uint16_t> : Mma16<bf16x8, bf16x4, __bf16, 3> {
-    static constexpr float REF_SHIFT = 0.f;
+    static constexpr float P_SCALE = 1.f;          // what the probabilities are multiplied by on their way into the second product
     // p = its leading 8 bits + the next 8 + the last 8 (cut off, not rounded: a subtraction each and one byte
     // permutation per pair)
     template <int NB> __device__ static void split(const float (&p)[NB][4], Parts<NB> &o)
@@ -103,18 +106,27 @@ template <> struct Mma<uint16_t> : Mma16<bf16x8, bf16x4, __bf16, 3> {
         *reinterpret_cast<bf16x4 *>(p) = bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
     }
 };
-template <> struct Mma<f16_t> : Mma16<f16x8, f16x4, _Float16, 2> {
-    static constexpr float REF_SHIFT = 15.f;       // probabilities are kept times 2^15 (the sum of a row alike, so it cancels)
-    // p = its leading 11 bits + the next 11, both rounded
+template <> struct Mma<f16_t> : Mma16<f16x8, f16x4, _Float16, 3> {
+    static constexpr float P_SCALE = 32768.f;      // (an exact product; the results are divided by it with the row's sum)
+    // 2^15 p = its leading 11 bits + the next 11 + the last 2 (cut off, not rounded: one conversion per pair)
     template <int NB> __device__ static void split(const float (&p)[NB][4], Parts<NB> &o)
     {
+        typedef __fp16 half2 __attribute__((ext_vector_type(2)));
+        typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const _Float16 hi = (_Float16)p[b][r];
-                o.v[0][b][r] = hi;
-                o.v[1][b][r] = (_Float16)(p[b][r] - (float)hi);
+            for (int r = 0; r < 4; r += 2) {
+                float x = p[b][r] * P_SCALE, y = p[b][r + 1] * P_SCALE;
+#pragma unroll
+                for (int i = 0; i < PARTS; ++i) {
+                    const half2 cut = __builtin_amdgcn_cvt_pkrtz(x, y);
+                    const f16x2 h = __builtin_bit_cast(f16x2, cut);
+                    o.v[i][b][r] = h[0];
+                    o.v[i][b][r + 1] = h[1];
+                    x -= (float)h[0];
+                    y -= (float)h[1];
+                }
             }
     }
     __device__ static void store4(f16_t *p, const floatx4 &v)
@@ -124,7 +136,7 @@ template <> struct Mma<f16_t> : Mma16<f16x8, f16x4, _Float16, 2> {
 };
 template <> struct Mma<float> {
     static constexpr int EPC = 4, CHUNK = 16, PARTS = 1;
-    static constexpr float REF_SHIFT = 0.f;
+    static constexpr float P_SCALE = 1.f;
     __device__ static int row_of_m(int m) { return m; }
     __device__ static int entry(int r, int q4) { return 4 * q4 + r; }
     __device__ static floatx4 score(const uintx4 &k, const uintx4 &q, floatx4 c)
@@ -392,7 +404,7 @@ void attn_tile_kernel(const RowParams<T> kp, int n_blocks)
                     for (int r = 0; r < 4; ++r) acc[qb][t][r] *= corr;
                 m_run[qb] = m_new;
             }
-            const float ref = (m_run[qb] == -INFINITY ? 0.f : m_run[qb]) - M::REF_SHIFT;
+            const float ref = m_run[qb] == -INFINITY ? 0.f : m_run[qb];
             float pv[NB][4];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
@@ -464,7 +476,7 @@ void attn_tile_kernel(const RowParams<T> kp, int n_blocks)
     if (wave == 0) {
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            const float inv = 1.f / l_tot[qb];
+            const float inv = 1.f / (l_tot[qb] * M::P_SCALE);
             float chk = 0.f;
 #pragma unroll
             for (int t = 0; t < NDT; ++t) {
@@ -477,7 +489,7 @@ void attn_tile_kernel(const RowParams<T> kp, int n_blocks)
                     for (int r = 0; r < 4; ++r) chk = fmaf(acc[qb][t][r], 0.f, chk);      // zero, or NaN if a value is not finite
                 }
             }
-            if (kp.lse != nullptr && live[qb] && q4 == 0) kp.lse[q_row[qb]] = (m_run[qb] - M::REF_SHIFT + log2f(l_tot[qb])) * 0.6931471805599453f;
+            if (kp.lse != nullptr && live[qb] && q4 == 0) kp.lse[q_row[qb]] = (m_run[qb] + log2f(l_tot[qb])) * 0.6931471805599453f;
             bad |= live[qb] && !(chk == 0.f);
         }
     }

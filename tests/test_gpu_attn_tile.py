@@ -54,3 +54,38 @@ def test_entries_a_row_does_not_see_never_reach_it(bad, dtype, mode, d_pool, d_s
     assert hp.vec_rel_err(b[:, :37], a[:, :37]) <= hp.TOL[dtype]
     assert torch.equal(run.lse[:, :37].isfinite(), torch.ones_like(run.lse[:, :37], dtype=torch.bool))
     assert not np.isfinite(b[0, 37:, :, 3]).any()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+def test_probabilities_enter_the_second_product_whole(dtype):
+    """The 24 bits of a probability: 512 sets of one head, three tokens, two of which have logit 0 and values that cancel the leading
+    22 bits of the third's contribution p = exp(x), so that the output is what is left of p.
+
+    Bound on the error of p, relative to 1 (x in (-1/2, 0)): the factor log2(e) and its product with x round once each (2^-25 + 2^-25
+    of at most 0.72, times ln 2 p: 2^-25), the exponential by at most one unit (2^-24), the three terms' sum by at most one unit of
+    its largest value per addition (3 * 2^-24); together below 2^-21.6.  Largest seen: 2^-24.0 (fp16 in two parts: 2^-21.4)."""
+    import torch
+    from paper_2604_12452_amd import lca
+    n, V = 512, 2.0 ** 14
+    rng = np.random.default_rng(3)
+    x = -rng.uniform(0.02, 0.5, n).astype(np.float32)
+    x = inputs.to_f64(inputs.to_storage(x, dtype), dtype)                # the logit itself: one product of x and 1
+    p = np.exp(x)
+    parts = []
+    for _ in range(2):                                                   # leading parts of p in the storage type
+        parts.append(inputs.to_f64(inputs.to_storage((p - sum(parts)).astype(np.float32), dtype), dtype))
+    Q, K, Vals = np.zeros((1, 3, n, 64)), np.zeros((1, 3, n, 64)), np.zeros((1, 3, n, 64))
+    Q[..., 0] = 1.0
+    K[0, 2, :, 0] = x
+    Vals[0, 0], Vals[0, 1], Vals[0, 2] = -V * parts[0][:, None], -V * parts[1][:, None], V
+    dev = [hp.to_dev(inputs.to_storage(a.astype(np.float32), dtype), dtype) for a in (Q, Vals, K)]
+    d = lca.Desc(B=1, L=3, H=n, S=n, d_pool=64, d_sel=64, g=4, w=64, n_q=1, mode=lca.MODE_GQA,
+                 dtype={"bf16": lca.BF16, "f16": lca.F16, "f32": lca.F32}[dtype])
+    O = torch.empty(1, 3, n, 64, dtype=lca.torch_dtype(d), device="cuda")
+    lse = torch.empty(1, 3, n, dtype=torch.float32, device="cuda")
+    lca.dense_attn(d, *dev, O, lse, lca.alloc_workspace(d))
+    got = hp.from_dev(O, dtype)[0, 2] * (2.0 + p[:, None]) / V           # p - parts[0] - parts[1]
+    err = np.abs(got - (p - parts[0] - parts[1])[:, None]).max()
+    print(f"  largest error of p: 2^{np.log2(err):.2f}", flush=True)
+    assert err <= 2.0 ** -21.6
+    assert np.abs(lse[0, 2].cpu().numpy() - np.log(2.0 + p)).max() <= 4e-7
