@@ -335,7 +335,6 @@ __global__ __launch_bounds__(256, 1) void decode_gqa_mfma_kernel(const DgParams 
         factor[w] = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - m_all);
         l_all += wave_ml[w][col][1] * factor[w];
     }
-    const float inv = 1.f / l_all;
     float *dst0 = kp.part + ((size_t)bs * wg_per_bs + blockIdx.x % wg_per_bs) * kp.hps * (D + 2);
     auto of_head = [](float v, int h) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), h)); };   // (lane h: head h)
     float2 v[4][4];
@@ -357,8 +356,8 @@ __global__ __launch_bounds__(256, 1) void decode_gqa_mfma_kernel(const DgParams 
         }
         if (kp.O != nullptr) {
             typedef E ex2 __attribute__((ext_vector_type(2)));
-            const float n = of_head(inv, h);
-            *reinterpret_cast<ex2 *>(reinterpret_cast<E *>(kp.O) + ((size_t)bs * kp.hps + h) * D + 2 * lane) = ex2{(E)(sum.x * n), (E)(sum.y * n)};
+            const float l = of_head(l_all, h);             // (divided by, not multiplied with a rounded 1 / l)
+            *reinterpret_cast<ex2 *>(reinterpret_cast<E *>(kp.O) + ((size_t)bs * kp.hps + h) * D + 2 * lane) = ex2{(E)(sum.x / l), (E)(sum.y / l)};
         } else {
             *reinterpret_cast<float2 *>(dst0 + (size_t)h * (D + 2) + 2 + 2 * lane) = sum;
         }

@@ -46,3 +46,22 @@ def test_decode_step_splits(oracle, dtype, mode, B, L, H, S, g, w):
     err = hp.vec_rel_err(hp.from_dev(O, dtype), ref)
     print(f"  decode err {err:.2e}", flush=True)
     assert err <= hp.TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,ulp", [("bf16", 2.0 ** -7), ("f16", 2.0 ** -10)])
+@pytest.mark.parametrize("k", [30, 60])
+def test_gqa_output_is_the_sum_divided_once(dtype, ulp, k):
+    """One workgroup, equal logits (a zero query): the output is the mean of the k value rows.  Half of them are a number of the
+    16-bit type and half the next one, so the mean lies exactly between the two and rounds to the even one; a product with a rounded
+    1 / k lands beside the tie and misses it in four columns of ten."""
+    import torch
+    from paper_2604_12452_amd import lca
+    d = lca.Desc(B=1, L=k, H=4, S=2, d_pool=128, d_sel=128, g=16, w=64, mode=lca.MODE_GQA, dtype={"bf16": lca.BF16, "f16": lca.F16}[dtype])
+    j = np.arange(128) * (1 if dtype == "bf16" else 8) + np.arange(128) % 2
+    low = 1.0 + ulp * j
+    v = np.tile(low, (1, 2, k, 1))
+    v[:, :, k // 2:] += ulp
+    dev = [hp.to_dev(inputs.to_storage(a.astype(np.float32), dtype), dtype) for a in (np.zeros((1, 4, 128)), v, np.ones((1, 2, k, 128)))]
+    O = torch.empty(1, 4, 128, dtype=lca.torch_dtype(d), device="cuda")
+    lca.decode_attn(d, dev[0], None, None, dev[1], dev[2], O, lca.alloc_workspace(d))
+    np.testing.assert_array_equal(hp.from_dev(O, dtype)[0], np.tile(np.where(j % 2 == 0, low, low + ulp), (4, 1)))
