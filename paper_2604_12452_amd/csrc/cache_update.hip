@@ -11,8 +11,9 @@
 // then one wavefront per group) / now: 28 heads over 4 KV heads 128 + 128, five sequences 8.8 / 6.0 us, g = 32 12.4 / 7.8 us;
 // 16 heads, one set, 512 + 64 13.4 / 8.6 us at one sequence, 13.9 / 9.2 us at 32, g = 32 32.8 / 10.9 us.
 // The summary query inside at 512 + 64 (five blocks of chunks one after another): 16.2 us with one wavefront per group.
-// Rows of more than 128 pieces do not fit two pieces per lane: one wavefront per (sequence, set), as in the any-width
-// condensation (group_rows.h).
+// Rows of more than 128 pieces do not fit two pieces per lane: cache_update_rows_kernel.  (One wavefront per (sequence, set)
+// that reads its rows again took longer: the call at fp32 512 + 64, one sequence, g = 4 / 16 / 64:
+// 10.7 / 22.5 / 73.5 us so, 8.0 / 13.1 / 35.6 us by four.)
 #include "group_rows.h"
 
 namespace lca {
@@ -29,26 +30,58 @@ struct UpdParams {
     float scale;
 };
 
+// Four wavefronts per (sequence, set), any widths: the wavefronts split the g rows for the scores, the threads split the columns for the
+// pooled row; every row is read again for it (from the caches), with as many loads in flight as there are rows.
+// dynamic LDS: qbar[d_qk] then score[g]
+constexpr int ROWS_THREADS = 256;
 template <typename T>
-__global__ __launch_bounds__(WAVE) void cache_update_kernel(const UpdParams kp)
+__global__ __launch_bounds__(ROWS_THREADS) void cache_update_rows_kernel(const UpdParams kp)
 {
-    constexpr int EPC = Elt<T>::EPC;
-    __shared__ float per_row[2][WAVE];
-    const int lane = threadIdx.x, bs = blockIdx.x, d_pool = kp.d_pool, d_sel = kp.d_sel, mla = kp.mla;
+    extern __shared__ float lds[];
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE, bs = blockIdx.x;
+    const int d_pool = kp.d_pool, d_sel = kp.d_sel, mla = kp.mla, g = kp.g, d_qk = mla ? d_pool + d_sel : d_sel;
+    float *const qbar = lds, *const score = lds + d_qk;
+    for (int col = tid; col < d_qk; col += ROWS_THREADS) qbar[col] = kp.qbar[(size_t)bs * d_qk + col];
+    __syncthreads();
+
+    auto ring_row = [&](int i) { const int r = kp.k_start + i; return r >= kp.k_cap ? r - kp.k_cap : r; };
     const size_t src = mla ? bs / kp.S : bs;                 // (sequence, KV head) whose ring is read
-    Rows<T, 16> pool;
-    Rows<T, 4> sel;
-    pool.init((const T *)kp.pool_tail + src * kp.k_cap * d_pool, d_pool, d_pool / EPC, kp.g, lane, kp.k_start, kp.k_cap);
-    sel.init((const T *)kp.sel_tail + src * kp.k_cap * d_sel, d_sel, d_sel / EPC, kp.g, lane, kp.k_start, kp.k_cap);
-    pool.request();
-    sel.request();
+    const T *const pool = (const T *)kp.pool_tail + src * kp.k_cap * d_pool, *const sel = (const T *)kp.sel_tail + src * kp.k_cap * d_sel;
+
+    // scores of the g oldest tail tokens: key = [pooled ; selected] (MLA, absorbed form) or the selected component (GQA)
+    for (int i = wave; i < g; i += ROWS_THREADS / WAVE) {
+        const int r = ring_row(i);
+        float a = 0.f;
+        if (mla)
+            for (int col = lane; col < d_pool; col += WAVE) a += qbar[col] * Elt<T>::ld(pool + (size_t)r * d_pool + col);
+        for (int col = lane; col < d_sel; col += WAVE) a += qbar[(mla ? d_pool : 0) + col] * Elt<T>::ld(sel + (size_t)r * d_sel + col);
+        for (int o = WAVE / 2; o > 0; o >>= 1) a += __shfl_xor(a, o, WAVE);
+        if (lane == 0) score[i] = a * kp.scale;
+    }
+    __syncthreads();
+
+    // group softmax and arg-max (every thread redundantly: g <= 64 values; a score that is not a number is never the largest)
+    float mx = -INFINITY;
+    int best = 0;
+    for (int i = 0; i < g; ++i)
+        if (score[i] > mx) { mx = score[i]; best = i; }
+    float z = 0.f;
+    for (int i = 0; i < g; ++i) z += __expf(score[i] - mx);
+    const float inv_z = 1.f / z;
+
+    // pooled component: softmax-weighted sum; selected component: the arg-max token's, copied
     const size_t unit = (size_t)bs * kp.m_cap + (kp.m - 1);
-    condense_group<T>(pool, sel, kp.qbar + (size_t)bs * (mla ? d_pool + d_sel : d_sel), mla, d_pool, kp.g, kp.scale, LCA_REDUCE_WEIGHTED,
-                      LCA_REDUCE_MAXSEL, (T *)kp.pool_rep + unit * d_pool, (T *)kp.sel_rep + unit * d_sel,
-                      kp.anchor != nullptr ? kp.anchor + unit : nullptr, (kp.m - 1) * kp.g, nullptr, per_row[0], per_row[1], lane);
+    for (int col = tid; col < d_pool; col += ROWS_THREADS) {
+        float a = 0.f;
+        for (int i = 0; i < g; ++i) a += __expf(score[i] - mx) * inv_z * Elt<T>::ld(pool + (size_t)ring_row(i) * d_pool + col);
+        Elt<T>::st((T *)kp.pool_rep + unit * d_pool + col, a);
+    }
+    const T *const from = sel + (size_t)ring_row(best) * d_sel;
+    for (int col = tid; col < d_sel; col += ROWS_THREADS) ((T *)kp.sel_rep)[unit * d_sel + col] = from[col];
+    if (kp.anchor != nullptr && tid == 0) kp.anchor[unit] = (kp.m - 1) * g + best;
 }
 
-// The same by eight wavefronts, for rows of up to 128 16-byte pieces (both components): wavefront w holds rows w, w + 8, .. of
+// Eight wavefronts, for rows of up to 128 16-byte pieces (both components): wavefront w holds rows w, w + 8, .. of
 // the group whole, piece l and l + 64 in lane l, all requested at once; it scores its rows, every wavefront then evaluates the
 // softmax, and the weighted rows are added up over the wavefronts in LDS.  SUMMARY: the summary query is computed here too, by
 // the whole workgroup, while the rows are on their way.  UPD_ROWS: rows of a wavefront, g / 8 rounded up to 2 or 8.
@@ -206,7 +239,7 @@ hipError_t run(const UpdateArgs &a, hipStream_t st)
         else cache_update_wide_kernel<T, false, 8><<<grid, UPD_WAVES * WAVE, 0, st>>>(wp);
         return hipGetLastError();
     }
-    cache_update_kernel<T><<<d.B * d.S, WAVE, 0, st>>>(kp);
+    cache_update_rows_kernel<T><<<grid, ROWS_THREADS, (size_t)(d.d_qk + d.g) * sizeof(float), st>>>(kp);
     return hipGetLastError();
 }
 
