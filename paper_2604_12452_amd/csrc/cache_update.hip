@@ -162,7 +162,8 @@ __global__ __launch_bounds__(UPD_WAVES *WAVE) void cache_update_wide_kernel(cons
     const float mine = lane < g ? kp.scale * score[lane] : -INFINITY;       // lane r: the score of row r
     float bmax;
     const int top = g <= 1 ? 0 : 1 << (31 - __builtin_clz(g - 1));
-    const int best = wave_argmax(mine, lane, top, &bmax);
+    // (a score that is not a number anchors nothing; it does reach the weights, and through them the whole pooled row)
+    const int best = wave_argmax(mine == mine ? mine : -INFINITY, lane, top, &bmax);
     const float p = lane < g ? __expf(mine - bmax) : 0.f;
     float z = p;
     for (int mask = top; mask >= 1; mask >>= 1) z += __shfl_xor(z, mask, WAVE);
