@@ -382,12 +382,15 @@ bool decode_gqa_mfma_supported(const Dims &d)
 // (they are 512 bytes per head).  Measured (step with merge, 28 heads over 4; four / two / one tile each): B = 1, L = 1500
 // 10.2 / 9.8 / 8.3 us; B = 5, L = 4001 12.2 / 11.1 / 10.3; B = 5, L = 16384 12.9 / 11.5 / 12.7 (80, 160, 260 workgroups); B = 5,
 // L = 65536 15.6 us with 200 workgroups and 17.8 us with 260 (a second round on 256 CUs); 160 pairs of 64K 93 us with two workgroups each, 76 us with one.
+// Up to 16 tiles one workgroup takes them all and writes the output itself, without the merge's launch (two to four workgroups / one:
+// 32 heads over 8, B = 1, L = 160 6.8 / 5.2 us, 500 6.8 / 7.2; B = 10, L = 300 8.2 / 6.5).
 int decode_gqa_mfma_parts(const Dims &d)
 {
     const int tiles = (d.m + BN - 1) / BN + (d.k + BN - 1) / BN;      // (an upper bound when the two kinds share tiles)
     const long pairs = (long)d.B * d.S;
     auto wgs_for = [&](int per_wave) { return (tiles + 4 * per_wave - 1) / (4 * per_wave); };
     int wgs = wgs_for(4);
+    if (wgs == 1) return 4;
     if (wgs_for(1) <= 48 && pairs * wgs_for(1) <= 200) wgs = wgs_for(1);
     else if (pairs * wgs_for(2) <= 160) wgs = wgs_for(2);
     const long most = pairs >= 256 ? 1 : 256 / pairs;

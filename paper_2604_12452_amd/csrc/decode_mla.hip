@@ -389,12 +389,16 @@ bool decode_mla_supported(const Dims &d)
 // (step with merge, 16 heads; four / two / one tile each): B = 1, L = 700 15.9 / 14.6 / 13.3 us; B = 1, L = 4001 16.7 / 14.4 / 14.4;
 // B = 1, L = 16384 15.4 / 14.1 / 15.8; B = 8, L = 1500 17.4 / 15.2 / 15.5; B = 32, L = 700 17.5 / 18.2 / 19.3 (192, 256 workgroups);
 // B = 150, L = 20000 103 us with two workgroups per sequence (300 on 256 CUs), 77 us with one.
+// Up to 16 tiles one workgroup takes them all: it writes the output itself, and the merge's launch costs more than a chain of up to
+// four tiles is long (two to four workgroups / one: B = 1, L = 80
+// 10.7 / 8.7 us, 160 10.8 / 10.1, 250 10.9 / 11.5; B = 60, L = 160 15.8 / 10.7).
 int decode_mla_parts(const Dims &d)
 {
     const int tiles = (d.m + BN - 1) / BN + (d.k + BN - 1) / BN;      // (an upper bound when the two kinds share tiles)
     const long pairs = (long)d.B * d.S;
     auto wgs_for = [&](int per_wave) { return (tiles + 4 * per_wave - 1) / (4 * per_wave); };
     int wgs = wgs_for(4);
+    if (wgs == 1) return 4;
     if (wgs_for(1) <= 16 && pairs * wgs_for(1) <= 200) wgs = wgs_for(1);
     else if (pairs * wgs_for(2) <= 160) wgs = wgs_for(2);
     const long most = pairs >= 256 ? 1 : 256 / pairs;

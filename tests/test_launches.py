@@ -23,3 +23,18 @@ def test_cache_update_by_row_width(desc, wide):
     last = t.cache_update(desc)[-1]
     assert (last.kernel.split("<")[0], last.block) == (("cache_update_wide_kernel", 512) if wide else ("cache_update_rows_kernel", 256))
     assert last.grid == desc.B * desc.S
+
+
+@pytest.mark.parametrize("desc,tiles,wgs", [
+    (_mla(L=1), 1, 1), (_mla(L=256), 16, 1), (_mla(L=257), 17, 5), (_mla(L=70, B=81), 5, 1), (_mla(L=237, w=128, B=63), 10, 1), (_mla(L=1024), 64, 16),
+    (_gqa(L=512), 16, 1), (_gqa(L=513), 17, 5), (_gqa(L=155, w=128, B=4, H=8), 6, 1), (_gqa(L=300, B=40), 10, 1), (_gqa(L=1600, w=2000, B=40), 50, 1),
+])
+@pytest.mark.parametrize("q8", [False, True])
+def test_decode_step_by_cache_length(desc, tiles, wgs, q8):
+    """Up to 16 tiles (16 entries each at 512 + 64, 32 at 128 / 128) one workgroup per (sequence, set) takes them all and there is nothing to
+    merge; so it is where the pairs alone fill the chip."""
+    bn = 16 if desc.mode == lca.MODE_MLA else 32
+    assert -(-desc.m // bn) + -(-desc.k // bn) == tiles
+    run = t.decode(desc, q8)
+    assert run[0].grid == desc.B * desc.S * wgs
+    assert len(run) == (1 if wgs == 1 else 2)
