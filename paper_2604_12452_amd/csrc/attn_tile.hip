@@ -43,7 +43,7 @@ typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
 constexpr int MAX_WAVES = 4;
 constexpr int RSRC_WORD3 = 0x00020000;   // raw buffer of dwords, gfx9 layout
-constexpr size_t LDS_LIMIT = 64 * 1024;
+constexpr size_t LDS_BYTES = 160 * 1024;      // of a CU
 
 // Per element type: columns of one fragment chunk (a 16-byte piece per lane, four lanes deep), and the two products.
 template <typename T> struct Mma;
@@ -507,10 +507,22 @@ hipError_t run(const AttnArgs &a, hipStream_t st)
 {
     const Dims &d = a.d;
     const Layout<T, NDT, NKC, QB, NB> lay(d.d_pool, d.d_sel, d.mode == LCA_MODE_MLA);
-    int waves = MAX_WAVES;
-    while (waves > 1 && (size_t)waves * lay.area + waves * 16 * QB * 8 > LDS_LIMIT) waves /= 2;
-    const long blocks = ((long)d.L * (d.H / d.S) + 16 * QB - 1) / (16 * QB);
-    attn_tile_kernel<T, NDT, NKC, QB, NB, NIT><<<(unsigned)(blocks * d.S * d.B), 64 * waves, (size_t)waves * lay.area + waves * 16 * QB * 8, st>>>(
+    const long blocks = ((long)d.L * (d.H / d.S) + 16 * QB - 1) / (16 * QB), grid = blocks * d.S * d.B;
+    // Wavefronts per workgroup.  No more than there are tiles (the last rows see the most): the others would only be merged.  A workgroup may
+    // take all of a CU's LDS while there is a CU for each, half of it while there are two per CU, then what leaves room for two; the widest
+    // classes fill a SIMD's registers with one wavefront, so from two workgroups per CU on they have two wavefronts at most.  Measured (at
+    // most 64 KB whatever the grid and the tiles / now): fp32 512 + 64, 2 heads, L = 500 146 / 55 us (one wavefront, four); bf16 256 + 32, 8 heads,
+    // L = 500 15.6 / 11.9, L = 1500 20.4 / 20.4; bf16 64 / 64, L = 20 4.9 / 4.1 (two tiles).  The rule with all of LDS at any grid: bf16
+    // 512 + 64 at L of a thousand and more up to 2.5 times as long.
+    const int t_last = d.L - 1, t_first = (int)((blocks - 1) * 16 * QB / (d.H / d.S));
+    auto visible = [&](int t) { return (a.dense || t + 1 <= d.w) ? 0 : (t + 1 - d.w) / d.g; };
+    const int tiles = (visible(t_last) + 16 * NB - 1) / (16 * NB) + (t_last + 1 - visible(t_first) * d.g + 16 * NB - 1) / (16 * NB);
+    const int cus = persistent_grid();
+    const size_t room = grid <= cus ? LDS_BYTES : grid <= 2 * cus ? LDS_BYTES / 2 : LDS_BYTES * 2 / 5;
+    constexpr bool full_registers = NDT > (sizeof(T) == 2 ? 16 : 8);
+    int waves = full_registers && grid > cus ? MAX_WAVES / 2 : MAX_WAVES;
+    while (waves > 1 && (waves / 2 >= tiles || (NDT > 8 && waves > tiles) || (size_t)waves * lay.area + waves * 16 * QB * 8 > room)) waves /= 2;
+    attn_tile_kernel<T, NDT, NKC, QB, NB, NIT><<<(unsigned)grid, 64 * waves, (size_t)waves * lay.area + waves * 16 * QB * 8, st>>>(
         attn_row::row_params<T>(a), (int)blocks);
     return hipGetLastError();
 }

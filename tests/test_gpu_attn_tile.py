@@ -24,6 +24,8 @@ pytestmark = pytest.mark.gpu
     ("f32", inputs.MODE_MLA, 256, 32, 90, 8, 20, 4, 1, 1),
     ("f32", inputs.MODE_MLA, 512, 64, 70, 8, 9, 2, 1, 1),
     ("f32", inputs.MODE_MLA, 128, 32, 16, 4, 3, 4, 1, 1),        # fewer tiles than wavefronts
+    ("f32", inputs.MODE_GQA, 416, 64, 70, 8, 9, 4, 2, 1),        # key and value rows apart: two wavefronts' areas take 141 KB ...
+    ("f32", inputs.MODE_GQA, 512, 64, 130, 4, 60, 2, 1, 2),      # ... of LDS
     # enough rows for two blocks per wavefront
     ("bf16", inputs.MODE_GQA, 64, 64, 1030, 16, 40, 16, 4, 2),
     ("f16", inputs.MODE_GQA, 128, 96, 1037, 32, 21, 32, 8, 1),

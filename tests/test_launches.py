@@ -38,3 +38,20 @@ def test_decode_step_by_cache_length(desc, tiles, wgs, q8):
     run = t.decode(desc, q8)
     assert run[0].grid == desc.B * desc.S * wgs
     assert len(run) == (1 if wgs == 1 else 2)
+
+
+def _odd(**kw):
+    return lca.Desc(**{**dict(B=1, L=500, H=8, S=1, d_pool=256, d_sel=32, g=16, w=128), **kw})
+
+
+@pytest.mark.parametrize("desc,waves", [
+    (_odd(), 4), (_odd(L=1500), 2), (_odd(d_pool=64, L=20), 1), (_odd(d_pool=64, L=40), 2), (_odd(d_pool=128, d_sel=64, L=90), 4),
+    (_odd(d_pool=512, d_sel=64, H=2, dtype=lca.F32), 4), (_odd(d_pool=512, d_sel=64, H=16, dtype=lca.F32), 2),
+    (_odd(d_pool=512, d_sel=64, H=32, L=4000, dtype=lca.F32), 1), (_odd(dtype=lca.F32, H=4, L=100), 4), (_odd(dtype=lca.F32, H=16), 2),
+    (_odd(d_pool=416, d_sel=64, S=2, L=90, mode=lca.MODE_GQA, dtype=lca.F32), 2), (_odd(d_pool=512, d_sel=64, S=8, L=900, mode=lca.MODE_GQA, dtype=lca.F32), 1),
+])
+def test_tiled_attention_wavefronts(desc, waves):
+    """As many as LDS and the registers leave room for at this grid, no more than there are tiles; never more LDS than a CU has."""
+    (run,) = t.prefill(desc)
+    assert run.kernel.startswith("attn_tile_kernel")
+    assert run.block == 64 * waves and run.lds <= 160 * 1024
