@@ -1,5 +1,6 @@
 // Straightforward attention kernel for any sizes and all element types: one wavefront per (sequence, token, head) row
-// (attn_row.h).  Serves the widths the tiled kernels have no instantiation for (pooled component above 512 columns).
+// (attn_row.h).  Serves what the tiled kernels do not take (attn_tile.hip): a pooled component above 512 columns, keys above 576,
+// both components together beyond the widest class's pieces, sequences of 4 GB and more, and rows that see a few entries only.
 #include "attn_row.h"
 
 namespace lca {

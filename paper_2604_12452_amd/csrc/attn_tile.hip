@@ -538,22 +538,35 @@ template <typename T> bool fits(const Dims &d, int ndt, int nkc, int nit)
     if ((long long)(d.L + 64) * d.P * widest * (long long)sizeof(T) >= (1ll << 32)) return false;
     return d.d_pool <= 16 * ndt && d.d_qk <= nkc * Mma<T>::CHUNK && (d.d_pool + d.d_sel) <= nit * 16 * Mma<T>::EPC;
 }
+// While a row sees this many entries or fewer, one wavefront per row is quicker: a tile is worked through whole, in all the columns of
+// its class, however little of it is real (so there is more to lose in GQA mode, whose keys are narrower than the class, and in fp32).
+// Measured (row by row / tiles, us): fp32 512 + 64, L = 2 / 16 / 32 12.0 / 19.7, 23.7 / 20.2, 39.9 / 32.6; fp32 GQA 512 / 64, L = 8
+// 11.0 / 21.1; fp32 128 + 32, L = 4 / 16 6.4 / 6.8, 10.1 / 6.9; bf16 GQA 512 / 64, L = 4 / 16 7.7 / 9.6, 18.5 / 9.7.
+// By class of the widths (64, 128, 256, 512 value columns), in 16 bits (GQA mode only) and in fp32 (MLA, GQA).
+constexpr int FEW_ENTRIES_16[4] = {0, 2, 4, 7}, FEW_ENTRIES_32[4][2] = {{2, 3}, {4, 6}, {8, 10}, {18, 40}};
+constexpr long FEW_ROWS = 8192;                   // ... and the rows' wavefronts are all on the chip at once
+
 template <typename T> hipError_t dispatch(const AttnArgs &a, hipStream_t st, bool &done)
 {
     const Dims &d = a.d;
     const long rows = (long)d.L * (d.H / d.S);
-    const bool wide = (rows + 31) / 32 * d.S * d.B >= 1024;
+    const bool wide = (rows + 31) / 32 * d.S * d.B >= 1024, gqa = d.mode != LCA_MODE_MLA;
+    const long entries = a.dense || d.m == 0 ? d.L : min((long)d.L, (long)d.m + d.w + d.g - 1);      // of the row that sees the most
+    const auto few = [&](int cls) {
+        const int most = sizeof(T) == 2 ? (gqa ? FEW_ENTRIES_16[cls] : 0) : FEW_ENTRIES_32[cls][gqa];
+        return entries <= most && (long)d.B * d.L * d.H <= FEW_ROWS;
+    };
     done = true;
     if constexpr (sizeof(T) == 2) {
-        if (fits<T>(d, 4, 2, 1)) return wide ? run<T, 4, 2, 2, 2, 1>(a, st) : run<T, 4, 2, 1, 2, 1>(a, st);
-        if (fits<T>(d, 8, 4, 2)) return run<T, 8, 4, 1, 2, 2>(a, st);
-        if (fits<T>(d, 16, 10, 3)) return run<T, 16, 10, 1, 1, 3>(a, st);
-        if (fits<T>(d, 32, 18, 5)) return run<T, 32, 18, 1, 1, 5>(a, st);
+        if (fits<T>(d, 4, 2, 1)) { if (!few(0)) return wide ? run<T, 4, 2, 2, 2, 1>(a, st) : run<T, 4, 2, 1, 2, 1>(a, st); }
+        else if (fits<T>(d, 8, 4, 2)) { if (!few(1)) return run<T, 8, 4, 1, 2, 2>(a, st); }
+        else if (fits<T>(d, 16, 10, 3)) { if (!few(2)) return run<T, 16, 10, 1, 1, 3>(a, st); }
+        else if (fits<T>(d, 32, 18, 5)) { if (!few(3)) return run<T, 32, 18, 1, 1, 5>(a, st); }
     } else {
-        if (fits<T>(d, 4, 4, 2)) return wide ? run<T, 4, 4, 2, 1, 2>(a, st) : run<T, 4, 4, 1, 1, 2>(a, st);
-        if (fits<T>(d, 8, 10, 4)) return run<T, 8, 10, 1, 1, 4>(a, st);
-        if (fits<T>(d, 16, 18, 5)) return run<T, 16, 18, 1, 1, 5>(a, st);
-        if (fits<T>(d, 32, 36, 9)) return run<T, 32, 36, 1, 1, 9>(a, st);
+        if (fits<T>(d, 4, 4, 2)) { if (!few(0)) return wide ? run<T, 4, 4, 2, 1, 2>(a, st) : run<T, 4, 4, 1, 1, 2>(a, st); }
+        else if (fits<T>(d, 8, 10, 4)) { if (!few(1)) return run<T, 8, 10, 1, 1, 4>(a, st); }
+        else if (fits<T>(d, 16, 18, 5)) { if (!few(2)) return run<T, 16, 18, 1, 1, 5>(a, st); }
+        else if (fits<T>(d, 32, 36, 9)) { if (!few(3)) return run<T, 32, 36, 1, 1, 9>(a, st); }
     }
     done = false;
     return hipSuccess;

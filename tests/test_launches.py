@@ -55,3 +55,20 @@ def test_tiled_attention_wavefronts(desc, waves):
     (run,) = t.prefill(desc)
     assert run.kernel.startswith("attn_tile_kernel")
     assert run.block == 64 * waves and run.lds <= 160 * 1024
+
+
+@pytest.mark.parametrize("kw,most", [
+    (dict(d_pool=512, d_sel=64, dtype=lca.F32), 18), (dict(d_pool=512, d_sel=64, dtype=lca.F32, mode=lca.MODE_GQA), 40),
+    (dict(d_pool=256, d_sel=32, dtype=lca.F32), 8), (dict(d_pool=128, d_sel=32, dtype=lca.F32), 4), (dict(d_pool=64, d_sel=64, dtype=lca.F32, mode=lca.MODE_GQA), 3),
+    (dict(d_pool=512, d_sel=64, mode=lca.MODE_GQA), 7), (dict(d_pool=128, d_sel=64, mode=lca.MODE_GQA, dtype=lca.F16), 2),
+])
+def test_rows_that_see_few_entries_are_taken_one_by_one(kw, most):
+    for L, w, g in ((most, 100, 4), (10 * most, most - 2, 64), (most + 4, most - 2, 2)):         # the longest row sees `most` entries, or more
+        run = t.prefill(_odd(H=1, L=L, w=w, g=g, **kw))
+        seen = max((max(0, i + 1 - w) // g) + i + 1 - max(0, i + 1 - w) // g * g for i in range(L))
+        assert (run[0].kernel.split("<")[0] == "attn_simple_kernel") == (min(L, max(0, L - w) // g + w + g - 1) <= most), (L, w, g, seen)
+        assert seen <= most or run[0].kernel.startswith("attn_tile_kernel")
+    assert t.prefill(_odd(H=1, L=most + 1, w=100, **kw))[0].kernel.startswith("attn_tile_kernel")
+    assert t.prefill(_odd(L=most + 1, **kw), dense=True)[0].kernel.startswith("attn_tile_kernel")
+    many = 8192 // most + 1
+    assert t.prefill(_odd(H=many, L=most, w=100, **kw))[0].kernel.startswith("attn_tile_kernel")      # more rows than wavefronts on the chip
