@@ -247,7 +247,8 @@ struct AnyParams {
     float scale;
 };
 
-template <typename T>
+// NP, NS: loads of the pooled / selected rows that a wavefront can hold.
+template <typename T, int NP, int NS>
 __global__ __launch_bounds__(ANY_WAVES *WAVE) void condense_any_kernel(const AnyParams kp)
 {
     constexpr int EPC = Elt<T>::EPC;
@@ -261,11 +262,11 @@ __global__ __launch_bounds__(ANY_WAVES *WAVE) void condense_any_kernel(const Any
     const int P = mla ? 1 : S, p = mla ? 0 : s;
     const T *const pool_base = (const T *)kp.POOL + (((size_t)b * kp.L + (size_t)j * g) * P + p) * d_pool;
     const T *const sel_base = (const T *)kp.SEL + (((size_t)b * kp.L + (size_t)j * g) * P + p) * d_sel;
-    Rows<T, 16> pool;
-    Rows<T, 4> sel;
+    Rows<T, NP> pool;
+    Rows<T, NS> sel;
     pool.init(pool_base, (size_t)P * d_pool, d_pool / EPC, g, lane);
     sel.init(sel_base, (size_t)P * d_sel, d_sel / EPC, g, lane);
-    pool.request();
+    if (mla || kp.pool_reduce != LCA_REDUCE_MAXSEL) pool.request();      // (else the anchor's row is all that is read)
     sel.request();
     const float *const qb = kp.qbar + (size_t)bs * d_qk;
 
@@ -299,8 +300,15 @@ hipError_t run_any(const CondenseArgs &a, hipStream_t st)
     const Dims &d = a.d;
     const AnyParams kp{a.POOL, a.SEL, a.qbar, a.pool_rep, a.sel_rep, a.anchor, a.alpha_dbg, d.L, d.S, d.m, d.g,
                        d.d_pool, d.d_sel, d.mode == LCA_MODE_MLA, d.pool_reduce, d.sel_reduce, d.scale};
-    const unsigned blocks = (d.m + ANY_WAVES - 1) / ANY_WAVES;
-    condense_any_kernel<T><<<blocks * d.S * d.B, ANY_WAVES * WAVE, 0, st>>>(kp);
+    const unsigned grid = (d.m + ANY_WAVES - 1) / ANY_WAVES * d.S * d.B;
+    // Small groups of narrow rows are many and short, bound by the instructions of a wavefront: the smallest form that holds the rows.
+    // One form for all (<16, 4>) / this rule, bf16: 16 sets of 64 + 64, L = 42872, g = 1 1015 / 397 us; 16 sets of 32 + 32, L = 20000, g = 2
+    // 229 / 97; 8 KV heads 64 / 64, L = 60000, g = 4 162 / 78; four, L = 2500, g = 16 9.6 / 9.2.
+    constexpr int EPC = Elt<T>::EPC;
+    const int pool = Rows<T, 1>::loads(d.d_pool / EPC, d.g), sel = Rows<T, 1>::loads(d.d_sel / EPC, d.g);
+    if (pool <= 1 && sel <= 1) condense_any_kernel<T, 1, 1><<<grid, ANY_WAVES * WAVE, 0, st>>>(kp);
+    else if (pool <= 4 && sel <= 4) condense_any_kernel<T, 4, 4><<<grid, ANY_WAVES * WAVE, 0, st>>>(kp);
+    else condense_any_kernel<T, 16, 4><<<grid, ANY_WAVES * WAVE, 0, st>>>(kp);
     return hipGetLastError();
 }
 

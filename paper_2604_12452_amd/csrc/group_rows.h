@@ -103,22 +103,21 @@ template <typename T, int N> struct Rows {
     int shift;               // log2 of the lanes per row
     int row0, c0;            // this lane's first row and piece
     bool held_all;           // one piece per lane and row, all of them in `held`
-    int first, cap;          // row r of the group is row (first + r) mod cap of `base` (first < cap)
     uintx4 held[N];
 
-    __device__ __forceinline__ void init(const T *b, size_t st, int ch, int gg, int lane, int row_first = 0, int ring = 1 << 30)
+    // log2 of the lanes that a row of `ch` pieces takes; loads that g such rows take
+    __host__ __device__ __forceinline__ static int row_shift(int ch) { return ch <= 1 ? 0 : ch > 32 ? 6 : 32 - __builtin_clz(ch - 1); }
+    __host__ __device__ __forceinline__ static int loads(int ch, int gg) { return (gg + (WAVE >> row_shift(ch)) - 1) >> (6 - row_shift(ch)); }
+
+    __device__ __forceinline__ void init(const T *b, size_t st, int ch, int gg, int lane)
     {
-        base = b; stride = st; chunks = ch; g = gg; first = row_first; cap = ring;
-        shift = ch <= 1 ? 0 : min(6, 32 - __builtin_clz(ch - 1));
+        base = b; stride = st; chunks = ch; g = gg;
+        shift = row_shift(ch);
         row0 = lane >> shift; c0 = lane & ((1 << shift) - 1);
-        held_all = ch <= WAVE && ((gg + (WAVE >> shift) - 1) >> (6 - shift)) <= N;
+        held_all = ch <= WAVE && loads(ch, gg) <= N;
     }
     __device__ __forceinline__ int rows_per_load() const { return WAVE >> shift; }
-    __device__ __forceinline__ const uintx4 *at(int row, int c) const
-    {
-        const int r = first + row;
-        return reinterpret_cast<const uintx4 *>(base + (r >= cap ? r - cap : r) * stride + c * Elt<T>::EPC);
-    }
+    __device__ __forceinline__ const uintx4 *at(int row, int c) const { return reinterpret_cast<const uintx4 *>(base + row * stride + c * Elt<T>::EPC); }
     __device__ __forceinline__ uintx4 fetch(int row, int c) const { return row < g && c < chunks ? *at(row, c) : uintx4{0, 0, 0, 0}; }
     __device__ __forceinline__ void request()
     {
@@ -131,22 +130,23 @@ template <typename T, int N> struct Rows {
     {
         float f[Elt<T>::EPC];
         if (held_all) {                          // (the exchanges of four loads' rows overlap)
-            static_assert(N % 4 == 0, "batches of four");
+            constexpr int BATCH = N < 4 ? N : 4;
+            static_assert(N % BATCH == 0, "whole batches");
 #pragma unroll
-            for (int i0 = 0; i0 < N; i0 += 4) {
+            for (int i0 = 0; i0 < N; i0 += BATCH) {
                 if (i0 * rows_per_load() >= g) break;
-                float a[4];
+                float a[BATCH];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; i < BATCH; ++i) {
                     unpack4<T>(held[i0 + i], f);
                     a[i] = c0 < chunks ? term(f, c0 * Elt<T>::EPC) : 0.f;
                 }
 #pragma unroll 1
                 for (int mask = (1 << shift) >> 1; mask >= 1; mask >>= 1)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) a[i] += __shfl_xor(a[i], mask, WAVE);
+                    for (int i = 0; i < BATCH; ++i) a[i] += __shfl_xor(a[i], mask, WAVE);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; i < BATCH; ++i) {
                     const int row = row0 + (i0 + i) * rows_per_load();
                     if (c0 == 0 && row < g) out[row] = add != nullptr ? add[row] + a[i] : a[i];
                 }
@@ -169,9 +169,10 @@ template <typename T, int N> struct Rows {
     __device__ __forceinline__ void weighted_sum(const float *weight, T *out) const
     {
         constexpr int EPC = Elt<T>::EPC;
+        const int lanes = min((int)WAVE, (g <= 1 ? 1 : 2 << (31 - __builtin_clz(g - 1))) << shift);       // that hold rows of the group
         auto finish = [&](float (&acc)[EPC], int c) {
 #pragma unroll 1
-            for (int mask = 1 << shift; mask < WAVE; mask <<= 1)
+            for (int mask = 1 << shift; mask < lanes; mask <<= 1)
 #pragma unroll
                 for (int e = 0; e < EPC; ++e) acc[e] += __shfl_xor(acc[e], mask, WAVE);
             if (row0 == 0 && c < chunks) *reinterpret_cast<uintx4 *>(out + c * EPC) = pack4<T>(acc);
@@ -278,8 +279,8 @@ __device__ __forceinline__ void summary_columns(const T *rows, int H, int hps, i
 // One group by one wavefront: scores against the summary query `qb` (Eq. 6), both components reduced (Eq. 7, Eq. 8 or an ablation's
 // strategy), the anchor's token index (first_token + row) and, if asked for, the weights.  row_val, row_norm: 64 floats of LDS each,
 // the wavefront's own.
-template <typename T>
-__device__ __forceinline__ void condense_group(const Rows<T, 16> &pool, const Rows<T, 4> &sel, const float *qb, int mla, int d_pool, int g, float scale,
+template <typename T, int NP, int NS>
+__device__ __forceinline__ void condense_group(const Rows<T, NP> &pool, const Rows<T, NS> &sel, const float *qb, int mla, int d_pool, int g, float scale,
                                                int pool_reduce, int sel_reduce, T *pool_out, T *sel_out, int32_t *anchor, int first_token,
                                                float *alpha_out, float *row_val, float *row_norm, int lane)
 {

@@ -11,6 +11,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype,mode,d_pool,d_sel,g,H,S,n_q", [
     ("bf16", inputs.MODE_GQA, 64, 64, 16, 16, 4, 0),        # 8 pieces per row, held
+    ("bf16", inputs.MODE_GQA, 64, 64, 8, 8, 4, 0),          # one load holds the group, and the last group size that it does
+    ("f16", inputs.MODE_MLA, 64, 56, 9, 8, 2, 0),           # two loads
+    ("bf16", inputs.MODE_GQA, 64, 64, 32, 8, 4, 0),         # four loads, and the last size
+    ("f32", inputs.MODE_GQA, 32, 32, 33, 8, 4, 0),          # five
     ("bf16", inputs.MODE_MLA, 512, 64, 24, 16, 1, 0),       # 24 rows of 64 pieces: read again
     ("f16", inputs.MODE_MLA, 512, 64, 5, 4, 2, 3),
     ("f32", inputs.MODE_GQA, 520, 32, 16, 4, 2, 0),         # 130 pieces per row: more than lanes
@@ -27,11 +31,12 @@ def test_any_width_condensation(oracle, dtype, mode, d_pool, d_sel, g, H, S, n_q
 
 
 @pytest.mark.parametrize("pool_reduce,sel_reduce", [(2, 1), (4, 4), (3, 2), (1, 4)])
-@pytest.mark.parametrize("dtype,d_pool,d_sel,g", [("bf16", 512, 64, 16), ("f32", 520, 64, 24)])
-def test_strategies_at_layer_widths(oracle, dtype, d_pool, d_sel, g, pool_reduce, sel_reduce):
+@pytest.mark.parametrize("dtype,d_pool,d_sel,g", [("bf16", 512, 64, 16), ("f32", 520, 64, 24), ("f16", 64, 32, 3)])
+@pytest.mark.parametrize("mode", [inputs.MODE_MLA, inputs.MODE_GQA])
+def test_strategies_at_layer_widths(oracle, mode, dtype, d_pool, d_sel, g, pool_reduce, sel_reduce):
     from paper_2604_12452_amd import lca
     import torch
-    wl = inputs.Workload("any_reduce", B=1, L=15 * g, H=4, S=1, d_pool=d_pool, d_sel=d_sel, g=g, w=30, dtype=dtype, seed=900 + g)
+    wl = inputs.Workload("any_reduce", B=1, L=15 * g, H=4, S=1, d_pool=d_pool, d_sel=d_sel, g=g, w=30, dtype=dtype, mode=mode, seed=900 + g)
     Q, POOL, SEL = inputs.gen_all(wl)
     Qf, POOLf, SELf = (inputs.to_f64(x, dtype) for x in (Q, POOL, SEL))
     od = hp.oracle_desc(oracle, wl, pool_reduce=pool_reduce, sel_reduce=sel_reduce)

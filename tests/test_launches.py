@@ -72,3 +72,15 @@ def test_rows_that_see_few_entries_are_taken_one_by_one(kw, most):
     assert t.prefill(_odd(L=most + 1, **kw), dense=True)[0].kernel.startswith("attn_tile_kernel")
     many = 8192 // most + 1
     assert t.prefill(_odd(H=many, L=most, w=100, **kw))[0].kernel.startswith("attn_tile_kernel")      # more rows than wavefronts on the chip
+
+
+@pytest.mark.parametrize("kw,held", [
+    (dict(d_pool=64, d_sel=64, g=8, mode=lca.MODE_GQA), "1, 1"), (dict(d_pool=64, d_sel=56, g=9), "4, 4"), (dict(d_pool=64, d_sel=64, g=32, mode=lca.MODE_GQA), "4, 4"),
+    (dict(d_pool=32, d_sel=32, g=33, dtype=lca.F32), "16, 4"), (dict(d_pool=512, d_sel=64, g=1, pool_reduce=lca.REDUCE_MEAN), "1, 1"),
+    (dict(d_pool=512, d_sel=64, g=24), "16, 4"), (dict(d_pool=8, d_sel=8, g=64), "1, 1"),
+    (dict(d_pool=1024, d_sel=1024, g=1, mode=lca.MODE_GQA, dtype=lca.F32), "1, 1"),      # (more pieces than lanes: nothing is held)
+])
+def test_any_width_condensation_by_rows_held(kw, held):
+    """The form of the any-width kernel whose registers hold the group's rows, and no more."""
+    run = t.condense(_odd(L=1000, **kw))
+    assert run[1].kernel.startswith("condense_any_kernel") and run[1].kernel.endswith(held + ">")
