@@ -19,18 +19,21 @@ using namespace group_rows;
 // Summary query: qbar[b,s,x] = mean over t in [L-n_q, L), h in set s of Q[b,t,h,x].
 // One workgroup per (b, s, 16 chunks of 16 bytes), see summary_columns.  Bound by the memory round trip: the lca_condense call of
 // 29 groups at 512 + 64 took 11.2 us with 64 chunks per workgroup and one row per load, and takes 8.4 us.
+// Sixteen wavefronts have 64 row slots.  Four are enough where there are no more than 16 rows, and where the workgroups alone fill the
+// chip (SQ_MANY): there most of sixteen would be waiting for one load.  The cache update's call, fp32 128 + 128, 16 sets, 42 sequences,
+// g = 2: 14.9 us with sixteen, 9.5 with four; fp32 960 + 64, 16 sets, 28 sequences, 64 queries 43.2 / 28.0; bf16 512 + 64, 128 sequences 13.7 / 12.7.
 // ---------------------------------------------------------------------------------------------
-constexpr int SQ_WAVES = 16;
-template <typename T>
-__global__ __launch_bounds__(SQ_WAVES *WAVE) void summary_query_kernel(const T *__restrict__ Q, float *__restrict__ qbar, int L, int H, int S,
+constexpr int SQ_WAVES = 16, SQ_WAVES_FEW = 4, SQ_MANY = 512;
+template <typename T, int WAVES>
+__global__ __launch_bounds__(WAVES *WAVE) void summary_query_kernel(const T *__restrict__ Q, float *__restrict__ qbar, int L, int H, int S,
                                                                        int d_qk, int n_q)
 {
-    __shared__ SummaryPart<T, SQ_WAVES> part;
+    __shared__ SummaryPart<T, WAVES> part;
     const int n_chunks = d_qk / Elt<T>::EPC;
     const int xblocks = (n_chunks + SQ_CHUNKS - 1) / SQ_CHUNKS;
     const int bs = blockIdx.x / xblocks, xb = blockIdx.x % xblocks;
     const int b = bs / S, s = bs % S, hps = H / S;
-    summary_columns<SQ_WAVES>(Q + (((size_t)b * L + (L - n_q)) * H + (size_t)s * hps) * d_qk, H, hps, d_qk, n_q, xb, part, qbar + (size_t)bs * d_qk);
+    summary_columns<WAVES>(Q + (((size_t)b * L + (L - n_q)) * H + (size_t)s * hps) * d_qk, H, hps, d_qk, n_q, xb, part, qbar + (size_t)bs * d_qk);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -329,18 +332,20 @@ bool try_reg(const CondenseArgs &a, hipStream_t st, hipError_t &err)
 }  // namespace
 
 // qbar [B,S,d_qk] = mean of the last n_q of the L queries in Q [B,L,H,d_qk] (and of each set's heads)
+template <typename T>
+static void run_summary_query(const Dims &d, const void *Q, int L, float *qbar, hipStream_t st)
+{
+    const int blocks = d.B * d.S * ((d.d_qk / Elt<T>::EPC + SQ_CHUNKS - 1) / SQ_CHUNKS);
+    if ((long)d.n_q * (d.H / d.S) <= SQ_WAVES_FEW * (WAVE / SQ_CHUNKS) || blocks >= SQ_MANY)
+        summary_query_kernel<T, SQ_WAVES_FEW><<<blocks, SQ_WAVES_FEW * WAVE, 0, st>>>((const T *)Q, qbar, L, d.H, d.S, d.d_qk, d.n_q);
+    else
+        summary_query_kernel<T, SQ_WAVES><<<blocks, SQ_WAVES * WAVE, 0, st>>>((const T *)Q, qbar, L, d.H, d.S, d.d_qk, d.n_q);
+}
 hipError_t launch_summary_query(const Dims &d, const void *Q, int L, float *qbar, hipStream_t st)
 {
-    if (d.dtype == LCA_BF16) {
-        const int sq_blocks = d.B * d.S * ((d.d_qk / 8 + SQ_CHUNKS - 1) / SQ_CHUNKS);
-        summary_query_kernel<uint16_t><<<sq_blocks, SQ_WAVES * WAVE, 0, st>>>((const uint16_t *)Q, qbar, L, d.H, d.S, d.d_qk, d.n_q);
-    } else if (d.dtype == LCA_F16) {
-        const int sq_blocks = d.B * d.S * ((d.d_qk / 8 + SQ_CHUNKS - 1) / SQ_CHUNKS);
-        summary_query_kernel<f16_t><<<sq_blocks, SQ_WAVES * WAVE, 0, st>>>((const f16_t *)Q, qbar, L, d.H, d.S, d.d_qk, d.n_q);
-    } else {
-        const int sq_blocks = d.B * d.S * ((d.d_qk / 4 + SQ_CHUNKS - 1) / SQ_CHUNKS);
-        summary_query_kernel<float><<<sq_blocks, SQ_WAVES * WAVE, 0, st>>>((const float *)Q, qbar, L, d.H, d.S, d.d_qk, d.n_q);
-    }
+    if (d.dtype == LCA_BF16) run_summary_query<uint16_t>(d, Q, L, qbar, st);
+    else if (d.dtype == LCA_F16) run_summary_query<f16_t>(d, Q, L, qbar, st);
+    else run_summary_query<float>(d, Q, L, qbar, st);
     return hipGetLastError();
 }
 

@@ -84,3 +84,12 @@ def test_any_width_condensation_by_rows_held(kw, held):
     """The form of the any-width kernel whose registers hold the group's rows, and no more."""
     run = t.condense(_odd(L=1000, **kw))
     assert run[1].kernel.startswith("condense_any_kernel") and run[1].kernel.endswith(held + ">")
+
+
+@pytest.mark.parametrize("desc,waves", [
+    (_mla(), 16), (_mla(n_q=1), 4), (_mla(n_q=2, H=17), 16), (_mla(H=1), 4), (_mla(B=102), 16), (_mla(B=103), 4), (_gqa(B=33, H=64, n_q=3), 16),
+    (_gqa(n_q=4), 4), (_gqa(n_q=5), 16),
+])
+def test_summary_query_wavefronts(desc, waves):
+    """Four wavefronts where there are at most 16 rows (queries x heads of a set) or 512 workgroups, else sixteen."""
+    assert t.condense(desc)[0].block == 64 * waves
