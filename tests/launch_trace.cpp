@@ -18,6 +18,7 @@ static std::map<const void *, std::string> &names()
     return m;
 }
 static std::string g_log;
+static int32_t g_mla[28];            // the parameter block of the last attn_mla_kernel launch, its first 112 bytes
 static dim3 g_grid, g_block;
 static size_t g_lds;
 
@@ -25,6 +26,7 @@ extern "C" {
 
 const char *trace_log() { return g_log.c_str(); }
 void trace_reset() { g_log.clear(); }
+const int32_t *trace_mla_params() { return g_mla; }
 
 void **__hipRegisterFatBinary(const void *) { static void *handle; return &handle; }
 void __hipUnregisterFatBinary(void **) {}
@@ -49,8 +51,9 @@ int __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, void **strea
     *grid = g_grid; *block = g_block; *lds = g_lds; *stream = nullptr;
     return 0;
 }
-int hipLaunchKernel(const void *host, dim3 grid, dim3 block, void **, size_t lds, void *)
+int hipLaunchKernel(const void *host, dim3 grid, dim3 block, void **args, size_t lds, void *)
 {
+    if (names()[host].rfind("attn_mla_kernel", 0) == 0) std::memcpy(g_mla, args[0], sizeof g_mla);
     char numbers[96];
     std::snprintf(numbers, sizeof numbers, "\t%llu\t%llu\t%zu\n", (unsigned long long)grid.x * grid.y * grid.z,
                   (unsigned long long)block.x * block.y * block.z, lds);

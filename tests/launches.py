@@ -24,6 +24,7 @@ def _load():
             subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-Wl,-Bsymbolic", "-o", so, os.path.join(here, "launch_trace.cpp"),
                             *objs], check=True)
             _lib = ctypes.CDLL(so)
+        _lib.trace_mla_params.restype = ctypes.POINTER(ctypes.c_int32 * 28)
         _lib.trace_log.restype = _lib.lca_last_error.restype = ctypes.c_char_p
         lca.load()
         for name in lca.EXPORTS:
@@ -65,3 +66,12 @@ def decode(desc, q8=False):
 
 def cache_update(desc):
     return launches("lca_cache_update", desc, lca.CacheLayout(desc.m, desc.w + desc.g), *[A] * 6, *WS, None)
+
+
+def mla_query_blocks(desc, **kw):
+    """Query blocks per sequence of the MLA prefill launch: the number behind the descriptor's sizes in the kernel's parameter block."""
+    prefill(desc, **kw)
+    words = list(_load().trace_mla_params().contents)
+    sizes = [desc.B, desc.L, desc.H, desc.S, desc.g, desc.w, desc.m, 0]
+    (at,) = [i for i in range(len(words) - len(sizes)) if words[i:i + len(sizes)] == sizes]
+    return words[at + len(sizes)]

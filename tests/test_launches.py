@@ -93,3 +93,15 @@ def test_any_width_condensation_by_rows_held(kw, held):
 def test_summary_query_wavefronts(desc, waves):
     """Four wavefronts where there are at most 16 rows (queries x heads of a set) or 512 workgroups, else sixteen."""
     assert t.condense(desc)[0].block == 64 * waves
+
+
+@pytest.mark.parametrize("desc,heads", [
+    (_mla(H=128, L=143, B=4), 1), (_mla(H=128, L=637), 1), (_mla(H=128, L=700), 4), (_mla(H=64, L=206, B=4), 1), (_mla(H=64, L=400), 4),
+    (_mla(H=32, L=100), 4), (_mla(H=126, S=2, L=100), 1), (_mla(H=132, S=2, L=100), 1), (_mla(H=132, S=2, L=900), 2),
+])
+def test_up_projection_items(desc, heads):
+    """Heads of a work item, which has 128 / heads rows: one where the matrices of more than 32 heads weigh more than the few tiles of an
+    item."""
+    assert t.mla_query_blocks(desc, up=True) == -(-desc.L * heads // 128)
+    hps = desc.H // desc.S
+    assert t.mla_query_blocks(desc) == -(-desc.L * (4 if hps % 4 == 0 else 2 if hps % 2 == 0 else 1) // 128)
