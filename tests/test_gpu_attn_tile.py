@@ -26,10 +26,15 @@ pytestmark = pytest.mark.gpu
     ("f32", inputs.MODE_MLA, 128, 32, 16, 4, 3, 4, 1, 1),        # fewer tiles than wavefronts
     ("f32", inputs.MODE_GQA, 416, 64, 70, 8, 9, 4, 2, 1),        # key and value rows apart: two wavefronts' areas take 141 KB ...
     ("f32", inputs.MODE_GQA, 512, 64, 130, 4, 60, 2, 1, 2),      # ... of LDS
-    # enough rows for two blocks per wavefront
+    ("f16", inputs.MODE_MLA, 256, 32, 150, 16, 33, 4, 1, 1),
+    ("f16", inputs.MODE_GQA, 384, 64, 70, 8, 9, 2, 1, 1),
+    ("f16", inputs.MODE_GQA, 64, 64, 131, 4, 10, 8, 2, 1),
+    # as many rows as two blocks per wavefront take, which only heads up to 64 wide have: with them ...
     ("bf16", inputs.MODE_GQA, 64, 64, 1030, 16, 40, 16, 4, 2),
-    ("f16", inputs.MODE_GQA, 128, 96, 1037, 32, 21, 32, 8, 1),
+    ("f16", inputs.MODE_GQA, 64, 64, 1030, 16, 40, 16, 4, 2),
     ("f32", inputs.MODE_GQA, 64, 32, 1025, 8, 17, 16, 4, 2),
+    # ... and one block each all the same
+    ("f16", inputs.MODE_GQA, 128, 96, 1037, 32, 21, 32, 8, 1),
     ("f32", inputs.MODE_MLA, 128, 32, 2053, 16, 50, 16, 1, 1),
     # no instantiation: the row-by-row kernel
     ("f32", inputs.MODE_GQA, 520, 32, 40, 4, 5, 2, 1, 1),

@@ -9,21 +9,31 @@ from tests import helpers as hp
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("dtype,mode,B,L,H,S,g,w", [
-    ("bf16", inputs.MODE_MLA, 1, 37, 16, 1, 4, 20),              # fewer tiles than wavefronts of one workgroup
-    ("bf16", inputs.MODE_MLA, 1, 1024, 16, 1, 16, 1024),         # 16 workgroups: one tile each, the merge's one-group form at its limit
-    ("f16", inputs.MODE_MLA, 2, 2200, 16, 1, 1, 100),            # 35 workgroups each, two tiles per wavefront, the last one ragged
-    ("bf16", inputs.MODE_MLA, 1, 16400, 16, 1, 2, 16),           # 64 workgroups
-    ("bf16", inputs.MODE_MLA, 20, 1500, 4, 1, 1, 30),            # 12 workgroups per sequence at most, four tiles each
-    ("bf16", inputs.MODE_MLA, 130, 300, 2, 1, 2, 30),            # more than half as many sequences as CUs: one workgroup each
-    ("bf16", inputs.MODE_MLA, 1, 512, 16, 1, 16, 512),           # 8 and 9 partial results: on both sides of eight rows per thread
-    ("f16", inputs.MODE_MLA, 1, 520, 7, 1, 16, 1024),
-    ("bf16", inputs.MODE_MLA, 1, 2100, 16, 1, 16, 4096),         # 17: the first with four groups
-    ("bf16", inputs.MODE_MLA, 1, 8300, 16, 1, 16, 9000),         # 65: more than a wavefront has lanes
-    ("bf16", inputs.MODE_GQA, 1, 6100, 28, 4, 1, 40),            # 48 workgroups per KV head
-    ("f16", inputs.MODE_GQA, 3, 2900, 14, 2, 2, 33),
-    ("bf16", inputs.MODE_GQA, 33, 400, 8, 4, 2, 64),             # 132 pairs
-])
+# ..., workgroups per (sequence, set); tests/test_launches.py checks these on the CPU, so that a changed rule cannot move the cases
+CASES = [
+    ("bf16", inputs.MODE_MLA, 1, 37, 16, 1, 4, 20, 1),              # fewer tiles than wavefronts of one workgroup
+    ("bf16", inputs.MODE_MLA, 1, 1024, 16, 1, 16, 1024, 16),        # one tile per wavefront, the merge's one-group form at its limit
+    ("f16", inputs.MODE_MLA, 2, 2200, 16, 1, 1, 100, 18),           # two tiles per wavefront, the last one ragged
+    ("bf16", inputs.MODE_MLA, 1, 16400, 16, 1, 2, 16, 65),          # one more than a wavefront has lanes: the merge for any number
+    ("bf16", inputs.MODE_MLA, 20, 1500, 4, 1, 1, 30, 6),            # four tiles per wavefront
+    ("bf16", inputs.MODE_MLA, 130, 300, 2, 1, 2, 30, 1),            # more than half as many sequences as CUs: one workgroup each
+    ("bf16", inputs.MODE_MLA, 1, 512, 16, 1, 16, 512, 8),           # 8 and 9 partial results: on both sides of eight rows per thread
+    ("f16", inputs.MODE_MLA, 1, 520, 7, 1, 16, 1024, 9),
+    ("bf16", inputs.MODE_MLA, 1, 2100, 16, 1, 16, 4096, 17),        # the first with four groups
+    ("bf16", inputs.MODE_MLA, 1, 8300, 16, 1, 16, 9000, 65),
+    ("bf16", inputs.MODE_GQA, 1, 6100, 28, 4, 1, 40, 48),
+    ("f16", inputs.MODE_GQA, 3, 2900, 14, 2, 2, 33, 12),
+    ("bf16", inputs.MODE_GQA, 33, 400, 8, 4, 2, 64, 1),             # 132 pairs
+    ("bf16", inputs.MODE_MLA, 1, 256, 16, 1, 16, 300, 1),           # 16 and 17 tiles: the longest cache of one workgroup, the shortest of several
+    ("f16", inputs.MODE_MLA, 1, 257, 16, 1, 16, 300, 5),
+    ("bf16", inputs.MODE_GQA, 2, 512, 8, 2, 16, 600, 1),
+    ("f16", inputs.MODE_GQA, 2, 513, 8, 2, 16, 600, 5),
+    ("bf16", inputs.MODE_MLA, 1, 7000, 16, 1, 16, 9000, 55),        # the merge's fourth group has work, and all of it
+    ("f16", inputs.MODE_MLA, 1, 8192, 16, 1, 16, 9000, 64),
+]
+
+
+@pytest.mark.parametrize("dtype,mode,B,L,H,S,g,w", [c[:-1] for c in CASES])
 def test_decode_step_splits(oracle, dtype, mode, B, L, H, S, g, w):
     import torch
     from paper_2604_12452_amd import lca

@@ -105,3 +105,25 @@ def test_up_projection_items(desc, heads):
     assert t.mla_query_blocks(desc, up=True) == -(-desc.L * heads // 128)
     hps = desc.H // desc.S
     assert t.mla_query_blocks(desc) == -(-desc.L * (4 if hps % 4 == 0 else 2 if hps % 2 == 0 else 1) // 128)
+
+
+def test_decode_split_cases_are_where_they_claim_to_be():
+    from tests.test_gpu_decode_splits import CASES
+    for dtype, mode, B, L, H, S, g, w, wgs in CASES:
+        d_pool, d_sel = (512, 64) if mode == lca.MODE_MLA else (128, 128)
+        run = t.decode(lca.Desc(B=B, L=L, H=H, S=S, d_pool=d_pool, d_sel=d_sel, g=g, w=w, mode=mode, dtype={"bf16": lca.BF16, "f16": lca.F16}[dtype]))
+        assert run[0].grid == B * S * wgs, (dtype, mode, B, L, wgs, run)
+        merge = "" if wgs == 1 else "decode_merge_kernel" if wgs > 64 else "decode_merge_few_kernel"
+        assert [k.kernel.split("<")[0] for k in run[1:]] == ([merge] if merge else [])
+
+
+def test_tiled_attention_cases_cover_every_instantiation():
+    from tests import test_gpu_attn_tile as cases
+    (mark,) = [m for m in cases.test_every_instantiation_all_rows.pytestmark if m.name == "parametrize"]
+    seen = set()
+    for dtype, mode, d_pool, d_sel, L, g, w, H, S, B in mark.args[1]:
+        d = lca.Desc(B=B, L=L, H=H, S=S, d_pool=d_pool, d_sel=d_sel, g=g, w=w, mode=mode, dtype={"bf16": lca.BF16, "f16": lca.F16, "f32": lca.F32}[dtype])
+        seen |= {t.prefill(d)[0].kernel, t.prefill(d, dense=True)[0].kernel}
+    built = {"unsigned short": 5, "f16_t": 5, "float": 5}
+    for T, n in built.items():
+        assert len([k for k in seen if k.startswith(f"attn_tile_kernel<{T},")]) == n, (T, sorted(seen))
