@@ -160,10 +160,12 @@ __device__ __forceinline__ Blk make_blk(const G64Params &kp, int unit, int it, i
     k.raw_lo_blk = mt_blk_lo * g;
     // fp16: a row's reference is the largest of the first entries it sees, and later logits may rise by 20 binades over it before
     // the item has to be repeated.  While the first representatives are a handful they are a poor sample (a row may see
-    // one): such items start with the raw tokens (a window of 32 or more), of which every row sees at least
-    // min(g, 32) in its first half tile.  Repeats
-    // cost L = 1100, 32 heads over 8 KV heads, 85 us instead of 34, L = 5003 136 instead of 110 (28 over 4: 138, now 97).  Starting
-    // every item with the raw tokens is no better: neighbouring tokens are alike, and 16 of them are a poor sample too (139 us).
+    // one): such items start with the raw tokens (a window of 32 or more), of which a row sees at least gcd(g, 32) in the first half
+    // tile where it sees any (its first token lies a multiple of g behind the item's): 16 of them for g = 16 or 48, 8 for 8 or 24, one for
+    // an odd g, which is as poor a sample as before.  Repeats cost L = 1100, 32 heads over 8 KV heads, 85 us instead of 34, L = 5003 136
+    // instead of 110 (28 over 4: 138, now 97), where neighbouring tokens are alike; where they are not and nothing is repeated in either order, the
+    // reference that is missing for longer costs up to 6 % (32 heads, 32 KV heads, four sequences of L = 912, w = 128: 46 / 49 us).  Starting
+    // every item with the raw tokens is no better: 16 neighbouring tokens are a poor sample too (139 us).
     const int n_rep = (k.mt_blk_hi + BN - 1) / BN, n_raw = (k.t_last + 1 - k.raw_lo_blk + BN - 1) / BN;
     k.flip = F16 && w >= 32 ? lt_mask(mt_blk_lo, FEW_REPS) : 0;
     const int rep0 = k.flip ? n_raw : 0, raw0 = k.flip ? 0 : n_rep;

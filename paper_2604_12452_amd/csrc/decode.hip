@@ -232,7 +232,7 @@ __global__ __launch_bounds__(WAVE *NWAVE) void decode_split_kernel(const T *__re
 // exp(max_sp - max) / sum, are computed once into LDS; then thread (group, column pair) sums every MERGE_GROUPS-th run of eight
 // splits' rows with 8-byte loads, eight of them in flight, and the groups' sums are added in order through LDS.  DP is even;
 // rows start 8 bytes into a (DP + 2)-float record, so 8 bytes is the alignment there is.  For more than 64 splits (one or two
-// lonely caches); fewer go to decode_merge_few_kernel.
+// lonely caches, or decode_split_kernel's many); fewer go to decode_merge_few_kernel.
 constexpr int MERGE_THREADS = 256, MERGE_GROUPS = 4;
 template <typename T>
 __global__ __launch_bounds__(MERGE_THREADS *MERGE_GROUPS) void decode_merge_kernel(const float *__restrict__ part, T *__restrict__ O, int HPS, int DP, int splits)

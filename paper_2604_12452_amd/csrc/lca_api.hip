@@ -102,7 +102,9 @@ lca_status hip_status(hipError_t e, const char *what)
 // launch.  So the thread's error state is read, and thereby cleared, right before a launch function runs.
 #define LCA_LAUNCH(call, what) ((void)hipGetLastError(), hip_status((call), (what)))
 
-// The two matrix-core kernels take their widths in a 16-bit type with a positive scale (their fixed-reference softmax
+// The two layer-width kernels take their widths in a 16-bit type with a positive scale (their fixed-reference softmax
+// orders logits by the raw products); the tiled kernel takes every other descriptor, a zero or negative scale included, that it has an
+// instantiation for and that is not a handful of entries per row; the rest runs row by row.
 lca_status run_attn(const lca::AttnArgs &a, hipStream_t st, const char *what)
 {
     if (lca::attn_mla_supported(a.d)) return LCA_LAUNCH(lca::launch_attn_mla(a, st), what);

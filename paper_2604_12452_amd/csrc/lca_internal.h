@@ -78,7 +78,7 @@ hipError_t launch_probe_mfma_bf16(int iters, int pattern, float *out, int *wavef
 bool condense_mla_mfma_supported(const Dims &d);
 hipError_t launch_condense_mla_mfma(const CondenseArgs &a, hipStream_t st);
 hipError_t launch_attn_simple(const AttnArgs &a, hipStream_t st);
-hipError_t launch_attn_tile(const AttnArgs &a, hipStream_t st, bool &done);      // done = false: no instantiation for these widths, nothing launched
+hipError_t launch_attn_tile(const AttnArgs &a, hipStream_t st, bool &done);      // done = false: nothing launched, launch_attn_simple's work
 bool attn_mla_supported(const Dims &d);
 size_t attn_mla_up_workspace_bytes(const Dims &d);
 hipError_t launch_attn_mla(const AttnArgs &a, hipStream_t st);
