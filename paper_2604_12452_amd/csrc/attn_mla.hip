@@ -87,6 +87,7 @@ struct MlaParams {
     float *lse;
     const uint16_t *W_up;   // UP variant: value up-projection W^UV in fragment order (pack_up_kernel), and O is [B, L, H, DU]
     int B, L, H, S, g, w, m, dense, n_qb;
+    int run_log2;           // log2 of the query blocks an XCD works on at a time (256 rows at most)
     int hw_log2;            // log2 of the heads of a work item (4, 2 or 1): its wavefronts are that many heads x 4 / heads groups of 32 rows
     float scale_log2, bias_log2;
 };
@@ -537,9 +538,9 @@ __device__ __forceinline__ float row_max(const floatx16 &sv, float c, float bias
 
 
 // Persistent kernel: one workgroup per CU walks a list of work items.  Workgroup w lives on XCD w%8 (round-
-// robin placement) and is slot w/8 of that XCD; the heaviest-first list of query blocks is dealt out to the XCDs in runs of 256
+// robin placement) and is slot w/8 of that XCD; the heaviest-first list of query blocks is dealt out to the XCDs in runs of up to 256
 // rows, back and forth, and an XCD's item list is (its blocks) x (all heads), so that at any time the slots of an XCD
-// work on the heads of 256 neighbouring rows, which see nearly the same keys, and share their K/V tiles in that XCD's L2.  The next item's queries and first
+// work on the heads of neighbouring rows, which see nearly the same keys, and share their K/V tiles in that XCD's L2.  The next item's queries and first
 // tiles are requested before the current item's output is written, so the transition costs no round trip.
 //
 // Iteration tl of the tile loop, after its barrier: the held-back last MFMAs of the O^T update of tile tl-1
@@ -614,7 +615,7 @@ __global__ __launch_bounds__(256) void attn_mla_kernel(const MlaParams kp)
 
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, n_slots = gridDim.x >> 3;
     const int n_units = kp.n_qb * kp.B, n_hg = H >> kp.hw_log2;             // (query block, sequence) pairs, heaviest first; head groups
-    const int run = kp.hw_log2 + 1;                                         // log2 of the query blocks an XCD works on at a time (256 rows)
+    const int run = kp.run_log2;
     const int items_per_xcd = (((n_units - 1) >> (run + 3)) + 1) * (n_hg << run);   // some may fall past n_units
     auto item = [&](int kidx, int &b, int &hg, int &qb) {     // false when the item does not exist
         hg = kidx % n_hg;
@@ -884,7 +885,13 @@ hipError_t launch_attn_mla(const AttnArgs &a, hipStream_t st)
     kp.scale_log2 = d.scale * 1.4426950408889634f;
     kp.bias_log2 = d.rep_logit_bias * 1.4426950408889634f;
     // persistent grid: one workgroup per CU (a workgroup takes all of a CU's LDS and registers)
-    const long run = 16l << kp.hw_log2, items = ((long)kp.n_qb * d.B + run - 1) / run * run * (d.H >> kp.hw_log2);
+    // Query blocks an XCD takes at a time: 256 rows, fewer while that leaves an XCD without work, one while there is a CU for every item (a long
+    // run keeps the slots of an XCD on the same keys; it is also as many times all heads for one XCD before the next has any).  256 rows always / so:
+    // 16 heads, L = 281 25.0 / 20.3 us, L = 1500 70.0 / 58.7; 64 heads, L = 640 125 / 46; 128 heads, L = 300 158 / 37; 16 heads, L = 8192 320 / 320.
+    const long units = (long)kp.n_qb * d.B;
+    kp.run_log2 = kp.hw_log2 + 1;
+    while (kp.run_log2 > 0 && ((8l << kp.run_log2) > units || units * (d.H >> kp.hw_log2) <= persistent_grid())) --kp.run_log2;
+    const long run = 8l << kp.run_log2, items = (units + run - 1) / run * run * (d.H >> kp.hw_log2);
     const long cus = persistent_grid();
     long grid = items < cus ? items : cus;
     grid = (grid + 7) / 8 * 8;

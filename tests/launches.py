@@ -68,10 +68,11 @@ def cache_update(desc):
     return launches("lca_cache_update", desc, lca.CacheLayout(desc.m, desc.w + desc.g), *[A] * 6, *WS, None)
 
 
-def mla_query_blocks(desc, **kw):
-    """Query blocks per sequence of the MLA prefill launch: the number behind the descriptor's sizes in the kernel's parameter block."""
+def mla_items(desc, **kw):
+    """(query blocks per sequence, log2 of the query blocks an XCD takes at a time, log2 of the heads of a work item) of the MLA prefill launch:
+    the numbers behind the descriptor's sizes in the kernel's parameter block."""
     prefill(desc, **kw)
     words = list(_load().trace_mla_params().contents)
     sizes = [desc.B, desc.L, desc.H, desc.S, desc.g, desc.w, desc.m, 0]
-    (at,) = [i for i in range(len(words) - len(sizes)) if words[i:i + len(sizes)] == sizes]
-    return words[at + len(sizes)]
+    (at,) = [i + len(sizes) for i in range(len(words) - len(sizes)) if words[i:i + len(sizes)] == sizes]
+    return tuple(words[at:at + 3])

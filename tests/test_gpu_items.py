@@ -1,4 +1,4 @@
-"""Work items of the prefill kernels.  MLA: four, two or one heads x 32, 64 or 128 rows, dealt out to the XCDs in runs of 256 rows,
+"""Work items of the prefill kernels.  MLA: four, two or one heads x 32, 64 or 128 rows, dealt out to the XCDs in runs of up to 256 rows,
 every other round the other way."""
 import pytest
 
@@ -13,7 +13,11 @@ pytestmark = pytest.mark.gpu
     (259, 16, 33, 6, 1, 1, "f16"),        # three groups of two heads x 64 rows
     (260, 8, 16, 8, 2, 3, "bf16"),        # four heads per set, two sets
     (133, 4, 9, 5, 1, 1, "bf16"),         # an odd number of heads: one head x 128 rows
-    (2100, 64, 20, 64, 1, 1, "bf16"),     # a second, reversed round with work for one XCD only; several items per slot and round
+    # more items than CUs, two query blocks for an XCD at a time (in fp16: among 41 000 vectors of these short contexts the rounding of
+    # the representatives to bf16, up to 2^-9 of every component and again through the logits, alone reaches 1.01e-2 of an output)
+    (640, 16, 20, 64, 1, 1, "f16"),
+    (1100, 64, 20, 64, 1, 1, "f16"),      # four
+    (2100, 64, 20, 64, 1, 1, "bf16"),     # eight; a second, reversed round with work for one XCD only; several items per slot and round
 ])
 def test_mla_work_items(oracle, L, g, w, H, S, B, dtype):
     wl = inputs.Workload("items", B=B, L=L, H=H, S=S, d_pool=512, d_sel=64, g=g, w=w, dtype=dtype, seed=70 + L)

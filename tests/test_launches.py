@@ -102,9 +102,17 @@ def test_summary_query_wavefronts(desc, waves):
 def test_up_projection_items(desc, heads):
     """Heads of a work item, which has 128 / heads rows: one where the matrices of more than 32 heads weigh more than the few tiles of an
     item."""
-    assert t.mla_query_blocks(desc, up=True) == -(-desc.L * heads // 128)
-    hps = desc.H // desc.S
-    assert t.mla_query_blocks(desc) == -(-desc.L * (4 if hps % 4 == 0 else 2 if hps % 2 == 0 else 1) // 128)
+    for run, h in ((t.mla_items(desc, up=True), heads), (t.mla_items(desc), 4 if desc.H // desc.S % 4 == 0 else 2 if desc.H // desc.S % 2 == 0 else 1)):
+        assert (run[0], 1 << run[2]) == (-(-desc.L * h // 128), h)
+
+
+@pytest.mark.parametrize("desc,run", [
+    (_mla(L=281), 0), (_mla(L=2048), 0), (_mla(L=2049), 3), (_mla(L=300, H=128), 0), (_mla(L=640, H=64), 1), (_mla(L=1100, H=64), 2), (_mla(L=2100, H=64), 3),
+    (_mla(L=8192), 3), (_mla(L=131072), 3), (_mla(L=2048, S=16), 0), (_mla(L=2049, S=16), 1), (_mla(L=800, H=12, S=2, B=3), 0), (_mla(L=1000, H=12, S=2, B=3), 2),
+])
+def test_mla_query_blocks_of_an_xcd(desc, run):
+    """256 rows at a time, fewer while that leaves an XCD without work, one block while there is a CU for every item."""
+    assert t.mla_items(desc)[1] == run
 
 
 def test_decode_split_cases_are_where_they_claim_to_be():
