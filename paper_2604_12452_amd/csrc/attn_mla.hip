@@ -872,13 +872,15 @@ hipError_t launch_attn_mla(const AttnArgs &a, hipStream_t st)
     // 32768 1915 / 1767, 131072 17.72 / 17.22 ms; with the up-projection, where four heads read four matrices, L = 20000 1082 / 993.
     const int hps = d.H / d.S;
     kp.hw_log2 = hps % 4 == 0 ? 2 : hps % 2 == 0 ? 1 : 0;
-    // The up-projection of more than 32 heads: their matrices (128 KB each) do not stay in a 4 MB L2, and items of one head x 128 rows read a
-    // quarter as much of them.  That decides while the longest item has few tiles to attend.  One head / four heads, 128 heads: L = 143, B = 4
-    // 178 / 228 us, L = 637 313 / 348, L = 1226, B = 2 711 / 571 (37 tiles); 64 heads: L = 206, B = 4 101 / 108, L = 716 175 / 173, L = 2988 481 / 394.
-    if (a.W_up != nullptr && d.H > 32) {
+    // The up-projection of more than 64 heads: their matrices (128 KB each) pass through an L2 of 4 MB for every few items, and items of one
+    // head x 128 rows read a quarter as much of them.  That decides while an item has few tiles to attend and there are many items (more
+    // than two per CU: with fewer the heads of a row block are spread over the chip).  One head / four heads, 128 heads: B = 4, L = 143 105 / 128 us, L = 511
+    // 311 / 379, B = 2, L = 944 277 / 306; but L = 289 116 / 78, L = 637 180 / 144, L = 3931 1324 / 1271; 64 heads: B = 4, L = 206 62 / 61, L = 2988 415 / 381.
+    if (a.W_up != nullptr && d.H > 64) {
         auto visible = [&](int t) { return t + 1 <= d.w ? 0 : (t + 1 - d.w) / d.g; };
         const int t_first = (d.L - 1) / BM * BM, tiles = (visible(d.L - 1) + BN - 1) / BN + (d.L - visible(t_first) * d.g + BN - 1) / BN;
-        if (d.H > 6 * tiles) kp.hw_log2 = 0;
+        const long items = ((long)d.L * (1 << kp.hw_log2) + BM - 1) / BM * d.B * (d.H >> kp.hw_log2);
+        if (tiles <= 40 && items > 512 && items >= 64l * tiles) kp.hw_log2 = 0;
     }
     const int rows = BM >> kp.hw_log2;
     kp.n_qb = (d.L + rows - 1) / rows;

@@ -32,9 +32,9 @@ def test_gqa_fp16_items_on_both_sides_of_the_segment_order(oracle, L, g, w, H, S
     _full_parity(oracle, wl)
 
 
-@pytest.mark.parametrize("L,g,w,H,B", [(131, 8, 20, 64, 1), (260, 16, 1000, 36, 2), (700, 4, 33, 36, 1)])
+@pytest.mark.parametrize("L,g,w,H,B", [(131, 8, 20, 68, 8), (260, 16, 1000, 68, 2), (700, 4, 33, 36, 1)])
 def test_up_projection_of_many_heads(L, g, w, H, B):
-    """More than 32 heads over one set, on both sides of the rule for heads per item: the projected output against the latent output
+    """Many heads over one set, on both sides of the rule for heads per item: the projected output against the latent output
     (whose items are of four heads) projected in float64."""
     import numpy as np
     import torch

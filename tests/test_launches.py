@@ -96,12 +96,13 @@ def test_summary_query_wavefronts(desc, waves):
 
 
 @pytest.mark.parametrize("desc,heads", [
-    (_mla(H=128, L=143, B=4), 1), (_mla(H=128, L=637), 1), (_mla(H=128, L=700), 4), (_mla(H=64, L=206, B=4), 1), (_mla(H=64, L=400), 4),
-    (_mla(H=32, L=100), 4), (_mla(H=126, S=2, L=100), 1), (_mla(H=132, S=2, L=100), 1), (_mla(H=132, S=2, L=900), 2),
+    (_mla(H=128, L=143, B=4), 1), (_mla(H=128, L=511, B=4, w=512), 1), (_mla(H=128, L=944, B=2, w=128, g=8), 1), (_mla(H=128, L=512), 4),
+    (_mla(H=128, L=513), 4), (_mla(H=128, L=581, w=128), 1), (_mla(H=128, L=60000), 4), (_mla(H=64, L=206, B=4), 4), (_mla(H=32, L=100), 4),
+    (_mla(H=132, S=2, L=300, B=3), 1), (_mla(H=132, S=2, L=300), 2),
 ])
 def test_up_projection_items(desc, heads):
-    """Heads of a work item, which has 128 / heads rows: one where the matrices of more than 32 heads weigh more than the few tiles of an
-    item."""
+    """Heads of a work item, which has 128 / heads rows: one where the matrices of more than 64 heads weigh more than the few tiles of many
+    items."""
     for run, h in ((t.mla_items(desc, up=True), heads), (t.mla_items(desc), 4 if desc.H // desc.S % 4 == 0 else 2 if desc.H // desc.S % 2 == 0 else 1)):
         assert (run[0], 1 << run[2]) == (-(-desc.L * h // 128), h)
 
