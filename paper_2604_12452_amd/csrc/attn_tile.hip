@@ -4,11 +4,14 @@
 //
 // What these shapes need is parallelism and reuse, not the last MFMA: one wavefront per query row, every key element a
 // scalar load of its own, took 128 us for 0.36 GFLOP in fp32 (L = 1024, 4 heads, 128 + 32) and 1.44 ms for 5.3 GFLOP in bf16
-// (L = 2500, 16 heads over 4 KV heads, 64 / 64).  This kernel takes 15.6 us (launch and memory latency: three tiles per wavefront)
-// and 32 us (request rate of the tile loads and vector ALU: softmax, the splitting of the probabilities).  Here
+// (L = 2500, 16 heads over 4 KV heads, 64 / 64).  With the condensation before it the first takes 20.5 us now (launches, memory latency, a chain of
+// fp32 products per tile), the second 31.3 us (vector ALU: exponentials and the splitting of the probabilities).  Two things the compiler does
+// are kept from it below, each of which had every tile wait for the next one's loads (21.9 and 38.5 us; fp32, 8 heads, L = 4096 153 us, now 126;
+// bf16 256 + 32, 8 heads, two times L = 4000 182, now 156): the queries' arrival left open until the loop, and load offsets computed in the
+// registers that loads fill.  Here
 //   * a workgroup owns 16 QB query rows of one condensed set, numbered (token, head of the set): the heads of a set see the
 //     same keys, so the rows of a workgroup span few tokens;
-//   * its wavefronts split the KEY tiles among them, each with a softmax (running maximum) of its own, and are merged through
+//   * its wavefronts split the KEY tiles among them, each with a softmax (a reference that follows the maximum) of its own, and are merged through
 //     LDS at the end: small problems, where a row sees a few hundred entries, still fill the chip, and nothing in the loop
 //     waits for another wavefront;
 //   * a tile (16 NB entries) travels memory -> registers -> the wavefront's own LDS area one tile ahead of its use, as
@@ -41,7 +44,8 @@ using tile16::f16x8;
 using tile16::floatx4;
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
-constexpr int MAX_WAVES = 4;
+// Wavefronts per workgroup at most: eight in fp32 where two of them fit a SIMD's registers (its tiles are long chains of small products).
+template <typename T> constexpr int max_waves(int ndt) { return sizeof(T) == 4 && ndt <= 8 ? 8 : 4; }
 constexpr int RSRC_WORD3 = 0x00020000;   // raw buffer of dwords, gfx9 layout
 constexpr size_t LDS_BYTES = 160 * 1024;      // of a CU
 
@@ -81,6 +85,7 @@ template <typename E8, typename E4, typename E, int NPARTS> struct Mma16 {
 };
 template <> struct Mma<uint16_t> : Mma16<bf16x8, bf16x4, __bf16, 3> {
     static constexpr float P_SCALE = 1.f;          // what the probabilities are multiplied by on their way into the second product
+    static constexpr float REF_SLACK = 8.f;        // binades a row's maximum may be above the reference of its exponentials
     // p = its leading 8 bits + the next 8 + the last 8 (cut off, not rounded: a subtraction each and one byte
     // permutation per pair)
     template <int NB> __device__ static void split(const float (&p)[NB][4], Parts<NB> &o)
@@ -108,6 +113,7 @@ template <> struct Mma<uint16_t> : Mma16<bf16x8, bf16x4, __bf16, 3> {
 };
 template <> struct Mma<f16_t> : Mma16<f16x8, f16x4, _Float16, 3> {
     static constexpr float P_SCALE = 32768.f;      // (an exact product; the results are divided by it with the row's sum)
+    static constexpr float REF_SLACK = 0.f;        // (2^15 p may not pass 65504)
     // 2^15 p = its leading 11 bits + the next 11 + the last 2 (cut off, not rounded: one conversion per pair)
     template <int NB> __device__ static void split(const float (&p)[NB][4], Parts<NB> &o)
     {
@@ -136,7 +142,7 @@ template <> struct Mma<f16_t> : Mma16<f16x8, f16x4, _Float16, 3> {
 };
 template <> struct Mma<float> {
     static constexpr int EPC = 4, CHUNK = 16, PARTS = 1;
-    static constexpr float P_SCALE = 1.f;
+    static constexpr float P_SCALE = 1.f, REF_SLACK = 8.f;
     __device__ static int row_of_m(int m) { return m; }
     __device__ static int entry(int r, int q4) { return 4 * q4 + r; }
     __device__ static floatx4 score(const uintx4 &k, const uintx4 &q, floatx4 c)
@@ -173,6 +179,24 @@ template <> struct Mma<float> {
         return c;
     }
     __device__ static void store4(float *p, const floatx4 &v) { *reinterpret_cast<floatx4 *>(p) = v; }
+};
+
+// Division by a number known on the host: two multiplications by 2^64 / d + 1, exact for every 32-bit x, where a division is thirty-odd
+// instructions, of which a workgroup would issue a dozen before its first load.
+struct Div {
+    unsigned lo, hi, one;                // the 64-bit factor; all ones for d = 1, whose factor has 65 bits
+    __device__ unsigned operator()(unsigned x) const { return (x & one) | ((unsigned)(((unsigned long long)x * hi + __umulhi(x, lo)) >> 32) & ~one); }
+};
+static Div make_div(unsigned d)
+{
+    const unsigned long long f = ~0ull / d + 1;           // (d = 1: not used; a power of two: exactly 2^64 / d)
+    return Div{(unsigned)f, (unsigned)(f >> 32), d == 1 ? ~0u : 0u};
+}
+
+template <typename T> struct TileParams {
+    RowParams<T> r;
+    int n_blocks;                        // workgroups per (sequence, set)
+    Div by_blocks, by_s, by_hps, by_g;
 };
 
 // Byte layout of one wavefront's LDS area, the same on both sides of the launch.
@@ -216,10 +240,11 @@ __device__ __forceinline__ float row_sum4(float x)
 // results nobody stores), QB: blocks of 16 query rows, NB: blocks of 16 entries per tile, NIT: 16-byte pieces of a
 // row / 16 (upper bound).
 template <typename T, int NDT, int NKC, int QB, int NB, int NIT>
-__global__ __launch_bounds__(64 * MAX_WAVES) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 && NDT <= 4 ? 3 : sizeof(T) == 2 && NDT <= 16 ? 2 : 1, 8)))
-void attn_tile_kernel(const RowParams<T> kp, int n_blocks)
+__global__ __launch_bounds__(64 * max_waves<T>(NDT)) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 && NDT <= 4 ? 3 : NDT <= 8 || (sizeof(T) == 2 && NDT <= 16) ? 2 : 1, 8)))
+void attn_tile_kernel(const TileParams<T> tp)
 {
     typedef Mma<T> M;
+    const RowParams<T> &kp = tp.r;
     extern __shared__ __attribute__((aligned(64))) char smem[];
     constexpr int TK = 16 * NB, ROWS = 16 * QB, MROW = 16 * NDT + 4;
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, q4 = lane >> 4;
@@ -229,21 +254,25 @@ void attn_tile_kernel(const RowParams<T> kp, int n_blocks)
 
     // which rows: the latest (heaviest) first
     const int hps = kp.H / kp.S, L = kp.L, g = kp.g;
-    const int blk = n_blocks - 1 - (int)(blockIdx.x % n_blocks), bs = blockIdx.x / n_blocks, s = bs % kp.S, b = bs / kp.S;
+    const int bs = tp.by_blocks(blockIdx.x), blk = tp.n_blocks - 1 - (int)(blockIdx.x - bs * tp.n_blocks), b = tp.by_s(bs), s = bs - b * kp.S;
     const int n_rows = L * hps, r0 = blk * ROWS, r_last = min(r0 + ROWS, n_rows) - 1;
-    auto visible = [&](int t) { return (kp.dense || t + 1 <= kp.w) ? 0 : (t + 1 - kp.w) / g; };
-    const int t_first = r0 / hps, t_last = r_last / hps;
+    const int w_seen = kp.dense ? L : kp.w;                // raw tokens a row sees before it sees a representative
+    auto visible = [&](int t) { return (int)tp.by_g(max(t + 1 - w_seen, 0)); };
+    const int t_first = tp.by_hps(r0), t_last = tp.by_hps(r_last);
     const int mt_first = visible(t_first), n_rep = visible(t_last), raw0 = mt_first * g;
     const int rep_tiles = (n_rep + TK - 1) / TK, n_tiles = rep_tiles + (t_last + 1 - raw0 + TK - 1) / TK;
     const int d_qk = kp.mla ? kp.d_pool + kp.d_sel : kp.d_sel;
-    const float c = kp.scale * 1.4426950408889634f, bias2 = kp.rep_bias * 1.4426950408889634f;
+    // The logits are c S with the queries' sign for c's: then the largest product is the largest logit, and one fused operation takes a
+    // product to its exponent.  (c is never zero: a hidden entry's -inf must stay one.  1e-37 times any finite product is no
+    // less than zero to an exponential.)
+    const float c_abs = fabsf(kp.scale) * 1.4426950408889634f, c = c_abs < 1e-37f ? 1e-37f : c_abs, bias2 = kp.rep_bias * 1.4426950408889634f;
 
     int t_row[QB], mt_row[QB];
     size_t q_row[QB];                    // row index of the query in Q, O and lse: (b L + t) H + h
     bool live[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        const int r = r0 + 16 * qb + col, rc = min(r, n_rows - 1), t = rc / hps;
+        const int r = r0 + 16 * qb + col, rc = min(r, n_rows - 1), t = tp.by_hps(rc);
         live[qb] = r < n_rows;
         t_row[qb] = t;
         mt_row[qb] = visible(t);
@@ -264,22 +293,40 @@ void attn_tile_kernel(const RowParams<T> kp, int n_blocks)
     static_assert(NIT > 1 || (16 * NDT <= 8 * M::EPC && NKC * M::CHUNK <= 8 * M::EPC), "at most eight pieces per component");
     const int r8 = lane >> 3, x8 = lane & 7, ncs = lay.nc - lay.cp;
     uintx4 held[4 * NB][NIT];
+    // The lane's offsets in a tile of the kind in hand, taken again only where the kind changes: computed beside the loads, they went into registers
+    // of the previous tile's pieces, and the wait that needs covered the loads just issued -- a round trip to memory in every tile.
+    int voff[NIT == 1 ? 2 : NIT], kind = -1;
+    auto set_kind = [&](bool is_rep) {
+        const int ps = (is_rep ? 1 : kp.P) * pool_bytes, ss = (is_rep ? 1 : kp.P) * sel_bytes;
+        if constexpr (NIT == 1) {
+            voff[0] = r8 * ps + x8 * 16;
+            voff[1] = r8 * ss + x8 * 16;
+        } else {
+#pragma unroll
+            for (int it = 0; it < NIT; ++it) {
+                const int x = sub + 16 * it;
+                voff[it] = x < lay.cp ? rr * ps + x * 16 : rr * ss + (x - lay.cp) * 16;
+            }
+        }
+        kind = is_rep;
+    };
     auto load_tile = [&](int tile) {
         const bool is_rep = tile < rep_tiles;
+        if (kind != (int)is_rep) set_kind(is_rep);
+#pragma unroll
+        for (int &v : voff) asm volatile("" : "+v"(v));
         const unsigned e0 = is_rep ? tile * TK : raw0 + (tile - rep_tiles) * TK, step = is_rep ? 1 : kp.P, last = is_rep ? n_rep - 1 : t_last;
         const unsigned ps = step * pool_bytes, ss = step * sel_bytes;           // bytes between rows of the segment
         const __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc((void *)(is_rep ? rep_p : raw_p), (short)0, last * ps + pool_bytes, RSRC_WORD3);
         const __amdgpu_buffer_rsrc_t srs = __builtin_amdgcn_make_buffer_rsrc((void *)(is_rep ? rep_s : raw_s), (short)0, last * ss + sel_bytes, RSRC_WORD3);
         if constexpr (NIT == 1) {
             if (x8 < lay.cp) {
-                const int voff = r8 * ps + x8 * 16;
 #pragma unroll
-                for (int i = 0; i < 2 * NB; ++i) held[i][0] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(prs, voff, (e0 + 8 * i) * ps, 0));
+                for (int i = 0; i < 2 * NB; ++i) held[i][0] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(prs, voff[0], (e0 + 8 * i) * ps, 0));
             }
             if (x8 < ncs) {
-                const int voff = r8 * ss + x8 * 16;
 #pragma unroll
-                for (int i = 0; i < 2 * NB; ++i) held[2 * NB + i][0] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(srs, voff, (e0 + 8 * i) * ss, 0));
+                for (int i = 0; i < 2 * NB; ++i) held[2 * NB + i][0] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(srs, voff[1], (e0 + 8 * i) * ss, 0));
             }
             return;
         }
@@ -287,14 +334,12 @@ void attn_tile_kernel(const RowParams<T> kp, int n_blocks)
         for (int it = 0; it < NIT; ++it) {
             const int x = sub + 16 * it;
             if (x < lay.cp) {
-                const int voff = rr * ps + x * 16;
 #pragma unroll
-                for (int i = 0; i < 4 * NB; ++i) held[i][it] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(prs, voff, (e0 + 4 * i) * ps, 0));
+                for (int i = 0; i < 4 * NB; ++i) held[i][it] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(prs, voff[it], (e0 + 4 * i) * ps, 0));
                 asm volatile("; pooled part");       // (keeps the two branches apart: merged into one load, the descriptor would be a per-lane choice)
             } else if (x < lay.nc) {
-                const int voff = rr * ss + (x - lay.cp) * 16;
 #pragma unroll
-                for (int i = 0; i < 4 * NB; ++i) held[i][it] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(srs, voff, (e0 + 4 * i) * ss, 0));
+                for (int i = 0; i < 4 * NB; ++i) held[i][it] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(srs, voff[it], (e0 + 4 * i) * ss, 0));
                 asm volatile("; selected part");
             }
         }
@@ -335,14 +380,29 @@ void attn_tile_kernel(const RowParams<T> kp, int n_blocks)
             const int x = M::CHUNK * kc + M::EPC * q4;
             qf[qb][kc] = x < d_qk ? *reinterpret_cast<const uintx4 *>(kp.Q + q_row[qb] * d_qk + x) : uintx4{0, 0, 0, 0};
         }
+    if (kp.scale < 0.f) {
+        constexpr unsigned SIGN = sizeof(T) == 2 ? 0x80008000u : 0x80000000u;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int kc = 0; kc < NKC; ++kc) qf[qb][kc] ^= SIGN;
+    }
     // the key columns past the width stay zero for the whole kernel (tiles are written over the real columns only)
-    for (int x = lane * 16; x < lay.stage; x += 64 * 16) *reinterpret_cast<uintx4 *>(area + x) = uintx4{0, 0, 0, 0};
+    if (d_qk < NKC * M::CHUNK || kp.d_pool < 16 * NDT)
+        for (int x = lane * 16; x < lay.stage; x += 64 * 16) *reinterpret_cast<uintx4 *>(area + x) = uintx4{0, 0, 0, 0};
+    // The queries arrive here: with loads of the next tile in flight the compiler could not tell theirs apart, and every tile's first product
+    // would wait for the tile after it (B = 1, L = 2500, 16 heads over 4 KV heads, 64 / 64: 3 500 cycles per tile so, with three wavefronts on a SIMD).
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+        for (int kc = 0; kc < NKC; ++kc) asm volatile("" : "+v"(qf[qb][kc]));
 
     floatx4 acc[QB][NDT];
-    float m_run[QB], l_run[QB];          // running maximum of the row (base 2); this lane's share of its sum
+    float m_run[QB], ref[QB], l_run[QB];     // reference of the row (base 2; -inf: none yet), the same or 0; this lane's share of the row's sum
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         m_run[qb] = -INFINITY;
+        ref[qb] = 0.f;
         l_run[qb] = 0.f;
 #pragma unroll
         for (int t = 0; t < NDT; ++t) acc[qb][t] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -374,43 +434,47 @@ void attn_tile_kernel(const RowParams<T> kp, int n_blocks)
         const float bias = is_rep ? bias2 : 0.f;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            float lg[NB][4];
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) lg[nb][r] = fmaf(sc[nb][qb][r], c, bias);
             if (!full) {                 // entries [lo, hi) of the tile's kind are visible to this lane's row
                 const int lo = is_rep ? 0 : mt_row[qb] * g, hi = is_rep ? mt_row[qb] : t_row[qb] + 1;
+                int e1 = e0 + M::entry(0, q4);
+                asm volatile("" : "+v"(e1));          // (the entries' numbers are taken here, not by every tile)
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const int e = e0 + 16 * nb + M::entry(r, q4);
-                        lg[nb][r] = e >= lo && e < hi ? lg[nb][r] : -INFINITY;
+                        const int e = e1 + 16 * nb + M::entry(r, 0);
+                        sc[nb][qb][r] = e >= lo && e < hi ? sc[nb][qb][r] : -INFINITY;
                     }
             }
-            float mx = lg[0][0];
+            // The reference of a row's exponentials is the largest logit it had seen when one last rose REF_SLACK binades above it.  So in the
+            // usual tile nothing is rescaled (a fifth of the tile's work; among 32 rows there nearly always is one with a new maximum) and
+            // no lane has to know another's maximum.
+            float mx = sc[0][qb][0];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                for (int r = nb == 0; r < 4; ++r) mx = fmaxf(mx, lg[nb][r]);
-            const float m_new = fmaxf(m_run[qb], row_max4(mx));
-            if (__builtin_amdgcn_ballot_w64(m_new > m_run[qb]) != 0) {
-                const float corr = __builtin_amdgcn_exp2f(m_run[qb] - (m_new == -INFINITY ? 0.f : m_new));
+                for (int r = nb == 0 ? 1 : 0; r < 4; r += nb == 0 && r == 1 ? 1 : 2) {
+                    if (r + 1 < 4 && !(nb == 0 && r == 1)) asm("v_max3_f32 %0, %1, %2, %3" : "=v"(mx) : "v"(mx), "v"(sc[nb][qb][r]), "v"(sc[nb][qb][r + 1]));
+                    else asm("v_max_f32 %0, %1, %2" : "=v"(mx) : "v"(mx), "v"(sc[nb][qb][r]));
+                }
+            if (__builtin_amdgcn_ballot_w64(fmaf(mx, c, bias) > m_run[qb] + M::REF_SLACK) != 0) {
+                const float to = fmaxf(m_run[qb], fmaf(row_max4(mx), c, bias));
+                ref[qb] = to == -INFINITY ? 0.f : to;
+                const float corr = __builtin_amdgcn_exp2f(m_run[qb] - ref[qb]);
                 l_run[qb] *= corr;
 #pragma unroll
                 for (int t = 0; t < NDT; ++t)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) acc[qb][t][r] *= corr;
-                m_run[qb] = m_new;
+                m_run[qb] = to;
             }
-            const float ref = m_run[qb] == -INFINITY ? 0.f : m_run[qb];
+            const float nb2 = bias - ref[qb];
             float pv[NB][4];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    pv[nb][r] = __builtin_amdgcn_exp2f(lg[nb][r] - ref);
+                    pv[nb][r] = __builtin_amdgcn_exp2f(fmaf(sc[nb][qb][r], c, nb2));
                     l_run[qb] += pv[nb][r];
                 }
             M::template split<NB>(pv, pb[qb]);
@@ -433,64 +497,129 @@ void attn_tile_kernel(const RowParams<T> kp, int n_blocks)
         __builtin_amdgcn_wave_barrier();
     }
 
-    // merge the wavefronts: the upper half hands its results to the lower half until one is left
+    float *const ml = reinterpret_cast<float *>(smem + n_waves * lay.area);     // [wave][row] (maximum, sum)
     float l_tot[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) l_tot[qb] = row_sum4(l_run[qb]);
-    float *const ml = reinterpret_cast<float *>(smem + n_waves * lay.area);     // [wave][row] (maximum, sum)
-    for (int half = n_waves >> 1; half > 0; half >>= 1) {
-        __syncthreads();
-        if (wave >= half && wave < 2 * half) {
-            float *const o = reinterpret_cast<float *>(smem + (wave - half) * lay.area);
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                if (q4 == 0) {
-                    ml[((wave - half) * ROWS + 16 * qb + col) * 2] = m_run[qb];
-                    ml[((wave - half) * ROWS + 16 * qb + col) * 2 + 1] = l_tot[qb];
-                }
-#pragma unroll
-                for (int t = 0; t < NDT; ++t) *reinterpret_cast<floatx4 *>(o + (16 * qb + col) * MROW + 16 * t + 4 * q4) = acc[qb][t];
-            }
-        }
-        __syncthreads();
-        if (wave < half) {
-            const float *const o = reinterpret_cast<const float *>(smem + wave * lay.area);
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                const float mo = ml[(wave * ROWS + 16 * qb + col) * 2], lo = ml[(wave * ROWS + 16 * qb + col) * 2 + 1];
-                const float m_new = fmaxf(m_run[qb], mo), m_eff = m_new == -INFINITY ? 0.f : m_new;
-                const float ca = __builtin_amdgcn_exp2f(m_run[qb] - m_eff), cb = __builtin_amdgcn_exp2f(mo - m_eff);
-                l_tot[qb] = l_tot[qb] * ca + lo * cb;
-                m_run[qb] = m_new;
-#pragma unroll
-                for (int t = 0; t < NDT; ++t) {
-                    const floatx4 v = *reinterpret_cast<const floatx4 *>(o + (16 * qb + col) * MROW + 16 * t + 4 * q4);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[qb][t][r] = acc[qb][t][r] * ca + v[r] * cb;
-                }
-            }
-        }
-    }
-
-    bool bad = false;
-    if (wave == 0) {
+    auto leave = [&]() {                 // this wavefront's results, in its area
+        float *const o = reinterpret_cast<float *>(area);
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            const float inv = 1.f / (l_tot[qb] * M::P_SCALE);
+            if (q4 == 0) *reinterpret_cast<float2 *>(ml + (wave * ROWS + 16 * qb + col) * 2) = float2{m_run[qb], l_tot[qb]};
+#pragma unroll
+            for (int t = 0; t < NDT; ++t) *reinterpret_cast<floatx4 *>(o + (16 * qb + col) * MROW + 16 * t + 4 * q4) = acc[qb][t];
+        }
+    };
+    bool bad = false;
+    // One wavefront stores from its registers, and the first of two does after adding the second's (not in fp32 at 512 columns, where the compiler
+    // then keeps more of the accumulators in memory: 256 + 64, L = 25 20.6 / 23.6 us).
+    constexpr bool PAIR = sizeof(T) == 2 || NDT < 32;
+    if (n_waves == 1 || (PAIR && n_waves == 2)) {
+        if (PAIR && n_waves == 2) {
+            if (wave == 1) leave();
+            __syncthreads();
+        }
+        if (wave == 0) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                if (PAIR && n_waves == 2) {
+                    const float2 other = *reinterpret_cast<const float2 *>(ml + (ROWS + 16 * qb + col) * 2);
+                    const float m_all = fmaxf(m_run[qb], other.x);
+                    const float ca = __builtin_amdgcn_exp2f(m_run[qb] - m_all), cb = __builtin_amdgcn_exp2f(other.x - m_all);
+                    l_tot[qb] = l_tot[qb] * ca + other.y * cb;
+                    m_run[qb] = m_all;
+                    const float *const o = reinterpret_cast<const float *>(smem + lay.area) + (16 * qb + col) * MROW + 4 * q4;
+#pragma unroll
+                    for (int t = 0; t < NDT; ++t) {
+                        const floatx4 v = *reinterpret_cast<const floatx4 *>(o + 16 * t);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) acc[qb][t][r] = acc[qb][t][r] * ca + v[r] * cb;
+                    }
+                }
+                const float inv = 1.f / (l_tot[qb] * M::P_SCALE);
+                float chk = 0.f;
+#pragma unroll
+                for (int t = 0; t < NDT; ++t) {
+                    const int x = 16 * t + 4 * q4;                 // this lane's four value columns
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[qb][t][r] *= inv;
+                    if (live[qb] && x < kp.d_pool) {
+                        M::store4(kp.O + q_row[qb] * kp.d_pool + x, acc[qb][t]);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) chk = fmaf(acc[qb][t][r], 0.f, chk);      // zero, or NaN if a value is not finite
+                    }
+                }
+                if (kp.lse != nullptr && live[qb] && q4 == 0) kp.lse[q_row[qb]] = (m_run[qb] + log2f(l_tot[qb])) * 0.6931471805599453f;
+                bad |= live[qb] && !(chk == 0.f);
+            }
+        }
+    } else {
+        // Every wavefront leaves its results in its area, then the threads share the columns of all rows, four each, over the
+        // wavefronts' areas.  (The upper half handing its results to the lower until one wavefront was left, which then stored alone, took
+        // 2.1 of a workgroup's 13.5 us at 64 / 64 with four wavefronts.)
+        size_t *const row_s = reinterpret_cast<size_t *>(ml + n_waves * ROWS * 2);   // [row] index of the row in Q, O and lse
+        leave();
+        if (wave == 0 && q4 == 0) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) row_s[16 * qb + col] = q_row[qb];
+        }
+        __syncthreads();
+        // a row's weights of the wavefronts, divided by its sum
+        constexpr int W = max_waves<T>(NDT);
+        auto weights = [&](int row, float (&f)[W], bool first) {
+            float2 mw[W];
+            float m_all = -INFINITY, l_all = 0.f;
+#pragma unroll
+            for (int w = 0; w < W; ++w) mw[w] = w < n_waves ? *reinterpret_cast<const float2 *>(ml + (w * ROWS + row) * 2) : float2{-INFINITY, 0.f};
+#pragma unroll
+            for (int w = 0; w < W; ++w) m_all = fmaxf(m_all, mw[w].x);
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                f[w] = __builtin_amdgcn_exp2f(mw[w].x - m_all);
+                l_all = fmaf(mw[w].y, f[w], l_all);
+            }
+            const float inv = 1.f / (l_all * M::P_SCALE);
+#pragma unroll
+            for (int w = 0; w < W; ++w) f[w] *= inv;
+            if (kp.lse != nullptr && first && r0 + row <= r_last) kp.lse[row_s[row]] = (m_all + log2f(l_all)) * 0.6931471805599453f;
+        };
+        // by every thread for itself where it has one item, else once per row, with one more barrier (0.5 us, against the exponentials of every
+        // item: B = 2, L = 4000, 8 heads, bf16 256 + 32 160 / 166 us)
+        constexpr int ITEMS = ROWS * 4 * NDT;
+        const bool own = ITEMS <= 64 * n_waves;
+        float f[W];
+        if (!own) {
+            if (tid < ROWS) {
+                weights(tid, f, true);
+#pragma unroll
+                for (int w = 0; w < W; ++w)
+                    if (w < n_waves) ml[(w * ROWS + tid) * 2] = f[w];
+            }
+            __syncthreads();
+        }
+        for (int i = tid; i < ITEMS; i += 64 * n_waves) {
+            const int row = i / (4 * NDT), x = 4 * (i % (4 * NDT));                  // this thread's four value columns
+            if (r0 + row > r_last || x >= kp.d_pool) continue;
+            floatx4 v[W], sum = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < W; ++w)
+                if (w < n_waves) v[w] = *reinterpret_cast<const floatx4 *>(smem + w * lay.area + (row * MROW + x) * 4);
+            if (own) weights(row, f, x == 0);
+            else {
+#pragma unroll
+                for (int w = 0; w < W; ++w)
+                    if (w < n_waves) f[w] = ml[(w * ROWS + row) * 2];
+            }
+#pragma unroll
+            for (int w = 0; w < W; ++w)
+                if (w < n_waves)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) sum[r] = fmaf(v[w][r], f[w], sum[r]);
             float chk = 0.f;
 #pragma unroll
-            for (int t = 0; t < NDT; ++t) {
-                const int x = 16 * t + 4 * q4;                 // this lane's four value columns
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[qb][t][r] *= inv;
-                if (live[qb] && x < kp.d_pool) {
-                    M::store4(kp.O + q_row[qb] * kp.d_pool + x, acc[qb][t]);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) chk = fmaf(acc[qb][t][r], 0.f, chk);      // zero, or NaN if a value is not finite
-                }
-            }
-            if (kp.lse != nullptr && live[qb] && q4 == 0) kp.lse[q_row[qb]] = (m_run[qb] + log2f(l_tot[qb])) * 0.6931471805599453f;
-            bad |= live[qb] && !(chk == 0.f);
+            for (int r = 0; r < 4; ++r) chk = fmaf(sum[r], 0.f, chk);      // zero, or NaN if a value is not finite
+            M::store4(kp.O + row_s[row] * kp.d_pool + x, sum);
+            bad |= !(chk == 0.f);
         }
     }
     if (__syncthreads_or(bad)) {                               // rare: a row met an infinity or a NaN, perhaps one it does not see
@@ -520,10 +649,16 @@ hipError_t run(const AttnArgs &a, hipStream_t st)
     const int cus = persistent_grid();
     const size_t room = grid <= cus ? LDS_BYTES : grid <= 2 * cus ? LDS_BYTES / 2 : LDS_BYTES * 2 / 5;
     constexpr bool full_registers = NDT > (sizeof(T) == 2 ? 16 : 8);
-    int waves = full_registers && grid > cus ? MAX_WAVES / 2 : MAX_WAVES;
-    while (waves > 1 && (waves / 2 >= tiles || (NDT > 8 && waves > tiles) || (size_t)waves * lay.area + waves * 16 * QB * 8 > room)) waves /= 2;
-    attn_tile_kernel<T, NDT, NKC, QB, NB, NIT><<<(unsigned)grid, 64 * waves, (size_t)waves * lay.area + waves * 16 * QB * 8, st>>>(
-        attn_row::row_params<T>(a), (int)blocks);
+    auto lds = [&](int waves) { return (size_t)waves * lay.area + (waves + 1) * 16 * QB * 8; };
+    int waves = full_registers && grid > cus ? 2 : grid > cus ? 4 : max_waves<T>(NDT);
+    // Where many workgroups keep every CU busy, half the wavefronts each leave half as much to merge.  Four wavefronts / two: 64 / 64, two row blocks, 16 heads
+    // over 4 KV heads, L = 2500 (1252 workgroups) 35.4 / 34.6 us with the condensation, B = 2, L = 4000 (4000) 54.2 / 46.0; fp32 128 + 32, 8 heads, L = 4096
+    // (2048) 142 / 132, but one row block and B = 3, L = 900 (1350) 63.3 / 66.4, longer workgroups not quite twice as many as fit; two / one:
+    // 256 + 32, 8 heads, B = 2, L = 4000 (4000) 162 / 157, but fp32 192 / 128, 7 heads, L = 2347 (1027, one per SIMD) 287 / 468.
+    if (!full_registers && grid >= (QB == 2 ? 4 : 8) * (long)cus && (QB == 2 ? waves > 2 : tiles >= 32 && waves > 1)) waves /= 2;
+    while (waves > 1 && (waves / 2 >= tiles || (NDT > 8 && waves > tiles) || lds(waves) > room)) waves /= 2;
+    const TileParams<T> tp{attn_row::row_params<T>(a), (int)blocks, make_div((unsigned)blocks), make_div(d.S), make_div(d.H / d.S), make_div(d.g)};
+    attn_tile_kernel<T, NDT, NKC, QB, NB, NIT><<<(unsigned)grid, 64 * waves, lds(waves), st>>>(tp);
     return hipGetLastError();
 }
 

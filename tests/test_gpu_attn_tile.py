@@ -1,6 +1,8 @@
 """The tiled attention kernel (csrc/attn_tile.hip): every instantiation (element type, width class, one or two blocks of
 query rows per wavefront) at ragged sizes on every row against the oracle, and entries a row does not see left out of it
 even when they are not finite."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 
@@ -96,3 +98,28 @@ def test_probabilities_enter_the_second_product_whole(dtype):
     print(f"  largest error of p: 2^{np.log2(err):.2f}", flush=True)
     assert err <= 2.0 ** -21.6
     assert np.abs(lse[0, 2].cpu().numpy() - np.log(2.0 + p)).max() <= 4e-7
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("scale", [1.0, -1.0, 0.0])
+@pytest.mark.parametrize("L,d_pool,B", [(15, 64, 1), (31, 64, 2), (60, 128, 1), (300, 128, 1), (300, 64, 1), (2100, 64, 40)])
+@pytest.mark.parametrize("step", [0.16, 0.18, 1.0])
+def test_rising_logits_over_one_to_eight_wavefronts(oracle, dtype, scale, L, d_pool, B, step):
+    """Every entry's logit lies `step` above the one before: 7.4 binades per tile of 32 entries, which the reference of the exponentials does
+    not follow, 8.3 and 46, which it does.  Up to 15 entries are one tile and wavefront, 300 split over eight in fp32, and 40 sequences of 2100
+    take two.  Tolerance: the stated bar (the largest logit is 2100, whose last fp32 bit is 1.2e-4: rows from 1000 on are left out at step 1)."""
+    wl = inputs.Workload("rising", B=B, L=L, H=1, S=1, d_pool=d_pool, d_sel=64, g=4, w=4096, dtype=dtype, mode=inputs.MODE_GQA, seed=5, n_q=1, scale=scale)
+    print(f"[case] {wl} step {step}", flush=True)
+    rng = np.random.default_rng(L)
+    Qf, Kf = np.zeros((B, L, 1, 64)), np.zeros((B, L, 1, 64))
+    Qf[..., 0] = 1.0
+    Kf[..., 0] = (step * np.arange(L) * (-1.0 if scale < 0 else 1.0))[None, :, None]
+    arrays = [inputs.to_storage(a.astype(np.float32), dtype) for a in (Qf, rng.standard_normal((B, L, 1, d_pool)), Kf)]
+    run = hp.GpuRun(wl, *arrays)
+    run.dense()
+    rows = np.unique(np.concatenate([np.arange(0, min(L, 1000), max(1, L // 60)), [min(L, 1000) - 1]])).astype(np.int32)
+    wide = [inputs.to_f64(a[:1], dtype) for a in arrays]
+    ref, _ = oracle.dense_attn_rows(hp.oracle_desc(oracle, replace(wl, B=1)), rows, wide[0][:, rows], wide[1], wide[2], want_lse=True)
+    got = hp.from_dev(run.O_dense, dtype)
+    assert hp.vec_rel_err(got[:1, rows], ref) <= hp.TOL[dtype]
+    assert np.isfinite(got).all()
