@@ -7,7 +7,7 @@
 // 16x16x32 MFMAs:
 //   S^T[key, head]  = K Q^T       A = 16 key rows from LDS (16-byte reads), B = Q^T in registers (18 k-steps)
 //   O^T[dv, head]  += V^T P^T     A = V^T through LDS transpose reads,       B = P^T = exp2(S^T - ref)
-// Every WAVEFRONT works alone on its own range of entries (no barriers in the loop) with two 18 KB LDS buffers of its
+// With long ranges every WAVEFRONT works alone on its own entries (no barriers in the loop; short ranges: see SHARED) with two 18 KB LDS buffers of its
 // own: a tile is 16 entries (16 latent rows of 1 KB at a 1040-byte stride, the RoPE parts XOR-swizzled), copied with
 // direct-to-LDS loads; the copy of tile t+1 is in flight while tile t is used -- twice: all 576 columns as keys, the
 // first 512 as values.  S^T row m of the tile comes from LDS row 4(m%4) + m/4, so that the S^T accumulators already
@@ -30,8 +30,7 @@ using namespace tile16;
 constexpr float SUM_LIMIT = 0x1p100f;
 
 constexpr int NKS = DQK / 32;                   // 18 k-steps of S^T
-constexpr int NDT = DP / 16;                    // 32 value tiles
-constexpr int PV_GROUP = 8;                     // value tiles whose V^T fragments are requested together
+constexpr int PV_GROUP = 8;                     // value tiles (of 16 columns) whose V^T fragments are requested together
 constexpr int MROW = DP + 4;                    // floats per head of a wavefront's output in LDS (merge at the end)
 static_assert(16 * MROW * 4 <= 2 * BUF_BYTES, "the output of 16 heads fits a wavefront's two tile buffers");
 constexpr float NEG_BIG = -1.0e30f;
@@ -71,27 +70,34 @@ template <typename E> __device__ __forceinline__ void cvt16_fp8(const uint4 &c, 
 // representatives is fetched into registers (its 8 KB + 1 KB of codes are contiguous) while the tile before it is used,
 // converted -- one instruction per two codes, the row's scale riding along -- and written into the same LDS layout
 // the 16-bit tiles use; from there on nothing differs.
-template <typename E, bool Q8>
+//
+// SHARED: the wavefronts of a workgroup take neighbouring tiles, a tile each per step, exchange P^T through LDS and every one works on a quarter of the
+// value columns over all four tiles.  Nothing is left to merge over the wavefronts (2.9 of the 8.5 us that a workgroup of two steps takes), the
+// accumulators are a quarter, and the first two tiles are requested at once; but two barriers per step keep the wavefronts' requests together, which
+// long ranges pay for (see launch_decode_mla).
+template <typename E, bool Q8, bool SHARED>
 __global__ __launch_bounds__(256, 1) void decode_mla_kernel(const DmParams kp)
 {
+    constexpr int NDT = DP / 16 / (SHARED ? 4 : 1), STRIDE = SHARED ? 4 : 1;     // value tiles of a wavefront; from one of its tiles to the next
     typedef E ex8 __attribute__((ext_vector_type(8)));
     typedef E ex4 __attribute__((ext_vector_type(4)));
     __shared__ __attribute__((aligned(1024))) char bufs[4][2][BUF_BYTES];
-    __shared__ float wave_ml[4][16][2];                                     // (reference, sum) per wavefront and head
+    __shared__ ex4 p_s[SHARED ? 4 : 1][64];                                 // P^T of a step: one tile per wavefront
+    __shared__ float max_s[4][16], sum_s[4][16];                            // per wavefront and head
 
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, q4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wg_per_bs = kp.n_parts / 4;
-    const int part = (blockIdx.x % wg_per_bs) * 4 + wave, bs = blockIdx.x / wg_per_bs;
+    const int wg_per_bs = kp.n_parts / 4, bs = blockIdx.x / wg_per_bs, wg = blockIdx.x - bs * wg_per_bs;
     const int b = bs / kp.S;
     const int m = kp.m, n = kp.m + kp.k;
     const int rep_tiles = Q8 ? (m + BN - 1) / BN : 0;                       // Q8: tiles [0, rep_tiles) hold representatives only
     const int tiles_total = Q8 ? rep_tiles + (kp.k + BN - 1) / BN : (n + BN - 1) / BN;
     const int tiles_per_part = (tiles_total + kp.n_parts - 1) / kp.n_parts;
-    const int t_lo = min(part * tiles_per_part, tiles_total), t_hi = min(t_lo + tiles_per_part, tiles_total);
+    // tiles [t_lo, t_hi) of the workgroup (SHARED) or of the wavefront, which takes first, first + STRIDE, ..: `mine` of them
+    const int t_lo = min((4 * wg + (SHARED ? 0 : wave)) * tiles_per_part, tiles_total), t_hi = min(t_lo + (SHARED ? 4 : 1) * tiles_per_part, tiles_total);
+    const int steps = (t_hi - t_lo + STRIDE - 1) / STRIDE, first = t_lo + (SHARED ? wave : 0), mine = (t_hi - first + STRIDE - 1) / STRIDE;
     const int e_hi = Q8 ? n : min(n, t_hi * BN);
-    char *buf0 = bufs[wave][0];
-    const unsigned buf_lds = lds_address(buf0);
+    const unsigned buf_lds = lds_address(bufs[wave][0]);
 
     // source rows: entry e < m is representative e, else tail token e - m in ring row (k_start + e - m) mod k_cap
     const uint16_t *prep = kp.pool_rep + (size_t)bs * kp.m_cap * DP, *srep = kp.sel_rep + (size_t)bs * kp.m_cap * DS;
@@ -102,14 +108,13 @@ __global__ __launch_bounds__(256, 1) void decode_mla_kernel(const DmParams kp)
     auto first_entry = [&](int tl) { return !Q8 ? tl * BN : tl < rep_tiles ? tl * BN : m + (tl - rep_tiles) * BN; };
     auto segment_end = [&](int tl) { return !Q8 ? e_hi : tl < rep_tiles ? m : n; };
 
-    ex8 qf[NKS];        // Q^T fragments, loaded below once the first tile's copy is on its way
-
     // per-lane LDS offsets inside a tile buffer
     const int krow = 4 * (col & 3) + (col >> 2);                            // LDS row behind S^T row `col` of the tile's 16 entries
     const int k_off = krow * RSB + 16 * q4;                                 // + 64*ks
     const int ksel_row = SEL_OFF + krow * (DS * 2);                         // chunk c at slot c ^ (row & 7)
-    const int v_off = (4 * (col >> 2) + q4) * RSB + 8 * (col & 3);          // + 32*t: transpose read of 4 keys (rows 4 apart) x 4 columns
+    const int v_off = (4 * (col >> 2) + q4) * RSB + 8 * (col & 3) + (SHARED ? 32 * NDT * wave : 0);   // + 32*t: transpose read of 4 keys (rows 4 apart) x 4 columns
 
+    ex8 qf[NKS];        // Q^T fragments
     floatx4 acc[NDT];
     float m_ref = NEG_BIG, l_run = 0.f, m_seen = NEG_BIG;
     const float c = kp.scale_log2;
@@ -188,42 +193,63 @@ __global__ __launch_bounds__(256, 1) void decode_mla_kernel(const DmParams kp)
         if (is_q8(tl)) fetch_q8(tl);
         else issue_dma(tl, bi);
     };
-    // (the queries travel together with the first tile: their latency is paid once, not before the first copy starts)
-    bool q_loaded = false;
+    // Q^T fragments: lane (col = head of the set, q4) holds q[head, 32 ks + 8 q4 .. +7]; columns past the set's heads are zero
     auto load_q = [&]() {
-        // Q^T fragments: lane (col = head of the set, q4) holds q[head, 32 ks + 8 q4 .. +7]; columns past the set's heads are zero
-        {
-            const uint16_t *qp = kp.q + ((size_t)bs * kp.hps + min(col, kp.hps - 1)) * DQK + 8 * q4;
+        const uint16_t *qp = kp.q + ((size_t)bs * kp.hps + min(col, kp.hps - 1)) * DQK + 8 * q4;
 #pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) {
-                qf[ks] = *reinterpret_cast<const ex8 *>(qp + 32 * ks);
-                if (col >= kp.hps) qf[ks] = ex8{0, 0, 0, 0, 0, 0, 0, 0};
-            }
-#pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) asm volatile("" : "+v"(qf[ks]));   // here before the loop starts (its waits count copies)
+        for (int ks = 0; ks < NKS; ++ks) {
+            qf[ks] = *reinterpret_cast<const ex8 *>(qp + 32 * ks);
+            if (col >= kp.hps) qf[ks] = ex8{0, 0, 0, 0, 0, 0, 0, 0};
         }
-        q_loaded = true;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) asm volatile("" : "+v"(qf[ks]));   // here, before the waits that count copies
     };
-    // One sweep over the wavefront's tiles.  Tile tl sits in buffer (tl - t_lo) & 1; tile tl+1 is on its way -- by direct-to-LDS
-    // copy into the other buffer, or into the registers -- while `body` uses tile tl.  (A tile of codes is never followed
-    // by one before it in kind, so behind the copies of a 16-bit tile only copies of a 16-bit tile can be in flight.)
+    // One sweep over the tiles, one per wavefront and step.  The tile of step `st` sits in buffer st & 1; the next one is on its way -- by
+    // direct-to-LDS copy into the other buffer, or into the registers -- while `body` uses it.  (A tile of codes is never
+    // followed by one before it in kind, so behind the copies of a 16-bit tile only copies of a 16-bit tile can be in flight.)
+    // The queries travel together with the first tile: their latency is paid once.
+    bool q_loaded = false;
     auto sweep = [&](auto &&body) {
-        if (t_lo < t_hi) issue(t_lo, 0);
-        if (!q_loaded) load_q();
-        for (int tl = t_lo; tl < t_hi; ++tl) {
-            const int bi = (tl - t_lo) & 1;
-            char *buf = buf0 + bi * BUF_BYTES;
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");              // this wavefront's reads of tile tl-1 (and tl-2) are done
-            if (is_q8(tl)) {
-                convert_q8(buf);
-                if (tl + 1 < t_hi) issue(tl + 1, bi ^ 1);
-            } else if (tl + 1 < t_hi) {
-                issue_dma(tl + 1, bi ^ 1);
-                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(COPIES) : "memory");   // tile tl has landed, tile tl+1 may still travel
-            } else {
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if constexpr (SHARED) {
+            // The first two tiles are requested together (codes, whose registers hold one tile: in a step before the first), by the
+            // same instructions as the others: code of their own would run once, and cold.
+            int asked = 0;                                                  // tiles requested so far
+            for (int st = Q8 ? -1 : 0; st < steps; ++st) {
+                const int tl = first + STRIDE * st;
+                char *buf = bufs[wave][st & 1];
+                if (Q8 && st >= 0 && st < mine && is_q8(tl)) convert_q8(buf);
+#pragma nounroll
+                for (; asked < mine && asked <= st + 1; ++asked) issue(first + STRIDE * asked, asked & 1);
+                if (!q_loaded) {
+                    load_q();
+                    q_loaded = true;
+                }
+                if (Q8 && st < 0) continue;
+                if (st < mine && !is_q8(tl)) {
+                    if (st + 1 < mine) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(COPIES) : "memory");   // this tile has landed, the next may still travel
+                    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                }
+                body(st, tl, buf);
             }
-            body(tl, buf);
+        } else {
+            if (steps > 0) issue(first, 0);
+            if (!q_loaded) load_q();
+            q_loaded = true;
+            for (int st = 0; st < steps; ++st) {
+                const int tl = first + st;
+                char *buf = bufs[wave][st & 1];
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // this wavefront's reads of the tiles before are done
+                if (is_q8(tl)) {
+                    convert_q8(buf);
+                    if (st + 1 < steps) issue(tl + 1, (st & 1) ^ 1);
+                } else if (st + 1 < steps) {
+                    issue_dma(tl + 1, (st & 1) ^ 1);
+                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(COPIES) : "memory");
+                } else {
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                }
+                body(st, tl, buf);
+            }
         }
     };
     // S^T = K Q^T for the tile's 16 entries, and the logits in base 2 (scale, bias of the representatives, entries past the
@@ -253,124 +279,215 @@ __global__ __launch_bounds__(256, 1) void decode_mla_kernel(const DmParams kp)
         return fmaxf(mx, __shfl_xor(mx, 32, 64));
     };
 
-    float l_tot = 0.f;
-    for (bool again = false;;) {                                            // normally one pass; a second one from the exact maxima
-#pragma unroll
-        for (int t = 0; t < NDT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-        l_run = 0.f;
-        m_ref = again ? m_seen : NEG_BIG;
-        bool ref_missing = !again;
+    if constexpr (SHARED) {
+        // The largest of a value over the wavefronts, per head (lane: head `col`); a barrier of the whole workgroup.
+        auto across_max = [&](float v) {
+            if (q4 == 0) max_s[wave][col] = v;
+            __syncthreads();
+            return fmaxf(fmaxf(max_s[0][col], max_s[1][col]), fmaxf(max_s[2][col], max_s[3][col]));
+        };
 
-        sweep([&](int tl, const char *buf) {
-            float lg[4];
-            tile_logits(tl, buf, lg);
-            if (ref_missing) {                                              // the first tile fixes the reference
-                const float mx = head_max(lg);
-                m_ref = (m_ref == NEG_BIG) ? mx : m_ref;
-                ref_missing = __builtin_amdgcn_ballot_w64(m_ref == NEG_BIG) != 0;
-            }
-            // P^T in the element type (B fragment of a 16x16x16 product: k-slot r of this lane is the key of register r) and
-            // its sum (of the rounded values, the ones the second product sees)
-            ex4 pb;
+        float l_all = 0.f;
+        for (bool again = false;;) {                                            // normally one pass; a second one from the exact maxima
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                pb[r] = (E)__builtin_amdgcn_exp2f(lg[r] - m_ref);
-                l_run += (float)pb[r];
-            }
-            // O^T += V^T P^T: fragments of PV_GROUP value tiles requested together, one group ahead
-            ex4 vf[2][PV_GROUP];
-            auto request = [&](int grp, int bsel) {
-#pragma unroll
-                for (int i = 0; i < PV_GROUP; ++i) vf[bsel][i] = lds_read_tr16((lds_b64_ptr)(buf + v_off + 32 * (grp * PV_GROUP + i)));
-            };
-            request(0, 0);
-#pragma unroll
-            for (int grp = 0; grp < NDT / PV_GROUP; ++grp) {
-                __builtin_amdgcn_sched_barrier(0);
-                if (grp + 1 < NDT / PV_GROUP) request(grp + 1, (grp + 1) & 1);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int i = 0; i < PV_GROUP; ++i) acc[grp * PV_GROUP + i] = mfma_16x16x16(vf[grp & 1][i], pb, acc[grp * PV_GROUP + i]);
-            }
-        });
+            for (int t = 0; t < NDT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+            l_run = 0.f;
+            m_ref = again ? m_seen : NEG_BIG;
+            bool ref_missing = !again;                                          // (the same in every wavefront)
 
-        l_tot = l_run + __shfl_xor(l_run, 16, 64);
-        l_tot += __shfl_xor(l_tot, 32, 64);
-        if (again || __builtin_amdgcn_ballot_w64(!(l_tot <= SUM_LIMIT)) == 0) break;
-        // (wave-uniform) a head ran out of exponent headroom: exact maxima of the range, then the pass again
-        m_seen = NEG_BIG;
-        sweep([&](int tl, const char *buf) {
-            float lg[4];
-            tile_logits(tl, buf, lg);
-            m_seen = fmaxf(m_seen, head_max(lg));
-        });
-        again = true;
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                      // the last tile's reads are done before the buffers are reused
-    char *buf = buf0;                                                       // the merge uses the wavefront's two buffers as one
+            sweep([&](int st, int tl, const char *buf) {
+                const int n_tiles = min(4, t_hi - t_lo - 4 * st);               // of this step
+                float lg[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+                if (wave < n_tiles) tile_logits(tl, buf, lg);
+                if (ref_missing) {                                              // the first step fixes the reference
+                    const float mx = across_max(head_max(lg));
+                    m_ref = (m_ref == NEG_BIG) ? mx : m_ref;
+                    ref_missing = __builtin_amdgcn_ballot_w64(m_ref == NEG_BIG) != 0;
+                }
+                // P^T in the element type (B fragment of a 16x16x16 product: k-slot r of this lane is the key of register r) and
+                // its sum (of the rounded values, the ones the second product sees)
+                ex4 pb;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    pb[r] = (E)__builtin_amdgcn_exp2f(lg[r] - m_ref);
+                    l_run += (float)pb[r];
+                }
+                p_s[wave][lane] = pb;
+                __syncthreads();                                                // every wavefront's P^T and tile are in LDS
+                // O^T += V^T P^T: this wavefront's value columns over every tile of the step
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+                    if (w < n_tiles) {
+                        const ex4 pw = p_s[w][lane];
+                        const char *const vals = bufs[w][st & 1] + v_off;
+                        ex4 vf[NDT];
+#pragma unroll
+                        for (int t = 0; t < NDT; ++t) vf[t] = lds_read_tr16((lds_b64_ptr)(vals + 32 * t));
+#pragma unroll
+                        for (int t = 0; t < NDT; ++t) acc[t] = mfma_16x16x16(vf[t], pw, acc[t]);
+                    }
+                __syncthreads();                                                // the step's tiles and P^T may be overwritten
+            });
 
-    // The four wavefronts' results (reference, sum, unnormalised output per head) are merged here, through LDS, so that
-    // one partial result per workgroup goes to memory: each wavefront publishes its references and sums and leaves its
-    // accumulators as they are in its own (now idle) tile buffer; then wavefront w adds up value columns
-    // [128 w, 128 w + 128) of every head over the four buffers, scaled to the common reference on the way, and writes
-    // them: as this workgroup's partial result (natural-log units), or -- when the workgroup has the whole (sequence, set)
-    // to itself -- normalised, as the final output.  Four heads' sixteen reads are in flight together: one head after another, with the
-    // accumulators rescaled before they were written, the merge took 7 500 of the 19 400 cycles of a two-tile step.
-    const bool any = t_lo < t_hi;
-    {
-        float *mine = reinterpret_cast<float *>(buf) + col * MROW + 4 * q4;   // [head][MROW] floats, 33 KB of the two buffers' 36.5 KB
+            float l_tot = l_run + __shfl_xor(l_run, 16, 64);
+            l_tot += __shfl_xor(l_tot, 32, 64);
+            if (q4 == 0) sum_s[wave][col] = l_tot;
+            __syncthreads();
+            l_all = (sum_s[0][col] + sum_s[1][col]) + (sum_s[2][col] + sum_s[3][col]);
+            if (again || __builtin_amdgcn_ballot_w64(!(l_all <= SUM_LIMIT)) == 0) break;
+            // (the same in every wavefront) a head ran out of exponent headroom: exact maxima of the workgroup's entries, then the pass again
+            m_seen = NEG_BIG;
+            sweep([&](int, int tl, const char *buf) {
+                if (tl >= t_hi) return;
+                float lg[4];
+                tile_logits(tl, buf, lg);
+                m_seen = fmaxf(m_seen, head_max(lg));
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");              // (nobody else reads this tile: no barrier before its buffer is filled again)
+            });
+            m_seen = across_max(m_seen);
+            again = true;
+        }
+
+        // Every wavefront has the whole sums of its value columns, scaled to the reference all of them share: the final output where the
+        // workgroup has the (sequence, set) to itself, else this workgroup's partial result (natural-log units).
+        if (col >= kp.hps) return;
+        const int x = 16 * NDT * wave + 4 * q4;
+        if (kp.O != nullptr) {
+            const float inv = 1.f / l_all;
+            E *const dst = reinterpret_cast<E *>(kp.O) + ((size_t)bs * kp.hps + col) * DP + x;
 #pragma unroll
-        for (int t = 0; t < NDT; ++t) *reinterpret_cast<floatx4 *>(mine + 16 * t) = acc[t];
-    }
-    if (q4 == 0) {
-        wave_ml[wave][col][0] = any ? m_ref : -INFINITY;
-        wave_ml[wave][col][1] = any ? l_tot : 0.f;
-    }
-    __syncthreads();
-    float m_all = -INFINITY, l_all = 0.f, factor[4];                        // of head `col`
+            for (int t = 0; t < NDT; ++t) *reinterpret_cast<ex4 *>(dst + 16 * t) = ex4{(E)(acc[t][0] * inv), (E)(acc[t][1] * inv), (E)(acc[t][2] * inv), (E)(acc[t][3] * inv)};
+            return;
+        }
+        float *const dst = kp.part + (((size_t)bs * wg_per_bs + wg) * kp.hps + col) * (DP + 2);
 #pragma unroll
-    for (int w = 0; w < 4; ++w) m_all = fmaxf(m_all, wave_ml[w][col][0]);
+        for (int t = 0; t < NDT; ++t) {
+            *reinterpret_cast<float2 *>(dst + 2 + x + 16 * t) = float2{acc[t][0], acc[t][1]};
+            *reinterpret_cast<float2 *>(dst + 2 + x + 16 * t + 2) = float2{acc[t][2], acc[t][3]};
+        }
+        if (wave == 0 && q4 == 0) {
+            dst[0] = steps <= 0 ? -INFINITY : m_ref * LN2;
+            dst[1] = l_all;
+        }
+    } else {
+        float l_tot = 0.f;
+        for (bool again = false;;) {                                            // normally one pass; a second one from the exact maxima
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        const float mw = wave_ml[w][col][0];
-        factor[w] = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - m_all);
-        l_all += wave_ml[w][col][1] * factor[w];
-    }
-    const float inv = 1.f / l_all;
-    float *dst0 = kp.part + ((size_t)bs * wg_per_bs + blockIdx.x % wg_per_bs) * kp.hps * (DP + 2);
-    const int x = 128 * wave + 2 * lane;
-    auto of_head = [](float v, int h) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), h)); };   // (lane h: head h)
-    for (int h0 = 0; h0 < kp.hps; h0 += 4) {
-        float2 v[4][4];
+            for (int t = 0; t < NDT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+            l_run = 0.f;
+            m_ref = again ? m_seen : NEG_BIG;
+            bool ref_missing = !again;
+
+            sweep([&](int, int tl, const char *buf) {
+                float lg[4];
+                tile_logits(tl, buf, lg);
+                if (ref_missing) {                                              // the first tile fixes the reference
+                    const float mx = head_max(lg);
+                    m_ref = (m_ref == NEG_BIG) ? mx : m_ref;
+                    ref_missing = __builtin_amdgcn_ballot_w64(m_ref == NEG_BIG) != 0;
+                }
+                // P^T in the element type (B fragment of a 16x16x16 product: k-slot r of this lane is the key of register r) and
+                // its sum (of the rounded values, the ones the second product sees)
+                ex4 pb;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+                for (int r = 0; r < 4; ++r) {
+                    pb[r] = (E)__builtin_amdgcn_exp2f(lg[r] - m_ref);
+                    l_run += (float)pb[r];
+                }
+                // O^T += V^T P^T: fragments of PV_GROUP value tiles requested together, one group ahead
+                ex4 vf[2][PV_GROUP];
+                auto request = [&](int grp, int bsel) {
 #pragma unroll
-            for (int w = 0; w < 4; ++w) v[i][w] = *reinterpret_cast<const float2 *>(reinterpret_cast<const float *>(bufs[w][0]) + (h0 + i) * MROW + x);
+                    for (int i = 0; i < PV_GROUP; ++i) vf[bsel][i] = lds_read_tr16((lds_b64_ptr)(buf + v_off + 32 * (grp * PV_GROUP + i)));
+                };
+                request(0, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int h = h0 + i;
-            if (h >= kp.hps) break;
-            float2 sum = float2{0.f, 0.f};
+                for (int grp = 0; grp < NDT / PV_GROUP; ++grp) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (grp + 1 < NDT / PV_GROUP) request(grp + 1, (grp + 1) & 1);
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const float f = of_head(factor[w], h);
-                sum.x = fmaf(v[i][w].x, f, sum.x);
-                sum.y = fmaf(v[i][w].y, f, sum.y);
-            }
-            if (kp.O != nullptr) {
-                typedef E ex2 __attribute__((ext_vector_type(2)));
-                const float n = of_head(inv, h);
-                *reinterpret_cast<ex2 *>(reinterpret_cast<E *>(kp.O) + ((size_t)bs * kp.hps + h) * DP + x) = ex2{(E)(sum.x * n), (E)(sum.y * n)};
-            } else {
-                *reinterpret_cast<float2 *>(dst0 + (size_t)h * (DP + 2) + 2 + x) = sum;
+                    for (int i = 0; i < PV_GROUP; ++i) acc[grp * PV_GROUP + i] = mfma_16x16x16(vf[grp & 1][i], pb, acc[grp * PV_GROUP + i]);
+                }
+            });
+
+            l_tot = l_run + __shfl_xor(l_run, 16, 64);
+            l_tot += __shfl_xor(l_tot, 32, 64);
+            if (again || __builtin_amdgcn_ballot_w64(!(l_tot <= SUM_LIMIT)) == 0) break;
+            // (wave-uniform) a head ran out of exponent headroom: exact maxima of the range, then the pass again
+            m_seen = NEG_BIG;
+            sweep([&](int, int tl, const char *buf) {
+                float lg[4];
+                tile_logits(tl, buf, lg);
+                m_seen = fmaxf(m_seen, head_max(lg));
+            });
+            again = true;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                      // the last tile's reads are done before the buffers are reused
+
+        // The four wavefronts' results (reference, sum, unnormalised output per head) are merged here, through LDS, so that
+        // one partial result per workgroup goes to memory: each wavefront publishes its references and sums and leaves its
+        // accumulators as they are in its own (now idle) tile buffer; then wavefront w adds up value columns
+        // [128 w, 128 w + 128) of every head over the four buffers, scaled to the common reference on the way, and writes
+        // them: as this workgroup's partial result (natural-log units), or -- when the workgroup has the whole (sequence, set)
+        // to itself -- normalised, as the final output.  Four heads' sixteen reads are in flight together: one head after another, with the
+        // accumulators rescaled before they were written, the merge took 7 500 of the 19 400 cycles of a two-tile step.
+        const bool any = t_lo < t_hi;
+        {
+            float *mine = reinterpret_cast<float *>(bufs[wave][0]) + col * MROW + 4 * q4;   // [head][MROW] floats, 33 KB of the two buffers' 36.5 KB
+#pragma unroll
+            for (int t = 0; t < NDT; ++t) *reinterpret_cast<floatx4 *>(mine + 16 * t) = acc[t];
+        }
+        if (q4 == 0) {
+            max_s[wave][col] = any ? m_ref : -INFINITY;
+            sum_s[wave][col] = any ? l_tot : 0.f;
+        }
+        __syncthreads();
+        float m_all = -INFINITY, l_all = 0.f, factor[4];                        // of head `col`
+#pragma unroll
+        for (int w = 0; w < 4; ++w) m_all = fmaxf(m_all, max_s[w][col]);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float mw = max_s[w][col];
+            factor[w] = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - m_all);
+            l_all += sum_s[w][col] * factor[w];
+        }
+        const float inv = 1.f / l_all;
+        float *dst0 = kp.part + ((size_t)bs * wg_per_bs + wg) * kp.hps * (DP + 2);
+        const int x = 128 * wave + 2 * lane;
+        auto of_head = [](float v, int h) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), h)); };   // (lane h: head h)
+        for (int h0 = 0; h0 < kp.hps; h0 += 4) {
+            float2 v[4][4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) v[i][w] = *reinterpret_cast<const float2 *>(reinterpret_cast<const float *>(bufs[w][0]) + (h0 + i) * MROW + x);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int h = h0 + i;
+                if (h >= kp.hps) break;
+                float2 sum = float2{0.f, 0.f};
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const float f = of_head(factor[w], h);
+                    sum.x = fmaf(v[i][w].x, f, sum.x);
+                    sum.y = fmaf(v[i][w].y, f, sum.y);
+                }
+                if (kp.O != nullptr) {
+                    typedef E ex2 __attribute__((ext_vector_type(2)));
+                    const float n = of_head(inv, h);
+                    *reinterpret_cast<ex2 *>(reinterpret_cast<E *>(kp.O) + ((size_t)bs * kp.hps + h) * DP + x) = ex2{(E)(sum.x * n), (E)(sum.y * n)};
+                } else {
+                    *reinterpret_cast<float2 *>(dst0 + (size_t)h * (DP + 2) + 2 + x) = sum;
+                }
             }
         }
-    }
-    if (kp.O != nullptr) return;
-    if (wave == 0 && q4 == 0 && col < kp.hps) {
-        float *dst = dst0 + (size_t)col * (DP + 2);
-        dst[0] = m_all == -INFINITY ? -INFINITY : m_all * LN2;
-        dst[1] = l_all;
+        if (kp.O != nullptr) return;
+        if (wave == 0 && q4 == 0 && col < kp.hps) {
+            float *dst = dst0 + (size_t)col * (DP + 2);
+            dst[0] = m_all == -INFINITY ? -INFINITY : m_all * LN2;
+            dst[1] = l_all;
+        }
     }
 }
 
@@ -407,6 +524,17 @@ int decode_mla_parts(const Dims &d)
     return 4 * wgs;
 }
 
+// Tiles per wavefront up to which the wavefronts of a workgroup share them: two, or four where the workgroup has the (sequence, set) to itself (nothing
+// else of a chip-filling grid then waits at its barriers).  Alone / shared, 16 heads: one tile B = 1, L = 700 11.2 / 9.6 us; two B = 1, L = 4001 12.2 / 10.9,
+// L = 131072 15.8 / 14.7, B = 8, L = 20000 14.9 / 13.8, 8-bit B = 1, L = 6000 13.0 / 11.6; three B = 16, L = 30000 18.6 / 19.4, but B = 60, L = 160, one workgroup
+// each, 10.3 / 9.3; four B = 32, L = 1000 16.5 / 17.8, B = 10, L = 250, one workgroup each, 11.6 / 11.5; eighteen B = 32, L = 131072 66.4 / 69.5.
+constexpr int SHARED_STEPS = 2, SHARED_STEPS_ONE = 4;
+template <typename E, bool Q8> static void run(const DmParams &kp, unsigned grid, int steps, hipStream_t st)
+{
+    if (steps <= (kp.n_parts == 4 ? SHARED_STEPS_ONE : SHARED_STEPS)) decode_mla_kernel<E, Q8, true><<<grid, 256, 0, st>>>(kp);
+    else decode_mla_kernel<E, Q8, false><<<grid, 256, 0, st>>>(kp);
+}
+
 hipError_t launch_decode_mla(const DecodeArgs &a, hipStream_t st)
 {
     const Dims &d = a.d;
@@ -420,12 +548,14 @@ hipError_t launch_decode_mla(const DecodeArgs &a, hipStream_t st)
     kp.pool_q8 = a.pool_q8; kp.sel_q8 = a.sel_q8; kp.scales = a.scales;
     kp.O = a.splits == 4 ? a.O : nullptr;
     const unsigned grid = d.B * d.S * (a.splits / 4);
-    if (a.pool_q8 != nullptr) {
-        if (d.dtype == LCA_F16) decode_mla_kernel<_Float16, true><<<grid, 256, 0, st>>>(kp);
-        else decode_mla_kernel<__bf16, true><<<grid, 256, 0, st>>>(kp);
+    const bool q8 = a.pool_q8 != nullptr;
+    const int tiles = q8 ? (d.m + BN - 1) / BN + (d.k + BN - 1) / BN : (d.m + d.k + BN - 1) / BN, steps = (tiles + a.splits - 1) / a.splits;
+    if (d.dtype == LCA_F16) {
+        if (q8) run<_Float16, true>(kp, grid, steps, st);
+        else run<_Float16, false>(kp, grid, steps, st);
     } else {
-        if (d.dtype == LCA_F16) decode_mla_kernel<_Float16, false><<<grid, 256, 0, st>>>(kp);
-        else decode_mla_kernel<__bf16, false><<<grid, 256, 0, st>>>(kp);
+        if (q8) run<__bf16, true>(kp, grid, steps, st);
+        else run<__bf16, false>(kp, grid, steps, st);
     }
     return hipGetLastError();
 }

@@ -75,3 +75,33 @@ def test_gqa_output_is_the_sum_divided_once(dtype, ulp, k):
     O = torch.empty(1, 4, 128, dtype=lca.torch_dtype(d), device="cuda")
     lca.decode_attn(d, dev[0], None, None, dev[1], dev[2], O, lca.alloc_workspace(d))
     np.testing.assert_array_equal(hp.from_dev(O, dtype)[0], np.tile(np.where(j % 2 == 0, low, low + ulp), (4, 1)))
+
+
+# ..., tiles per wavefront: one and two (shared by the wavefronts of a workgroup), three and four in a workgroup that has the sequence to itself, four otherwise
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("B,L,H,g,w,steps", [(1, 30, 16, 4, 64, 1), (2, 150, 7, 4, 200, 3), (1, 250, 16, 4, 300, 4), (1, 600, 16, 4, 700, 1), (1, 2205, 5, 2, 90, 2), (20, 1500, 4, 1, 30, 4)])
+@pytest.mark.parametrize("late", [0.0, 100.0])
+def test_mla_step_over_shared_tiles(oracle, dtype, B, L, H, g, w, steps, late):
+    """Partial last tiles and steps, and (late) logits that rise past any fixed reference in the last third of the cache, so that the workgroup
+    runs its tiles again from exact maxima; with sequences whose caches end in a tile of one entry."""
+    import torch
+    from paper_2604_12452_amd import lca
+    wl = inputs.Workload("shared", B=B, L=L, H=H, S=1, d_pool=512, d_sel=64, g=g, w=w, dtype=dtype, mode=inputs.MODE_MLA)
+    print(f"[case] {wl} late {late}", flush=True)
+    desc = hp.lca_desc(wl)
+    rng = np.random.default_rng(7 + L)
+    def draw(*shape, std=1.0):
+        x = rng.standard_normal(shape, dtype=np.float32) * np.float32(std)
+        return x
+    host = dict(q=draw(B, H, 576, std=576 ** -0.5), pool_rep=draw(B, 1, desc.m, 512), sel_rep=draw(B, 1, desc.m, 64),
+                pool_tail=draw(B, 1, desc.k, 512), sel_tail=draw(B, 1, desc.k, 64))
+    if late:
+        host["sel_tail"][:, :, desc.k - max(1, desc.k // 3):] *= late
+    host = {n: inputs.to_storage(x, dtype) for n, x in host.items()}
+    dev = {n: hp.to_dev(x, dtype) for n, x in host.items()}
+    O = torch.full((B, H, 512), float("nan"), dtype=lca.torch_dtype(desc), device="cuda")
+    ws = torch.full((lca.workspace_size(desc),), 0xFF, dtype=torch.uint8, device="cuda")
+    lca.decode_attn(desc, dev["q"], dev["pool_rep"], dev["sel_rep"], dev["pool_tail"], dev["sel_tail"], O, ws)
+    torch.cuda.synchronize()
+    ref = oracle.decode_attn(hp.oracle_desc(oracle, wl), *(inputs.to_f64(host[n], dtype) for n in ("q", "pool_rep", "sel_rep", "pool_tail", "sel_tail")))
+    assert hp.vec_rel_err(hp.from_dev(O, dtype), ref) <= hp.TOL[dtype]

@@ -136,3 +136,15 @@ def test_tiled_attention_cases_cover_every_instantiation():
     built = {"unsigned short": 5, "f16_t": 5, "float": 5}
     for T, n in built.items():
         assert len([k for k in seen if k.startswith(f"attn_tile_kernel<{T},")]) == n, (T, sorted(seen))
+
+
+@pytest.mark.parametrize("desc,shared", [
+    (_mla(L=256), True), (_mla(L=1024), True), (_mla(L=4001), True), (_mla(L=131072), True), (_mla(L=1500, B=20), False), (_mla(L=131072, B=32), False),
+    (_mla(L=150, B=60), True), (_mla(L=1500, B=300), False),
+])
+@pytest.mark.parametrize("q8", [False, True])
+def test_mla_decode_step_tiles_shared_by_the_wavefronts(desc, shared, q8):
+    """Up to two tiles per wavefront, four in a workgroup with a sequence of its own: fewer pass the barriers than the merge costs."""
+    run = t.decode(desc, q8)
+    name = run[0].kernel                                       # (the last template argument; the demangler gives up on some of these names)
+    assert (name.endswith(", true>") or "Lb1EEEv" in name, name.endswith(", false>") or "Lb0EEEv" in name) == (shared, not shared), name
