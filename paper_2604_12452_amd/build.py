@@ -1,4 +1,5 @@
-"""Compile csrc/*.hip for gfx950 into paper_2604_12452_amd/liblca.so (in-tree, so it travels with the tree)."""
+"""Compile csrc/*.hip for gfx950 into paper_2604_12452_amd/liblca.so, and binding/bind.cpp into _lcabind.so beside it (in-tree, so they travel with
+the tree)."""
 from __future__ import annotations
 
 import os
@@ -11,6 +12,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "liblca.so")
+BIND_SRC = os.path.join(PKG, "binding", "bind.cpp")
+BIND = os.path.join(PKG, "_lcabind.so")       # the binding's marshalling in native code (lca.py does without where it does not load)
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -35,10 +38,27 @@ def _compile(src: str, force: bool) -> str:
     return obj
 
 
+def _build_binding(force: bool) -> None:
+    import sysconfig
+    import torch
+    deps = [BIND_SRC, os.path.join(ROOT, "include", "lca.h")]
+    if not force and os.path.exists(BIND) and all(os.path.getmtime(BIND) >= os.path.getmtime(d) for d in deps):
+        return
+    base = os.path.dirname(torch.__file__)
+    tmp = BIND + f".{os.getpid()}.tmp"
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                    "-I", os.path.join(ROOT, "include"), "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(base, "include"),
+                    "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"), BIND_SRC, "-o", tmp,
+                    "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"], check=True)
+    os.replace(tmp, BIND)
+
+
 def build(force: bool = False, verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(sources()))) as ex:
+        binding = ex.submit(_build_binding, force)
         objs = list(ex.map(lambda s: _compile(s, force), sources()))
+        binding.result()
     tmp = LIB + f".{os.getpid()}.tmp"
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], check=True)
     os.replace(tmp, LIB)

@@ -1,4 +1,5 @@
-"""Thin ctypes binding of liblca (see include/lca.h): argument marshalling only.
+"""Thin ctypes binding of liblca (see include/lca.h): argument marshalling only, done in native code (binding/bind.cpp) for the calls
+whose arguments are plain descriptors and tensors and here for all others.
 
 Every step of the path runs inside the library's HIP kernels.  Tensors are torch tensors on the GPU
 (torch is used for device memory and streams only); bf16 data may be passed as ``torch.bfloat16`` or
@@ -103,6 +104,7 @@ class Desc:
 
 
 _lib = None
+_bind = None            # the checks and marshalling below in native code (binding/bind.cpp); its functions return -1 where these have to look themselves
 _raw_stream = None      # torch's own "address of the current stream" call, where there is one (a Stream object costs ten times as much)
 
 
@@ -142,7 +144,26 @@ def load() -> ctypes.CDLL:
         }.items():
             getattr(lib, name).argtypes = args
         _lib = lib
+        _load_bind(lib)
     return _lib
+
+
+def _load_bind(lib) -> None:
+    """The native marshalling, where it was built and fits the torch that is imported; everything works without it."""
+    global _bind
+    try:
+        from . import _lcabind as bind
+        bind.setup(Desc, CacheLayout, {name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS}, _stream)
+        _bind = bind
+    except ImportError:
+        pass
+
+
+def _done(status: int) -> bool:
+    """Whether the native marshalling took the call (raises on the library's own errors)."""
+    if status > 0:
+        _check(status)
+    return status == 0
 
 
 def _ptr(t):
@@ -246,6 +267,8 @@ def cache_bytes(desc: Desc):
 
 
 def condense(desc: Desc, Q, POOL, SEL, pool_rep, sel_rep, anchor_idx, alpha_dbg, workspace, stream=None):
+    if _bind is not None and _done(_bind.condense(desc, Q, POOL, SEL, pool_rep, sel_rep, anchor_idx, alpha_dbg, workspace, stream)):
+        return
     cd, m, _ = _plan(*desc._key())
     _fit_inputs(desc, Q, POOL, SEL)
     _fit_reps(desc, pool_rep, sel_rep, m)
@@ -267,6 +290,8 @@ def condense_noalloc(desc: Desc, Q, POOL, SEL, pool_rep, sel_rep, anchor_idx, al
 
 
 def prefill_attn(desc: Desc, Q, POOL, SEL, pool_rep, sel_rep, O, lse, workspace, stream=None):
+    if _bind is not None and _done(_bind.prefill_attn(desc, Q, POOL, SEL, pool_rep, sel_rep, O, lse, workspace, stream)):
+        return
     cd, m, _ = _plan(*desc._key())
     _fit_inputs(desc, Q, POOL, SEL)
     _fit_reps(desc, pool_rep, sel_rep, m)
@@ -278,6 +303,8 @@ def prefill_attn(desc: Desc, Q, POOL, SEL, pool_rep, sel_rep, O, lse, workspace,
 
 
 def prefill_attn_up(desc: Desc, Q, POOL, SEL, pool_rep, sel_rep, W_up, O_up, lse, workspace, stream=None):
+    if _bind is not None and _done(_bind.prefill_attn_up(desc, Q, POOL, SEL, pool_rep, sel_rep, W_up, O_up, lse, workspace, stream)):
+        return
     cd, m, _ = _plan(*desc._key())
     _fit_inputs(desc, Q, POOL, SEL)
     _fit_reps(desc, pool_rep, sel_rep, m)
@@ -289,6 +316,8 @@ def prefill_attn_up(desc: Desc, Q, POOL, SEL, pool_rep, sel_rep, W_up, O_up, lse
 
 
 def dense_attn(desc: Desc, Q, POOL, SEL, O, lse, workspace, stream=None):
+    if _bind is not None and _done(_bind.dense_attn(desc, Q, POOL, SEL, O, lse, workspace, stream)):
+        return
     _fit_inputs(desc, Q, POOL, SEL)
     _fit(desc, O, "O", desc.B * desc.L * desc.H * desc.d_pool)
     _fit(desc, lse, "lse", desc.B * desc.L * desc.H, "f32", optional=True)
@@ -311,6 +340,8 @@ def _fit_decode(desc: Desc, layout, q, pool_rep, sel_rep, pool_tail, sel_tail, O
 
 
 def decode_attn(desc: Desc, q, pool_rep, sel_rep, pool_tail, sel_tail, O, workspace, stream=None):
+    if _bind is not None and _done(_bind.decode_attn(desc, q, pool_rep, sel_rep, pool_tail, sel_tail, O, workspace, stream)):
+        return
     cd = _fit_decode(desc, None, q, pool_rep, sel_rep, pool_tail, sel_tail, O)
     _check(load().lca_decode_attn(ctypes.byref(cd), _ptr(q), _ptr(pool_rep), _ptr(sel_rep), _ptr(pool_tail),
                                   _ptr(sel_tail), _ptr(O), _ptr(workspace), _nbytes(workspace),
@@ -318,6 +349,8 @@ def decode_attn(desc: Desc, q, pool_rep, sel_rep, pool_tail, sel_tail, O, worksp
 
 
 def decode_attn_cached(desc: Desc, layout: CacheLayout, q, pool_rep, sel_rep, pool_tail, sel_tail, O, workspace, stream=None):
+    if _bind is not None and _done(_bind.decode_attn_cached(desc, layout, q, pool_rep, sel_rep, pool_tail, sel_tail, O, workspace, stream)):
+        return
     cl = layout.c()
     cd = _fit_decode(desc, layout, q, pool_rep, sel_rep, pool_tail, sel_tail, O)
     _check(load().lca_decode_attn_cached(ctypes.byref(cd), ctypes.byref(cl), _ptr(q), _ptr(pool_rep), _ptr(sel_rep), _ptr(pool_tail),
@@ -325,6 +358,8 @@ def decode_attn_cached(desc: Desc, layout: CacheLayout, q, pool_rep, sel_rep, po
 
 
 def cache_update(desc: Desc, layout: CacheLayout, q_recent, pool_tail, sel_tail, pool_rep, sel_rep, anchor_idx, workspace, stream=None):
+    if _bind is not None and _done(_bind.cache_update(desc, layout, q_recent, pool_tail, sel_tail, pool_rep, sel_rep, anchor_idx, workspace, stream)):
+        return
     cl = layout.c()
     _fit(desc, q_recent, "q_recent", desc.B * (desc.n_q or desc.g) * desc.H * desc.d_qk)
     _fit_tails(desc, pool_tail, sel_tail, layout.k_cap)
@@ -336,6 +371,8 @@ def cache_update(desc: Desc, layout: CacheLayout, q_recent, pool_tail, sel_tail,
 
 
 def quantize_cache(desc: Desc, layout, pool_rep, sel_rep, pool_q8, sel_q8, scales, first_row=0, stream=None):
+    if _bind is not None and _done(_bind.quantize_cache(desc, layout, pool_rep, sel_rep, pool_q8, sel_q8, scales, stream, first_row)):
+        return
     cd, m, _ = _plan(*desc._key())
     cl = layout.c() if layout is not None else None
     rows = layout.m_cap if layout is not None else m
@@ -349,6 +386,8 @@ def quantize_cache(desc: Desc, layout, pool_rep, sel_rep, pool_q8, sel_q8, scale
 
 
 def decode_attn_q8(desc: Desc, layout, q, pool_q8, sel_q8, scales, pool_tail, sel_tail, O, workspace, stream=None):
+    if _bind is not None and _done(_bind.decode_attn_q8(desc, layout, q, pool_q8, sel_q8, scales, pool_tail, sel_tail, O, workspace, stream)):
+        return
     cl = layout.c() if layout is not None else None
     cd = _fit_decode(desc, layout, q, pool_q8, sel_q8, pool_tail, sel_tail, O, rep_kind="u8", scales=scales)
     _check(load().lca_decode_attn_q8(ctypes.byref(cd), ctypes.byref(cl) if cl is not None else None, _ptr(q), _ptr(pool_q8), _ptr(sel_q8),
