@@ -72,11 +72,11 @@ constexpr int GRID = 256;               // most workgroups the persistent kernel
 constexpr int RING = 4;                 // fragments in flight per operand
 constexpr float NEG_BIG = -1.0e30f;
 constexpr float L_LIMIT = 0x1p90f;      // a row sum beyond this (or not finite) makes the workgroup repeat the item from exact maxima
-// fp16 ends at 65504: the fp16 kernels keep the largest exponential of each row (one v_max3 per pair) and repeat the item
-// from exact maxima if it left the type's range.  The reference sits 4 binades above the first maximum a row sees
+// fp16 ends at 65504: an exponential past it is an infinity in the second product, which no column of its row survives (infinity times a value is an
+// infinity, or no number), so the item is repeated from exact maxima if the row's first accumulator is not finite.  (Keeping the largest exponential instead, one
+// v_max3 per pair, costs a ninth of the vector instructions: 28 heads over 4 KV heads, three times L = 5003 260 us so, 257 us as it is.)  The reference sits 4 binades above the first maximum a row sees
 // (first entries at 2^-4): later logits may be 2^19 times larger before that happens, at the price of 4 of fp16's 24
 // binades at the bottom.
-constexpr float P_LIMIT_F16 = 65000.f;
 constexpr float REF_SHIFT_F16 = 4.f;
 constexpr int FEW_REPS = 16;            // fp16: with fewer visible representatives an item starts with its raw tokens (make_blk)
 constexpr int RSRC_WORD3 = 0x00020000;  // raw buffer of dwords, gfx9 layout
@@ -326,7 +326,7 @@ __device__ __forceinline__ bf16x8 load_v(const Addr &a, int half, int i)
 }
 
 // per-lane softmax state of the two query rows (base-2 logits)
-struct RowState { float m_ref[2], l_run[2], p_max[2]; };      // p_max, fp16 only: the largest exponential of the row so far
+struct RowState { float m_ref[2], l_run[2]; };
 
 // Queries of a work item: the loads are issued row-wise -- load i: lane l fetches the 16-byte piece l&15 of row
 // 4i + (l>>4), four whole rows per instruction -- and q_to_fragments turns the registers into the fragments of the
@@ -436,7 +436,7 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
 #pragma unroll
                     for (int i = 0; i < NDV; ++i) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %1, 0" : "=a"(acc[rb][i]) : "v"(zf));
             }
-            st.m_ref[0] = m_exact[0]; st.m_ref[1] = m_exact[1]; st.l_run[0] = 0.f; st.l_run[1] = 0.f; st.p_max[0] = 0.f; st.p_max[1] = 0.f;
+            st.m_ref[0] = m_exact[0]; st.m_ref[1] = m_exact[1]; st.l_run[0] = 0.f; st.l_run[1] = 0.f;
             bool need_ref = pass == 0;
 
             floatx16 s[2][2];            // S^T of half H and row block rb lives in s[H % 2][rb]
@@ -457,7 +457,6 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
                 st.l_run[rb] += p_prev;
                 LCA_PIN_V(st.l_run[rb]);
                 if (e & 1) {
-                    if (F16) asm volatile("v_max3_f32 %0, %0, %1, %2" : "+v"(st.p_max[rb]) : "v"(p_prev2), "v"(p_prev));
                     unsigned bits;
                     if (F16) bits = __builtin_bit_cast(unsigned, f16x2{(_Float16)p_prev2, (_Float16)p_prev});
                     else bits = __builtin_bit_cast(unsigned, bf16x2{(__bf16)p_prev2, (__bf16)p_prev});
@@ -647,7 +646,7 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
 #pragma unroll
             for (int rb = 0; rb < 2; ++rb) {
                 l_tot[rb] = st.l_run[rb] + __shfl_xor(st.l_run[rb], 32, 64);
-                redo |= !(l_tot[rb] <= L_LIMIT) | (F16 && st.p_max[rb] > P_LIMIT_F16);
+                redo |= !(l_tot[rb] <= L_LIMIT) | (F16 && !(acc[rb][0][0] * 0.f == 0.f));
             }
             // every wavefront is done with the stages; repeat the item if a row sum ran out of range
             if (!__syncthreads_or(pass == 0 && redo)) break;

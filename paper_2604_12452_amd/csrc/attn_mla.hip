@@ -74,11 +74,11 @@ constexpr int CHAIN_DEPTH = LCA_CHAIN_DEPTH;   // key fragments in flight ahead 
 constexpr int DU = 128;                  // UP variant: width of a head's value after the up-projection
 constexpr float NEG_BIG = -1.0e30f;     // stands for -inf in running maxima (keeps exp2 arguments finite)
 constexpr float L_LIMIT = 0x1p90f;      // a row sum beyond this (or not finite) makes the workgroup repeat the item from exact maxima
-// fp16 ends at 65504: the fp16 kernels keep the largest exponential of each row (one v_max3 per pair) and repeat the item
-// from exact maxima if it left the type's range.  The reference sits 4 binades above the first maximum a row sees
+// fp16 ends at 65504: an exponential past it is an infinity in the second product, which no column of its row survives (infinity times a value is an
+// infinity, or no number), so the item is repeated from exact maxima if the row's first accumulator is not finite.  (Keeping the largest exponential
+// instead took one v_max3 per pair.)  The reference sits 4 binades above the first maximum a row sees
 // (first entries at 2^-4): later logits may be 2^19 times larger before that happens, at the price of 4 of fp16's 24
 // binades at the bottom.
-constexpr float P_LIMIT_F16 = 65000.f;
 constexpr float REF_SHIFT_F16 = 4.f;
 
 struct MlaParams {
@@ -101,7 +101,6 @@ __device__ __forceinline__ constexpr int acc_entry(int r, int G) { return lds_ro
 // per-lane softmax state (base-2 logits): reference and running sum over this lane's keys
 struct RowState {
     float m_ref, l_run;
-    float p_max;        // fp16 only: the largest exponential of the row so far
 };
 
 // Fragments of the V^T operand: a ring of 2*PV_GROUP steps, requested PV_GROUP steps ahead of their use.
@@ -259,7 +258,6 @@ __device__ __forceinline__ void chain_and_softmax(ChainFrags &cf, lds_cptr kb, c
                     else bits = __builtin_bit_cast(unsigned, bf16x2{(__bf16)pf[0], (__bf16)pf[1]});
                     asm volatile("" : "+v"(bits));      // (pins the conversion to this slot: the compiler would gather four of them where the fragment is complete)
                     pb.p[k] = __builtin_bit_cast(bf16x2, bits);
-                    if (F16) asm volatile("v_max3_f32 %0, %0, %1, %2" : "+v"(st.p_max) : "v"(pf[0]), "v"(pf[1]));
                     st.l_run += pf[0];       // (two plain additions: v_dot2c_f32_bf16 stalls next to MFMAs, about 25 cycles each)
                     st.l_run += pf[1];
                 }
@@ -666,7 +664,7 @@ __global__ __launch_bounds__(256) void attn_mla_kernel(const MlaParams kp)
 #pragma unroll
             for (int i = 0; i < NDV; ++i) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %1, 0" : "=a"(acc[i]) : "v"(zf));   // (zeros in either type)
         }
-        st.m_ref = m_exact; st.l_run = 0.f; st.p_max = 0.f;
+        st.m_ref = m_exact; st.l_run = 0.f;
         bool need_ref = pass == 0;          // wave-uniform: some row of this wavefront has no reference yet
 
         // the first tiles and the queries of this item are on their way; then the S^T chain of tile 0
@@ -736,7 +734,7 @@ __global__ __launch_bounds__(256) void attn_mla_kernel(const MlaParams kp)
         // every wavefront is done with the tile stages; repeat the item if a row sum ran out of range
         {
             const float l_chk = st.l_run + __shfl_xor(st.l_run, 32, 64);
-            const bool redo = pass == 0 && (!(l_chk <= L_LIMIT) | (F16 && st.p_max > P_LIMIT_F16));
+            const bool redo = pass == 0 && (!(l_chk <= L_LIMIT) | (F16 && !(acc[0][0] * 0.f == 0.f)));
             if (!__syncthreads_or(redo)) break;
             {
                 // exact row maxima, one tile at a time (no overlap: this path is rare): tile tl goes into stage tl%2

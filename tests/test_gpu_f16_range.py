@@ -1,0 +1,29 @@
+"""fp16 prefill kernels whose exponentials leave the type's range: the rows are repeated from exact maxima, however small the excess over 65504 and whatever
+the values are (a zero column hides no infinity: zero times an infinity is no number)."""
+import numpy as np
+import pytest
+
+from paper_2604_12452_amd import inputs
+from tests import helpers as hp
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("mode,d_pool,d_sel,H,S", [(inputs.MODE_GQA, 128, 128, 4, 2), (inputs.MODE_MLA, 512, 64, 4, 1)])
+@pytest.mark.parametrize("rise", [13.5, 13.9, 14.2, 20.0, 60.0])       # nats above the first entries: 4 + 16 binades, where 65504 lies, are 13.86
+@pytest.mark.parametrize("zero_column", [False, True])
+def test_exponentials_past_65504(oracle, mode, d_pool, d_sel, H, S, rise, zero_column):
+    wl = inputs.Workload("range", B=1, L=300, H=H, S=S, d_pool=d_pool, d_sel=d_sel, g=4, w=512, dtype="f16", mode=mode, seed=3, n_q=1)
+    print(f"[case] {wl} rise {rise}", flush=True)
+    Q, POOL, SEL = (inputs.to_f64(x, "f16") for x in inputs.gen_all(wl))
+    Q[:] = 0.0
+    Q[..., -1] = 1.0                                     # the logit is the selected component's last column
+    SEL[:] = 0.0
+    SEL[0, 200, ..., -1] = rise
+    if zero_column:
+        POOL[..., 0] = 0.0
+    arrays = [inputs.to_storage(x.astype(np.float32), "f16") for x in (Q, POOL, SEL)]
+    run = hp.GpuRun(wl, *arrays)
+    run.dense()
+    rows = np.arange(wl.L, dtype=np.int32)
+    hp.check_dense(oracle, wl, run, rows, *(inputs.to_f64(a, "f16") for a in arrays))
