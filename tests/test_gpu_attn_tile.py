@@ -123,3 +123,46 @@ def test_rising_logits_over_one_to_eight_wavefronts(oracle, dtype, scale, L, d_p
     got = hp.from_dev(run.O_dense, dtype)
     assert hp.vec_rel_err(got[:1, rows], ref) <= hp.TOL[dtype]
     assert np.isfinite(got).all()
+
+
+def _peaked(dtype, a, scale, L=60, at=(20, 45), seed=4):
+    """(run, values, lse) of plain attention where every query is `a` in all 64 columns and so are the keys of the tokens `at`, with the scale's sign;
+    the other keys are zero."""
+    from paper_2604_12452_amd import lca
+    import torch
+    rng = np.random.default_rng(seed)
+    Q, K = np.full((1, L, 2, 64), a), np.zeros((1, L, 1, 64))
+    K[0, list(at)] = -a if scale < 0 else a
+    V = inputs.to_f64(inputs.to_storage(rng.standard_normal((1, L, 1, 64)).astype(np.float32), dtype), dtype)
+    d = lca.Desc(B=1, L=L, H=2, S=1, d_pool=64, d_sel=64, g=4, w=2 * L, n_q=1, mode=lca.MODE_GQA, scale=scale,
+                 dtype={"bf16": lca.BF16, "f16": lca.F16, "f32": lca.F32}[dtype])
+    dev = [hp.to_dev(inputs.to_storage(x.astype(np.float32), dtype), dtype) for x in (Q, V, K)]
+    O = torch.empty(1, L, 2, 64, dtype=lca.torch_dtype(d), device="cuda")
+    lse = torch.empty(1, L, 2, dtype=torch.float32, device="cuda")
+    lca.dense_attn(d, *dev, O, lse, lca.alloc_workspace(d))
+    return hp.from_dev(O, dtype)[0], V[0, :, 0], lse[0].cpu().numpy().astype(np.float64)
+
+
+def _check_peaked(dtype, logit, got, V, lse, at, lse_tol):
+    """Rows against the weighted mean of the values they see: exp(logit) for the tokens `at`, one for the others."""
+    for t in range(len(V)):
+        z = np.array([logit if i in at else 0.0 for i in range(t + 1)])
+        p = np.exp(z - z.max())
+        ref = (p / p.sum()) @ V[:t + 1]
+        assert hp.vec_rel_err(got[t], np.broadcast_to(ref, got[t].shape)) <= hp.TOL[dtype], t
+        want = z.max() + np.log(p.sum())
+        assert np.abs(lse[t] - want).max() <= lse_tol * max(1.0, abs(want)), (t, lse[t], want)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("scale", [1.0, -0.25])
+@pytest.mark.parametrize("logit", [2.0e3, 4.0e6, 4.67e7, 1.5e9, 6.0e10])
+def test_two_keys_with_very_large_logits(dtype, scale, logit):
+    """Where a unit in the last place of a logit is several binades of its exponential: from 2^26 in base 2 on, the fp16 parts of a probability that is
+    not taken from the logit as it was rounded hold less than its whole (4.67e7 is 2^26 log 2; at 6e10 the unit is 2^13).  The two keys' logits
+    are equal, so the rows are means of values.
+    lse: 64 additions of products, the factor and its product round once each, 66 times 2^-24."""
+    a = inputs.to_f64(inputs.to_storage(np.array([np.sqrt(logit / (64 * abs(scale)))], dtype=np.float32), dtype), dtype)[0]
+    print(f"[case] {dtype} scale {scale} logit {logit}", flush=True)
+    got, V, lse = _peaked(dtype, a, scale)
+    _check_peaked(dtype, 64 * a * a * abs(scale), got, V, lse, (20, 45), 66 * 2.0 ** -24)
