@@ -86,7 +86,6 @@ template <typename E8, typename E4, typename E, int NPARTS> struct Mma16 {
 template <> struct Mma<uint16_t> : Mma16<bf16x8, bf16x4, __bf16, 3> {
     static constexpr float P_SCALE = 1.f;          // what the probabilities are multiplied by on their way into the second product
     static constexpr float REF_SLACK = 8.f;        // binades a row's maximum may be above the reference of its exponentials
-    static constexpr bool ROUNDED = false;         // whether the exponentials take the logits as rounded numbers
     // p = its leading 8 bits + the next 8 + the last 8 (cut off, not rounded: a subtraction each and one byte
     // permutation per pair)
     template <int NB> __device__ static void split(const float (&p)[NB][4], Parts<NB> &o)
@@ -115,7 +114,6 @@ template <> struct Mma<uint16_t> : Mma16<bf16x8, bf16x4, __bf16, 3> {
 template <> struct Mma<f16_t> : Mma16<f16x8, f16x4, _Float16, 3> {
     static constexpr float P_SCALE = 32768.f;      // (an exact product; the results are divided by it with the row's sum)
     static constexpr float REF_SLACK = 0.f;        // (2^15 p may not pass 65504)
-    static constexpr bool ROUNDED = true;          // (nor by what rounding left of the reference)
     // 2^15 p = its leading 11 bits + the next 11 + the last 2 (cut off, not rounded: one conversion per pair)
     template <int NB> __device__ static void split(const float (&p)[NB][4], Parts<NB> &o)
     {
@@ -145,7 +143,6 @@ template <> struct Mma<f16_t> : Mma16<f16x8, f16x4, _Float16, 3> {
 template <> struct Mma<float> {
     static constexpr int EPC = 4, CHUNK = 16, PARTS = 1;
     static constexpr float P_SCALE = 1.f, REF_SLACK = 8.f;
-    static constexpr bool ROUNDED = false;
     __device__ static int row_of_m(int m) { return m; }
     __device__ static int entry(int r, int q4) { return 4 * q4 + r; }
     __device__ static floatx4 score(const uintx4 &k, const uintx4 &q, floatx4 c)
@@ -265,9 +262,7 @@ void attn_tile_kernel(const TileParams<T> tp)
     const int mt_first = visible(t_first), n_rep = visible(t_last), raw0 = mt_first * g;
     const int rep_tiles = (n_rep + TK - 1) / TK, n_tiles = rep_tiles + (t_last + 1 - raw0 + TK - 1) / TK;
     const int d_qk = kp.mla ? kp.d_pool + kp.d_sel : kp.d_sel;
-    // The logits are c S with the queries' sign for c's: then the largest product is the largest logit, and few operations take a
-    // product to its exponent.  (c is never zero: a hidden entry's -inf must stay one.  1e-37 times any finite product is no
-    // less than zero to an exponential.)
+    // The logits are c S with the queries' sign for c's.  (1e-37 times any finite product is no less than zero to an exponential.)
     const float c_abs = fabsf(kp.scale) * 1.4426950408889634f, c = c_abs < 1e-37f ? 1e-37f : c_abs, bias2 = kp.rep_bias * 1.4426950408889634f;
 
     int t_row[QB], mt_row[QB];
@@ -437,6 +432,15 @@ void attn_tile_kernel(const TileParams<T> tp)
         const float bias = is_rep ? bias2 : 0.f;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
+            // The products become logits before anything else reads them: the reference is then one of the logits as they were rounded.  (With one fused
+            // operation from product to exponent, what rounding left of the reference became part of every exponent, several binades from base-2 logits of 2^26
+            // on, which three parts in fp16 cannot hold; and the products' first reader was a maximum in assembly, for which the compiler keeps none of the
+            // wait states behind a matrix product.  Fused / so, 16 heads over 4 KV heads, 64 / 64, L = 2500, the attention alone: bf16 22.2 / 22.7 us, fp16
+            // 25.3 / 25.4; at 128 columns and more within 1 %.)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sc[nb][qb][r] = fmaf(sc[nb][qb][r], c, bias);
             if (!full) {                 // entries [lo, hi) of the tile's kind are visible to this lane's row
                 const int lo = is_rep ? 0 : mt_row[qb] * g, hi = is_rep ? mt_row[qb] : t_row[qb] + 1;
                 int e1 = e0 + M::entry(0, q4);
@@ -456,12 +460,9 @@ void attn_tile_kernel(const TileParams<T> tp)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                for (int r = nb == 0 ? 1 : 0; r < 4; r += nb == 0 && r == 1 ? 1 : 2) {
-                    if (r + 1 < 4 && !(nb == 0 && r == 1)) asm("v_max3_f32 %0, %1, %2, %3" : "=v"(mx) : "v"(mx), "v"(sc[nb][qb][r]), "v"(sc[nb][qb][r + 1]));
-                    else asm("v_max_f32 %0, %1, %2" : "=v"(mx) : "v"(mx), "v"(sc[nb][qb][r]));
-                }
-            if (__builtin_amdgcn_ballot_w64(fmaf(mx, c, bias) > m_run[qb] + M::REF_SLACK) != 0) {
-                const float to = fmaxf(m_run[qb], fmaf(row_max4(mx), c, bias));
+                for (int r = nb == 0; r < 4; ++r) mx = fmaxf(mx, sc[nb][qb][r]);
+            if (__builtin_amdgcn_ballot_w64(mx > m_run[qb] + M::REF_SLACK) != 0) {
+                const float to = fmaxf(m_run[qb], row_max4(mx));
                 ref[qb] = to == -INFINITY ? 0.f : to;
                 const float corr = __builtin_amdgcn_exp2f(m_run[qb] - ref[qb]);
                 l_run[qb] *= corr;
@@ -471,17 +472,12 @@ void attn_tile_kernel(const TileParams<T> tp)
                     for (int r = 0; r < 4; ++r) acc[qb][t][r] *= corr;
                 m_run[qb] = to;
             }
-            // One fused operation takes a product to its exponent.  The reference is a rounded logit, though, and what its rounding left becomes part of every
-            // exponent: nothing to speak of in a usual row, but several binades from logits of 2^26 on.  Parts and sum in fp32's range agree on it; three parts in
-            // fp16 hold three times 65504 of 2^15 p and the sum has all of it, so there the logit is rounded before the reference is subtracted, and no
-            // exponent is above zero (64 / 64, 16 heads over 4 KV heads, L = 2500, the attention alone: 25.3 us fused, 25.9 us so).
-            const float nb2 = bias - ref[qb];
             float pv[NB][4];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    pv[nb][r] = __builtin_amdgcn_exp2f(M::ROUNDED ? fmaf(sc[nb][qb][r], c, bias) - ref[qb] : fmaf(sc[nb][qb][r], c, nb2));
+                    pv[nb][r] = __builtin_amdgcn_exp2f(sc[nb][qb][r] - ref[qb]);
                     l_run[qb] += pv[nb][r];
                 }
             M::template split<NB>(pv, pb[qb]);
