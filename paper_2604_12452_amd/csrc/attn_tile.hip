@@ -262,8 +262,7 @@ void attn_tile_kernel(const TileParams<T> tp)
     const int mt_first = visible(t_first), n_rep = visible(t_last), raw0 = mt_first * g;
     const int rep_tiles = (n_rep + TK - 1) / TK, n_tiles = rep_tiles + (t_last + 1 - raw0 + TK - 1) / TK;
     const int d_qk = kp.mla ? kp.d_pool + kp.d_sel : kp.d_sel;
-    // The logits are c S with the queries' sign for c's.  (1e-37 times any finite product is no less than zero to an exponential.)
-    const float c_abs = fabsf(kp.scale) * 1.4426950408889634f, c = c_abs < 1e-37f ? 1e-37f : c_abs, bias2 = kp.rep_bias * 1.4426950408889634f;
+    const float c = kp.scale * 1.4426950408889634f, bias2 = kp.rep_bias * 1.4426950408889634f;
 
     int t_row[QB], mt_row[QB];
     size_t q_row[QB];                    // row index of the query in Q, O and lse: (b L + t) H + h
@@ -378,13 +377,6 @@ void attn_tile_kernel(const TileParams<T> tp)
             const int x = M::CHUNK * kc + M::EPC * q4;
             qf[qb][kc] = x < d_qk ? *reinterpret_cast<const uintx4 *>(kp.Q + q_row[qb] * d_qk + x) : uintx4{0, 0, 0, 0};
         }
-    if (kp.scale < 0.f) {
-        constexpr unsigned SIGN = sizeof(T) == 2 ? 0x80008000u : 0x80000000u;
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-            for (int kc = 0; kc < NKC; ++kc) qf[qb][kc] ^= SIGN;
-    }
     // the key columns past the width stay zero for the whole kernel (tiles are written over the real columns only)
     if (d_qk < NKC * M::CHUNK || kp.d_pool < 16 * NDT)
         for (int x = lane * 16; x < lay.stage; x += 64 * 16) *reinterpret_cast<uintx4 *>(area + x) = uintx4{0, 0, 0, 0};

@@ -166,3 +166,32 @@ def test_two_keys_with_very_large_logits(dtype, scale, logit):
     print(f"[case] {dtype} scale {scale} logit {logit}", flush=True)
     got, V, lse = _peaked(dtype, a, scale)
     _check_peaked(dtype, 64 * a * a * abs(scale), got, V, lse, (20, 45), 66 * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("scale,a", [(0.0, 1.0e18), (-0.0, 1.0e18), (0.0, 1.0), (2.0e-39, 1.0e18), (-2.0e-39, 1.0e18), (3.0e-38, 2.0e17), (1.0e-37, 1.5e18)])
+def test_products_up_to_the_largest_number_and_a_scale_of_nothing(dtype, scale, a):
+    """A scale of zero makes every entry count alike whatever the products are (64 a a = 6.4e37), and one below the least normal number is used as it is."""
+    a = inputs.to_f64(inputs.to_storage(np.array([a], dtype=np.float32), dtype), dtype)[0]
+    print(f"[case] {dtype} scale {scale} a {a}", flush=True)
+    got, V, lse = _peaked(dtype, a, scale)
+    _check_peaked(dtype, 64 * a * a * abs(float(np.float32(scale))), got, V, lse, (20, 45), 1e-5)
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_scale_zero_leaves_what_is_no_number(sign):
+    """A scale of zero times an infinity is no number: rows whose query, or one of whose keys, is not finite are none."""
+    import torch
+    from paper_2604_12452_amd import lca
+    d = lca.Desc(B=1, L=40, H=2, S=1, d_pool=64, d_sel=64, g=4, w=64, n_q=1, mode=lca.MODE_GQA, scale=0.0, dtype=lca.F32)
+    Q, K, V = torch.ones(1, 40, 2, 64, device="cuda"), torch.ones(1, 40, 1, 64, device="cuda"), torch.randn(1, 40, 1, 64, device="cuda")
+    Q[0, 5, 0, 3], Q[0, 6, 1, 9], K[0, 20, 0, 7] = float("inf"), -float("inf"), sign * float("inf")
+    O = torch.empty(1, 40, 2, 64, device="cuda")
+    lca.dense_attn(d, Q, V, K, O, None, lca.alloc_workspace(d))
+    bad = ~O.isfinite().all(-1)[0]
+    want = torch.zeros(40, 2, dtype=torch.bool, device="cuda")
+    want[5, 0] = want[6, 1] = True
+    want[20:] = True
+    assert torch.equal(bad, want)
+    mean = V[0, :, 0].cumsum(0) / torch.arange(1, 41, device="cuda")[:, None]
+    assert (O[0, 7:20] - mean[7:20, None]).abs().max() <= 1e-5
