@@ -185,7 +185,11 @@ template <> struct Mma<float> {
 // instructions, of which a workgroup would issue a dozen before its first load.
 struct Div {
     unsigned lo, hi, one;                // the 64-bit factor; all ones for d = 1, whose factor has 65 bits
-    __device__ unsigned operator()(unsigned x) const { return (x & one) | ((unsigned)(((unsigned long long)x * hi + __umulhi(x, lo)) >> 32) & ~one); }
+    template <bool PLAIN> __device__ int of(unsigned x, unsigned d) const      // (PLAIN: an ordinary division by d all the same)
+    {
+        if constexpr (PLAIN) return (int)(x / d);
+        else return (int)((x & one) | ((unsigned)(((unsigned long long)x * hi + __umulhi(x, lo)) >> 32) & ~one));
+    }
 };
 static Div make_div(unsigned d)
 {
@@ -247,6 +251,11 @@ void attn_tile_kernel(const TileParams<T> tp)
     const RowParams<T> &kp = tp.r;
     extern __shared__ __attribute__((aligned(64))) char smem[];
     constexpr int TK = 16 * NB, ROWS = 16 * QB, MROW = 16 * NDT + 4;
+    // fp32 at 512 columns: queries, accumulators and the next tile are 416 of a lane's 512 registers, and with the rest some are kept in memory.  Which ones makes a fifth
+    // of the time at few tiles, and it is the fewest with the queries free to arrive late, one way through the merge and ordinary divisions.
+    // As the narrower classes are / so: 192 + 128, 7 heads, B = 4, L = 114 25.2 / 21.4 us; 256 + 64, 16 heads, B = 2, L = 25 23.2 / 20.2; GQA 384 / 64,
+    // 16 heads over 4 KV heads, L = 455 61.7 / 55.1; 512 + 64, 2 heads, L = 500 50.2 / 53.8.
+    constexpr bool SPILLS = sizeof(T) == 4 && NDT >= 32;
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, q4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_waves = blockDim.x >> 6;
     const Layout<T, NDT, NKC, QB, NB> lay(kp.d_pool, kp.d_sel, kp.mla);
@@ -254,11 +263,11 @@ void attn_tile_kernel(const TileParams<T> tp)
 
     // which rows: the latest (heaviest) first
     const int hps = kp.H / kp.S, L = kp.L, g = kp.g;
-    const int bs = tp.by_blocks(blockIdx.x), blk = tp.n_blocks - 1 - (int)(blockIdx.x - bs * tp.n_blocks), b = tp.by_s(bs), s = bs - b * kp.S;
+    const int bs = tp.by_blocks.template of<SPILLS>(blockIdx.x, tp.n_blocks), blk = tp.n_blocks - 1 - (int)(blockIdx.x - bs * tp.n_blocks), b = tp.by_s.template of<SPILLS>(bs, kp.S), s = bs - b * kp.S;
     const int n_rows = L * hps, r0 = blk * ROWS, r_last = min(r0 + ROWS, n_rows) - 1;
     const int w_seen = kp.dense ? L : kp.w;                // raw tokens a row sees before it sees a representative
-    auto visible = [&](int t) { return (int)tp.by_g(max(t + 1 - w_seen, 0)); };
-    const int t_first = tp.by_hps(r0), t_last = tp.by_hps(r_last);
+    auto visible = [&](int t) { return tp.by_g.template of<SPILLS>(max(t + 1 - w_seen, 0), g); };
+    const int t_first = tp.by_hps.template of<SPILLS>(r0, hps), t_last = tp.by_hps.template of<SPILLS>(r_last, hps);
     const int mt_first = visible(t_first), n_rep = visible(t_last), raw0 = mt_first * g;
     const int rep_tiles = (n_rep + TK - 1) / TK, n_tiles = rep_tiles + (t_last + 1 - raw0 + TK - 1) / TK;
     const int d_qk = kp.mla ? kp.d_pool + kp.d_sel : kp.d_sel;
@@ -269,7 +278,7 @@ void attn_tile_kernel(const TileParams<T> tp)
     bool live[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        const int r = r0 + 16 * qb + col, rc = min(r, n_rows - 1), t = tp.by_hps(rc);
+        const int r = r0 + 16 * qb + col, rc = min(r, n_rows - 1), t = tp.by_hps.template of<SPILLS>(rc, hps);
         live[qb] = r < n_rows;
         t_row[qb] = t;
         mt_row[qb] = visible(t);
@@ -385,7 +394,8 @@ void attn_tile_kernel(const TileParams<T> tp)
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-        for (int kc = 0; kc < NKC; ++kc) asm volatile("" : "+v"(qf[qb][kc]));
+        for (int kc = 0; kc < NKC; ++kc)
+            if (!SPILLS) asm volatile("" : "+v"(qf[qb][kc]));
 
     floatx4 acc[QB][NDT];
     float m_run[QB], ref[QB], l_run[QB];     // reference of the row (base 2; -inf: none yet), the same or 0; this lane's share of the row's sum
@@ -506,24 +516,21 @@ void attn_tile_kernel(const TileParams<T> tp)
         }
     };
     bool bad = false;
-    // One wavefront stores from its registers, and the first of two does after adding the second's (not in fp32 at 512 columns, where the compiler
-    // then keeps more of the accumulators in memory: 256 + 64, L = 25 20.6 / 23.6 us).
-    constexpr bool PAIR = sizeof(T) == 2 || NDT < 32;
-    if (n_waves == 1 || (PAIR && n_waves == 2)) {
-        if (PAIR && n_waves == 2) {
-            if (wave == 1) leave();
+    // Up to two wavefronts, the first adds the second's results to its own and stores from its registers; where registers are short, any number of them, half
+    // handing their results to the other half until one is left.
+    if (SPILLS || n_waves <= 2) {
+        for (int half = n_waves >> 1; half > 0; half >>= 1) {
+            if (wave >= half && wave < 2 * half) leave();
             __syncthreads();
-        }
-        if (wave == 0) {
+            if (wave < half) {
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                if (PAIR && n_waves == 2) {
-                    const float2 other = *reinterpret_cast<const float2 *>(ml + (ROWS + 16 * qb + col) * 2);
-                    const float m_all = fmaxf(m_run[qb], other.x);
-                    const float ca = __builtin_amdgcn_exp2f(m_run[qb] - m_all), cb = __builtin_amdgcn_exp2f(other.x - m_all);
+                for (int qb = 0; qb < QB; ++qb) {
+                    const float2 other = *reinterpret_cast<const float2 *>(ml + ((wave + half) * ROWS + 16 * qb + col) * 2);
+                    const float m_all = fmaxf(m_run[qb], other.x), m_ref = m_all == -INFINITY ? 0.f : m_all;      // (-inf: neither saw an entry of the row)
+                    const float ca = __builtin_amdgcn_exp2f(m_run[qb] - m_ref), cb = __builtin_amdgcn_exp2f(other.x - m_ref);
                     l_tot[qb] = l_tot[qb] * ca + other.y * cb;
                     m_run[qb] = m_all;
-                    const float *const o = reinterpret_cast<const float *>(smem + lay.area) + (16 * qb + col) * MROW + 4 * q4;
+                    const float *const o = reinterpret_cast<const float *>(smem + (wave + half) * lay.area) + (16 * qb + col) * MROW + 4 * q4;
 #pragma unroll
                     for (int t = 0; t < NDT; ++t) {
                         const floatx4 v = *reinterpret_cast<const floatx4 *>(o + 16 * t);
@@ -531,6 +538,11 @@ void attn_tile_kernel(const TileParams<T> tp)
                         for (int r = 0; r < 4; ++r) acc[qb][t][r] = acc[qb][t][r] * ca + v[r] * cb;
                     }
                 }
+            }
+        }
+        if (wave == 0) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
                 const float inv = 1.f / (l_tot[qb] * M::P_SCALE);
                 float chk = 0.f;
 #pragma unroll
