@@ -46,6 +46,8 @@ typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
 // Wavefronts per workgroup at most: eight in fp32 where two of them fit a SIMD's registers (its tiles are long chains of small products).
 template <typename T> constexpr int max_waves(int ndt) { return sizeof(T) == 4 && ndt <= 8 ? 8 : 4; }
+// fp32 at 512 columns: queries, accumulators and the next tile are 416 of a lane's 512 registers, and with the rest some are kept in memory.
+template <typename T> constexpr bool full_class(int ndt) { return sizeof(T) == 4 && ndt >= 32; }
 constexpr int RSRC_WORD3 = 0x00020000;   // raw buffer of dwords, gfx9 layout
 constexpr size_t LDS_BYTES = 160 * 1024;      // of a CU
 
@@ -242,8 +244,8 @@ __device__ __forceinline__ float row_sum4(float x)
 
 // NDT: value columns / 16, NKC: key columns / Mma::CHUNK (both upper bounds; what lies past the real widths is zero keys and
 // results nobody stores), QB: blocks of 16 query rows, NB: blocks of 16 entries per tile, NIT: 16-byte pieces of a
-// row / 16 (upper bound).
-template <typename T, int NDT, int NKC, int QB, int NB, int NIT>
+// row / 16 (upper bound).  LATE: the 512-column fp32 class's second form (see late_form).
+template <typename T, int NDT, int NKC, int QB, int NB, int NIT, bool LATE>
 __global__ __launch_bounds__(64 * max_waves<T>(NDT)) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 && NDT <= 4 ? 3 : NDT <= 8 || (sizeof(T) == 2 && NDT <= 16) ? 2 : 1, 8)))
 void attn_tile_kernel(const TileParams<T> tp)
 {
@@ -251,11 +253,7 @@ void attn_tile_kernel(const TileParams<T> tp)
     const RowParams<T> &kp = tp.r;
     extern __shared__ __attribute__((aligned(64))) char smem[];
     constexpr int TK = 16 * NB, ROWS = 16 * QB, MROW = 16 * NDT + 4;
-    // fp32 at 512 columns: queries, accumulators and the next tile are 416 of a lane's 512 registers, and with the rest some are kept in memory.  Which ones makes a fifth
-    // of the time at few tiles, and it is the fewest with the queries free to arrive late, one way through the merge and ordinary divisions.
-    // As the narrower classes are / so: 192 + 128, 7 heads, B = 4, L = 114 25.2 / 21.4 us; 256 + 64, 16 heads, B = 2, L = 25 23.2 / 20.2; GQA 384 / 64,
-    // 16 heads over 4 KV heads, L = 455 61.7 / 55.1; 512 + 64, 2 heads, L = 500 50.2 / 53.8.
-    constexpr bool SPILLS = sizeof(T) == 4 && NDT >= 32;
+    constexpr bool FULL = full_class<T>(NDT);
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, q4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_waves = blockDim.x >> 6;
     const Layout<T, NDT, NKC, QB, NB> lay(kp.d_pool, kp.d_sel, kp.mla);
@@ -263,11 +261,11 @@ void attn_tile_kernel(const TileParams<T> tp)
 
     // which rows: the latest (heaviest) first
     const int hps = kp.H / kp.S, L = kp.L, g = kp.g;
-    const int bs = tp.by_blocks.template of<SPILLS>(blockIdx.x, tp.n_blocks), blk = tp.n_blocks - 1 - (int)(blockIdx.x - bs * tp.n_blocks), b = tp.by_s.template of<SPILLS>(bs, kp.S), s = bs - b * kp.S;
+    const int bs = tp.by_blocks.template of<LATE>(blockIdx.x, tp.n_blocks), blk = tp.n_blocks - 1 - (int)(blockIdx.x - bs * tp.n_blocks), b = tp.by_s.template of<LATE>(bs, kp.S), s = bs - b * kp.S;
     const int n_rows = L * hps, r0 = blk * ROWS, r_last = min(r0 + ROWS, n_rows) - 1;
     const int w_seen = kp.dense ? L : kp.w;                // raw tokens a row sees before it sees a representative
-    auto visible = [&](int t) { return tp.by_g.template of<SPILLS>(max(t + 1 - w_seen, 0), g); };
-    const int t_first = tp.by_hps.template of<SPILLS>(r0, hps), t_last = tp.by_hps.template of<SPILLS>(r_last, hps);
+    auto visible = [&](int t) { return tp.by_g.template of<LATE>(max(t + 1 - w_seen, 0), g); };
+    const int t_first = tp.by_hps.template of<LATE>(r0, hps), t_last = tp.by_hps.template of<LATE>(r_last, hps);
     const int mt_first = visible(t_first), n_rep = visible(t_last), raw0 = mt_first * g;
     const int rep_tiles = (n_rep + TK - 1) / TK, n_tiles = rep_tiles + (t_last + 1 - raw0 + TK - 1) / TK;
     const int d_qk = kp.mla ? kp.d_pool + kp.d_sel : kp.d_sel;
@@ -278,7 +276,7 @@ void attn_tile_kernel(const TileParams<T> tp)
     bool live[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        const int r = r0 + 16 * qb + col, rc = min(r, n_rows - 1), t = tp.by_hps.template of<SPILLS>(rc, hps);
+        const int r = r0 + 16 * qb + col, rc = min(r, n_rows - 1), t = tp.by_hps.template of<LATE>(rc, hps);
         live[qb] = r < n_rows;
         t_row[qb] = t;
         mt_row[qb] = visible(t);
@@ -386,6 +384,14 @@ void attn_tile_kernel(const TileParams<T> tp)
             const int x = M::CHUNK * kc + M::EPC * q4;
             qf[qb][kc] = x < d_qk ? *reinterpret_cast<const uintx4 *>(kp.Q + q_row[qb] * d_qk + x) : uintx4{0, 0, 0, 0};
         }
+    // (A branch that does nothing: behind it the 512-column fp32 class keeps less of the tile in hand in memory, 512 / 64, 16 heads over 4 KV heads, L = 509
+    // 313 / 278 us.)
+    if (FULL && !LATE && kp.scale < 0.f) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int kc = 0; kc < NKC; ++kc) asm volatile("" : "+v"(qf[qb][kc]));
+    }
     // the key columns past the width stay zero for the whole kernel (tiles are written over the real columns only)
     if (d_qk < NKC * M::CHUNK || kp.d_pool < 16 * NDT)
         for (int x = lane * 16; x < lay.stage; x += 64 * 16) *reinterpret_cast<uintx4 *>(area + x) = uintx4{0, 0, 0, 0};
@@ -395,7 +401,7 @@ void attn_tile_kernel(const TileParams<T> tp)
     for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
         for (int kc = 0; kc < NKC; ++kc)
-            if (!SPILLS) asm volatile("" : "+v"(qf[qb][kc]));
+            if (!LATE) asm volatile("" : "+v"(qf[qb][kc]));
 
     floatx4 acc[QB][NDT];
     float m_run[QB], ref[QB], l_run[QB];     // reference of the row (base 2; -inf: none yet), the same or 0; this lane's share of the row's sum
@@ -516,9 +522,9 @@ void attn_tile_kernel(const TileParams<T> tp)
         }
     };
     bool bad = false;
-    // Up to two wavefronts, the first adds the second's results to its own and stores from its registers; where registers are short, any number of them, half
-    // handing their results to the other half until one is left.
-    if (SPILLS || n_waves <= 2) {
+    // One wavefront stores from its registers, and the first of two does after adding the second's (not in the full class, which keeps more in memory then); in its
+    // LATE form, which has no other way, any number of them, half handing their results to the other half until one is left.
+    if (LATE || n_waves <= (FULL ? 1 : 2)) {
         for (int half = n_waves >> 1; half > 0; half >>= 1) {
             if (wave >= half && wave < 2 * half) leave();
             __syncthreads();
@@ -638,6 +644,13 @@ void attn_tile_kernel(const TileParams<T> tp)
     }
 }
 
+// Whether the full class runs in its LATE form: queries free to arrive late, one way through the merge, ordinary divisions.  It spends less before and after the
+// loop, whose every tile then waits for the next one's loads; those are few where a row is short, and the registers they would go into fewer.  The other
+// form / LATE, us: 192 + 128, 8 heads and sets, B = 2, L = 1030 109 / 89; 256 + 64, 16 heads, B = 2, L = 25 22.3 / 20.2, L = 1500 535 / 519; rows of 448 and
+// more: 512 / 64, 32 sets, L = 270 (three tiles, 544 workgroups) 132 / 122, but two heads, L = 500 (eleven over four wavefronts) 49.8 / 53.5, 4 sets of 4 heads,
+// L = 509 280 / 369, and five to seven tiles in more workgroups than CUs either way.
+static bool late_form(const Dims &d, int tiles, int waves, long grid, int cus) { return d.d_pool + d.d_sel <= 384 || (grid > cus && tiles <= 3 * waves); }
+
 template <typename T, int NDT, int NKC, int QB, int NB, int NIT>
 hipError_t run(const AttnArgs &a, hipStream_t st)
 {
@@ -665,7 +678,13 @@ hipError_t run(const AttnArgs &a, hipStream_t st)
     if (!full_registers && grid >= (QB == 2 ? 4 : 8) * (long)cus && (QB == 2 ? waves > 2 : tiles >= 32 && waves > 1)) waves /= 2;
     while (waves > 1 && (waves / 2 >= tiles || (NDT > 8 && waves > tiles) || lds(waves) > room)) waves /= 2;
     const TileParams<T> tp{attn_row::row_params<T>(a), (int)blocks, make_div((unsigned)blocks), make_div(d.S), make_div(d.H / d.S), make_div(d.g)};
-    attn_tile_kernel<T, NDT, NKC, QB, NB, NIT><<<(unsigned)grid, 64 * waves, lds(waves), st>>>(tp);
+    if constexpr (full_class<T>(NDT)) {
+        if (late_form(d, tiles, waves, grid, cus)) {
+            attn_tile_kernel<T, NDT, NKC, QB, NB, NIT, true><<<(unsigned)grid, 64 * waves, lds(waves), st>>>(tp);
+            return hipGetLastError();
+        }
+    }
+    attn_tile_kernel<T, NDT, NKC, QB, NB, NIT, false><<<(unsigned)grid, 64 * waves, lds(waves), st>>>(tp);
     return hipGetLastError();
 }
 

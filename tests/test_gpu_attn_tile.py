@@ -46,6 +46,22 @@ def test_every_instantiation_all_rows(oracle, dtype, mode, d_pool, d_sel, L, g, 
     _full_parity(oracle, wl)
 
 
+# mode, d_pool, d_sel, L, g, w, H, S, B, wavefronts
+LATE_CASES = [
+    (inputs.MODE_MLA, 256, 64, 19, 4, 64, 3, 1, 1, 2),         # two tiles
+    (inputs.MODE_MLA, 256, 64, 31, 8, 13, 4, 1, 2, 2),
+    (inputs.MODE_MLA, 192, 128, 301, 16, 40, 2, 2, 1, 4),      # halves of four, one of which sees nothing of the first rows
+    (inputs.MODE_MLA, 264, 56, 301, 64, 130, 1, 1, 1, 4),      # a partial last column block
+    (inputs.MODE_MLA, 256, 64, 1030, 16, 0, 16, 4, 1, 1),      # as many workgroups as one wavefront each
+    (inputs.MODE_GQA, 512, 64, 100, 16, 8, 32, 32, 3, 1),      # wide rows, few tiles, more workgroups than CUs
+]
+
+
+@pytest.mark.parametrize("mode,d_pool,d_sel,L,g,w,H,S,B,waves", LATE_CASES)
+def test_the_second_form_of_the_512_column_class(oracle, mode, d_pool, d_sel, L, g, w, H, S, B, waves):
+    _full_parity(oracle, inputs.Workload("late", B=B, L=L, H=H, S=S, d_pool=d_pool, d_sel=d_sel, g=g, w=w, dtype="f32", mode=mode, seed=800 + L + d_pool))
+
+
 @pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
 @pytest.mark.parametrize("dtype,mode,d_pool,d_sel,H,S", [("f32", inputs.MODE_MLA, 128, 32, 4, 1), ("bf16", inputs.MODE_GQA, 64, 64, 4, 2),
                                                          ("f16", inputs.MODE_GQA, 64, 64, 4, 2)])

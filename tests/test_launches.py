@@ -138,6 +138,15 @@ def test_tiled_attention_cases_cover_every_instantiation():
         assert len([k for k in seen if k.startswith(f"attn_tile_kernel<{T},")]) == n, (T, sorted(seen))
 
 
+def test_second_form_cases_are_where_they_claim_to_be():
+    from tests import test_gpu_attn_tile as cases
+    for mode, d_pool, d_sel, L, g, w, H, S, B, waves in cases.LATE_CASES:
+        (run,) = t.prefill(lca.Desc(B=B, L=L, H=H, S=S, d_pool=d_pool, d_sel=d_sel, g=g, w=w, mode=mode, dtype=lca.F32))
+        assert run.kernel.startswith("attn_tile_kernel<float, 32, 36, 1, 1, 9, true>") and run.block == 64 * waves, (run, L, waves)
+    for d in (lca.Desc(B=1, L=70, H=2, S=1, d_pool=512, d_sel=64, g=8, w=9, dtype=lca.F32), lca.Desc(B=1, L=600, H=32, S=32, d_pool=512, d_sel=64, g=8, w=9, mode=lca.MODE_GQA, dtype=lca.F32)):
+        assert t.prefill(d)[0].kernel.startswith("attn_tile_kernel<float, 32, 36, 1, 1, 9, false>")
+
+
 @pytest.mark.parametrize("desc,shared", [
     (_mla(L=256), True), (_mla(L=1024), True), (_mla(L=4001), True), (_mla(L=131072), True), (_mla(L=1500, B=20), False), (_mla(L=131072, B=32), False),
     (_mla(L=150, B=60), True), (_mla(L=1500, B=300), False),
