@@ -675,7 +675,10 @@ hipError_t run(const AttnArgs &a, hipStream_t st)
     // over 4 KV heads, L = 2500 (1252 workgroups) 35.4 / 34.6 us with the condensation, B = 2, L = 4000 (4000) 54.2 / 46.0; fp32 128 + 32, 8 heads, L = 4096
     // (2048) 142 / 132, but one row block and B = 3, L = 900 (1350) 63.3 / 66.4, longer workgroups not quite twice as many as fit; two / one:
     // 256 + 32, 8 heads, B = 2, L = 4000 (4000) 162 / 157, but fp32 192 / 128, 7 heads, L = 2347 (1027, one per SIMD) 287 / 468.
-    if (!full_registers && grid >= (QB == 2 ? 4 : 8) * (long)cus && (QB == 2 ? waves > 2 : tiles >= 32 && waves > 1)) waves /= 2;
+    // Two row blocks and many tiles: not while the workgroups fill the CUs only a few times over, when the last ones make a long tail (fp32, 16 heads over one KV head:
+    // 8 / 8, B = 2, L = 1086, 1086 workgroups of 69 tiles, 64.5 / 80.1; 64 / 64, L = 2230, 1115 of 141, 126 / 150; 8 / 8, L = 2420, 1210 of 152, 141 / 155).
+    const bool halve = QB == 2 ? waves > 2 && grid >= (tiles > 64 ? 5 : 4) * (long)cus : waves > 1 && grid >= 8 * (long)cus && tiles >= 32;
+    if (!full_registers && halve) waves /= 2;
     while (waves > 1 && (waves / 2 >= tiles || (NDT > 8 && waves > tiles) || lds(waves) > room)) waves /= 2;
     const TileParams<T> tp{attn_row::row_params<T>(a), (int)blocks, make_div((unsigned)blocks), make_div(d.S), make_div(d.H / d.S), make_div(d.g)};
     if constexpr (full_class<T>(NDT)) {

@@ -138,6 +138,17 @@ def test_tiled_attention_cases_cover_every_instantiation():
         assert len([k for k in seen if k.startswith(f"attn_tile_kernel<{T},")]) == n, (T, sorted(seen))
 
 
+@pytest.mark.parametrize("B,L,H,S,g,w,dtype,waves", [
+    (2, 1086, 16, 1, 1, 512, lca.F32, 4), (1, 2230, 16, 1, 1, 256, lca.F32, 4), (1, 2500, 16, 1, 1, 256, lca.F32, 4), (1, 2600, 16, 1, 1, 256, lca.F32, 2),
+    (2, 1086, 16, 1, 16, 512, lca.F32, 2), (1, 2500, 16, 4, 16, 512, lca.BF16, 2),
+])
+def test_wavefronts_of_two_row_blocks(B, L, H, S, g, w, dtype, waves):
+    """Half of them from four workgroups per CU on, from five where a workgroup has more than 64 tiles."""
+    (run,) = t.prefill(lca.Desc(B=B, L=L, H=H, S=S, d_pool=64, d_sel=64, g=g, w=w, mode=lca.MODE_GQA, dtype=dtype))
+    assert "4, 2, 2, 2, 1" in run.kernel or "4, 4, 2, 1, 2" in run.kernel, run
+    assert run.block == 64 * waves, run
+
+
 def test_second_form_cases_are_where_they_claim_to_be():
     from tests import test_gpu_attn_tile as cases
     for mode, d_pool, d_sel, L, g, w, H, S, B, waves in cases.LATE_CASES:
