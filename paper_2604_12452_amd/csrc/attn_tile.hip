@@ -522,9 +522,10 @@ void attn_tile_kernel(const TileParams<T> tp)
         }
     };
     bool bad = false;
-    // One wavefront stores from its registers, and the first of two does after adding the second's (not in the full class, which keeps more in memory then); in its
-    // LATE form, which has no other way, any number of them, half handing their results to the other half until one is left.
-    if (LATE || n_waves <= (FULL ? 1 : 2)) {
+    // One wavefront stores from its registers, and the first of two (in fp32 up to 128 columns of four, half of them handing over to the other half first) does after adding the
+    // second's; not in the full class, which keeps more in memory then, but its LATE form has no other way.  (Four in fp32, the other way / so: 8 + 8, 32 heads,
+    // B = 2, L = 39 5.3 / 4.9 us; 64 / 128, 32 heads over 8 KV heads, B = 4, L = 44 9.9 / 9.3; but 256 / 64, L = 83 13.6 / 15.1.)
+    if (LATE || n_waves <= (FULL ? 1 : sizeof(T) == 4 && NDT <= 8 ? 4 : 2)) {
         for (int half = n_waves >> 1; half > 0; half >>= 1) {
             if (wave >= half && wave < 2 * half) leave();
             __syncthreads();
