@@ -2,6 +2,7 @@
 // plain torch tensors, in one C call.  A function here either makes the library call and returns its status, or touches nothing and
 // returns -1: an argument is of another kind (a raw address, a tensor subclass, a field that is no plain number), or does not fit (wrong type, too
 // small, not contiguous, not on the device).  Then lca.py takes its own way, which handles the first and words the exception for the second.
+// An exception that arises on the way and is not about the arguments ends the call.
 //
 // Why: a decode step's host time was 11.6 us -- two launches of 3.1 us each, 0.7 us in the library, the rest here -- and the step is not longer
 // than that on the GPU at one sequence; a prefill of two calls and three launches took 20 us whatever its size.  With the checks in Python the
@@ -31,10 +32,18 @@ const char *const FLOAT_FIELDS[N_FLOATS] = {"scale", "rep_logit_bias"};
 const char *const LAYOUT_FIELDS[N_LAYOUT] = {"m_cap", "k_cap", "k_start"};
 PyObject *int_names[N_INTS], *float_names[N_FLOATS], *layout_names[N_LAYOUT];
 
+// Something that lca.py will meet again and word itself is cleared here; what is not the call's own (an interrupt, a signal handler's exception) stays set, and
+// the call ends with it.
+bool missing()
+{
+    if (PyErr_ExceptionMatches(PyExc_AttributeError)) PyErr_Clear();
+    return false;
+}
+
 bool read_int(PyObject *o, PyObject *name, int32_t &out)
 {
     PyObject *v = PyObject_GetAttr(o, name);
-    if (v == nullptr) return PyErr_Clear(), false;
+    if (v == nullptr) return missing();
     int overflow = 0;
     const long x = PyLong_CheckExact(v) ? PyLong_AsLongAndOverflow(v, &overflow) : 0;
     const bool ok = PyLong_CheckExact(v) && overflow == 0 && x >= INT32_MIN && x <= INT32_MAX;
@@ -46,7 +55,7 @@ bool read_int(PyObject *o, PyObject *name, int32_t &out)
 bool read_float(PyObject *o, PyObject *name, float &out)
 {
     PyObject *v = PyObject_GetAttr(o, name);
-    if (v == nullptr) return PyErr_Clear(), false;
+    if (v == nullptr) return missing();
     const double x = PyFloat_CheckExact(v) ? PyFloat_AS_DOUBLE(v) : 0.0;
     const bool ok = PyFloat_CheckExact(v);
     out = (float)x;
@@ -150,10 +159,14 @@ struct Args {
     {
         if (!ok) return nullptr;                 // (asked for last: without a device there may be no stream to ask for)
         PyObject *v = PyObject_CallOneArg(stream_of, *o++);
-        void *p = v != nullptr && PyLong_CheckExact(v) ? PyLong_AsVoidPtr(v) : nullptr;
-        ok = v != nullptr && PyLong_CheckExact(v) && !(p == nullptr && PyErr_Occurred());
-        PyErr_Clear();
-        Py_XDECREF(v);
+        if (v == nullptr) return ok = missing(), nullptr;
+        void *p = PyLong_CheckExact(v) ? PyLong_AsVoidPtr(v) : nullptr;
+        ok = PyLong_CheckExact(v);
+        if (p == nullptr && PyErr_Occurred()) {             // (a number past any address)
+            ok = false;
+            PyErr_Clear();
+        }
+        Py_DECREF(v);
         return p;
     }
 };
@@ -166,7 +179,7 @@ template <typename F> PyObject *run(F &&f)
     Py_END_ALLOW_THREADS
     return PyLong_FromLong((long)st);
 }
-PyObject *pass() { return PyLong_FromLong(-1); }
+PyObject *pass() { return PyErr_Occurred() ? nullptr : PyLong_FromLong(-1); }
 
 typedef const void *CP;
 typedef void *VP;
@@ -181,7 +194,6 @@ template <bool LAYOUT, typename F> PyObject *guarded(PyObject *const *args, Py_s
         Args a{args + (LAYOUT ? 2 : 1), c};
         return body(c, a);
     } catch (...) {
-        PyErr_Clear();
         return pass();
     }
 }
