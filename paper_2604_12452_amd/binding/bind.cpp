@@ -12,6 +12,8 @@
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
+#include <cstring>
+
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "lca.h"
@@ -326,13 +328,19 @@ PyObject *quantize_cache(PyObject *, PyObject *const *args, Py_ssize_t n)      /
     });
 }
 
-// setup(Desc, CacheLayout, {entry point: address}, stream function)
+// setup(Desc, CacheLayout, {entry point: address}, stream function, what is imported): torch's accessors are compiled in, so this module reads sizes and
+// addresses of tensors of the torch it was built for, and of no other's.
 PyObject *setup(PyObject *, PyObject *args)
 {
     PyObject *dt, *lt, *addresses, *fn;
-    if (!PyArg_ParseTuple(args, "OOO!O", &dt, &lt, &PyDict_Type, &addresses, &fn)) return nullptr;
+    const char *imported;
+    if (!PyArg_ParseTuple(args, "OOO!Os", &dt, &lt, &PyDict_Type, &addresses, &fn, &imported)) return nullptr;
     if (!PyType_Check(dt) || !PyType_Check(lt) || !PyCallable_Check(fn)) {
-        PyErr_SetString(PyExc_TypeError, "setup(Desc, CacheLayout, addresses, stream function)");
+        PyErr_SetString(PyExc_TypeError, "setup(Desc, CacheLayout, addresses, stream function, what is imported)");
+        return nullptr;
+    }
+    if (std::strcmp(imported, LCA_BUILT_FOR) != 0) {
+        PyErr_Format(PyExc_ImportError, "built for %s, but %s is imported", LCA_BUILT_FOR, imported);
         return nullptr;
     }
     void *found[N_ENTRIES];

@@ -41,14 +41,17 @@ def _compile(src: str, force: bool) -> str:
 def _build_binding(force: bool) -> None:
     import sysconfig
     import torch
-    deps = [BIND_SRC, os.path.join(ROOT, "include", "lca.h")]
-    if not force and os.path.exists(BIND) and all(os.path.getmtime(BIND) >= os.path.getmtime(d) for d in deps):
-        return
+    from .lca import bind_tag
+    tag = bind_tag()
+    if not force and os.path.exists(BIND) and all(os.path.getmtime(BIND) >= os.path.getmtime(d) for d in (BIND_SRC, os.path.join(ROOT, "include", "lca.h"))):
+        with open(BIND, "rb") as f:
+            if tag.encode() + b"\0" in f.read():
+                return
     base = os.path.dirname(torch.__file__)
     tmp = BIND + f".{os.getpid()}.tmp"
     subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-                    "-I", os.path.join(ROOT, "include"), "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(base, "include"),
-                    "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"), BIND_SRC, "-o", tmp,
+                    f'-DLCA_BUILT_FOR="{tag}"', "-I", os.path.join(ROOT, "include"), "-isystem", sysconfig.get_paths()["include"], "-isystem",
+                    os.path.join(base, "include"), "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"), BIND_SRC, "-o", tmp,
                     "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"], check=True)
     os.replace(tmp, BIND)
 

@@ -10,12 +10,15 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
+import warnings
 from dataclasses import dataclass
 from functools import lru_cache
 from operator import index
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "liblca.so")
+BIND_PATH = os.path.join(_PKG, "_lcabind.so")
 
 OK, ERR_INVALID_ARG, ERR_UNSUPPORTED, ERR_WORKSPACE, ERR_HIP = range(5)
 MODE_MLA, MODE_GQA = 0, 1
@@ -148,15 +151,23 @@ def load() -> ctypes.CDLL:
     return _lib
 
 
+def bind_tag() -> str:
+    """What the native marshalling is built for: the torch and the Python whose objects it reads."""
+    import torch
+    return f"torch {torch.__version__} {torch.version.git_version} python {sys.version_info[0]}.{sys.version_info[1]}"
+
+
 def _load_bind(lib) -> None:
     """The native marshalling, where it was built and fits the torch that is imported; everything works without it."""
     global _bind
+    if not os.path.exists(BIND_PATH):
+        return
     try:
         from . import _lcabind as bind
-        bind.setup(Desc, CacheLayout, {name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS}, _stream)
+        bind.setup(Desc, CacheLayout, {name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS}, _stream, bind_tag())
         _bind = bind
-    except ImportError:
-        pass
+    except Exception as e:
+        warnings.warn(f"{BIND_PATH} is not used, calls are marshalled in Python: {e}", RuntimeWarning)
 
 
 def _done(status: int) -> bool:

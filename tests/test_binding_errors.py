@@ -62,3 +62,40 @@ def test_an_exception_while_the_stream_is_asked_for_ends_the_call(bind, error):
 
     with pytest.raises(error):
         lca.dense_attn(desc, *t, None, lca.alloc_workspace(desc), stream=Stream())
+
+
+def test_another_torch_is_refused(bind):
+    """The module reads tensors by accessors compiled into it: one built for another torch, or Python, must not be used."""
+    addresses = dict.fromkeys(lca.EXPORTS, 1)
+    for tag in ("torch 2.9.0 abc python 3.10", lca.bind_tag() + " ", ""):
+        with pytest.raises(ImportError):
+            bind.setup(lca.Desc, lca.CacheLayout, addresses, lca._stream, tag)
+
+
+@pytest.mark.parametrize("error", [ImportError("built for another"), KeyError("lca_condense"), ValueError("no address")])
+def test_a_module_that_does_not_fit_is_done_without(bind, monkeypatch, error):
+    import paper_2604_12452_amd as package
+
+    class Other:
+        @staticmethod
+        def setup(*_):
+            raise error
+    monkeypatch.setattr(package, "_lcabind", Other, raising=False)
+    monkeypatch.setattr(lca, "_bind", None)
+    monkeypatch.setitem(__import__("sys").modules, "paper_2604_12452_amd._lcabind", Other)
+    with pytest.warns(RuntimeWarning, match="marshalled in Python"):
+        lca._load_bind(lca.load())
+    assert lca._bind is None
+
+
+def test_a_binding_for_another_torch_is_built_again(monkeypatch, tmp_path):
+    from paper_2604_12452_amd import build
+    bind = tmp_path / "_lcabind.so"
+    monkeypatch.setattr(build, "BIND", str(bind))
+    ran = []
+    monkeypatch.setattr(build.subprocess, "run", lambda cmd, check: (ran.append(cmd), open(cmd[cmd.index("-o") + 1], "wb").write(lca.bind_tag().encode() + b"\0")))
+    bind.write_bytes(b"torch 2.9.0 abc python 3.10\0")
+    build._build_binding(False)
+    assert len(ran) == 1 and f'-DLCA_BUILT_FOR="{lca.bind_tag()}"' in ran[0]
+    build._build_binding(False)
+    assert len(ran) == 1
