@@ -5,6 +5,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -57,16 +58,22 @@ def _build_binding(force: bool) -> None:
 
 
 def build(force: bool = False, verbose: bool = True) -> str:
+    """Build the library and, where torch, its headers and g++ are there, the binding's native part; without it calls are marshalled in Python."""
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(sources()))) as ex:
         binding = ex.submit(_build_binding, force)
         objs = list(ex.map(lambda s: _compile(s, force), sources()))
-        binding.result()
     tmp = LIB + f".{os.getpid()}.tmp"
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], check=True)
     os.replace(tmp, LIB)
     if verbose:
         print(f"built {LIB}")
+    try:
+        binding.result()
+    except (ImportError, OSError, subprocess.CalledProcessError) as e:
+        if os.path.exists(BIND):
+            os.remove(BIND)                     # (of another source or torch)
+        warnings.warn(f"{BIND} was not built, calls are marshalled in Python: {e}", RuntimeWarning)
     return LIB
 
 

@@ -88,6 +88,25 @@ def test_a_module_that_does_not_fit_is_done_without(bind, monkeypatch, error):
     assert lca._bind is None
 
 
+@pytest.mark.parametrize("error", [ImportError("No module named 'torch'"), FileNotFoundError("g++"), None])
+def test_the_library_is_built_without_the_binding(monkeypatch, tmp_path, error):
+    """A machine without torch, g++ or their headers: the C library is there, a binding of another build is not."""
+    import subprocess
+
+    from paper_2604_12452_amd import build
+    lib, bind = tmp_path / "liblca.so", tmp_path / "_lcabind.so"
+    bind.write_bytes(b"of another build")
+
+    def fail(force):
+        raise error or subprocess.CalledProcessError(1, "g++")
+    monkeypatch.setattr(build, "LIB", str(lib))
+    monkeypatch.setattr(build, "BIND", str(bind))
+    monkeypatch.setattr(build, "_build_binding", fail)
+    with pytest.warns(RuntimeWarning, match="was not built"):
+        assert build.build(verbose=False) == str(lib)
+    assert lib.exists() and not bind.exists()
+
+
 def test_a_binding_for_another_torch_is_built_again(monkeypatch, tmp_path):
     from paper_2604_12452_amd import build
     bind = tmp_path / "_lcabind.so"
