@@ -82,8 +82,9 @@ def test_gqa_output_is_the_sum_divided_once(dtype, ulp, k):
 @pytest.mark.parametrize("B,L,H,g,w,steps", [(1, 30, 16, 4, 64, 1), (2, 150, 7, 4, 200, 3), (1, 250, 16, 4, 300, 4), (1, 600, 16, 4, 700, 1), (1, 2205, 5, 2, 90, 2), (20, 1500, 4, 1, 30, 4)])
 @pytest.mark.parametrize("late", [0.0, 100.0])
 def test_mla_step_over_shared_tiles(oracle, dtype, B, L, H, g, w, steps, late):
-    """Partial last tiles and steps, and (late) logits that rise past any fixed reference in the last third of the cache, so that the workgroup
-    runs its tiles again from exact maxima; with sequences whose caches end in a tile of one entry."""
+    """Partial last tiles and steps, and (late) logits that rise past any fixed reference in the last third of the raw tail, so that a workgroup of two steps
+    or more that has them in a later one runs its tiles again from exact maxima (in one step the reference is the exact maximum); with sequences whose
+    caches end in a tile of one entry."""
     import torch
     from paper_2604_12452_amd import lca
     wl = inputs.Workload("shared", B=B, L=L, H=H, S=1, d_pool=512, d_sel=64, g=g, w=w, dtype=dtype, mode=inputs.MODE_MLA)
@@ -105,3 +106,51 @@ def test_mla_step_over_shared_tiles(oracle, dtype, B, L, H, g, w, steps, late):
     torch.cuda.synchronize()
     ref = oracle.decode_attn(hp.oracle_desc(oracle, wl), *(inputs.to_f64(host[n], dtype) for n in ("q", "pool_rep", "sel_rep", "pool_tail", "sel_tail")))
     assert hp.vec_rel_err(hp.from_dev(O, dtype), ref) <= hp.TOL[dtype]
+
+
+# B, L, H, g, w, steps of a workgroup: codes and tail in one workgroup, codes alone and then both in several, one step each, four unshared
+Q8_STEPS = [(1, 250, 16, 4, 100, 3), (2, 280, 7, 4, 230, 4), (1, 2205, 5, 2, 90, 2), (1, 600, 16, 2, 200, 1), (20, 1500, 4, 1, 30, 4)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("B,L,H,g,w,steps", Q8_STEPS)
+@pytest.mark.parametrize("late", [None, "tail", "codes"])
+def test_mla_q8_step_over_shared_tiles(oracle, dtype, B, L, H, g, w, steps, late):
+    """The same over 8-bit representatives, whose tiles are converted in place one step behind their request: logits that rise past the first step's maximum
+    in the raw tail, or among the representatives."""
+    import torch
+    from oracle import q8
+    from paper_2604_12452_amd import lca
+    wl = inputs.Workload("shared_q8", B=B, L=L, H=H, S=1, d_pool=512, d_sel=64, g=g, w=w, dtype=dtype, mode=inputs.MODE_MLA)
+    print(f"[case] {wl} late {late}", flush=True)
+    desc = hp.lca_desc(wl)
+    m, k = desc.m, desc.k
+    rng = np.random.default_rng(11 + L)
+    draw = lambda *shape, std=1.0: rng.standard_normal(shape, dtype=np.float32) * np.float32(std)
+    host = dict(q=draw(B, H, 576, std=576 ** -0.5), pool_rep=draw(B, 1, m, 512), sel_rep=draw(B, 1, m, 64), pool_tail=draw(B, 1, k, 512), sel_tail=draw(B, 1, k, 64))
+    if late == "tail":
+        host["sel_tail"][:, :, k - max(1, k // 3):] *= 400.0
+    if late == "codes":
+        host["sel_rep"][:, :, 80:96] *= 400.0                # the sixth tile
+    dev = {n: hp.to_dev(inputs.to_storage(x, dtype), dtype) for n, x in host.items()}
+    codes = [torch.zeros(dev[n].shape, dtype=torch.uint8, device="cuda") for n in ("pool_rep", "sel_rep")]
+    scales = torch.ones(B, 1, m, 2, device="cuda")
+    lca.quantize_cache(desc, None, dev["pool_rep"], dev["sel_rep"], *codes, scales)
+    O = torch.full((B, H, 512), float("nan"), dtype=lca.torch_dtype(desc), device="cuda")
+    ws = torch.full((lca.workspace_size(desc),), 0xFF, dtype=torch.uint8, device="cuda")
+    lca.decode_attn_q8(desc, None, dev["q"], *codes, scales, dev["pool_tail"], dev["sel_tail"], O, ws)
+    again = torch.full_like(O, float("nan"))
+    lca.decode_attn_q8(desc, None, dev["q"], *codes, scales, dev["pool_tail"], dev["sel_tail"], again, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(O.view(torch.int16), again.view(torch.int16))
+    sc = scales.cpu().numpy().astype(np.float64)
+    reps = [q8.dequantize_rows(c.cpu().numpy(), sc[..., i]) for i, c in enumerate(codes)]
+    q, pt, st = (hp.from_dev(dev[n], dtype) for n in ("q", "pool_tail", "sel_tail"))
+    assert hp.vec_rel_err(hp.from_dev(O, dtype), oracle.decode_attn(hp.oracle_desc(oracle, wl), q, *reps, pt, st)) <= hp.TOL[dtype]
+    if (late == "tail" and steps > 1 and B < 20) or (late == "codes" and steps == 2):
+        # some workgroup's later step holds a logit out of reach of the maximum of its first four tiles (bf16: 2^100, fp16: 65504)
+        z = np.einsum("bhd,bed->bhe", q, np.concatenate([np.concatenate([reps[0], reps[1]], -1), np.concatenate([pt, st], -1)], 2)[:, 0]) * wl.scale * 1.4426950408889634
+        tiles = [z[..., i:min(i + 16, m)] for i in range(0, m, 16)] + [z[..., i:i + 16] for i in range(m, m + k, 16)]
+        wg = [tiles[i:i + 4 * steps] for i in range(0, len(tiles), 4 * steps)]
+        top = lambda ts: np.concatenate(ts, -1).max(-1)
+        assert max((top(ts[4:]) - top(ts[:4])).max() for ts in wg if len(ts) > 4) > (100 if dtype == "bf16" else 16)

@@ -168,3 +168,12 @@ def test_mla_decode_step_tiles_shared_by_the_wavefronts(desc, shared, q8):
     run = t.decode(desc, q8)
     name = run[0].kernel                                       # (the last template argument; the demangler gives up on some of these names)
     assert (name.endswith(", true>") or "Lb1EEEv" in name, name.endswith(", false>") or "Lb0EEEv" in name) == (shared, not shared), name
+
+
+def test_q8_steps_are_where_they_claim_to_be():
+    from tests.test_gpu_decode_splits import Q8_STEPS
+    for B, L, H, g, w, steps in Q8_STEPS:
+        d = _mla(B=B, L=L, H=H, g=g, w=w)
+        run = t.decode(d, True)
+        tiles = -(-d.m // 16) + -(-d.k // 16)
+        assert -(-tiles // (4 * run[0].grid // B)) == steps, (L, tiles, run)
