@@ -123,7 +123,7 @@ def test_probabilities_enter_the_second_product_whole(dtype):
 def test_rising_logits_over_one_to_eight_wavefronts(oracle, dtype, scale, L, d_pool, B, step):
     """Every entry's logit lies `step` above the one before: 7.4 binades per tile of 32 entries, which the reference of the exponentials does
     not follow, 8.3 and 46, which it does.  Up to 15 entries are one tile and wavefront, 300 split over eight in fp32, and 40 sequences of 2100
-    take two.  Tolerance: the stated bar (the largest logit is 2100, whose last fp32 bit is 1.2e-4: rows from 1000 on are left out at step 1)."""
+    take two.  Tolerance: the stated bar (the largest logit is 2100, whose last fp32 bit is 1.2e-4: rows from 1000 on are left to the test below)."""
     wl = inputs.Workload("rising", B=B, L=L, H=1, S=1, d_pool=d_pool, d_sel=64, g=4, w=4096, dtype=dtype, mode=inputs.MODE_GQA, seed=5, n_q=1, scale=scale)
     print(f"[case] {wl} step {step}", flush=True)
     rng = np.random.default_rng(L)
@@ -139,6 +139,33 @@ def test_rising_logits_over_one_to_eight_wavefronts(oracle, dtype, scale, L, d_p
     got = hp.from_dev(run.O_dense, dtype)
     assert hp.vec_rel_err(got[:1, rows], ref) <= hp.TOL[dtype]
     assert np.isfinite(got).all()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("scale", [1.0, -1.0])
+@pytest.mark.parametrize("step", [0.16, 0.18, 1.0])
+def test_rising_logits_in_long_rows_of_the_last_sequence(oracle, dtype, scale, step):
+    """The same in the rows with the most tiles, first and last sequence, and their lse.  A logit of up to 2100 is good to 2^-13 (its fp32 product with the
+    scale and log2 e), which is what a probability and lse lose besides the type's bar; at steps below one 16-bit storage rounds the keys
+    themselves, the same for the oracle."""
+    B, L = 40, 2100
+    wl = inputs.Workload("rising", B=B, L=L, H=1, S=1, d_pool=64, d_sel=64, g=4, w=4096, dtype=dtype, mode=inputs.MODE_GQA, seed=5, n_q=1, scale=scale)
+    print(f"[case] {wl} step {step}", flush=True)
+    rng = np.random.default_rng(L)
+    Qf, Kf = np.zeros((B, L, 1, 64)), np.zeros((B, L, 1, 64))
+    Qf[..., 0] = 1.0
+    Kf[..., 0] = (step * np.arange(L) * (-1.0 if scale < 0 else 1.0))[None, :, None]
+    arrays = [inputs.to_storage(a.astype(np.float32), dtype) for a in (Qf, rng.standard_normal((B, L, 1, 64)), Kf)]
+    run = hp.GpuRun(wl, *arrays)
+    run.dense()
+    rows = np.unique(np.concatenate([np.arange(7, L, 97), np.arange(L - 3, L)])).astype(np.int32)
+    got, lse = hp.from_dev(run.O_dense, dtype), run.lse_dense.cpu().numpy().astype(np.float64)
+    assert np.isfinite(got).all() and np.isfinite(lse).all()
+    for b in (0, B - 1):
+        wide = [inputs.to_f64(a[b:b + 1], dtype) for a in arrays]
+        ref, ref_lse = oracle.dense_attn_rows(hp.oracle_desc(oracle, replace(wl, B=1)), rows, wide[0][:, rows], wide[1], wide[2], want_lse=True)
+        assert hp.vec_rel_err(got[b:b + 1, rows], ref) <= hp.TOL[dtype] + 2.0 ** -12
+        assert np.abs(lse[b:b + 1, rows] - ref_lse).max() <= 2.0 ** -12
 
 
 def _peaked(dtype, a, scale, L=60, at=(20, 45), seed=4):
