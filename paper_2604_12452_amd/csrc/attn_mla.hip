@@ -76,7 +76,7 @@ constexpr float NEG_BIG = -1.0e30f;     // stands for -inf in running maxima (ke
 constexpr float L_LIMIT = 0x1p90f;      // a row sum beyond this (or not finite) makes the workgroup repeat the item from exact maxima
 // fp16 ends at 65504: an exponential past it is an infinity in the second product, which no column of its row survives (infinity times a value is an
 // infinity, or no number), so the item is repeated from exact maxima if the row's first accumulator is not finite.  (Keeping the largest exponential
-// instead took one v_max3 per pair.)  The reference sits 4 binades above the first maximum a row sees
+// instead took one v_max3 per pair, which no case here shows: L = 8192, 16 heads 317 us either way.  A value that is not finite itself has its rows repeated for nothing.)  The reference sits 4 binades above the first maximum a row sees
 // (first entries at 2^-4): later logits may be 2^19 times larger before that happens, at the price of 4 of fp16's 24
 // binades at the bottom.
 constexpr float REF_SHIFT_F16 = 4.f;

@@ -502,13 +502,15 @@ bool decode_mla_supported(const Dims &d)
 // Wavefronts per (sequence, set), a multiple of 4 (a workgroup's, which leave one partial result): four tiles for each, where
 // the cache is long enough to fill the chip that way, never more workgroups than CUs (a second round costs as much as the
 // first).  A short or lonely cache is bound by the chain of tiles a wavefront works through: two tiles for each while the
-// workgroups stay below 160, one while they stay below 200 and the merge has few results to add (16 of 33 KB).  Measured
-// (step with merge, 16 heads; four / two / one tile each): B = 1, L = 700 15.9 / 14.6 / 13.3 us; B = 1, L = 4001 16.7 / 14.4 / 14.4;
-// B = 1, L = 16384 15.4 / 14.1 / 15.8; B = 8, L = 1500 17.4 / 15.2 / 15.5; B = 32, L = 700 17.5 / 18.2 / 19.3 (192, 256 workgroups);
-// B = 150, L = 20000 103 us with two workgroups per sequence (300 on 256 CUs), 77 us with one.
+// workgroups stay below 160, one while they stay below 200 and the merge has few results to add (16 of 33 KB).  Measured with
+// the wavefronts of a workgroup sharing its tiles (step with merge, 16 heads, 16 bits; four / two / one tile each): B = 1, L = 700 13.8 / 10.7 / 9.7 us, L = 4001
+// 14.3 / 11.2 / 10.6, L = 16384 14.1 / 11.5 / 11.1, L = 131072 16.1 / 14.9 / 17.1; B = 8, L = 1500 14.8 / 12.2 / 12.3; B = 16, L = 4001 15.9 / 14.1 / 15.7;
+// B = 32, L = 700 15.9 / 14.4 / 18.1 (96, 192, 352 workgroups), L = 1500 17.3 / 20.7 / 20.6; B = 150, L = 20000 96 us with two workgroups per sequence
+// (300 on 256 CUs), 71.5 us with one.  (So more results than 16 would pay by now for one or two sequences, and two tiles for up to 200 workgroups; the lines
+// lie where they did when each wavefront worked alone.)
 // Up to 16 tiles one workgroup takes them all: it writes the output itself, and the merge's launch costs more than a chain of up to
-// four tiles is long (two to four workgroups / one: B = 1, L = 80
-// 10.7 / 8.7 us, 160 10.8 / 10.1, 250 10.9 / 11.5; B = 60, L = 160 15.8 / 10.7).
+// four tiles is long (one workgroup / two tiles / one tile each: B = 1, L = 80 7.6 / 7.6 / 9.0, 160 9.2 / 10.5 / 9.2; B = 60, L = 160 9.6 / 12.4 / 12.5; not any more at
+// the end of that range, 250 11.5 / 10.6 / 9.3).
 int decode_mla_parts(const Dims &d)
 {
     const int tiles = (d.m + BN - 1) / BN + (d.k + BN - 1) / BN;      // (an upper bound when the two kinds share tiles)
