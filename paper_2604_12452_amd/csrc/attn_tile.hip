@@ -4,9 +4,9 @@
 //
 // What these shapes need is parallelism and reuse, not the last MFMA: one wavefront per query row, every key element a
 // scalar load of its own, took 128 us for 0.36 GFLOP in fp32 (L = 1024, 4 heads, 128 + 32) and 1.44 ms for 5.3 GFLOP in bf16
-// (L = 2500, 16 heads over 4 KV heads, 64 / 64).  With the condensation before it the first takes 20.5 us now (launches, memory latency, a chain of
-// fp32 products per tile), the second 31.3 us (vector ALU: exponentials and the splitting of the probabilities).  Two things the compiler does
-// are kept from it below, each of which had every tile wait for the next one's loads (21.9 and 38.5 us; fp32, 8 heads, L = 4096 153 us, now 126;
+// (L = 2500, 16 heads over 4 KV heads, 64 / 64).  With the condensation before it the first takes 20.4 us now (launches, memory latency, a chain of
+// fp32 products per tile), the second 32.2 us (vector ALU: exponentials and the splitting of the probabilities).  Two things the compiler does
+// are kept from it below, each of which had every tile wait for the next one's loads (21.9 and 38.5 us; fp32, 8 heads, L = 4096 153 us, now 128;
 // bf16 256 + 32, 8 heads, two times L = 4000 182, now 156): the queries' arrival left open until the loop, and load offsets computed in the
 // registers that loads fill.  Here
 //   * a workgroup owns 16 QB query rows of one condensed set, numbered (token, head of the set): the heads of a set see the
@@ -443,8 +443,8 @@ void attn_tile_kernel(const TileParams<T> tp)
             // The products become logits before anything else reads them: the reference is then one of the logits as they were rounded.  (With one fused
             // operation from product to exponent, what rounding left of the reference became part of every exponent, several binades from base-2 logits of 2^26
             // on, which three parts in fp16 cannot hold; and the products' first reader was a maximum in assembly, for which the compiler keeps none of the
-            // wait states behind a matrix product.  Fused / so, 16 heads over 4 KV heads, 64 / 64, L = 2500, the attention alone: bf16 22.2 / 22.7 us, fp16
-            // 25.3 / 25.4; at 128 columns and more within 1 %.)
+            // wait states behind a matrix product.  Fused / so, 16 heads over 4 KV heads, 64 / 64, L = 2500, the attention alone: bf16 22.2 / 23.0 us, fp16
+            // 25.3 / 25.7; at 128 columns and more within 2 %.)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
