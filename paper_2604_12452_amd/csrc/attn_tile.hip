@@ -5,7 +5,7 @@
 // What these shapes need is parallelism and reuse, not the last MFMA: one wavefront per query row, every key element a
 // scalar load of its own, took 128 us for 0.36 GFLOP in fp32 (L = 1024, 4 heads, 128 + 32) and 1.44 ms for 5.3 GFLOP in bf16
 // (L = 2500, 16 heads over 4 KV heads, 64 / 64).  With the condensation before it the first takes 20.4 us now (launches, memory latency, a chain of
-// fp32 products per tile), the second 32.2 us (vector ALU: exponentials and the splitting of the probabilities).  Two things the compiler does
+// fp32 products per tile), the second 32.0 us (vector ALU: exponentials and the splitting of the probabilities).  Two things the compiler does
 // are kept from it below, each of which had every tile wait for the next one's loads (21.9 and 38.5 us; fp32, 8 heads, L = 4096 153 us, now 128;
 // bf16 256 + 32, 8 heads, two times L = 4000 182, now 156): the queries' arrival left open until the loop, and load offsets computed in the
 // registers that loads fill.  Here
@@ -384,9 +384,10 @@ void attn_tile_kernel(const TileParams<T> tp)
             const int x = M::CHUNK * kc + M::EPC * q4;
             qf[qb][kc] = x < d_qk ? *reinterpret_cast<const uintx4 *>(kp.Q + q_row[qb] * d_qk + x) : uintx4{0, 0, 0, 0};
         }
-    // (A branch that does nothing: behind it the 512-column fp32 class keeps less of the tile in hand in memory, 512 / 64, 16 heads over 4 KV heads, L = 509
-    // 313 / 278 us.)
-    if (FULL && !LATE && kp.scale < 0.f) {
+    // (A branch that does nothing.  Behind it the compiler arranges the queries and what follows otherwise: 512 columns in fp32 keep less of the tile in hand in
+    // memory, 512 / 64, 16 heads over 4 KV heads, L = 509 313 / 278 us; in 16 bits 64 / 64, L = 20 3.8 / 3.7 us, B = 2, L = 4000 32.9 / 32.1, fp16 L = 2500
+    // 25.7 / 25.4; the other fp32 classes 2 % either way.)
+    if ((FULL || sizeof(T) == 2) && !LATE && kp.scale < 0.f) {
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
@@ -443,8 +444,8 @@ void attn_tile_kernel(const TileParams<T> tp)
             // The products become logits before anything else reads them: the reference is then one of the logits as they were rounded.  (With one fused
             // operation from product to exponent, what rounding left of the reference became part of every exponent, several binades from base-2 logits of 2^26
             // on, which three parts in fp16 cannot hold; and the products' first reader was a maximum in assembly, for which the compiler keeps none of the
-            // wait states behind a matrix product.  Fused / so, 16 heads over 4 KV heads, 64 / 64, L = 2500, the attention alone: bf16 22.2 / 23.0 us, fp16
-            // 25.3 / 25.7; at 128 columns and more within 2 %.)
+            // wait states behind a matrix product.  Fused / so, 16 heads over 4 KV heads, 64 / 64, L = 2500, the attention alone: bf16 22.2 / 22.7 us, fp16
+            // 25.3 / 25.4; at 128 columns and more within 1 %.)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
