@@ -177,3 +177,27 @@ def test_q8_steps_are_where_they_claim_to_be():
         run = t.decode(d, True)
         tiles = -(-d.m // 16) + -(-d.k // 16)
         assert -(-tiles // (4 * run[0].grid // B)) == steps, (L, tiles, run)
+
+
+@pytest.mark.parametrize("desc,halves", [
+    (_mla(L=1), True), (_mla(L=1024), True), (_mla(L=1025), True), (_mla(L=1600), True), (_mla(L=1900), False), (_mla(L=2048), False), (_mla(L=3000), False),
+    (_mla(L=8192), False), (_mla(H=8, L=2048), True), (_mla(H=8, L=3000), False), (_mla(H=1, L=16384), True), (_mla(H=1, L=32768), True), (_mla(H=2, L=10000), False),
+    (_mla(B=2, L=1000), True), (_mla(B=3, L=1000), False), (_mla(B=16, L=64), True), (_mla(B=17, L=64), False), (_mla(B=3, L=400), True), (_mla(B=64, L=64), False),
+    (_mla(S=16, L=1024), True), (_mla(S=16, L=4096), False), (_mla(H=3, L=5000), True),
+])
+@pytest.mark.parametrize("up", [False, True])
+def test_mla_items_halved_while_they_are_few(desc, halves, up):
+    """Two workgroups' worth of every item while each finds a CU of its own, or a second round that is short."""
+    run = t.prefill(desc, up=up)[-1]
+    assert run.kernel.startswith("attn_mla_kernel_halves" if halves else "attn_mla_kernel<"), run
+    n_qb, run_log2, hw = t.mla_items(desc, up=up)
+    deal = 8 << run_log2                             # (the query blocks are dealt out to the XCDs in whole rounds)
+    items = -(-n_qb * desc.B // deal) * deal * (desc.H >> hw) * (2 if halves else 1)
+    assert run.grid == min(256, items) and run.block == 256
+
+
+def test_mla_batches_are_where_they_claim_to_be():
+    from tests.test_gpu_item_rounds import MANY
+    for B, L, H, S, g, w, _, up in MANY:
+        for n, name in ((B, "attn_mla_kernel<"), (1, "attn_mla_kernel_halves")):
+            assert t.prefill(_mla(B=n, L=L, H=H, S=S, g=g, w=w), up=up)[-1].kernel.startswith(name), (B, L, n)
