@@ -31,8 +31,8 @@
 // 16 MFMAs of the update that follows it cover the arrival of the first key fragments.
 //
 // Softmax uses one fixed reference per row (the first entries the row sees), so O^T is never rescaled and no
-// maxima are taken in the steady state; a row sum that ends beyond 2^90 makes the workgroup find exact maxima
-// (S^T chains alone) and run the item again from those.
+// maxima are taken in the steady state; a row sum that ends beyond 2^90 makes the workgroup run the item again, from the
+// logarithm of the row sums or, where those are not finite, from exact maxima (S^T chains alone).
 #include <type_traits>
 
 #include "lca_internal.h"
@@ -71,9 +71,9 @@ constexpr int COPIES = 2 * BN / NW / 4; // direct-to-LDS loads per wavefront and
 constexpr int GRID = 256;               // most workgroups the persistent kernel is launched with (one per CU of the chip)
 constexpr int RING = 4;                 // fragments in flight per operand
 constexpr float NEG_BIG = -1.0e30f;
-constexpr float L_LIMIT = 0x1p90f;      // a row sum beyond this (or not finite) makes the workgroup repeat the item from exact maxima
+constexpr float L_LIMIT = 0x1p90f;      // a row sum beyond this (or not finite) makes the workgroup repeat the item
 // fp16 ends at 65504: an exponential past it is an infinity in the second product, which no column of its row survives (infinity times a value is an
-// infinity, or no number), so the item is repeated from exact maxima if the row's first accumulator is not finite.  (Keeping the largest exponential instead, one
+// infinity, or no number), so the item is repeated if the row's first accumulator is not finite.  (Keeping the largest exponential instead, one
 // v_max3 per pair, costs a ninth of the vector instructions: the attention alone, in turn on one GPU, 28 heads over 4 KV heads, three times L = 5003 242.6 us so,
 // 239.3 us as it is, 32 over 8, L = 16000 383.8 and 376.5.  A value that is not finite itself has its rows repeated for nothing.)  The reference sits 4 binades above the first maximum a row sees
 // (first entries at 2^-4): later logits may be 2^19 times larger before that happens, at the price of 4 of fp16's 24
@@ -656,7 +656,20 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
             }
             // every wavefront is done with the stages; repeat the item if a row sum ran out of range
             if (!__syncthreads_or(pass == 0 && redo)) break;
-            {
+            // Where the row sums are finite they bound the maxima well enough: from the logarithm of its sum as reference (in fp16 15 binades below it) a row's exponentials
+            // add up to 1 (2^15) and none can pass the type's limit.  Only a sum that is not finite takes the exact maxima, a pass of its own whose tiles nothing
+            // overlaps.  A few repeated items are enough to be what a call waits for (they are among the last ones): fp16, 28 heads over 4 KV heads, three times L = 5003,
+            // neighbouring tokens alike, exact maxima / row sums 303 / 272 us, 32 over 8, L = 16000 439 / 410.
+            bool unbounded = false;
+#pragma unroll
+            for (int rb = 0; rb < 2; ++rb) {
+                unbounded |= !(l_tot[rb] < INFINITY);
+                m_exact[rb] = l_tot[rb] > 0.f ? st.m_ref[rb] + log2f(l_tot[rb]) - (F16 ? 15.f : 0.f) : NEG_BIG;
+            }
+            if (!__syncthreads_or(unbounded)) {
+                pass = 2;
+                issue_first_copies(cur);
+            } else {
                 // exact row maxima, one tile at a time (no overlap: this path is rare): tile tl goes into stage tl%2 after the
                 // barrier of tile tl-1, which every wavefront reaches after its chains over tile tl-2
                 m_exact[0] = NEG_BIG; m_exact[1] = NEG_BIG;

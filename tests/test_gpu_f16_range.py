@@ -27,3 +27,25 @@ def test_exponentials_past_65504(oracle, mode, d_pool, d_sel, H, S, rise, zero_c
     run.dense()
     rows = np.arange(wl.L, dtype=np.int32)
     hp.check_dense(oracle, wl, run, rows, *(inputs.to_f64(a, "f16") for a in arrays))
+
+
+@pytest.mark.parametrize("dtype,rise", [("f16", 14.5), ("f16", 30.0), ("f16", 85.0), ("f16", 95.0), ("bf16", 65.0), ("bf16", 85.0), ("bf16", 95.0)])
+@pytest.mark.parametrize("w", [40, 300])
+def test_gqa_repeats_from_row_sums(oracle, dtype, rise, w):
+    """Rows that end beyond the limit are repeated from the logarithm of their sum where that is finite (a rise of up to 2^128, 88.7 nats), from
+    exact maxima beyond.  w = 300: fp16 items whose references come from a sample of the tokens that all their rows see; w = 40: too few of those."""
+    wl = inputs.Workload("sums", B=1, L=700, H=6, S=2, d_pool=128, d_sel=128, g=16, w=w, dtype=dtype, mode=inputs.MODE_GQA, seed=5)
+    print(f"[case] {wl} rise {rise}", flush=True)
+    Q, POOL, SEL = (inputs.to_f64(x, dtype) for x in inputs.gen_all(wl))
+    Q[..., -1] = 1.0
+    SEL[..., -1] = 0.0
+    SEL[0, (70, 333, 651), ..., -1] = rise
+    Q, POOL, SEL = (inputs.to_storage(x.astype(np.float32), dtype) for x in (Q, POOL, SEL))
+    Qf, POOLf, SELf = (inputs.to_f64(x, dtype) for x in (Q, POOL, SEL))
+    run = hp.GpuRun(wl, Q, POOL, SEL).condense()
+    ref, differ = hp.check_condense(oracle, wl, run, Qf[:, wl.L - wl.nq:], POOLf, SELf)
+    rows = np.arange(wl.L, dtype=np.int32)
+    run.prefill()
+    hp.check_prefill(oracle, wl, run, rows, Qf, POOLf, SELf, ref, differ)
+    run.dense()
+    hp.check_dense(oracle, wl, run, rows, Qf, POOLf, SELf)
