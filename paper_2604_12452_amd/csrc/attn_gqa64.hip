@@ -80,6 +80,11 @@ constexpr float L_LIMIT = 0x1p90f;      // a row sum beyond this (or not finite)
 // binades at the bottom.
 constexpr float REF_SHIFT_F16 = 4.f;
 constexpr int FEW_REPS = 16;            // fp16: with fewer visible representatives an item starts with its raw tokens (make_blk)
+// ... and a row's reference is the largest logit of this many tokens, evenly spread over those that every row of the item sees (a few neighbouring tokens, alike
+// as they are, made one item in a hundred repeat, and those are among the last of a call): fp16, neighbouring tokens alike, 28 heads over 4 KV heads, three times
+// L = 5003 first entries / sample 279 / 260 us, 32 over 8, L = 16000 424 / 403 (bf16, which repeats nothing: 246 and 383); where nothing is repeated either way
+// the sample's copy and 16 MFMAs cost an item 0.3 us (three times L = 1000, w = 512 46.8 / 47.3, L = 5003, g = 32 246.8 / 248.2).
+constexpr int NSAMPLE = 32;
 constexpr int RSRC_WORD3 = 0x00020000;  // raw buffer of dwords, gfx9 layout
 
 struct G64Params {
@@ -371,6 +376,7 @@ template <bool F16>
 __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params kp)
 {
     __shared__ __attribute__((aligned(1024))) char stages[NSTAGE][STAGE_BYTES];
+    __shared__ __attribute__((aligned(1024))) char sample[F16 ? NSAMPLE * RB : 1024];
 
     const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, G = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -418,13 +424,22 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
     floatx16 acc[2][NDV];
     RowState st;
     char *const qbuf = &stages[3][0] + wave * (32 * RB);
-    auto issue_first_copies = [&](const Blk &k) {
+    // How far apart the sampled tokens of an item are: over those that every row of it sees; 0: too few, or nothing to sample
+    auto sample_step = [&](const Blk &k) { return k.flip ? max(0, k.t0 + 1 - k.mt_blk_hi * kp.g) / NSAMPLE : 0; };
+    auto issue_first_copies = [&](const Blk &k, bool with_sample) {
+        if (F16 && with_sample && sample_step(k) > 0) {
+            const unsigned step = sample_step(k) * k.raw_stride, first = (unsigned)(k.mt_blk_hi * kp.g) * k.raw_stride + 4 * wave * step;
+            const int4v rs = {(int)k.raw_k.lo, (int)k.raw_k.hi, (int)k.raw_k.bytes, RSRC_WORD3};
+            const unsigned m0 = lds_address(sample) + 4 * wave * RB;
+            dma_1k<0>((lane >> 4) * step + chunk_k, rs, first, m0);
+            dma_1k<16 * RB>((lane >> 4) * step + chunk_k, rs, first + 16 * step, m0);
+        }
         for (int tl = 0; tl < 3; ++tl) {
             const CopyCtl cc = make_copy(k, tl, tl, wave, lds0);
             issue_copy_all(cc, (lane >> 4) * cc.stride + chunk_k, (lane >> 4) * cc.stride + chunk_v);
         }
     };
-    issue_first_copies(cur);
+    issue_first_copies(cur, true);
     load_q(kp, cur, lane, qf);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     q_to_fragments(qbuf, lane, qf);
@@ -590,6 +605,22 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
             // ---- tile 0 has landed (tiles 1 and 2 may be on their way); S^T chain of half 0 ----
             asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * COPIES) : "memory");
             __syncthreads();
+            if (F16 && pass == 0 && sample_step(cur) > 0) {          // references from the sample (every row sees all of it)
+                Addr ax = adr;
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) ax.k[ks] += lds_address(sample) - lds0;
+#pragma unroll
+                for (int rb = 0; rb < 2; ++rb) {
+                    floatx16 sv;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sv[r] = 0.f;
+#pragma unroll
+                    for (int ks = 0; ks < NKS; ++ks)
+                        sv = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, load_k(ax, 0, ks)), __builtin_bit_cast(f16x8, qf[rb][ks]), sv, 0, 0, 0);
+                    st.m_ref[rb] = row_max(sv, c, 0.f) + REF_SHIFT_F16;      // (-1e30 + 4 is -1e30: no number above it, no reference yet)
+                }
+                need_ref = __builtin_amdgcn_ballot_w64((st.m_ref[0] == NEG_BIG) | (st.m_ref[1] == NEG_BIG)) != 0;
+            }
 #pragma unroll
             for (int f = 0; f < RING; ++f) kf[f] = load_k(a, 0, f);
 #pragma unroll
@@ -668,7 +699,7 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
             }
             if (!__syncthreads_or(unbounded)) {
                 pass = 2;
-                issue_first_copies(cur);
+                issue_first_copies(cur, false);
             } else {
                 // exact row maxima, one tile at a time (no overlap: this path is rare): tile tl goes into stage tl%2 after the
                 // barrier of tile tl-1, which every wavefront reaches after its chains over tile tl-2
@@ -700,7 +731,7 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
                 }
                 __syncthreads();
                 pass = 2;
-                issue_first_copies(cur);
+                issue_first_copies(cur, false);
             }
         }
 
@@ -720,7 +751,7 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
             (void *)(kp.O + (((size_t)out_b * L + out_t0) * H + out_h) * D), (short)0, rows_valid > 0 ? ((rows_valid - 1) * H * D + D) * 2 : 0, RSRC_WORD3);
         if (has_next) {
             cur = make_blk<F16>(kp, nu, nqb, wave, n);
-            issue_first_copies(cur);
+            issue_first_copies(cur, true);
             load_q(kp, cur, lane, qf);
         }
 
