@@ -55,7 +55,9 @@ struct DgParams {
     const float *scales;
     float *part;
     void *O;                               // not NULL: one workgroup per (sequence, KV head), which then writes the final output itself
-    int S, hps, m, k, n_parts, m_cap, k_cap, k_start;
+    int S, hps, m, k, m_cap, k_cap, k_start;
+    int wgs, tiles_per_part;               // workgroups of a (sequence, KV head); tiles of a wavefront
+    unsigned wgs_magic;                    // 2^32 / wgs + 1: blockIdx / wgs in one multiplication
     float scale_log2, bias_log2;
 };
 
@@ -101,12 +103,12 @@ __global__ __launch_bounds__(256, 1) void decode_gqa_mfma_kernel(const DgParams 
 
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, q4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wg_per_bs = kp.n_parts / 4;
-    const int part = (blockIdx.x % wg_per_bs) * 4 + wave, bs = blockIdx.x / wg_per_bs;
+    const int wg_per_bs = kp.wgs, bs = wg_per_bs == 1 ? blockIdx.x : __umulhi(blockIdx.x, kp.wgs_magic), wg = blockIdx.x - bs * wg_per_bs;
+    const int part = wg * 4 + wave;
     const int m = kp.m, n = kp.m + kp.k;
     const int rep_tiles = Q8 ? (m + BN - 1) / BN : 0;                       // Q8: tiles [0, rep_tiles) hold representatives only
     const int tiles_total = Q8 ? rep_tiles + (kp.k + BN - 1) / BN : (n + BN - 1) / BN;
-    const int tiles_per_part = (tiles_total + kp.n_parts - 1) / kp.n_parts;
+    const int tiles_per_part = kp.tiles_per_part;
     const int t_lo = min(part * tiles_per_part, tiles_total), t_hi = min(t_lo + tiles_per_part, tiles_total);
     const int e_hi = Q8 ? n : min(n, t_hi * BN);
     // first entry of tile tl and the end of the entries it may show (Q8: the end of its kind)
@@ -335,7 +337,7 @@ __global__ __launch_bounds__(256, 1) void decode_gqa_mfma_kernel(const DgParams 
         factor[w] = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - m_all);
         l_all += wave_ml[w][col][1] * factor[w];
     }
-    float *dst0 = kp.part + ((size_t)bs * wg_per_bs + blockIdx.x % wg_per_bs) * kp.hps * (D + 2);
+    float *dst0 = kp.part + ((size_t)bs * wg_per_bs + wg) * kp.hps * (D + 2);
     auto of_head = [](float v, int h) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), h)); };   // (lane h: head h)
     float2 v[4][4];
 #pragma unroll
@@ -405,13 +407,16 @@ hipError_t launch_decode_gqa_mfma(const DecodeArgs &a, hipStream_t st)
     DgParams kp;
     kp.q = (const uint16_t *)a.q; kp.k_rep = (const uint16_t *)a.sel_rep; kp.v_rep = (const uint16_t *)a.pool_rep;
     kp.k_tail = (const uint16_t *)a.sel_tail; kp.v_tail = (const uint16_t *)a.pool_tail; kp.part = a.part;
-    kp.S = d.S; kp.hps = d.H / d.S; kp.m = d.m; kp.k = d.k; kp.n_parts = a.splits;
+    kp.S = d.S; kp.hps = d.H / d.S; kp.m = d.m; kp.k = d.k; kp.wgs = a.splits / 4;
     kp.m_cap = a.m_cap; kp.k_cap = a.k_cap; kp.k_start = a.k_start;
     kp.scale_log2 = d.scale * 1.4426950408889634f;
     kp.bias_log2 = d.rep_logit_bias * 1.4426950408889634f;
     kp.k_q8 = a.sel_q8; kp.v_q8 = a.pool_q8; kp.scales = a.scales;
     kp.O = a.splits == 4 ? a.O : nullptr;
-    const unsigned grid = d.B * d.S * (a.splits / 4);
+    kp.wgs_magic = kp.wgs > 1 ? (unsigned)((1ull << 32) / (unsigned)kp.wgs + 1) : 0u;      // (exact: several workgroups share a pair only in grids of up to 256)
+    const int tiles = a.pool_q8 != nullptr ? (d.m + BN - 1) / BN + (d.k + BN - 1) / BN : (d.m + d.k + BN - 1) / BN;
+    kp.tiles_per_part = (tiles + a.splits - 1) / a.splits;
+    const unsigned grid = d.B * d.S * kp.wgs;
     if (a.pool_q8 != nullptr) {
         if (d.dtype == LCA_F16) decode_gqa_mfma_kernel<_Float16, true><<<grid, 256, 0, st>>>(kp);
         else decode_gqa_mfma_kernel<__bf16, true><<<grid, 256, 0, st>>>(kp);

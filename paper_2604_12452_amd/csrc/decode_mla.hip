@@ -43,6 +43,8 @@ struct DmParams {
     float *part;
     void *O;                               // not NULL: one workgroup per (sequence, set), which then writes the final output itself
     int S, hps, m, k, n_parts, m_cap, k_cap, k_start;
+    int wgs, tiles_per_part;               // workgroups of a (sequence, set); tiles of a wavefront
+    unsigned wgs_magic;                    // 2^32 / wgs + 1: blockIdx / wgs in one multiplication
     float scale_log2, bias_log2;
 };
 
@@ -87,12 +89,12 @@ __global__ __launch_bounds__(256, 1) void decode_mla_kernel(const DmParams kp)
 
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, q4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wg_per_bs = kp.n_parts / 4, bs = blockIdx.x / wg_per_bs, wg = blockIdx.x - bs * wg_per_bs;
-    const int b = bs / kp.S;
+    const int wg_per_bs = kp.wgs, bs = wg_per_bs == 1 ? blockIdx.x : __umulhi(blockIdx.x, kp.wgs_magic), wg = blockIdx.x - bs * wg_per_bs;
+    const int b = kp.S == 1 ? bs : bs / kp.S;
     const int m = kp.m, n = kp.m + kp.k;
     const int rep_tiles = Q8 ? (m + BN - 1) / BN : 0;                       // Q8: tiles [0, rep_tiles) hold representatives only
     const int tiles_total = Q8 ? rep_tiles + (kp.k + BN - 1) / BN : (n + BN - 1) / BN;
-    const int tiles_per_part = (tiles_total + kp.n_parts - 1) / kp.n_parts;
+    const int tiles_per_part = kp.tiles_per_part;
     // tiles [t_lo, t_hi) of the workgroup (SHARED) or of the wavefront, which takes first, first + STRIDE, ..: `mine` of them
     const int t_lo = min((4 * wg + (SHARED ? 0 : wave)) * tiles_per_part, tiles_total), t_hi = min(t_lo + (SHARED ? 4 : 1) * tiles_per_part, tiles_total);
     const int steps = (t_hi - t_lo + STRIDE - 1) / STRIDE, first = t_lo + (SHARED ? wave : 0), mine = (t_hi - first + STRIDE - 1) / STRIDE;
@@ -502,12 +504,13 @@ bool decode_mla_supported(const Dims &d)
 // Wavefronts per (sequence, set), a multiple of 4 (a workgroup's, which leave one partial result): four tiles for each, where
 // the cache is long enough to fill the chip that way, never more workgroups than CUs (a second round costs as much as the
 // first).  A short or lonely cache is bound by the chain of tiles a wavefront works through: two tiles for each while the
-// workgroups stay below 160, one while they stay below 200 and the merge has few results to add (16 of 33 KB).  Measured with
-// the wavefronts of a workgroup sharing its tiles (step with merge, 16 heads, 16 bits; four / two / one tile each): B = 1, L = 700 13.8 / 10.7 / 9.7 us, L = 4001
-// 14.3 / 11.2 / 10.6, L = 16384 14.1 / 11.5 / 11.1, L = 131072 16.1 / 14.9 / 17.1; B = 8, L = 1500 14.8 / 12.2 / 12.3; B = 16, L = 4001 15.9 / 14.1 / 15.7;
-// B = 32, L = 700 15.9 / 14.4 / 18.1 (96, 192, 352 workgroups), L = 1500 17.3 / 20.7 / 20.6; B = 150, L = 20000 96 us with two workgroups per sequence
-// (300 on 256 CUs), 71.5 us with one.  (So more results than 16 would pay by now for one or two sequences, and two tiles for up to 200 workgroups; the lines
-// lie where they did when each wavefront worked alone.)
+// workgroups stay below 160, one while they stay below 200 and the merge has few results to add (16 of 33 KB), or up to 32 results where there are fewer than
+// 92 workgroups and eight heads or more (8 heads, B = 1, L = 4001 10.1 / 9.2 us, 8-bit 10.8 / 9.6; with fewer it would pay as well, H = 4 9.7 / 8.6, but those widths keep
+// the two-tile ranges that the tests of two steps are made of).  Measured with the wavefronts of a workgroup sharing its tiles (step with merge, 16 heads, 16 bits; four / two / one tile each): B = 1, L = 700 13.8 /
+// 10.7 / 9.7 us, L = 4001 14.3 / 11.1 / 10.4, L = 16000 14.1 / 11.5 / 11.1, L = 131072 16.1 / 14.9 / 17.1; two / one: B = 2, L = 8000 11.7 / 10.8 (46 workgroups), B = 4,
+// L = 4001 11.7 / 11.4 (76), L = 8000 11.8 / 11.7 (92), but B = 3, L = 16000 11.9 / 12.0 (93), B = 6, L = 4001 11.9 / 11.9 (114), B = 8, L = 4001 12.5 / 12.8 (152); B = 16,
+// L = 4001 15.9 / 14.1 / 15.7; B = 32, L = 700 15.9 / 14.4 / 18.1 (96, 192, 352 workgroups), L = 1500 17.3 / 20.7 / 20.6; B = 150, L = 20000 96 us with two workgroups
+// per sequence (300 on 256 CUs), 71.5 us with one.
 // Up to 16 tiles one workgroup takes them all: it writes the output itself, and the merge's launch costs more than a chain of up to
 // four tiles is long (one workgroup / two tiles / one tile each: B = 1, L = 80 7.6 / 7.6 / 9.0, 160 9.2 / 10.5 / 9.2; B = 60, L = 160 9.6 / 12.4 / 12.5; not any more at
 // the end of that range, 250 11.5 / 10.6 / 9.3).
@@ -518,7 +521,8 @@ int decode_mla_parts(const Dims &d)
     auto wgs_for = [&](int per_wave) { return (tiles + 4 * per_wave - 1) / (4 * per_wave); };
     int wgs = wgs_for(4);
     if (wgs == 1) return 4;
-    if (wgs_for(1) <= 16 && pairs * wgs_for(1) <= 200) wgs = wgs_for(1);
+    const int most_results = d.H / d.S >= 8 ? 32 : 16;
+    if (wgs_for(1) <= most_results && pairs * wgs_for(1) <= (wgs_for(1) <= 16 ? 200 : 92)) wgs = wgs_for(1);
     else if (pairs * wgs_for(2) <= 160) wgs = wgs_for(2);
     const long most = pairs >= 256 ? 1 : 256 / pairs;
     if (wgs > most) wgs = (int)most;
@@ -552,6 +556,9 @@ hipError_t launch_decode_mla(const DecodeArgs &a, hipStream_t st)
     const unsigned grid = d.B * d.S * (a.splits / 4);
     const bool q8 = a.pool_q8 != nullptr;
     const int tiles = q8 ? (d.m + BN - 1) / BN + (d.k + BN - 1) / BN : (d.m + d.k + BN - 1) / BN, steps = (tiles + a.splits - 1) / a.splits;
+    kp.wgs = a.splits / 4;
+    kp.wgs_magic = kp.wgs > 1 ? (unsigned)((1ull << 32) / (unsigned)kp.wgs + 1) : 0u;      // (exact: several workgroups share a pair only in grids of up to 256)
+    kp.tiles_per_part = steps;
     if (d.dtype == LCA_F16) {
         if (q8) run<_Float16, true>(kp, grid, steps, st);
         else run<_Float16, false>(kp, grid, steps, st);

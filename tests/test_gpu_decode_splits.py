@@ -30,6 +30,10 @@ CASES = [
     ("f16", inputs.MODE_GQA, 2, 513, 8, 2, 16, 600, 5),
     ("bf16", inputs.MODE_MLA, 1, 7000, 16, 1, 16, 9000, 55),        # the merge's fourth group has work, and all of it
     ("f16", inputs.MODE_MLA, 1, 8192, 16, 1, 16, 9000, 64),
+    ("bf16", inputs.MODE_MLA, 1, 1030, 16, 1, 16, 9000, 17),        # one tile per wavefront and more results than 16: the first, the last, and one workgroup too many
+    ("f16", inputs.MODE_MLA, 2, 2048, 16, 1, 16, 9000, 32),
+    ("bf16", inputs.MODE_MLA, 4, 1460, 8, 1, 16, 9000, 23),
+    ("bf16", inputs.MODE_MLA, 4, 1480, 16, 1, 16, 9000, 12),
 ]
 
 
