@@ -7,6 +7,7 @@
 // quantize_narrow_kernel (widths 8 << l, l <= 6: every layer width here): a row's 8-element pieces sit in 1 << l lanes,
 // a wavefront takes 64 >> l rows at once, the row maximum is a reduction over those lanes, the codes leave as one
 // 8-byte store per lane.  quantize_kernel (any other width): one wavefront per row.
+#include "lanes.h"
 #include "lca_internal.h"
 
 namespace lca {
@@ -34,8 +35,7 @@ template <> __device__ __forceinline__ void unpack8<f16_t>(const uint4 &c, float
 
 __device__ __forceinline__ float wave_max(float x)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
+    x = lanes::over_group<64>(x, lanes::Max());
     return x;
 }
 
@@ -122,8 +122,7 @@ __global__ __launch_bounds__(256) void quantize_narrow_kernel(const T *__restric
     float amax = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(f[i]));
-#pragma unroll
-    for (int o = LPR / 2; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+    amax = lanes::over_group<LPR>(amax, lanes::Max());
     const int e = scale_exponent(amax);
 #pragma unroll
     for (int i = 0; i < 8; ++i) f[i] = ldexpf(f[i], -e);               // exact

@@ -55,7 +55,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void cache_update_rows_kernel(const U
         if (mla)
             for (int col = lane; col < d_pool; col += WAVE) a += qbar[col] * Elt<T>::ld(pool + (size_t)r * d_pool + col);
         for (int col = lane; col < d_sel; col += WAVE) a += qbar[(mla ? d_pool : 0) + col] * Elt<T>::ld(sel + (size_t)r * d_sel + col);
-        for (int o = WAVE / 2; o > 0; o >>= 1) a += __shfl_xor(a, o, WAVE);
+        a = lanes::over_group<WAVE>(a, lanes::Sum());
         if (lane == 0) score[i] = a * kp.scale;
     }
     __syncthreads();
@@ -151,23 +151,18 @@ __global__ __launch_bounds__(UPD_WAVES *WAVE) void cache_update_wide_kernel(cons
         }
     }
 #pragma unroll
-    for (int mask = WAVE / 2; mask >= 1; mask >>= 1)
-#pragma unroll
-        for (int i = 0; i < UPD_ROWS; ++i)
-            if (i * UPD_WAVES < g) a[i] += __shfl_xor(a[i], mask, WAVE);
+    for (int i = 0; i < UPD_ROWS; ++i)
+        if (i * UPD_WAVES < g) a[i] = lanes::over_group<WAVE>(a[i], lanes::Sum());
 #pragma unroll
     for (int i = 0; i < UPD_ROWS; ++i)
         if (lane == 0) score[wave + i * UPD_WAVES] = a[i];
     __syncthreads();
     const float mine = lane < g ? kp.scale * score[lane] : -INFINITY;       // lane r: the score of row r
     float bmax;
-    const int top = g <= 1 ? 0 : 1 << (31 - __builtin_clz(g - 1));
     // (a score that is not a number anchors nothing; it does reach the weights, and through them the whole pooled row)
-    const int best = wave_argmax(mine == mine ? mine : -INFINITY, lane, top, &bmax);
+    const int best = wave_argmax(mine == mine ? mine : -INFINITY, &bmax);
     const float p = lane < g ? __expf(mine - bmax) : 0.f;
-    float z = p;
-    for (int mask = top; mask >= 1; mask >>= 1) z += __shfl_xor(z, mask, WAVE);
-    const float alpha = p / readlane_f(z, 0);
+    const float alpha = p / lanes::over_group<WAVE>(p, lanes::Sum());
 
     // pooled component: the weighted rows (Eq. 7), this wavefront's first, then over the wavefronts
     const size_t unit = (size_t)bs * kp.m_cap + (kp.m - 1);

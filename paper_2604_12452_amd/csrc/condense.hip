@@ -39,26 +39,26 @@ __global__ __launch_bounds__(WAVES *WAVE) void summary_query_kernel(const T *__r
 // ---------------------------------------------------------------------------------------------
 // wave helpers
 // ---------------------------------------------------------------------------------------------
-// Sum R per-lane partial values across the wave so that lane l ends with the total of value
+// Sum R <= 8 per-lane partial values across the wave so that lane l ends with the total of value
 // (l >> (6 - log2 R)).  log2(R) halving exchanges, then an all-reduce over the remaining lane bits.
 template <int R>
 __device__ __forceinline__ float wave_reduce_scatter(float (&v)[R], int lane)
 {
-    int mask = 32;
+    // (the lanes whose bit is set keep the second half of the values: what a swap of one register's upper lanes against the other's lower ones leaves in place)
+    if constexpr (R > 1) {
 #pragma unroll
-    for (int n = R; n > 1; n >>= 1, mask >>= 1) {
-        const bool hi = (lane & mask) != 0;
-#pragma unroll
-        for (int i = 0; i < n / 2; ++i) {
-            const float lo_half = v[i], hi_half = v[i + n / 2];      // (values first: a choice between two array elements
-            const float send = hi ? lo_half : hi_half;               // would become an indexed access to the array)
-            const float keep = hi ? hi_half : lo_half;
-            v[i] = keep + __shfl_xor(send, mask, WAVE);
-        }
+        for (int i = 0; i < R / 2; ++i) { lanes::swap32(v[i], v[i + R / 2]); v[i] += v[i + R / 2]; }
     }
-    float x = v[0];
-    for (; mask >= 1; mask >>= 1) x += __shfl_xor(x, mask, WAVE);
-    return x;
+    if constexpr (R > 2) {
+#pragma unroll
+        for (int i = 0; i < R / 4; ++i) { lanes::swap16(v[i], v[i + R / 4]); v[i] += v[i + R / 4]; }
+    }
+    if constexpr (R > 4) {
+        const bool hi = (lane & 8) != 0;
+        const float lo_half = v[0], hi_half = v[1];      // (values first: a choice between two array elements would become an indexed access to the array)
+        v[0] = (hi ? hi_half : lo_half) + lanes::dpp<lanes::ROR + 8>(hi ? lo_half : hi_half);
+    }
+    return lanes::over_group<WAVE / R>(v[0], lanes::Sum());
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -145,9 +145,7 @@ void condense_reg_kernel(const T *__restrict__ POOL, const T *__restrict__ SEL, 
                     for (int e = 0; e < EPC; ++e) ssum = fmaf(f[e], qs[e], ssum);
                 }
             }
-#pragma unroll
-            for (int mask = LPR >> 1; mask >= 1; mask >>= 1) ssum += __shfl_xor(ssum, mask, WAVE);
-            float dot = ssum;
+            float dot = lanes::over_group<LPR>(ssum, lanes::Sum());
             if (MLA) {   // pool part of the score: per-lane partial dots of all rows, reduce-scattered
                 float qp[EPC];
 #pragma unroll
@@ -167,14 +165,8 @@ void condense_reg_kernel(const T *__restrict__ POOL, const T *__restrict__ SEL, 
             const float score = scale * dot;              // row my_row of this sub-block
             if (alpha_dbg != nullptr && sub == 0) alpha_dbg[unit * G + sb * R + my_row] = score;   // normalised below
             // sub-block maximum and its lowest row
-            float bmax = score;
-            int brow = my_row;
-#pragma unroll
-            for (int mask = 32; mask >= LPR; mask >>= 1) {
-                const float os = __shfl_xor(bmax, mask, WAVE);
-                const int orow = __shfl_xor(brow, mask, WAVE);
-                if (os > bmax || (os == bmax && orow < brow)) { bmax = os; brow = orow; }
-            }
+            float bmax;
+            const int brow = wave_argmax(score, &bmax) >> SH;
             if (bmax > best_score) { best_score = bmax; best_row = sb * R + brow; }   // earlier sub-block wins ties
             // online softmax over sub-blocks (Eq. 6) and weighted pooling (Eq. 7)
             const float m_new = fmaxf(m_run, bmax);

@@ -19,6 +19,7 @@
 // copy of the next tile travels while the current one is used; there is no barrier anywhere.  With one wavefront per SIMD
 // every instruction costs its full issue latency, so the summary queries themselves (Algorithm 1, step 1) stay in the small
 // kernel launched in front of this one: computed here, once per workgroup, they took longer than that launch.
+#include "lanes.h"
 #include "lca_internal.h"
 #include "mla_tile16.h"
 
@@ -105,8 +106,7 @@ __global__ __launch_bounds__(256, 1) void condense_mfma_kernel(const CmParams kp
             for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) mx = fmaxf(mx, fmaxf(fabsf(qa[ks][e]), fabsf(qb[ks][e])));
-            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            mx = lanes::across32(lanes::across16(mx, lanes::Max()), lanes::Max());
             // pre = 2^-floor(log2 mx) (1 for a zero query), built from the exponent bits; exact, and so is its reciprocal
             const int biased = (int)((__float_as_uint(mx) >> 23) & 255u);
             const int pre_exp = mx == 0.f ? 127 : min(254, max(1, 254 - biased));
@@ -184,10 +184,12 @@ __global__ __launch_bounds__(256, 1) void condense_mfma_kernel(const CmParams kp
             for (int r = 1; r < 4; ++r)
                 if (lg[r] > tmax) { tmax = lg[r]; te = 4 * r + q4; }
 #pragma unroll
-            for (int mask = 16; mask <= 32; mask <<= 1) {
-                const float os = __shfl_xor(tmax, mask, 64);
-                const int oe = __shfl_xor(te, mask, 64);
-                if (os > tmax || (os == tmax && oe < te)) { tmax = os; te = oe; }
+            for (int mask = 16; mask <= 32; mask <<= 1) {                  // (both lanes of an exchange see the same two pairs, in the same order)
+                float os = tmax, e = __int_as_float(te), oe = e;
+                if (mask == 16) { lanes::swap16(tmax, os); lanes::swap16(e, oe); }
+                else { lanes::swap32(tmax, os); lanes::swap32(e, oe); }
+                te = __float_as_int(e);
+                if (os > tmax || (os == tmax && __float_as_int(oe) < te)) { tmax = os; te = __float_as_int(oe); }
             }
             const bool improved = tmax > best;                  // an earlier tile of the group wins ties
             if (improved) { best = tmax; best_e = tt * BN + te; }
@@ -242,8 +244,7 @@ __global__ __launch_bounds__(256, 1) void condense_mfma_kernel(const CmParams kp
             if (tt != tpg - 1) continue;
 
             // ---- the group is complete: representative j of every set ----
-            float l_tot = l_run + __shfl_xor(l_run, 16, 64);
-            l_tot += __shfl_xor(l_tot, 32, 64);
+            const float l_tot = lanes::across32(lanes::across16(l_run, lanes::Sum()), lanes::Sum());
             const float inv = 1.f / l_tot;
             const int a_tok = j * G + best_e;
             // pooled vectors: accumulator tile t, register r = component 16 t + 4 q4 + r of set `col`; staged in this tile's buffer

@@ -8,6 +8,7 @@
 //   decode_merge_kernel   merges the splits and writes O.
 // The MLA and GQA layer widths have matrix-core kernels of their own (decode_mla.hip, decode_gqa_mfma.hip), which
 // share the merge kernel; decode_split_kernel serves the other instantiated shapes.
+#include "lanes.h"
 #include "lca_internal.h"
 
 namespace lca {
@@ -244,10 +245,7 @@ __global__ __launch_bounds__(MERGE_THREADS *MERGE_GROUPS) void decode_merge_kern
     const float *base = part + (bs * splits * HPS + h) * (size_t)(DP + 2);
     const size_t stride = (size_t)HPS * (DP + 2);
     auto block_reduce = [&](float v, bool is_max) {
-        for (int o = 32; o > 0; o >>= 1) {
-            const float u = __shfl_xor(v, o, WAVE);
-            v = is_max ? fmaxf(v, u) : v + u;
-        }
+        v = is_max ? lanes::over_group<WAVE>(v, lanes::Max()) : lanes::over_group<WAVE>(v, lanes::Sum());
         __syncthreads();                                  // red[] free again
         if ((tid & (WAVE - 1)) == 0) red[tid / WAVE] = v;
         __syncthreads();
@@ -320,13 +318,9 @@ __global__ __launch_bounds__(MERGE_THREADS *GROUPS) void decode_merge_few_kernel
 #pragma unroll
     for (int u = 0; u < SPAN; ++u)
         v[u] = sp0 + u < splits && x < DP ? *reinterpret_cast<const float2 *>(base + 2 + x + (sp0 + u) * stride) : float2{0.f, 0.f};
-    float mx = ml.x;
-#pragma unroll
-    for (int o = WAVE / 2; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, WAVE));
+    const float mx = lanes::over_group<WAVE>(ml.x, lanes::Max());
     const float e = lane < splits ? __expf(ml.x - mx) : 0.f;
-    float l = lane < splits ? ml.y * e : 0.f;
-#pragma unroll
-    for (int o = WAVE / 2; o > 0; o >>= 1) l += __shfl_xor(l, o, WAVE);
+    const float l = lanes::over_group<WAVE>(lane < splits ? ml.y * e : 0.f, lanes::Sum());
     float2 sum = float2{0.f, 0.f};
 #pragma unroll
     for (int u = 0; u < SPAN; ++u)

@@ -15,6 +15,7 @@
 // 2^100 (or, in fp16, an exponential left the type's range and the sum is infinite) the wavefront collects the
 // exact maximum of its range and runs it again.  The four wavefronts' results are merged in LDS into one partial
 // result per workgroup; the workgroups' partial results are merged by decode_merge_kernel.
+#include "lanes.h"
 #include "lca_internal.h"
 
 namespace lca {
@@ -214,8 +215,7 @@ __global__ __launch_bounds__(256, 1) void decode_gqa_mfma_kernel(const DgParams 
         for (int blk = 0; blk < 2; ++blk)
 #pragma unroll
             for (int r = 0; r < 4; ++r) mx = fmaxf(mx, lg[blk][r]);
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        return fmaxf(mx, __shfl_xor(mx, 32, 64));
+        return lanes::across32(lanes::across16(mx, lanes::Max()), lanes::Max());
     };
     // (the queries travel together with the first tile: their latency is paid once, not before the first copy starts)
     bool q_loaded = false;
@@ -297,8 +297,7 @@ __global__ __launch_bounds__(256, 1) void decode_gqa_mfma_kernel(const DgParams 
             }
         });
 
-        l_tot = l_run + __shfl_xor(l_run, 16, 64);
-        l_tot += __shfl_xor(l_tot, 32, 64);
+        l_tot = lanes::across32(lanes::across16(l_run, lanes::Sum()), lanes::Sum());
         if (again || __builtin_amdgcn_ballot_w64(!(l_tot <= SUM_LIMIT)) == 0) break;
         // (wave-uniform) a head ran out of exponent headroom: exact maxima of the range, then the pass again
         m_seen = NEG_BIG;

@@ -17,6 +17,7 @@
 // exponential left the type's range and the sum is infinite) the wavefront collects the exact maximum of its range
 // and runs it again.  The four wavefronts' results (reference, sum, unnormalised output per head) are merged in LDS
 // into one partial result per workgroup; the workgroups' partial results are merged by decode_merge_kernel.
+#include "lanes.h"
 #include "lca_internal.h"
 #include "mla_tile16.h"
 
@@ -277,8 +278,7 @@ __global__ __launch_bounds__(256, 1) void decode_mla_kernel(const DmParams kp)
     };
     auto head_max = [&](const float (&lg)[4]) {
         float mx = fmaxf(fmaxf(fmaxf(lg[0], lg[1]), fmaxf(lg[2], lg[3])), NEG_BIG);
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        return fmaxf(mx, __shfl_xor(mx, 32, 64));
+        return lanes::across32(lanes::across16(mx, lanes::Max()), lanes::Max());
     };
 
     if constexpr (SHARED) {
@@ -331,8 +331,7 @@ __global__ __launch_bounds__(256, 1) void decode_mla_kernel(const DmParams kp)
                 __syncthreads();                                                // the step's tiles and P^T may be overwritten
             });
 
-            float l_tot = l_run + __shfl_xor(l_run, 16, 64);
-            l_tot += __shfl_xor(l_tot, 32, 64);
+            float l_tot = lanes::across32(lanes::across16(l_run, lanes::Sum()), lanes::Sum());
             if (q4 == 0) sum_s[wave][col] = l_tot;
             __syncthreads();
             l_all = (sum_s[0][col] + sum_s[1][col]) + (sum_s[2][col] + sum_s[3][col]);
@@ -413,8 +412,7 @@ __global__ __launch_bounds__(256, 1) void decode_mla_kernel(const DmParams kp)
                 }
             });
 
-            l_tot = l_run + __shfl_xor(l_run, 16, 64);
-            l_tot += __shfl_xor(l_tot, 32, 64);
+            l_tot = lanes::across32(lanes::across16(l_run, lanes::Sum()), lanes::Sum());
             if (again || __builtin_amdgcn_ballot_w64(!(l_tot <= SUM_LIMIT)) == 0) break;
             // (wave-uniform) a head ran out of exponent headroom: exact maxima of the range, then the pass again
             m_seen = NEG_BIG;

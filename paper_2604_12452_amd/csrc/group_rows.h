@@ -1,6 +1,7 @@
 // Pieces shared by the condensation kernels and the online cache update: element conversions, and the rows of one group
 // spread over a wavefront.
 #pragma once
+#include "lanes.h"
 #include "lca_internal.h"
 
 namespace lca {
@@ -73,18 +74,13 @@ __device__ __forceinline__ float readlane_f(float v, int lane)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
-// Lane r holds v_r (r < g <= 2 top, top a power of two); returns, in every lane, the row with the largest v (lowest row on ties).
-__device__ __forceinline__ int wave_argmax(float v, int lane, int top, float *vmax_out)
+// Lane r holds v_r (lanes without a row: -inf); returns the row with the largest v (lowest row on ties; numbers only, row 0 if there is none).
+__device__ __forceinline__ int wave_argmax(float v, float *vmax_out)
 {
-    float bmax = v;
-    int brow = lane;
-    for (int mask = top; mask >= 1; mask >>= 1) {
-        const float os = __shfl_xor(bmax, mask, WAVE);
-        const int orow = __shfl_xor(brow, mask, WAVE);
-        if (os > bmax || (os == bmax && orow < brow)) { bmax = os; brow = orow; }
-    }
-    if (vmax_out) *vmax_out = readlane_f(bmax, 0);
-    return __builtin_amdgcn_readfirstlane(brow);
+    const float vmax = lanes::over_group<WAVE>(v, lanes::Max());
+    if (vmax_out) *vmax_out = vmax;
+    const unsigned long long at = __builtin_amdgcn_ballot_w64(v == vmax);
+    return at != 0 ? __builtin_ctzll(at) : 0;
 }
 
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
@@ -141,10 +137,7 @@ template <typename T, int N> struct Rows {
                     unpack4<T>(held[i0 + i], f);
                     a[i] = c0 < chunks ? term(f, c0 * Elt<T>::EPC) : 0.f;
                 }
-#pragma unroll 1
-                for (int mask = (1 << shift) >> 1; mask >= 1; mask >>= 1)
-#pragma unroll
-                    for (int i = 0; i < BATCH; ++i) a[i] += __shfl_xor(a[i], mask, WAVE);
+                lanes::over_group(a, shift, lanes::Sum());
 #pragma unroll
                 for (int i = 0; i < BATCH; ++i) {
                     const int row = row0 + (i0 + i) * rows_per_load();
@@ -156,25 +149,21 @@ template <typename T, int N> struct Rows {
         }
         for (int r = 0; r < g; r += rows_per_load()) {
             const int row = r + row0;
-            float a = 0.f;
+            float a[1] = {0.f};
             for (int c = c0; c < chunks; c += WAVE) {
                 unpack4<T>(fetch(row, c), f);
-                a += term(f, c * Elt<T>::EPC);
+                a[0] += term(f, c * Elt<T>::EPC);
             }
-            for (int mask = (1 << shift) >> 1; mask >= 1; mask >>= 1) a += __shfl_xor(a, mask, WAVE);
-            if (c0 == 0 && row < g) out[row] = add != nullptr ? add[row] + a : a;
+            lanes::over_group(a, shift, lanes::Sum());
+            if (c0 == 0 && row < g) out[row] = add != nullptr ? add[row] + a[0] : a[0];
         }
     }
     // out = sum of weight[row] * row
     __device__ __forceinline__ void weighted_sum(const float *weight, T *out) const
     {
         constexpr int EPC = Elt<T>::EPC;
-        const int lanes = min((int)WAVE, (g <= 1 ? 1 : 2 << (31 - __builtin_clz(g - 1))) << shift);       // that hold rows of the group
         auto finish = [&](float (&acc)[EPC], int c) {
-#pragma unroll 1
-            for (int mask = 1 << shift; mask < lanes; mask <<= 1)
-#pragma unroll
-                for (int e = 0; e < EPC; ++e) acc[e] += __shfl_xor(acc[e], mask, WAVE);
+            lanes::over_strided(acc, shift, lanes::Sum());                     // (lanes without a row of the group add zeros)
             if (row0 == 0 && c < chunks) *reinterpret_cast<uintx4 *>(out + c * EPC) = pack4<T>(acc);
         };
         float f[EPC], acc[EPC];
@@ -257,10 +246,8 @@ __device__ __forceinline__ void summary_columns(const T *rows, int H, int hps, i
             }
         }
     }
-#pragma unroll
-    for (int mask = SQ_CHUNKS; mask < WAVE; mask <<= 1)
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) acc[e] += __shfl_xor(acc[e], mask, WAVE);
+    static_assert(SQ_CHUNKS == 16, "the four rows of a wavefront are its four groups of 16 lanes");
+    lanes::over_strided(acc, 4, lanes::Sum());
     if ((threadIdx.x & (WAVE - 1)) < SQ_CHUNKS) {
 #pragma unroll
         for (int e = 0; e < EPC; ++e) part[wave][sub][e] = acc[e];
@@ -305,12 +292,9 @@ __device__ __forceinline__ void condense_group(const Rows<T, NP> &pool, const Ro
     __builtin_amdgcn_wave_barrier();
     const float my_score = lane < g ? scale * row_val[lane] : -INFINITY;      // lane r holds the score of row r
     float bmax;
-    const int top = g <= 1 ? 0 : 1 << (31 - __builtin_clz(g - 1));               // lanes 0 .. 2 top - 1 hold the rows
-    const int brow = wave_argmax(my_score, lane, top, &bmax);
+    const int brow = wave_argmax(my_score, &bmax);
     const float pmine = lane < g ? __expf(my_score - bmax) : 0.f;
-    float z = pmine;
-    for (int mask = top; mask >= 1; mask >>= 1) z += __shfl_xor(z, mask, WAVE);
-    const float alpha = pmine / readlane_f(z, 0);
+    const float alpha = pmine / lanes::over_group<WAVE>(pmine, lanes::Sum());
 
     // one component: a weighted sum of the group's rows, or one of them
     auto reduce = [&](auto &rows, int strategy, T *out) {
@@ -318,7 +302,7 @@ __device__ __forceinline__ void condense_group(const Rows<T, NP> &pool, const Ro
         if (strategy == LCA_REDUCE_MAXPOOL) {
             rows.row_sums(square, row_norm, nullptr);
             __builtin_amdgcn_wave_barrier();
-            pick = wave_argmax(lane < g ? row_norm[lane] : -INFINITY, lane, top, nullptr);
+            pick = wave_argmax(lane < g ? row_norm[lane] : -INFINITY, nullptr);
         }
         if (strategy == LCA_REDUCE_MAXSEL || strategy == LCA_REDUCE_MAXPOOL) {
             rows.copy_row(pick, out, lane);
