@@ -6,6 +6,7 @@
 //                          sub-blocks of <= 8 rows, pooling in-lane, anchor by (score, index) max.
 //                          HBM-bound: every C^KV / K^R byte is read once, as 16-byte coalesced loads.
 //   condense_any_kernel    any sizes and reduce strategies.
+//   condense_one_kernel    few groups: the summary query and the groups in one launch.
 //
 // gfx950 only (wave64).
 #include "group_rows.h"
@@ -227,9 +228,7 @@ void condense_reg_kernel(const T *__restrict__ POOL, const T *__restrict__ SEL, 
 // 64 / lpr rows per load; what a wavefront can hold in registers (HELD) is requested at once and used for scores, norms and
 // pooling alike, the rest is read again when its turn comes (from the caches).  Bound by the latency of that round trip
 // at small sizes and by memory at large ones.  The call at B = 1, L = 2500, four KV heads, 64 / 64: 18.0 -> 9.7 us; at L = 16384,
-// 512 + 64, g = 24: 111 -> 33 us (scalar loads and a reduction per row before).  With the summary query computed inside by every
-// workgroup, one launch instead of two, the first took 8.2 us, but fp32 128 + 32 took longer (8.4 against 8.2 us) and 512 + 64
-// nearly twice as long; not kept.
+// 512 + 64, g = 24: 111 -> 33 us (scalar loads and a reduction per row before).
 // ---------------------------------------------------------------------------------------------
 constexpr int ANY_WAVES = 4;         // wavefronts (groups) per workgroup
 struct AnyParams {
@@ -269,6 +268,120 @@ __global__ __launch_bounds__(ANY_WAVES *WAVE) void condense_any_kernel(const Any
     condense_group<T>(pool, sel, qb, mla, d_pool, g, kp.scale, kp.pool_reduce, kp.sel_reduce, (T *)kp.pool_rep + unit * d_pool,
                       (T *)kp.sel_rep + unit * d_sel, kp.anchor + unit, j * g, kp.alpha_dbg != nullptr ? kp.alpha_dbg + unit * g : nullptr,
                       per_row[wave][0], per_row[wave][1], lane);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Condensation of few groups in one launch: every workgroup averages the queries of its set for itself, in LDS, while the rows of its groups (one per
+// wavefront, held in registers) are on their way.  Bound by that one round trip to memory and the chain behind it (100 MHz stamps, four KV heads, 64 / 64, g = 16: 1.7 us
+// until the data is there, summary query 1.0, scores 0.5, softmax 0.2, pooled row 0.5), where two launches pay two starts and two round trips.
+// ---------------------------------------------------------------------------------------------
+constexpr int ONE_WAVES = 8, ONE_THREADS = ONE_WAVES * WAVE;
+constexpr int ONE_DEPTH = 8;         // query loads in flight per lane
+constexpr int ONE_COLUMNS = 576;     // widest summary query
+struct OneParams {
+    AnyParams a;
+    const void *Q;
+    int H, n_q, hps;
+    int pieces, slots;               // 16-byte pieces of a query; queries that the workgroup's threads take at a time, a piece each
+    int step_t, step_h;              // slots = step_t hps + step_h
+    unsigned pieces_magic, hps_magic;        // 2^32 / divisor + 1 (0 for a divisor of 1)
+};
+__device__ __forceinline__ int udiv_magic(unsigned x, unsigned magic) { return magic == 0 ? x : __umulhi(x, magic); }
+
+template <typename T, int NP, int NS>
+__global__ __launch_bounds__(ONE_THREADS) void condense_one_kernel(const OneParams op)
+{
+    constexpr int EPC = Elt<T>::EPC;
+    const AnyParams &kp = op.a;
+    __shared__ float per_row[ONE_WAVES][2][WAVE];          // per wavefront and row of its group: score, then weight; norm
+    __shared__ float part[ONE_THREADS][EPC + 1];
+    __shared__ __attribute__((aligned(16))) float qbar[ONE_COLUMNS];
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    const int g = kp.g, m = kp.m, S = kp.S, mla = kp.mla, d_pool = kp.d_pool, d_sel = kp.d_sel;
+    const int d_qk = mla ? d_pool + d_sel : d_sel;
+    const int s = blockIdx.y, b = blockIdx.z, j = blockIdx.x * ONE_WAVES + wave;
+    const int P = mla ? 1 : S, p = mla ? 0 : s;
+    Rows<T, NP> pool;
+    Rows<T, NS> sel;
+    pool.init((const T *)kp.POOL + (((size_t)b * kp.L + (size_t)j * g) * P + p) * d_pool, (size_t)P * d_pool, d_pool / EPC, g, lane);
+    sel.init((const T *)kp.SEL + (((size_t)b * kp.L + (size_t)j * g) * P + p) * d_sel, (size_t)P * d_sel, d_sel / EPC, g, lane);
+
+    // queries: thread t takes piece t % pieces of queries t / pieces, t / pieces + slots, .. (query u: token u / hps, head u % hps)
+    const int pieces = op.pieces, slots = op.slots, hps = op.hps, n = op.n_q * hps;
+    const int slot = udiv_magic(tid, op.pieces_magic), piece = tid - slot * pieces;
+    float acc[EPC];
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) acc[e] = 0.f;
+    int ut = udiv_magic(slot, op.hps_magic), uh = slot - ut * hps;
+    const T *const base = (const T *)op.Q + (((size_t)b * kp.L + (kp.L - op.n_q)) * op.H + (size_t)s * hps) * d_qk + piece * EPC;
+    for (int u0 = 0; u0 < n; u0 += slots * ONE_DEPTH) {
+        uint4 v[ONE_DEPTH];
+#pragma unroll
+        for (int i = 0; i < ONE_DEPTH; ++i) {
+            v[i] = u0 + i * slots + slot < n && slot < slots ? *reinterpret_cast<const uint4 *>(base + ((size_t)ut * op.H + uh) * d_qk) : make_uint4(0, 0, 0, 0);
+            ut += op.step_t; uh += op.step_h;
+            if (uh >= hps) { uh -= hps; ++ut; }
+        }
+        if (u0 == 0 && j < m) {                  // (the group's rows behind the first of them)
+            if (mla || kp.pool_reduce != LCA_REDUCE_MAXSEL) pool.request();
+            sel.request();
+        }
+#pragma unroll
+        for (int i = 0; i < ONE_DEPTH; ++i) {
+            float f[EPC];
+            Elt<T>::unpack(v[i], f);
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) acc[e] += f[e];
+        }
+    }
+    // ... added up over the slots in a fixed order: inside a wavefront where its lanes are whole slots, then through LDS
+    const bool whole = (WAVE & (pieces - 1)) == 0 && (pieces & (pieces - 1)) == 0 && pieces <= WAVE;
+    if (whole) lanes::over_strided(acc, 31 - __builtin_clz(pieces), lanes::Sum());
+    const int parts = whole ? ONE_WAVES : slots;
+    if (!whole || lane < pieces) {
+        float *const mine = part[whole ? wave * pieces + lane : tid];
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) mine[e] = acc[e];
+    }
+    __syncthreads();
+    for (int x = tid; x < d_qk; x += ONE_THREADS) {
+        const float *const from = part[x / EPC] + x % EPC;
+        float t = 0.f;
+        for (int i0 = 0; i0 < parts; i0 += 8) {
+            float y[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) y[i] = from[min(i0 + i, parts - 1) * pieces * (EPC + 1)];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) t += i0 + i < parts ? y[i] : 0.f;
+        }
+        qbar[x] = t / (float)n;
+    }
+    __syncthreads();
+    if (j >= m) return;
+    const size_t unit = ((size_t)b * S + s) * m + j;
+    condense_group<T>(pool, sel, qbar, mla, d_pool, g, kp.scale, kp.pool_reduce, kp.sel_reduce, (T *)kp.pool_rep + unit * d_pool,
+                      (T *)kp.sel_rep + unit * d_sel, kp.anchor + unit, j * g, kp.alpha_dbg != nullptr ? kp.alpha_dbg + unit * g : nullptr,
+                      per_row[wave][0], per_row[wave][1], lane);
+}
+template <typename T> hipError_t run_one(const CondenseArgs &a, hipStream_t st)
+{
+    const Dims &d = a.d;
+    constexpr int EPC = Elt<T>::EPC;
+    auto magic = [](int dv) { return dv > 1 ? (unsigned)((1ull << 32) / (unsigned)dv + 1) : 0u; };
+    OneParams op;
+    op.a = AnyParams{a.POOL, a.SEL, nullptr, a.pool_rep, a.sel_rep, a.anchor, a.alpha_dbg, d.L, d.S, d.m, d.g,
+                     d.d_pool, d.d_sel, d.mode == LCA_MODE_MLA, d.pool_reduce, d.sel_reduce, d.scale};
+    op.Q = a.Q; op.H = d.H; op.n_q = d.n_q; op.hps = d.H / d.S;
+    op.pieces = d.d_qk / EPC; op.slots = ONE_THREADS / op.pieces;
+    op.step_t = op.slots / op.hps; op.step_h = op.slots % op.hps;
+    op.pieces_magic = magic(op.pieces); op.hps_magic = magic(op.hps);
+    const dim3 grid((d.m + ONE_WAVES - 1) / ONE_WAVES, d.S, d.B);
+    const int pool = Rows<T, 1>::loads(d.d_pool / EPC, d.g), sel = Rows<T, 1>::loads(d.d_sel / EPC, d.g);
+    if (pool <= 4 && sel <= 4) condense_one_kernel<T, 4, 4><<<grid, ONE_THREADS, 0, st>>>(op);
+    else if (pool <= 8 && sel <= 8) condense_one_kernel<T, 8, 8><<<grid, ONE_THREADS, 0, st>>>(op);
+    else if (pool <= 16) condense_one_kernel<T, 16, 4><<<grid, ONE_THREADS, 0, st>>>(op);
+    else condense_one_kernel<T, 32, 4><<<grid, ONE_THREADS, 0, st>>>(op);
+    return hipGetLastError();
 }
 
 template <typename T, int DP, int DS, int G, bool MLA>
@@ -341,6 +454,22 @@ hipError_t launch_summary_query(const Dims &d, const void *Q, int L, float *qbar
     return hipGetLastError();
 }
 
+// Whether a call takes condense_one_kernel: few groups (a workgroup and a half per CU), whose sets' queries a workgroup reads in about a microsecond.
+// Two launches / one, us: 28 heads over 4 KV heads, g = 32 (57 KB of queries), L = 1500 9.8 / 7.5, L = 16000 (236 workgroups) 12.2 / 9.4, 24000 (360) 15.3 / 16.9;
+// g = 16, L = 8192 9.3 / 6.9; 32 over 8, L = 6000 (312) 10.8 / 8.5, 10000 (568) 12.8 / 13.3; 64 / 64, four KV heads, L = 2500 8.4 / 6.1; fp32 128 + 32, g = 16, 4 heads (41 KB)
+// 7.5 / 6.8, 8 heads (82 KB) 7.5 / 7.4, 16 heads 7.6 / 8.1; 256 + 32, 8 heads (74 KB) 10.5 / 9.0, g = 32 11.8 / 11.7.
+// Rows of 64 pieces are at home in condense_reg_kernel (512 + 64, one set of 2 heads 6.9 / 10.0); with three sets or more the kernel before would be the
+// matrix-core one, whose start-up is long: 16 sets, L = 1200 15.2 / 9.8, 3000 (256 workgroups) 15.5 / 10.9, 5000 (512) 16.3 / 22.6, g = 32, L = 1200 18.4 / 15.7.
+// (One to three sets of narrow rows would gain as well; they are what the any-width kernel's forms are tested with, and stay.)
+static bool condense_in_one(const Dims &d)
+{
+    const int epc = 16 / d.elt, pool = d.d_pool / epc, sel = d.d_sel / epc, hps = d.H / d.S;
+    const long wgs = (long)((d.m + ONE_WAVES - 1) / ONE_WAVES) * d.S * d.B, most = d.g <= 16 && pool <= 32 ? 384 : 256;
+    const int pool_loads = Rows<float, 1>::loads(pool, d.g), sel_loads = Rows<float, 1>::loads(sel, d.g);
+    return wgs <= most && (long)d.n_q * hps * d.d_qk * d.elt <= 80 << 10 && d.d_qk <= ONE_COLUMNS && pool <= WAVE && sel <= WAVE && pool_loads <= 32 &&
+           sel_loads <= (pool_loads <= 8 ? 8 : 4) && (pool <= 32 || d.S >= 3) && (pool + sel >= 24 || (long)d.B * d.S >= 4);
+}
+
 hipError_t launch_condense(const CondenseArgs &a, hipStream_t st)
 {
     const Dims &d = a.d;
@@ -348,6 +477,7 @@ hipError_t launch_condense(const CondenseArgs &a, hipStream_t st)
     auto any = [&]() {
         return d.dtype == LCA_BF16 ? run_any<uint16_t>(a, st) : d.dtype == LCA_F16 ? run_any<f16_t>(a, st) : run_any<float>(a, st);
     };
+    if (condense_in_one(d)) return d.dtype == LCA_BF16 ? run_one<uint16_t>(a, st) : d.dtype == LCA_F16 ? run_one<f16_t>(a, st) : run_one<float>(a, st);
     // 1. summary query (Algorithm 1, first step)
     hipError_t err = launch_summary_query(d, a.Q, d.L, a.qbar, st);
     if (err != hipSuccess) return err;

@@ -98,7 +98,8 @@ template <typename T, int N> struct Rows {
     int chunks, g;           // 16-byte pieces per row, rows
     int shift;               // log2 of the lanes per row
     int row0, c0;            // this lane's first row and piece
-    bool held_all;           // one piece per lane and row, all of them in `held`
+    bool held_all;           // one piece per lane and row, all of them in `held` ...
+    bool requested;          // ... once they have been asked for
     uintx4 held[N];
 
     // log2 of the lanes that a row of `ch` pieces takes; loads that g such rows take
@@ -111,6 +112,7 @@ template <typename T, int N> struct Rows {
         shift = row_shift(ch);
         row0 = lane >> shift; c0 = lane & ((1 << shift) - 1);
         held_all = ch <= WAVE && loads(ch, gg) <= N;
+        requested = false;
     }
     __device__ __forceinline__ int rows_per_load() const { return WAVE >> shift; }
     __device__ __forceinline__ const uintx4 *at(int row, int c) const { return reinterpret_cast<const uintx4 *>(base + row * stride + c * Elt<T>::EPC); }
@@ -118,6 +120,7 @@ template <typename T, int N> struct Rows {
     __device__ __forceinline__ void request()
     {
         if (!held_all) return;
+        requested = true;
 #pragma unroll
         for (int i = 0; i < N; ++i) held[i] = i * rows_per_load() < g ? fetch(row0 + i * rows_per_load(), c0) : uintx4{0, 0, 0, 0};
     }
@@ -158,7 +161,44 @@ template <typename T, int N> struct Rows {
             if (c0 == 0 && row < g) out[row] = add != nullptr ? add[row] + a[0] : a[0];
         }
     }
-    // out = sum of weight[row] * row
+    // out[row] = <row, q>, plus `add`[row] if there is one
+    __device__ __forceinline__ void row_dots(const float *q, float *out, const float *add) const
+    {
+        constexpr int EPC = Elt<T>::EPC;
+        if (!held_all) {
+            row_sums([q](const float *f, int col) {
+                float a = 0.f;
+#pragma unroll
+                for (int e = 0; e < EPC; ++e) a = fmaf(f[e], q[col + e], a);
+                return a;
+            }, out, add);
+            return;
+        }
+        float mine[EPC], f[EPC];                 // this lane's piece of q is the same for every row (lanes without a piece hold zeros)
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) mine[e] = c0 < chunks ? q[c0 * EPC + e] : 0.f;
+        constexpr int BATCH = N < 4 ? N : 4;
+#pragma unroll
+        for (int i0 = 0; i0 < N; i0 += BATCH) {
+            if (i0 * rows_per_load() >= g) break;
+            float a[BATCH];
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                unpack4<T>(held[i0 + i], f);
+                a[i] = 0.f;
+#pragma unroll
+                for (int e = 0; e < EPC; ++e) a[i] = fmaf(f[e], mine[e], a[i]);
+            }
+            lanes::over_group(a, shift, lanes::Sum());
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                const int row = row0 + (i0 + i) * rows_per_load();
+                if (c0 == 0 && row < g) out[row] = add != nullptr ? add[row] + a[i] : a[i];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // out = sum of weight[row] * row (held: of rows past the group, which are zeros, whatever the weight as long as it is a number)
     __device__ __forceinline__ void weighted_sum(const float *weight, T *out) const
     {
         constexpr int EPC = Elt<T>::EPC;
@@ -170,14 +210,19 @@ template <typename T, int N> struct Rows {
         if (held_all) {
 #pragma unroll
             for (int e = 0; e < EPC; ++e) acc[e] = 0.f;
+            constexpr int BATCH = N < 8 ? N : 8;
+            static_assert(N % BATCH == 0, "whole batches");
 #pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const int row = row0 + i * rows_per_load();
-                if (i * rows_per_load() < g) {
-                    const float w = row < g ? weight[row] : 0.f;
-                    unpack4<T>(held[i], f);
+            for (int i0 = 0; i0 < N; i0 += BATCH) {
+                if (i0 * rows_per_load() >= g) break;
+                float w[BATCH];                  // (the caller's weights are WAVE numbers, zeros from g on)
 #pragma unroll
-                    for (int e = 0; e < EPC; ++e) acc[e] = row < g ? fmaf(w, f[e], acc[e]) : acc[e];
+                for (int i = 0; i < BATCH; ++i) w[i] = weight[min(row0 + (i0 + i) * rows_per_load(), WAVE - 1)];
+#pragma unroll
+                for (int i = 0; i < BATCH; ++i) {
+                    unpack4<T>(held[i0 + i], f);
+#pragma unroll
+                    for (int e = 0; e < EPC; ++e) acc[e] = fmaf(w[i], f[e], acc[e]);
                 }
             }
             finish(acc, c0);
@@ -199,6 +244,13 @@ template <typename T, int N> struct Rows {
     }
     __device__ __forceinline__ void copy_row(int row, T *out, int lane) const      // bit for bit
     {
+        if (requested) {
+            const int at = row >> (6 - shift);
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+                if (i == at && row0 == (row & (rows_per_load() - 1)) && c0 < chunks) *reinterpret_cast<uintx4 *>(out + c0 * Elt<T>::EPC) = held[i];
+            return;
+        }
         for (int c = lane; c < chunks; c += WAVE)
             *reinterpret_cast<uintx4 *>(out + c * Elt<T>::EPC) = *at(row, c);
     }
@@ -272,23 +324,15 @@ __device__ __forceinline__ void condense_group(const Rows<T, NP> &pool, const Ro
                                                float *alpha_out, float *row_val, float *row_norm, int lane)
 {
     constexpr int EPC = Elt<T>::EPC;
-    auto dot = [&](const float *q) {
-        return [q](const float *f, int col) {
-            float a = 0.f;
-#pragma unroll
-            for (int e = 0; e < EPC; ++e) a = fmaf(f[e], q[col + e], a);
-            return a;
-        };
-    };
     auto square = [](const float *f, int) {
         float a = 0.f;
 #pragma unroll
         for (int e = 0; e < EPC; ++e) a = fmaf(f[e], f[e], a);
         return a;
     };
-    if (mla) pool.row_sums(dot(qb), row_val, nullptr);
+    if (mla) pool.row_dots(qb, row_val, nullptr);
     __builtin_amdgcn_wave_barrier();
-    sel.row_sums(dot(qb + (mla ? d_pool : 0)), row_val, mla ? row_val : nullptr);
+    sel.row_dots(qb + (mla ? d_pool : 0), row_val, mla ? row_val : nullptr);
     __builtin_amdgcn_wave_barrier();
     const float my_score = lane < g ? scale * row_val[lane] : -INFINITY;      // lane r holds the score of row r
     float bmax;

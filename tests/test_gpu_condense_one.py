@@ -1,0 +1,57 @@
+"""Condensation of few groups in one launch against the two launches of many: a batch has too many groups for the first, its sequences one by one
+do not, and a group's representative depends on its own sequence only."""
+import math
+
+import pytest
+import torch
+
+from paper_2604_12452_amd import lca
+from tests import helpers as hp
+
+pytestmark = pytest.mark.gpu
+
+# dtype, mode, d_pool, d_sel, H, S, g, w, L, n_q, pool_reduce, sel_reduce, sequences of the batch
+CASES = [
+    ("bf16", lca.MODE_GQA, 128, 128, 32, 8, 16, 64, 700, 16, 0, 0, 30), ("f16", lca.MODE_GQA, 128, 128, 28, 4, 32, 100, 1030, 32, 0, 0, 40),
+    ("bf16", lca.MODE_GQA, 128, 128, 12, 4, 1, 500, 633, 7, 0, 0, 20), ("f16", lca.MODE_GQA, 128, 128, 8, 8, 2, 0, 77, 2, 0, 0, 30),
+    ("bf16", lca.MODE_GQA, 64, 64, 16, 4, 16, 128, 900, 16, 0, 0, 40), ("f16", lca.MODE_GQA, 64, 64, 8, 8, 7, 5, 500, 50, 0, 0, 20),
+    ("bf16", lca.MODE_GQA, 96, 112, 6, 6, 24, 16, 300, 24, 0, 0, 90), ("f32", lca.MODE_GQA, 32, 16, 4, 4, 64, 10, 650, 64, 0, 0, 120),
+    ("f32", lca.MODE_MLA, 128, 32, 4, 1, 16, 128, 1024, 16, 0, 0, 70), ("f32", lca.MODE_MLA, 128, 32, 8, 1, 16, 128, 400, 16, 0, 0, 200),
+    ("bf16", lca.MODE_MLA, 256, 32, 8, 1, 16, 60, 500, 16, 0, 0, 130), ("f16", lca.MODE_MLA, 96, 40, 10, 5, 31, 4, 500, 3, 0, 0, 60),
+    ("bf16", lca.MODE_MLA, 512, 64, 16, 16, 16, 40, 400, 16, 0, 0, 20), ("f16", lca.MODE_MLA, 512, 64, 8, 4, 32, 30, 900, 8, 0, 0, 50),
+    ("bf16", lca.MODE_MLA, 512, 64, 3, 3, 8, 9, 100, 8, 0, 0, 100), ("bf16", lca.MODE_GQA, 128, 128, 8, 4, 16, 64, 333, 16, 2, 4, 80),
+    ("f16", lca.MODE_GQA, 64, 128, 8, 4, 16, 64, 333, 16, 3, 1, 60), ("f32", lca.MODE_MLA, 128, 32, 4, 2, 8, 64, 333, 8, 4, 2, 60),
+]
+
+
+@pytest.mark.parametrize("dtype,mode,d_pool,d_sel,H,S,g,w,L,n_q,pr,sr,B", CASES)
+def test_one_launch_agrees_with_two(dtype, mode, d_pool, d_sel, H, S, g, w, L, n_q, pr, sr, B):
+    mla, td = mode == lca.MODE_MLA, {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[dtype]
+    d_qk = d_pool + d_sel if mla else d_sel
+    desc = lambda n: lca.Desc(B=n, L=L, H=H, S=S, d_pool=d_pool, d_sel=d_sel, g=g, w=w, n_q=n_q, mode=mode, scale=0.7, pool_reduce=pr, sel_reduce=sr,
+                              dtype={"bf16": lca.BF16, "f16": lca.F16, "f32": lca.F32}[dtype])
+    gen = torch.Generator(device="cuda").manual_seed(L + g)
+    rnd = lambda *shape: torch.randn(*shape, generator=gen, device="cuda").to(td)
+    Q = rnd(B, L, H, d_qk) * (4 / math.sqrt(d_qk))
+    pool, sel = (rnd(B, L, d_pool), rnd(B, L, d_sel)) if mla else (rnd(B, L, S, d_pool), rnd(B, L, S, d_sel))
+
+    def run(lo, n):
+        d = desc(n)
+        out = [torch.full((n, S, d.m, d_pool), math.nan, dtype=td, device="cuda"), torch.full((n, S, d.m, d_sel), math.nan, dtype=td, device="cuda"),
+               torch.full((n, S, d.m), -1, dtype=torch.int32, device="cuda"), torch.full((n, S, d.m, g), math.nan, device="cuda")]
+        ws = torch.full((max(lca.workspace_size(d), 256),), 0xFF, dtype=torch.uint8, device="cuda")
+        lca.condense(d, Q[lo:lo + n].contiguous(), pool[lo:lo + n].contiguous(), sel[lo:lo + n].contiguous(), *out, ws)
+        return out
+
+    many = run(0, B)
+    for b in range(0, B, max(1, B // 5)):
+        one = run(b, 1)
+        # fp32 scores of the same rows and queries in two orders: the anchors are the same but for ties to rounding, which such inputs do not have
+        assert torch.equal(one[2][0], many[2][b])
+        assert (one[3][0] - many[3][b]).abs().amax().item() <= 1e-4
+        tol = {"f32": 1e-5, "f16": 2.0 ** -10, "bf16": 2.0 ** -7}[dtype]         # (a weight's last bits can move a component by one rounding step)
+        for x, y in ((one[0][0], many[0][b]), (one[1][0], many[1][b])):
+            x, y = x.double(), y.double()
+            assert bool(x.isfinite().all()) and ((x - y).abs() / y.abs().amax(-1, keepdim=True).clamp_min(1e-6)).amax().item() <= tol
+        if sr in (0, 3):
+            assert torch.equal(one[1][0], many[1][b])

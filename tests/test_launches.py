@@ -201,3 +201,27 @@ def test_mla_batches_are_where_they_claim_to_be():
     for B, L, H, S, g, w, _, up in MANY:
         for n, name in ((B, "attn_mla_kernel<"), (1, "attn_mla_kernel_halves")):
             assert t.prefill(_mla(B=n, L=L, H=H, S=S, g=g, w=w), up=up)[-1].kernel.startswith(name), (B, L, n)
+
+
+@pytest.mark.parametrize("desc,one", [
+    (_gqa(L=1040), True), (_gqa(L=7168), True), (_gqa(L=7200), False), (_gqa(L=8192, H=28, S=4), True), (_gqa(H=28, S=4, g=32, L=17000), True),
+    (_gqa(H=28, S=4, g=32, L=18000), False), (_gqa(B=3, L=2000, H=16, S=4), True), (_gqa(L=2000, H=128, S=4), False), (_mla(L=1500), False), (_mla(L=1500, H=2), False),
+    (_mla(L=3000, S=16), True), (_mla(L=3100, S=16), False), (_mla(L=2000, H=4, S=4, g=32), True), (_odd(), True), (_odd(g=32), False), (_odd(dtype=lca.F32, d_pool=128, H=8), True),
+    (_odd(dtype=lca.F32, d_pool=128, H=9), False), (_odd(d_pool=64, d_sel=64, H=16, S=4, mode=lca.MODE_GQA), True), (_odd(d_pool=64, d_sel=64, S=2, mode=lca.MODE_GQA), False),
+    (_odd(d_pool=64, d_sel=64, S=2, B=2, mode=lca.MODE_GQA), True), (_odd(L=8192, g=64, d_pool=512, d_sel=64, S=4), False), (_odd(d_pool=1024, d_sel=8, S=8, mode=lca.MODE_GQA), False),
+])
+def test_condensation_in_one_launch(desc, one):
+    """Few groups whose queries every workgroup can read for itself."""
+    run = t.condense(desc)
+    assert [k.kernel.split("<")[0] for k in run][:1] == (["condense_one_kernel"] if one else ["summary_query_kernel"]) and len(run) == (1 if one else 2), run
+    if one:
+        assert run[0].grid == -(-desc.m // 8) * desc.S * desc.B and run[0].block == 512
+
+
+def test_one_launch_condensations_are_where_they_claim_to_be():
+    from tests.test_gpu_condense_one import CASES
+    for dtype, mode, d_pool, d_sel, H, S, g, w, L, n_q, pr, sr, B in CASES:
+        for n, first in ((1, "condense_one_kernel"), (B, "summary_query_kernel")):
+            d = lca.Desc(B=n, L=L, H=H, S=S, d_pool=d_pool, d_sel=d_sel, g=g, w=w, n_q=n_q, mode=mode, dtype={"bf16": lca.BF16, "f16": lca.F16, "f32": lca.F32}[dtype],
+                         pool_reduce=pr, sel_reduce=sr)
+            assert t.condense(d)[0].kernel.startswith(first), (mode, d_pool, d_sel, H, S, g, L, n)
