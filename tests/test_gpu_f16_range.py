@@ -49,3 +49,22 @@ def test_gqa_repeats_from_row_sums(oracle, dtype, rise, w):
     hp.check_prefill(oracle, wl, run, rows, Qf, POOLf, SELf, ref, differ)
     run.dense()
     hp.check_dense(oracle, wl, run, rows, Qf, POOLf, SELf)
+
+
+@pytest.mark.parametrize("B,H", [(1, 4), (3, 16)])                    # pairs of wavefronts per 32 rows; one
+@pytest.mark.parametrize("rise", [13.5, 14.5, 16.3, 17.0, 18.5, 30.0])   # nats: 65504 lies 4 + 16 binades (13.9) above an ordinary reference, 8 + 16 (16.6) above one of few representatives
+def test_mla_references_of_few_representatives(oracle, B, H, rise):
+    """Rows that see 1 to 15 representatives keep more room above the largest of them; whatever rises past it is repeated."""
+    wl = inputs.Workload("few", B=B, L=700, H=H, S=1, d_pool=512, d_sel=64, g=16, w=300, dtype="f16", mode=inputs.MODE_MLA, seed=6)
+    print(f"[case] {wl} rise {rise}", flush=True)
+    Q, POOL, SEL = (inputs.to_f64(x, "f16") for x in inputs.gen_all(wl))
+    Q[..., -1] = 1.0
+    SEL[..., -1] = 0.0
+    SEL[:, (333, 651), ..., -1] = rise
+    Q, POOL, SEL = (inputs.to_storage(x.astype(np.float32), "f16") for x in (Q, POOL, SEL))
+    Qf, POOLf, SELf = (inputs.to_f64(x, "f16") for x in (Q, POOL, SEL))
+    run = hp.GpuRun(wl, Q, POOL, SEL).condense()
+    ref, differ = hp.check_condense(oracle, wl, run, Qf[:, wl.L - wl.nq:], POOLf, SELf)
+    run.prefill()
+    rows = np.arange(0, wl.L, 1 if B == 1 else 5, dtype=np.int32)
+    hp.check_prefill(oracle, wl, run, rows, Qf[:, rows], POOLf, SELf, ref, differ)
