@@ -160,7 +160,7 @@ __global__ __launch_bounds__(UPD_WAVES *WAVE) void cache_update_wide_kernel(cons
     const float mine = lane < g ? kp.scale * score[lane] : -INFINITY;       // lane r: the score of row r
     float bmax;
     // (a score that is not a number anchors nothing; it does reach the weights, and through them the whole pooled row)
-    const int best = wave_argmax(mine == mine ? mine : -INFINITY, &bmax);
+    const int best = wave_argmax(mine == mine ? mine : -INFINITY, g, &bmax);
     const float p = lane < g ? __expf(mine - bmax) : 0.f;
     const float alpha = p / lanes::over_group<WAVE>(p, lanes::Sum());
 

@@ -167,7 +167,7 @@ void condense_reg_kernel(const T *__restrict__ POOL, const T *__restrict__ SEL, 
             if (alpha_dbg != nullptr && sub == 0) alpha_dbg[unit * G + sb * R + my_row] = score;   // normalised below
             // sub-block maximum and its lowest row
             float bmax;
-            const int brow = wave_argmax(score, &bmax) >> SH;
+            const int brow = wave_argmax(score, WAVE, &bmax) >> SH;
             if (bmax > best_score) { best_score = bmax; best_row = sb * R + brow; }   // earlier sub-block wins ties
             // online softmax over sub-blocks (Eq. 6) and weighted pooling (Eq. 7)
             const float m_new = fmaxf(m_run, bmax);

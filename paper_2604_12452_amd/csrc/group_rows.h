@@ -74,12 +74,13 @@ __device__ __forceinline__ float readlane_f(float v, int lane)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
-// Lane r holds v_r (lanes without a row: -inf); returns the row with the largest v (lowest row on ties; numbers only, row 0 if there is none).
-__device__ __forceinline__ int wave_argmax(float v, float *vmax_out)
+// Lane r < rows holds v_r, the others -inf; returns the row with the largest v (lowest row on ties; numbers only, row 0 if there is none).
+__device__ __forceinline__ int wave_argmax(float v, int rows, float *vmax_out)
 {
     const float vmax = lanes::over_group<WAVE>(v, lanes::Max());
     if (vmax_out) *vmax_out = vmax;
-    const unsigned long long at = __builtin_amdgcn_ballot_w64(v == vmax);
+    // (rows only: where no row is a number the maximum is the -inf of the lanes behind them)
+    const unsigned long long at = __builtin_amdgcn_ballot_w64(v == vmax) & (~0ull >> (WAVE - rows));
     return at != 0 ? __builtin_ctzll(at) : 0;
 }
 
@@ -336,7 +337,7 @@ __device__ __forceinline__ void condense_group(const Rows<T, NP> &pool, const Ro
     __builtin_amdgcn_wave_barrier();
     const float my_score = lane < g ? scale * row_val[lane] : -INFINITY;      // lane r holds the score of row r
     float bmax;
-    const int brow = wave_argmax(my_score, &bmax);
+    const int brow = wave_argmax(my_score, g, &bmax);
     const float pmine = lane < g ? __expf(my_score - bmax) : 0.f;
     const float alpha = pmine / lanes::over_group<WAVE>(pmine, lanes::Sum());
 
@@ -346,7 +347,7 @@ __device__ __forceinline__ void condense_group(const Rows<T, NP> &pool, const Ro
         if (strategy == LCA_REDUCE_MAXPOOL) {
             rows.row_sums(square, row_norm, nullptr);
             __builtin_amdgcn_wave_barrier();
-            pick = wave_argmax(lane < g ? row_norm[lane] : -INFINITY, nullptr);
+            pick = wave_argmax(lane < g ? row_norm[lane] : -INFINITY, g, nullptr);
         }
         if (strategy == LCA_REDUCE_MAXSEL || strategy == LCA_REDUCE_MAXPOOL) {
             rows.copy_row(pick, out, lane);

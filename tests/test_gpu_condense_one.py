@@ -5,7 +5,7 @@ import math
 import pytest
 import torch
 
-from paper_2604_12452_amd import lca
+from paper_2604_12452_amd import inputs, lca
 from tests import helpers as hp
 
 pytestmark = pytest.mark.gpu
@@ -55,3 +55,50 @@ def test_one_launch_agrees_with_two(dtype, mode, d_pool, d_sel, H, S, g, w, L, n
             assert bool(x.isfinite().all()) and ((x - y).abs() / y.abs().amax(-1, keepdim=True).clamp_min(1e-6)).amax().item() <= tol
         if sr in (0, 3):
             assert torch.equal(one[1][0], many[1][b])
+
+
+# dtype, mode, d_pool, d_sel, H, S, n_q, sel_reduce, B: one launch twice (held rows fill the registers at g = 16, or not), rows held by the any-width kernel (queries
+# of more than 80 KB), rows that it reads again, the fixed-size kernel
+NAN_CASES = [
+    ("f16", lca.MODE_GQA, 128, 128, 8, 4, 4, 0, 1), ("f32", lca.MODE_MLA, 128, 32, 4, 1, 4, 0, 2), ("bf16", lca.MODE_GQA, 128, 128, 8, 4, 4, lca.REDUCE_MAXPOOL, 1),
+    ("bf16", lca.MODE_GQA, 64, 64, 64, 4, 50, 0, 1), ("f32", lca.MODE_GQA, 520, 32, 4, 2, 4, 0, 1), ("bf16", lca.MODE_GQA, 16, 1024, 4, 2, 4, lca.REDUCE_MAXPOOL, 1),
+    ("bf16", lca.MODE_MLA, 512, 64, 2, 1, 4, 0, 1),
+]
+
+
+@pytest.mark.parametrize("dtype,mode,d_pool,d_sel,H,S,n_q,sr,B", NAN_CASES)
+@pytest.mark.parametrize("g,bad", [(7, [0]), (16, [1, 3]), (33, [32]), (7, range(7)), (16, range(16)), (33, range(33)), (16, None)])
+def test_scores_that_are_not_numbers_anchor_nothing(dtype, mode, d_pool, d_sel, H, S, n_q, sr, B, g, bad):
+    """The anchor is the best of the rows whose score is a number, the first row if none is (rows `bad` of the last group, which ends with the input; None: a query,
+    and with it every score of its set)."""
+    m = max(3, -(-n_q // g))
+    wl = inputs.Workload("nan", B=B, L=m * g, H=H, S=S, d_pool=d_pool, d_sel=d_sel, g=g, w=0, n_q=n_q, dtype=dtype, mode=mode, seed=g)
+    print(f"[case] {wl}", flush=True)
+    td = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(g)
+    rnd = lambda *shape: torch.randn(*shape, generator=gen, device="cuda").to(td)
+    shape = () if mode == lca.MODE_MLA else (S,)
+    Q, pool, sel = rnd(B, m * g, H, wl.d_qk), rnd(B, m * g, *shape, d_pool), rnd(B, m * g, *shape, d_sel)
+    if bad is None:
+        Q[:, -1, 0, -1] = math.nan
+    else:
+        for r in bad:
+            sel[:, (m - 1) * g + r, ..., 1] = math.nan
+    d = hp.lca_desc(wl, sel_reduce=sr)
+    out = [torch.full((B, S, m, d_pool), 7., dtype=td, device="cuda"), torch.full((B, S, m, d_sel), 7., dtype=td, device="cuda"),
+           torch.full((B, S, m), -1, dtype=torch.int32, device="cuda"), None]
+    lca.condense(d, Q, pool, sel, *out, lca.alloc_workspace(d))
+    anchor = out[2].cpu()
+    qbar = Q[:, -n_q:].double().reshape(B, n_q, S, H // S, -1).mean((1, 3))
+    for b in range(B):
+        for s in range(S):
+            p, k = (pool[b], sel[b]) if mode == lca.MODE_MLA else (pool[b, :, s], sel[b, :, s])
+            key = (torch.cat([p, k], -1) if mode == lca.MODE_MLA else k).double()
+            pick = lambda v: int(v.nan_to_num(nan=-math.inf).argmax()) if not v.isnan().all() else 0
+            for j in range(m):
+                rows = slice(j * g, (j + 1) * g)
+                score = key[rows] @ qbar[b, s]
+                assert int(anchor[b, s, j]) == j * g + pick(score)
+                best = pick((k[rows].double() ** 2).sum(-1)) if sr == lca.REDUCE_MAXPOOL else pick(score)
+                torch.testing.assert_close(out[1][b, s, j], k[j * g + best], rtol=0, atol=0, equal_nan=True)
+                assert bool(out[0][b, s, j].isnan().all()) == bool(score.isnan().any())

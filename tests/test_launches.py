@@ -225,3 +225,12 @@ def test_one_launch_condensations_are_where_they_claim_to_be():
             d = lca.Desc(B=n, L=L, H=H, S=S, d_pool=d_pool, d_sel=d_sel, g=g, w=w, n_q=n_q, mode=mode, dtype={"bf16": lca.BF16, "f16": lca.F16, "f32": lca.F32}[dtype],
                          pool_reduce=pr, sel_reduce=sr)
             assert t.condense(d)[0].kernel.startswith(first), (mode, d_pool, d_sel, H, S, g, L, n)
+
+
+def test_cases_without_a_number_are_where_they_claim_to_be():
+    from tests.test_gpu_condense_one import NAN_CASES
+    names = []
+    for dtype, mode, d_pool, d_sel, H, S, n_q, sr, B in NAN_CASES:
+        d = lca.Desc(B=B, L=64, H=H, S=S, d_pool=d_pool, d_sel=d_sel, g=16, w=0, n_q=n_q, mode=mode, sel_reduce=sr, dtype={"bf16": lca.BF16, "f16": lca.F16, "f32": lca.F32}[dtype])
+        names.append(t.condense(d)[-1].kernel.split("<")[0])
+    assert names == ["condense_one_kernel"] * 3 + ["condense_any_kernel"] * 3 + ["condense_reg_kernel"]
