@@ -617,6 +617,7 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
 #pragma unroll
                     for (int ks = 0; ks < NKS; ++ks)
                         sv = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, load_k(ax, 0, ks)), __builtin_bit_cast(f16x8, qf[rb][ks]), sv, 0, 0, 0);
+                    asm volatile("s_nop 15\n\ts_nop 7" : "+v"(sv));        // (row_max is assembly: nobody else waits for the products)
                     st.m_ref[rb] = row_max(sv, c, 0.f) + REF_SHIFT_F16;      // (-1e30 + 4 is -1e30: no number above it, no reference yet)
                 }
                 need_ref = __builtin_amdgcn_ballot_w64((st.m_ref[0] == NEG_BIG) | (st.m_ref[1] == NEG_BIG)) != 0;

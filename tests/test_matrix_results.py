@@ -1,8 +1,10 @@
-"""The tiled attention's listing: no assembly statement is the first to read what a matrix product wrote.  The compiler spaces its own instructions
+"""The listings of the tiled and the GQA attention: no assembly statement is the first to read what a matrix product wrote.  The compiler spaces its own instructions
 behind a product as far as the product's registers need, and nothing before an assembly statement, whose text it does not look at."""
 import os
 import re
 import subprocess
+
+import pytest
 
 from paper_2604_12452_amd import build
 
@@ -46,9 +48,9 @@ def _step(fresh, text):
     return (fresh | written if name.startswith("v_mfma") else fresh - read - written), read & fresh
 
 
-def first_reads_in_assembly(listing):
+def first_reads_in_assembly(listing, own_products=True):
     """Assembly statements of a function that may, on some way through its blocks, be the first to read a register that a matrix product wrote, without a
-    wait of their own in between."""
+    wait of their own in between.  own_products=False: of products that the compiler issues (those that are assembly themselves are spaced by hand)."""
     blocks = _blocks(listing)
     at = {b[0]: i for i, b in enumerate(blocks) if b[0]}
     entry, found, todo = [set() for _ in blocks], [], list(range(len(blocks)))
@@ -57,6 +59,8 @@ def first_reads_in_assembly(listing):
         fresh, last = entry[i], ""
         for text, inside in blocks[i][1]:
             fresh, first = _step(fresh, text)
+            if inside and not own_products and text.startswith("v_mfma"):
+                fresh, first = fresh - set(_registers(re.split(r"[\s,]+", text)[1])), set()
             if inside and first and text not in found:
                 found.append(text)
             last = text
@@ -88,3 +92,14 @@ def test_no_assembly_statement_reads_a_matrix_product_first(tmp_path):
     for name, listing in kernels:
         assert listing.count("v_mfma_f32") >= 16
         assert first_reads_in_assembly(listing) == [], name
+
+
+@pytest.mark.parametrize("form", [[], ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]])        # results where the compiler puts them; in vector registers, as it may
+def test_no_assembly_statement_of_the_gqa_attention_reads_the_compilers_products_first(tmp_path, form):
+    out = tmp_path / "attn_gqa64.s"
+    subprocess.run([build.HIPCC, *[f for f in build.FLAGS if f != "-fPIC"], *form, "-S", "--cuda-device-only", os.path.join(build.CSRC, "attn_gqa64.hip"), "-o", str(out)],
+                   check=True, capture_output=True)
+    kernels = re.findall(r"^(_ZN?\w*attn_gqa64_kernel\w+):(.*?)^\.Lfunc_end", out.read_text(), re.M | re.S)
+    assert len(kernels) == 2
+    for name, listing in kernels:
+        assert first_reads_in_assembly(listing, own_products=False) == [], name
