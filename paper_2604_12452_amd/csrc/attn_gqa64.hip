@@ -32,7 +32,7 @@
 //
 // Softmax uses one fixed reference per row (the first entries the row sees), so O^T is never rescaled and no
 // maxima are taken in the steady state; a row sum that ends beyond 2^90 makes the workgroup run the item again, from the
-// logarithm of the row sums or, where those are not finite, from exact maxima (S^T chains alone).
+// logarithm of the row sums or, where those are not finite or the logits too large, from exact maxima (S^T chains alone).
 #include <type_traits>
 
 #include "lca_internal.h"
@@ -72,6 +72,7 @@ constexpr int GRID = 256;               // most workgroups the persistent kernel
 constexpr int RING = 4;                 // fragments in flight per operand
 constexpr float NEG_BIG = -1.0e30f;
 constexpr float L_LIMIT = 0x1p90f;      // a row sum beyond this (or not finite) makes the workgroup repeat the item
+constexpr float SUM_REF_LIMIT = 0x1p20f;  // a reference from row sums may be this large
 // fp16 ends at 65504: an exponential past it is an infinity in the second product, which no column of its row survives (infinity times a value is an
 // infinity, or no number), so the item is repeated if the row's first accumulator is not finite.  (Keeping the largest exponential instead, one
 // v_max3 per pair, costs a ninth of the vector instructions: the attention alone, in turn on one GPU, 28 heads over 4 KV heads, three times L = 5003 242.6 us so,
@@ -689,14 +690,16 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
             // every wavefront is done with the stages; repeat the item if a row sum ran out of range
             if (!__syncthreads_or(pass == 0 && redo)) break;
             // Where the row sums are finite they bound the maxima well enough: from the logarithm of its sum as reference (in fp16 15 binades below it) a row's exponentials
-            // add up to 1 (2^15) and none can pass the type's limit.  Only a sum that is not finite takes the exact maxima, a pass of its own whose tiles nothing
+            // add up to 1 (2^15) and none can pass the type's limit, as long as the reference is not rounded by as much as the binade that is left (up to 2^20: by 2^-5).  Only a
+            // sum that is not finite, or a larger reference, takes the exact maxima, a pass of its own whose tiles nothing
             // overlaps.  A few repeated items are enough to be what a call waits for (they are among the last ones): fp16, 28 heads over 4 KV heads, three times L = 5003,
             // neighbouring tokens alike, exact maxima / row sums 303 / 272 us, 32 over 8, L = 16000 439 / 410.
             bool unbounded = false;
 #pragma unroll
             for (int rb = 0; rb < 2; ++rb) {
-                unbounded |= !(l_tot[rb] < INFINITY);
-                m_exact[rb] = l_tot[rb] > 0.f ? st.m_ref[rb] + log2f(l_tot[rb]) - (F16 ? 15.f : 0.f) : NEG_BIG;
+                m_exact[rb] = st.m_ref[rb] + log2f(l_tot[rb]) - (F16 ? 15.f : 0.f);
+                if (st.m_ref[rb] == NEG_BIG) m_exact[rb] = NEG_BIG;                // (a row past the end that saw nothing)
+                else unbounded |= !(fabsf(m_exact[rb]) <= SUM_REF_LIMIT);
             }
             if (!__syncthreads_or(unbounded)) {
                 pass = 2;

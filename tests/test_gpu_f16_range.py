@@ -68,3 +68,28 @@ def test_mla_references_of_few_representatives(oracle, B, H, rise):
     run.prefill()
     rows = np.arange(0, wl.L, 1 if B == 1 else 5, dtype=np.int32)
     hp.check_prefill(oracle, wl, run, rows, Qf[:, rows], POOLf, SELf, ref, differ)
+
+
+@pytest.mark.parametrize("base,rise", [(2.0 ** 12, 24.0), (2.0 ** 12, 26.0), (2.0 ** 12, 40.0), (2.0 ** 13, 24.0), (2.0 ** 13, 32.0), (2.0 ** 13, 56.0)])
+@pytest.mark.parametrize("w", [40, 300])
+def test_gqa_repeats_where_a_reference_is_rounded_to_binades(oracle, base, rise, w):
+    """Logits of 2^24 and 2^26 that rise by `rise` nats: the fp32 values a reference can take lie 2 and 8 binades apart there, more than a reference from row sums
+    has room below 65504, so these rows are repeated from exact maxima."""
+    wl = inputs.Workload("binades", B=1, L=700, H=6, S=2, d_pool=128, d_sel=128, g=16, w=w, dtype="f16", mode=inputs.MODE_GQA, seed=7)
+    print(f"[case] {wl} base {base} rise {rise}", flush=True)
+    Q, POOL, SEL = (inputs.to_f64(x, "f16") for x in inputs.gen_all(wl))
+    Q[:] = 0.0
+    Q[..., -1] = base
+    Q[..., -2] = 1.0
+    SEL[:] = 0.0
+    SEL[..., -1] = base
+    SEL[0, (71, 333, 651), ..., -2] = rise
+    Q, POOL, SEL = (inputs.to_storage(x.astype(np.float32), "f16") for x in (Q, POOL, SEL))
+    Qf, POOLf, SELf = (inputs.to_f64(x, "f16") for x in (Q, POOL, SEL))
+    run = hp.GpuRun(wl, Q, POOL, SEL).condense()
+    ref, differ = hp.check_condense(oracle, wl, run, Qf[:, wl.L - wl.nq:], POOLf, SELf)
+    rows = np.arange(wl.L, dtype=np.int32)
+    run.prefill(lse=False)
+    hp.check_prefill(oracle, wl, run, rows, Qf, POOLf, SELf, ref, differ)
+    run.dense(lse=False)
+    hp.check_dense(oracle, wl, run, rows, Qf, POOLf, SELf)
