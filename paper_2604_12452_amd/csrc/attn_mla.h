@@ -60,16 +60,10 @@ constexpr float L_LIMIT = 0x1p90f;      // a row sum beyond this (or not finite)
 // instead took one v_max3 per pair, which no case here shows: L = 8192, 16 heads 317 us either way.  A value that is not finite itself has its rows repeated for nothing.)  The reference sits 4 binades above the first maximum a row sees
 // (first entries at 2^-4): later logits may be 2^19 times larger before that happens, at the price of 4 of fp16's 24
 // binades at the bottom.
+// (A row that sees a few representatives first, a poor sample of its logits, has its item repeated now and then: three times L = 1200, g = 32, 16 heads 95 us, in one
+// call of six to twelve 170-182.  8 binades avoided that, but where the representative is the row's maximum, a group far above a window of ordinary tokens, they took the
+// bits those tokens need: 12 nats above 2048 tokens, a tenth of their size, error 1.7e-2.)
 constexpr float REF_SHIFT_F16 = 4.f;
-// A row whose reference is the largest of fewer than 16 representatives (one, for a row just past its window) has poor knowledge of its logits: with 4 binades one call in six to
-// twelve had an item to repeat, three times the work of the item that it then waits for.  With 8, 2^23 times larger may come, and as the maxima do lie some ten binades above such a
-// reference the exponentials have more of the type's bits, not fewer.  fp16, calls over twelve inputs, 4 / 8: 16 heads, three times L = 1200, g = 32 95-98 us and twice 170-182 / 95-98;
-// three times L = 2759, g = 32, w = 2048, up-projection 381-388 and twice 534 / 381-388; 16 sets, L = 1400, g = 8 52-54 and once 108 / 52-53.  Error against 64 bits the same
-// to four digits.  (Raw tokens first, 16 to 32 of them: 4, as the rows that see no more than those lose bits with 8, 2.257e-4 for 2.256e-4.)
-constexpr float REF_SHIFT_FEW_F16 = 8.f;
-constexpr int FEW_REPS = 16;
-__device__ __forceinline__ constexpr float ref_shift_f16(bool few) { return few ? REF_SHIFT_FEW_F16 : REF_SHIFT_F16; }
-
 // Accumulator register r of lane group G (lanes 32G..32G+31) of a 32x32 tile holds S^T row
 // m = 8*(r/4) + 4G + r%4.  S^T row m is computed from LDS row (= tile entry) pi(m): inside each half of 16,
 // pi(8h + 4G + j) = 4j + 2h + G.

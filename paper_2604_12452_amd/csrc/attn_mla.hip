@@ -390,8 +390,7 @@ __global__ __launch_bounds__(256) void attn_mla_kernel(const MlaParams kp)
                 if (ctl.full == 0) mask_tile(scur, cur, ctl.is_rep != 0, ctl.is_rep ? tl * BN : cur.raw_lo_blk + (tl - cur.n_rep_tiles) * BN, G);
                 if (need_ref) {              // the first visible entries of a row fix its reference
                     const float mx = row_max(scur, c, ctl.bias);
-                    const bool few = ctl.is_rep != 0 && cur.mt_row < FEW_REPS;
-                    st.m_ref = (st.m_ref == NEG_BIG) ? (F16 ? mx + ref_shift_f16(few) : mx) : st.m_ref;    // (-1e30 + 8 is -1e30)
+                    st.m_ref = (st.m_ref == NEG_BIG) ? (F16 ? mx + REF_SHIFT_F16 : mx) : st.m_ref;    // (-1e30 + 4 is -1e30)
                     need_ref = __builtin_amdgcn_ballot_w64(st.m_ref == NEG_BIG) != 0;
                 }
             }

@@ -379,8 +379,7 @@ __global__ __launch_bounds__(256) void attn_mla_kernel_halves(const MlaParams kp
 #pragma unroll
                         for (int b = 0; b < 2; ++b) {
                             const float mx = row_max4(scur[b], c, bias);
-                            const bool few = tl < cur.n_rep_tiles && (b == 0 ? cur.mt_row : mt_row1) < tl * BN + HK * half + FEW_REPS;
-                            st.m_ref[b] = (st.m_ref[b] == NEG_BIG) ? (F16 ? mx + ref_shift_f16(few) : mx) : st.m_ref[b];
+                            st.m_ref[b] = (st.m_ref[b] == NEG_BIG) ? (F16 ? mx + REF_SHIFT_F16 : mx) : st.m_ref[b];
                         }
                         need_ref = __builtin_amdgcn_ballot_w64((st.m_ref[0] == NEG_BIG) | (st.m_ref[1] == NEG_BIG)) != 0;
                     }

@@ -52,9 +52,9 @@ def test_gqa_repeats_from_row_sums(oracle, dtype, rise, w):
 
 
 @pytest.mark.parametrize("B,H", [(1, 4), (3, 16)])                    # pairs of wavefronts per 32 rows; one
-@pytest.mark.parametrize("rise", [13.5, 14.5, 16.3, 17.0, 18.5, 30.0])   # nats: 65504 lies 4 + 16 binades (13.9) above an ordinary reference, 8 + 16 (16.6) above one of few representatives
+@pytest.mark.parametrize("rise", [13.5, 14.5, 16.3, 17.0, 18.5, 30.0])   # nats: 65504 lies 4 + 16 binades (13.9) above the first entries
 def test_mla_references_of_few_representatives(oracle, B, H, rise):
-    """Rows that see 1 to 15 representatives keep more room above the largest of them; whatever rises past it is repeated."""
+    """Rows whose reference comes from 1 to 15 representatives: whatever rises past the room above the largest of them is repeated."""
     wl = inputs.Workload("few", B=B, L=700, H=H, S=1, d_pool=512, d_sel=64, g=16, w=300, dtype="f16", mode=inputs.MODE_MLA, seed=6)
     print(f"[case] {wl} rise {rise}", flush=True)
     Q, POOL, SEL = (inputs.to_f64(x, "f16") for x in inputs.gen_all(wl))
@@ -93,3 +93,25 @@ def test_gqa_repeats_where_a_reference_is_rounded_to_binades(oracle, base, rise,
     hp.check_prefill(oracle, wl, run, rows, Qf, POOLf, SELf, ref, differ)
     run.dense(lse=False)
     hp.check_dense(oracle, wl, run, rows, Qf, POOLf, SELf)
+
+
+@pytest.mark.parametrize("B,H,L,w", [(1, 4, 1300, 1024), (1, 4, 2300, 2048), (3, 16, 1300, 1024), (1, 16, 2300, 2048)])    # pairs of wavefronts per 32 rows, twice; one, twice
+@pytest.mark.parametrize("above", [8.0, 10.5, 12.0, 12.5, 13.0, 14.0])        # nats
+@pytest.mark.parametrize("value", [1.0, 0.1])
+def test_mla_first_group_above_a_window_of_tokens(oracle, B, H, L, w, above, value):
+    """The representative that fixes the reference of a row is the row's maximum, with a window of ordinary tokens far below it whose sum counts."""
+    wl = inputs.Workload("sink", B=B, L=L, H=H, S=1, d_pool=512, d_sel=64, g=16, w=w, dtype="f16", mode=inputs.MODE_MLA, seed=8)
+    print(f"[case] {wl} {above} nats, value {value}", flush=True)
+    Q, POOL, SEL = (inputs.to_f64(x, "f16") for x in inputs.gen_all(wl))
+    Q[:] = 0.0
+    Q[..., -1] = 1.0
+    SEL[:] = 0.0
+    SEL[:, :16, ..., -1] = above
+    POOL[:, :16] *= value
+    Q, POOL, SEL = (inputs.to_storage(x.astype(np.float32), "f16") for x in (Q, POOL, SEL))
+    Qf, POOLf, SELf = (inputs.to_f64(x, "f16") for x in (Q, POOL, SEL))
+    run = hp.GpuRun(wl, Q, POOL, SEL).condense()
+    ref, differ = hp.check_condense(oracle, wl, run, Qf[:, wl.L - wl.nq:], POOLf, SELf)
+    run.prefill()
+    rows = np.arange(w + 15, L, 9, dtype=np.int32)
+    print("  rel err %.3e %.3e" % hp.check_prefill(oracle, wl, run, rows, Qf[:, rows], POOLf, SELf, ref, differ))
