@@ -1,5 +1,5 @@
 // What the two MLA attention kernels share (attn_mla.hip: four wavefronts on 128 (query row, head) pairs; attn_mla_halves.hip: on 64, two for
-// every 32): types, the tile's layout in LDS, the copies, the work item and the tile loop's bookkeeping.
+// every 32): types, the tile's layout in LDS, the direct-to-LDS load and the work item.
 #pragma once
 #include <type_traits>
 
@@ -31,7 +31,6 @@ typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 // fp16 runs through the same code (template parameter F16): fragments travel in the bf16 vector types as plain 16-bit
 // containers, and only the matrix instructions, the two conversions (P^T, output) and the softmax range differ.
-union Pb { bf16x8 v[2]; bf16x2 p[8]; };     // P^T of one tile: the B operands of the two k-steps of the second product
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef int int4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) const char *lds_cptr;
@@ -48,10 +47,6 @@ constexpr int STAGE_BYTES = SEL_OFF + BN * DS * 2;   // 37 376
 constexpr int COPIES_PER_TILE = 9;      // direct-to-LDS loads one wavefront issues per tile (8 latent rows + 1 RoPE block)
 constexpr int NKS = DQK / 16;           // 36 k-steps of S^T
 constexpr int NDV = DV / 32;            // 16 value tiles
-#ifndef LCA_CHAIN_DEPTH
-#define LCA_CHAIN_DEPTH 6
-#endif
-constexpr int CHAIN_DEPTH = LCA_CHAIN_DEPTH;   // key fragments in flight ahead of the S^T chain
 constexpr int DU = 128;                  // UP variant: width of a head's value after the up-projection
 constexpr float NEG_BIG = -1.0e30f;     // stands for -inf in running maxima (keeps exp2 arguments finite)
 constexpr float L_LIMIT = 0x1p90f;      // a row sum beyond this (or not finite) makes the workgroup repeat the item from exact maxima
@@ -64,11 +59,6 @@ constexpr float L_LIMIT = 0x1p90f;      // a row sum beyond this (or not finite)
 // call of six to twelve 170-182.  8 binades avoided that, but where the representative is the row's maximum, a group far above a window of ordinary tokens, they took the
 // bits those tokens need: 12 nats above 2048 tokens, a tenth of their size, error 1.7e-2.)
 constexpr float REF_SHIFT_F16 = 4.f;
-// Accumulator register r of lane group G (lanes 32G..32G+31) of a 32x32 tile holds S^T row
-// m = 8*(r/4) + 4G + r%4.  S^T row m is computed from LDS row (= tile entry) pi(m): inside each half of 16,
-// pi(8h + 4G + j) = 4j + 2h + G.
-__device__ __forceinline__ constexpr int lds_row_of_m(int m) { return (m & 16) + 4 * (m & 3) + 2 * ((m >> 3) & 1) + ((m >> 2) & 1); }
-__device__ __forceinline__ constexpr int acc_entry(int r, int G) { return lds_row_of_m(8 * (r >> 2) + 4 * G + (r & 3)); }
 
 // Tile copies go through raw buffer descriptors (base, size in bytes) so that rows past the end of a segment
 // need no clamping: the hardware range check turns them into zeros (such entries are masked anyway).
@@ -81,13 +71,6 @@ __device__ __forceinline__ Seg make_seg(const void *p, long bytes)
     return Seg{(unsigned)a, (unsigned)(a >> 32) & 0xFFFFu, (unsigned)bytes};
 }
 constexpr int RSRC_WORD3 = 0x00020000;   // raw buffer of dwords, gfx9 layout
-
-// What one wavefront needs to copy its 8 rows of one key tile into one stage (all wavefront-uniform).
-struct CopyCtl {
-    int4v pool_rs, sel_rs;               // descriptors of the latent / RoPE part of the tile's segment
-    unsigned soff_lo, soff_hi, soff_sel; // byte offsets of the wavefront's rows 0 and 4 (latent) and row 0 (RoPE) in the segment
-    unsigned m0_pool, m0_sel;            // LDS addresses of the wavefront's first row in the stage
-};
 
 // One direct-to-LDS load of 64 x 16 bytes: lane l fetches segment bytes [soff + IMM + voff, +16) into LDS bytes
 // [m0 + IMM + 16 l, +16) (the instruction offset moves both sides).  Inline assembly on purpose: the compiler
@@ -106,49 +89,8 @@ __device__ __forceinline__ unsigned lds_address(const void *p)
     return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char *)p;
 }
 
-// One of the 9 copies a wavefront makes per tile: J < 8 moves latent row 8*wave + J (1 KB; LDS rows are RSB
-// apart, the instruction offset (J%4) KB already moves the LDS side by as much), J == 8 moves the RoPE parts
-// of rows 8*wave .. 8*wave+7 (1 KB; lane l fills slot l&7 of local row l>>3 with the chunk the swizzle assigns
-// to that slot: voff_sel = (l>>3)*128 + chunk*16).
-template <int J>
-__device__ __forceinline__ void issue_copy_part(const CopyCtl &c, unsigned voff_pool, unsigned voff_sel)
-{
-    if constexpr (J < 4) dma_1k<J * RSB - J * 1024, J * 1024>(voff_pool, c.pool_rs, c.soff_lo, c.m0_pool);
-    else if constexpr (J < 8) dma_1k<J * RSB - (J - 4) * 1024, (J - 4) * 1024>(voff_pool, c.pool_rs, c.soff_hi, c.m0_pool);
-    else dma_1k<0, 0>(voff_sel, c.sel_rs, c.soff_sel, c.m0_sel);
-}
-template <int J>
-__device__ __forceinline__ void issue_copy_from(const CopyCtl &c, unsigned voff_pool, unsigned voff_sel)
-{
-    if constexpr (J < COPIES_PER_TILE) {
-        issue_copy_part<J>(c, voff_pool, voff_sel);
-        issue_copy_from<J + 1>(c, voff_pool, voff_sel);
-    }
-}
-
-__device__ __forceinline__ void issue_copy_part_dyn(int j, const CopyCtl &c, unsigned voff_pool, unsigned voff_sel)
-{
-    switch (j) {      // j is a constant after unrolling
-    case 0: issue_copy_part<0>(c, voff_pool, voff_sel); break;
-    case 1: issue_copy_part<1>(c, voff_pool, voff_sel); break;
-    case 2: issue_copy_part<2>(c, voff_pool, voff_sel); break;
-    case 3: issue_copy_part<3>(c, voff_pool, voff_sel); break;
-    case 4: issue_copy_part<4>(c, voff_pool, voff_sel); break;
-    case 5: issue_copy_part<5>(c, voff_pool, voff_sel); break;
-    case 6: issue_copy_part<6>(c, voff_pool, voff_sel); break;
-    case 7: issue_copy_part<7>(c, voff_pool, voff_sel); break;
-    default: issue_copy_part<8>(c, voff_pool, voff_sel); break;
-    }
-}
-
-// LDS addresses of this lane's four key fragments of the RoPE part (k-steps 32..35) of a stage: chunk 2j + G of the
-// lane's row sits at slot (2j + G) ^ xs.  `first` = address of the slot of j = 0 (x6 = xs & 6 already applied);
-// slot bits 1..2 are address bits 5..6, which are zero in the row's base address, so j enters as an exclusive or.
+// LDS addresses of this lane's key fragments of the RoPE part of a stage (how many and in which order is the kernel's)
 struct KSel { unsigned a[4]; };
-__device__ __forceinline__ KSel make_ksel(unsigned first)
-{
-    return KSel{{first, first ^ (1u << 5), first ^ (2u << 5), first ^ (3u << 5)}};
-}
 
 template <bool F16>
 __device__ __forceinline__ floatx16 pv_mfma(const bf16x8 &a, const bf16x8 &b, const floatx16 &c)
@@ -156,7 +98,7 @@ __device__ __forceinline__ floatx16 pv_mfma(const bf16x8 &a, const bf16x8 &b, co
     if (F16) return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
-// Everything one wavefront needs to know about one work item = 128 (row, head) pairs of one sequence: BM / heads query rows of
+// Everything one wavefront needs to know about one work item = 128 (or 64) (row, head) pairs of one sequence: as many query rows of
 // each of its heads, which share a condensed set.
 struct Blk {
     int b, h, t0, t_last, t_w0;              // sequence, this wavefront's head, first / last query row of the item, first of the wavefront
@@ -198,135 +140,11 @@ __device__ __forceinline__ Blk make_blk(const MlaParams &kp, int b, int h, int t
     return k;
 }
 
-// Copy of tile tc into stage `sd` (LDS address of stage 0 = lds0).  A tile past the item's last one lies past the
-// end of the raw segment: its copy moves zeros.
-__device__ __forceinline__ CopyCtl make_copy(const Blk &k, int tc, int sd, int wave, unsigned lds0)
-{
-    CopyCtl c;
-    const bool is_rep = tc < k.n_rep_tiles;
-    const Seg &ps = is_rep ? k.rep_pool : k.raw_pool, &ss = is_rep ? k.rep_sel : k.raw_sel;
-    c.pool_rs = int4v{(int)ps.lo, (int)ps.hi, (int)ps.bytes, RSRC_WORD3};
-    c.sel_rs = int4v{(int)ss.lo, (int)ss.hi, (int)ss.bytes, RSRC_WORD3};
-    const unsigned row0 = (is_rep ? tc * BN : k.raw_lo_blk + (tc - k.n_rep_tiles) * BN) + 8 * wave;   // first entry of this wavefront's share
-    c.soff_lo = row0 * (DP * 2);
-    c.soff_hi = c.soff_lo + 4 * (DP * 2);
-    c.soff_sel = row0 * (DS * 2);
-    c.m0_pool = lds0 + sd * STAGE_BYTES + 8 * wave * RSB;
-    c.m0_sel = lds0 + sd * STAGE_BYTES + SEL_OFF + 8 * wave * (DS * 2);
-    return c;
-}
-
-// What iteration tl of the tile loop needs besides the data: the copy of tile tl+3, this lane's read addresses in
-// the stages of the S^T chain (tile tl+1) and of the O^T update (tile tl), and how tile tl is treated.
-struct Ctl {
-    CopyCtl cc;
-    lds_cptr kb, vp0, vp1;  // (vp1: value tiles 8..15, where they are not simply behind the others)
-    KSel ksel;
-    float bias;             // base-2 logit bias of tile tl (representatives may carry one)
-    int is_rep, full;       // tile tl, as masks (-1 / 0): a tile of representatives; every entry visible to every row of this wavefront
-};
-// The same, computed in small steps (STEP 0..8) so that the work can be dealt out over the free issue slots of
-// the O^T update; `t` carries intermediate values from step to step.  The empty assembly statements pin each
-// step's results to its place (the compiler would otherwise gather the steps where their last result is needed).
-struct CtlTmp { int tc, rep_c; unsigned row0, chain_lds, pv_lds; unsigned p0, p1, p2, q0, q1, q2; };
 #define LCA_PIN_S(x) asm volatile("" : "+s"(x))
 #define LCA_PIN_V(x) asm volatile("" : "+v"(x))
 // -1 if a < b, else 0 (|a - b| < 2^31), by scalar arithmetic: a comparison result turned into an integer would travel
 // through a vector register.  Unsigned subtraction so that the compiler cannot turn it back into a comparison.
 __device__ __forceinline__ int lt_mask(int a, int b) { return (int)((unsigned)a - (unsigned)b) >> 31; }
-template <int STEP, bool HALVES>
-__device__ __forceinline__ void ctl_step(Ctl &c, CtlTmp &t, const Blk &k, const MlaParams &kp, int tl, int wave, unsigned lds0, int k_off,
-                                         int ksel_off, int v_off, int v_off1 = 0)
-{
-    if constexpr (STEP == 0) {
-        t.tc = tl + 3;
-        t.rep_c = lt_mask(t.tc, k.n_rep_tiles);
-        c.is_rep = lt_mask(tl, k.n_rep_tiles);
-        LCA_PIN_S(t.rep_c); LCA_PIN_S(c.is_rep);
-    } else if constexpr (STEP == 1) {
-        t.p0 = t.rep_c ? k.rep_pool.lo : k.raw_pool.lo;
-        t.p1 = t.rep_c ? k.rep_pool.hi : k.raw_pool.hi;
-        t.p2 = t.rep_c ? k.rep_pool.bytes : k.raw_pool.bytes;
-        LCA_PIN_S(t.p0); LCA_PIN_S(t.p1); LCA_PIN_S(t.p2);
-    } else if constexpr (STEP == 2) {
-        t.q0 = t.rep_c ? k.rep_sel.lo : k.raw_sel.lo;
-        t.q1 = t.rep_c ? k.rep_sel.hi : k.raw_sel.hi;
-        t.q2 = t.rep_c ? k.rep_sel.bytes : k.raw_sel.bytes;
-        LCA_PIN_S(t.q0); LCA_PIN_S(t.q1); LCA_PIN_S(t.q2);
-    } else if constexpr (STEP == 3) {
-        t.row0 = (t.rep_c ? t.tc * BN : k.raw_lo_blk + (t.tc - k.n_rep_tiles) * BN) + 8 * wave;
-        LCA_PIN_S(t.row0);
-    } else if constexpr (STEP == 4) {
-        c.cc.soff_lo = t.row0 * (DP * 2);
-        c.cc.soff_hi = c.cc.soff_lo + 4 * (DP * 2);
-        c.cc.soff_sel = t.row0 * (DS * 2);
-        LCA_PIN_S(c.cc.soff_lo); LCA_PIN_S(c.cc.soff_hi); LCA_PIN_S(c.cc.soff_sel);
-    } else if constexpr (STEP == 5) {
-        const unsigned sbase = lds0 + ((tl + 3) & (NSTAGE - 1)) * STAGE_BYTES;
-        c.cc.m0_pool = sbase + 8 * wave * RSB;
-        c.cc.m0_sel = sbase + SEL_OFF + 8 * wave * (DS * 2);
-        LCA_PIN_S(c.cc.m0_pool); LCA_PIN_S(c.cc.m0_sel);
-    } else if constexpr (STEP == 6) {
-        // past the last tile the chain runs over a stage that holds zeros or an old tile: S^T that nobody reads
-        t.chain_lds = lds0 + ((tl + 1) & (NSTAGE - 1)) * STAGE_BYTES;
-        t.pv_lds = lds0 + (tl & (NSTAGE - 1)) * STAGE_BYTES;
-        LCA_PIN_S(t.chain_lds); LCA_PIN_S(t.pv_lds);
-    } else if constexpr (STEP == 7) {
-        c.full = lt_mask(tl, k.rep_full_end) | (~lt_mask(tl, k.raw_full_lo) & lt_mask(tl, k.raw_full_hi));
-        LCA_PIN_S(c.full);
-        c.cc.pool_rs = int4v{(int)t.p0, (int)t.p1, (int)t.p2, RSRC_WORD3};
-        c.cc.sel_rs = int4v{(int)t.q0, (int)t.q1, (int)t.q2, RSRC_WORD3};
-    } else {
-        unsigned kb = t.chain_lds + k_off, vp0 = t.pv_lds + v_off;
-        if constexpr (HALVES) {
-            unsigned vp1 = t.pv_lds + v_off1;
-            LCA_PIN_V(vp1);
-            c.vp1 = (lds_cptr)(uintptr_t)vp1;
-            c.ksel.a[0] = t.chain_lds + ksel_off; c.ksel.a[1] = c.ksel.a[0] ^ (1u << 6);
-        } else c.ksel = make_ksel(t.chain_lds + ksel_off);
-        c.bias = c.is_rep ? kp.bias_log2 : 0.f;
-        LCA_PIN_V(kb); LCA_PIN_V(vp0); LCA_PIN_V(c.bias);
-        LCA_PIN_V(c.ksel.a[0]); LCA_PIN_V(c.ksel.a[1]);
-        if constexpr (!HALVES) { LCA_PIN_V(c.ksel.a[2]); LCA_PIN_V(c.ksel.a[3]); }
-        c.kb = (lds_cptr)(uintptr_t)kb; c.vp0 = (lds_cptr)(uintptr_t)vp0;
-    }
-}
-template <bool HALVES>
-__device__ __forceinline__ Ctl make_ctl(const Blk &k, const MlaParams &kp, int tl, int wave, unsigned lds0, int k_off, int ksel_off, int v_off, int v_off1 = 0)
-{
-    Ctl c;
-    CtlTmp t;
-    auto step = [&](auto n) { ctl_step<decltype(n)::value, HALVES>(c, t, k, kp, tl, wave, lds0, k_off, ksel_off, v_off, v_off1); };
-    step(std::integral_constant<int, 0>()); step(std::integral_constant<int, 1>()); step(std::integral_constant<int, 2>());
-    step(std::integral_constant<int, 3>()); step(std::integral_constant<int, 4>()); step(std::integral_constant<int, 5>());
-    step(std::integral_constant<int, 6>()); step(std::integral_constant<int, 7>()); step(std::integral_constant<int, 8>());
-    return c;
-}
-
-// copies of tiles 0..2 of a work item into stages 0..2
-__device__ __forceinline__ void issue_first_copies(const Blk &k, int wave, unsigned lds0, unsigned voff_pool, unsigned voff_sel)
-{
-    for (int tl = 0; tl < 3; ++tl) {
-        const CopyCtl c = make_copy(k, tl, tl, wave, lds0);
-        issue_copy_from<0>(c, voff_pool, voff_sel);
-    }
-}
-
-// Queries of a work item.  The second product wants lane (n, G) to hold Q[row n][16 ks + 8 G .. +7] for every
-// k-step ks, but loading them that way makes every load instruction touch 32 rows = 32 cache lines for 16 bytes
-// each.  So the loads are issued row-wise -- load i = 4c + q: lane l fetches the 16-byte piece l%8 of the 128-byte
-// column block c of row 8q + l/8, eight whole cache lines per instruction -- and q_to_fragments turns the
-// registers into fragments through a private 4 KB LDS buffer, one column block (four k-steps) at a time.
-__device__ __forceinline__ void load_q(const MlaParams &kp, const Blk &k, int wave, int lane, bf16x8 (&qf)[NKS])
-{
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int t = min(k.t_w0 + 8 * q + (lane >> 3), kp.L - 1);
-        const uint16_t *qp = kp.Q + (((size_t)k.b * kp.L + t) * kp.H + k.h) * DQK + (lane & 7) * 8;
-#pragma unroll
-        for (int c = 0; c < NKS / 4; ++c) qf[4 * c + q] = *reinterpret_cast<const bf16x8 *>(qp + c * 64);
-    }
-}
 
 }  // namespace
 }  // namespace lca

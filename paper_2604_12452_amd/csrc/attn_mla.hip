@@ -42,6 +42,18 @@
 namespace lca {
 namespace {
 
+union Pb { bf16x8 v[2]; bf16x2 p[8]; };     // P^T of one tile: the B operands of the two k-steps of the second product
+#ifndef LCA_CHAIN_DEPTH
+#define LCA_CHAIN_DEPTH 6
+#endif
+constexpr int CHAIN_DEPTH = LCA_CHAIN_DEPTH;   // key fragments in flight ahead of the S^T chain
+
+// Accumulator register r of lane group G (lanes 32G..32G+31) of a 32x32 tile holds S^T row
+// m = 8*(r/4) + 4G + r%4.  S^T row m is computed from LDS row (= tile entry) pi(m): inside each half of 16,
+// pi(8h + 4G + j) = 4j + 2h + G.
+__device__ __forceinline__ constexpr int lds_row_of_m(int m) { return (m & 16) + 4 * (m & 3) + 2 * ((m >> 3) & 1) + ((m >> 2) & 1); }
+__device__ __forceinline__ constexpr int acc_entry(int r, int G) { return lds_row_of_m(8 * (r >> 2) + 4 * G + (r & 3)); }
+
 // per-lane softmax state (base-2 logits): reference and running sum over this lane's keys
 struct RowState {
     float m_ref, l_run;
@@ -68,6 +80,48 @@ __device__ __forceinline__ void pv_load_step(PvFrags &f, lds_cptr vp0, int j)
     f.hi[buf][i] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_b64_ptr)(vp + 2 * RSB));
 }
 
+// What one wavefront needs to copy its 8 rows of one key tile into one stage (all wavefront-uniform).
+struct CopyCtl {
+    int4v pool_rs, sel_rs;               // descriptors of the latent / RoPE part of the tile's segment
+    unsigned soff_lo, soff_hi, soff_sel; // byte offsets of the wavefront's rows 0 and 4 (latent) and row 0 (RoPE) in the segment
+    unsigned m0_pool, m0_sel;            // LDS addresses of the wavefront's first row in the stage
+};
+
+// One of the 9 copies a wavefront makes per tile: J < 8 moves latent row 8*wave + J (1 KB; LDS rows are RSB
+// apart, the instruction offset (J%4) KB already moves the LDS side by as much), J == 8 moves the RoPE parts
+// of rows 8*wave .. 8*wave+7 (1 KB; lane l fills slot l&7 of local row l>>3 with the chunk the swizzle assigns
+// to that slot: voff_sel = (l>>3)*128 + chunk*16).
+template <int J>
+__device__ __forceinline__ void issue_copy_part(const CopyCtl &c, unsigned voff_pool, unsigned voff_sel)
+{
+    if constexpr (J < 4) dma_1k<J * RSB - J * 1024, J * 1024>(voff_pool, c.pool_rs, c.soff_lo, c.m0_pool);
+    else if constexpr (J < 8) dma_1k<J * RSB - (J - 4) * 1024, (J - 4) * 1024>(voff_pool, c.pool_rs, c.soff_hi, c.m0_pool);
+    else dma_1k<0, 0>(voff_sel, c.sel_rs, c.soff_sel, c.m0_sel);
+}
+template <int J>
+__device__ __forceinline__ void issue_copy_from(const CopyCtl &c, unsigned voff_pool, unsigned voff_sel)
+{
+    if constexpr (J < COPIES_PER_TILE) {
+        issue_copy_part<J>(c, voff_pool, voff_sel);
+        issue_copy_from<J + 1>(c, voff_pool, voff_sel);
+    }
+}
+
+__device__ __forceinline__ void issue_copy_part_dyn(int j, const CopyCtl &c, unsigned voff_pool, unsigned voff_sel)
+{
+    switch (j) {      // j is a constant after unrolling
+    case 0: issue_copy_part<0>(c, voff_pool, voff_sel); break;
+    case 1: issue_copy_part<1>(c, voff_pool, voff_sel); break;
+    case 2: issue_copy_part<2>(c, voff_pool, voff_sel); break;
+    case 3: issue_copy_part<3>(c, voff_pool, voff_sel); break;
+    case 4: issue_copy_part<4>(c, voff_pool, voff_sel); break;
+    case 5: issue_copy_part<5>(c, voff_pool, voff_sel); break;
+    case 6: issue_copy_part<6>(c, voff_pool, voff_sel); break;
+    case 7: issue_copy_part<7>(c, voff_pool, voff_sel); break;
+    default: issue_copy_part<8>(c, voff_pool, voff_sel); break;
+    }
+}
+
 // S^T chain of one tile (36 MFMAs into `snext`, key fragments prefetched CHAIN_DEPTH deep) and, when SOFTMAX,
 // the vector work that turns the previous tile's S^T (`scur`) into P^T fragments, spread over the
 // chain's issue slots.  `kb` / `ksel` = LDS addresses of this lane's key fragments in the chain's tile (latent part: first one; RoPE part: all four).
@@ -79,6 +133,14 @@ __device__ __forceinline__ void pv_load_step(PvFrags &f, lds_cptr vp0, int j)
 // the explicit wait states are left out: the caller keeps every reader of the chain's result behind MFMAs of
 // the O^T update.
 struct ChainFrags { bf16x8 fr[CHAIN_DEPTH]; };
+
+// LDS addresses of this lane's four key fragments of the RoPE part (k-steps 32..35) of a stage: chunk 2j + G of the
+// lane's row sits at slot (2j + G) ^ xs.  `first` = address of the slot of j = 0 (x6 = xs & 6 already applied);
+// slot bits 1..2 are address bits 5..6, which are zero in the row's base address, so j enters as an exclusive or.
+__device__ __forceinline__ KSel make_ksel(unsigned first)
+{
+    return KSel{{first, first ^ (1u << 5), first ^ (2u << 5), first ^ (3u << 5)}};
+}
 __device__ __forceinline__ bf16x8 chain_frag(lds_cptr kb, const KSel &ksel, int ks)
 {
     // key fragment of k-step ks: latent columns from the row-strided part, RoPE columns (ks >= 32) from the swizzled part
@@ -177,6 +239,123 @@ __device__ __forceinline__ void pv_tail(const PvFrags &f, const Pb &pb, floatx16
     LCA_FENCE();
 }
 
+// Copy of tile tc into stage `sd` (LDS address of stage 0 = lds0).  A tile past the item's last one lies past the
+// end of the raw segment: its copy moves zeros.
+__device__ __forceinline__ CopyCtl make_copy(const Blk &k, int tc, int sd, int wave, unsigned lds0)
+{
+    CopyCtl c;
+    const bool is_rep = tc < k.n_rep_tiles;
+    const Seg &ps = is_rep ? k.rep_pool : k.raw_pool, &ss = is_rep ? k.rep_sel : k.raw_sel;
+    c.pool_rs = int4v{(int)ps.lo, (int)ps.hi, (int)ps.bytes, RSRC_WORD3};
+    c.sel_rs = int4v{(int)ss.lo, (int)ss.hi, (int)ss.bytes, RSRC_WORD3};
+    const unsigned row0 = (is_rep ? tc * BN : k.raw_lo_blk + (tc - k.n_rep_tiles) * BN) + 8 * wave;   // first entry of this wavefront's share
+    c.soff_lo = row0 * (DP * 2);
+    c.soff_hi = c.soff_lo + 4 * (DP * 2);
+    c.soff_sel = row0 * (DS * 2);
+    c.m0_pool = lds0 + sd * STAGE_BYTES + 8 * wave * RSB;
+    c.m0_sel = lds0 + sd * STAGE_BYTES + SEL_OFF + 8 * wave * (DS * 2);
+    return c;
+}
+
+// What iteration tl of the tile loop needs besides the data: the copy of tile tl+3, this lane's read addresses in
+// the stages of the S^T chain (tile tl+1) and of the O^T update (tile tl), and how tile tl is treated.
+struct Ctl {
+    CopyCtl cc;
+    lds_cptr kb, vp0;
+    KSel ksel;
+    float bias;             // base-2 logit bias of tile tl (representatives may carry one)
+    int is_rep, full;       // tile tl, as masks (-1 / 0): a tile of representatives; every entry visible to every row of this wavefront
+};
+// The same, computed in small steps (STEP 0..8) so that the work can be dealt out over the free issue slots of
+// the O^T update; `t` carries intermediate values from step to step.  The empty assembly statements pin each
+// step's results to its place (the compiler would otherwise gather the steps where their last result is needed).
+struct CtlTmp { int tc, rep_c; unsigned row0, chain_lds, pv_lds; unsigned p0, p1, p2, q0, q1, q2; };
+template <int STEP>
+__device__ __forceinline__ void ctl_step(Ctl &c, CtlTmp &t, const Blk &k, const MlaParams &kp, int tl, int wave, unsigned lds0, int k_off,
+                                         int ksel_off, int v_off)
+{
+    if constexpr (STEP == 0) {
+        t.tc = tl + 3;
+        t.rep_c = lt_mask(t.tc, k.n_rep_tiles);
+        c.is_rep = lt_mask(tl, k.n_rep_tiles);
+        LCA_PIN_S(t.rep_c); LCA_PIN_S(c.is_rep);
+    } else if constexpr (STEP == 1) {
+        t.p0 = t.rep_c ? k.rep_pool.lo : k.raw_pool.lo;
+        t.p1 = t.rep_c ? k.rep_pool.hi : k.raw_pool.hi;
+        t.p2 = t.rep_c ? k.rep_pool.bytes : k.raw_pool.bytes;
+        LCA_PIN_S(t.p0); LCA_PIN_S(t.p1); LCA_PIN_S(t.p2);
+    } else if constexpr (STEP == 2) {
+        t.q0 = t.rep_c ? k.rep_sel.lo : k.raw_sel.lo;
+        t.q1 = t.rep_c ? k.rep_sel.hi : k.raw_sel.hi;
+        t.q2 = t.rep_c ? k.rep_sel.bytes : k.raw_sel.bytes;
+        LCA_PIN_S(t.q0); LCA_PIN_S(t.q1); LCA_PIN_S(t.q2);
+    } else if constexpr (STEP == 3) {
+        t.row0 = (t.rep_c ? t.tc * BN : k.raw_lo_blk + (t.tc - k.n_rep_tiles) * BN) + 8 * wave;
+        LCA_PIN_S(t.row0);
+    } else if constexpr (STEP == 4) {
+        c.cc.soff_lo = t.row0 * (DP * 2);
+        c.cc.soff_hi = c.cc.soff_lo + 4 * (DP * 2);
+        c.cc.soff_sel = t.row0 * (DS * 2);
+        LCA_PIN_S(c.cc.soff_lo); LCA_PIN_S(c.cc.soff_hi); LCA_PIN_S(c.cc.soff_sel);
+    } else if constexpr (STEP == 5) {
+        const unsigned sbase = lds0 + ((tl + 3) & (NSTAGE - 1)) * STAGE_BYTES;
+        c.cc.m0_pool = sbase + 8 * wave * RSB;
+        c.cc.m0_sel = sbase + SEL_OFF + 8 * wave * (DS * 2);
+        LCA_PIN_S(c.cc.m0_pool); LCA_PIN_S(c.cc.m0_sel);
+    } else if constexpr (STEP == 6) {
+        // past the last tile the chain runs over a stage that holds zeros or an old tile: S^T that nobody reads
+        t.chain_lds = lds0 + ((tl + 1) & (NSTAGE - 1)) * STAGE_BYTES;
+        t.pv_lds = lds0 + (tl & (NSTAGE - 1)) * STAGE_BYTES;
+        LCA_PIN_S(t.chain_lds); LCA_PIN_S(t.pv_lds);
+    } else if constexpr (STEP == 7) {
+        c.full = lt_mask(tl, k.rep_full_end) | (~lt_mask(tl, k.raw_full_lo) & lt_mask(tl, k.raw_full_hi));
+        LCA_PIN_S(c.full);
+        c.cc.pool_rs = int4v{(int)t.p0, (int)t.p1, (int)t.p2, RSRC_WORD3};
+        c.cc.sel_rs = int4v{(int)t.q0, (int)t.q1, (int)t.q2, RSRC_WORD3};
+    } else {
+        unsigned kb = t.chain_lds + k_off, vp0 = t.pv_lds + v_off;
+        c.ksel = make_ksel(t.chain_lds + ksel_off);
+        c.bias = c.is_rep ? kp.bias_log2 : 0.f;
+        LCA_PIN_V(kb); LCA_PIN_V(vp0); LCA_PIN_V(c.bias);
+        LCA_PIN_V(c.ksel.a[0]); LCA_PIN_V(c.ksel.a[1]); LCA_PIN_V(c.ksel.a[2]); LCA_PIN_V(c.ksel.a[3]);
+        c.kb = (lds_cptr)(uintptr_t)kb; c.vp0 = (lds_cptr)(uintptr_t)vp0;
+    }
+}
+__device__ __forceinline__ Ctl make_ctl(const Blk &k, const MlaParams &kp, int tl, int wave, unsigned lds0, int k_off, int ksel_off, int v_off)
+{
+    Ctl c;
+    CtlTmp t;
+    auto step = [&](auto n) { ctl_step<decltype(n)::value>(c, t, k, kp, tl, wave, lds0, k_off, ksel_off, v_off); };
+    step(std::integral_constant<int, 0>()); step(std::integral_constant<int, 1>()); step(std::integral_constant<int, 2>());
+    step(std::integral_constant<int, 3>()); step(std::integral_constant<int, 4>()); step(std::integral_constant<int, 5>());
+    step(std::integral_constant<int, 6>()); step(std::integral_constant<int, 7>()); step(std::integral_constant<int, 8>());
+    return c;
+}
+
+// copies of tiles 0..2 of a work item into stages 0..2
+__device__ __forceinline__ void issue_first_copies(const Blk &k, int wave, unsigned lds0, unsigned voff_pool, unsigned voff_sel)
+{
+    for (int tl = 0; tl < 3; ++tl) {
+        const CopyCtl c = make_copy(k, tl, tl, wave, lds0);
+        issue_copy_from<0>(c, voff_pool, voff_sel);
+    }
+}
+
+// Queries of a work item.  The second product wants lane (n, G) to hold Q[row n][16 ks + 8 G .. +7] for every
+// k-step ks, but loading them that way makes every load instruction touch 32 rows = 32 cache lines for 16 bytes
+// each.  So the loads are issued row-wise -- load i = 4c + q: lane l fetches the 16-byte piece l%8 of the 128-byte
+// column block c of row 8q + l/8, eight whole cache lines per instruction -- and q_to_fragments turns the
+// registers into fragments through a private 4 KB LDS buffer, one column block (four k-steps) at a time.
+__device__ __forceinline__ void load_q(const MlaParams &kp, const Blk &k, int wave, int lane, bf16x8 (&qf)[NKS])
+{
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int t = min(k.t_w0 + 8 * q + (lane >> 3), kp.L - 1);
+        const uint16_t *qp = kp.Q + (((size_t)k.b * kp.L + t) * kp.H + k.h) * DQK + (lane & 7) * 8;
+#pragma unroll
+        for (int c = 0; c < NKS / 4; ++c) qf[4 * c + q] = *reinterpret_cast<const bf16x8 *>(qp + c * 64);
+    }
+}
 // `buf`: 4 KB of LDS private to this wavefront.  Piece p of row r sits at r*128 + ((p ^ (r>>1)) & 7)*16, which makes
 // the row-wise writes and the fragment reads (16 lanes = 16 rows, one piece each) free of bank conflicts.  LDS
 // operations of one wavefront run in order, so the reads of one block need no wait before the next block's writes.
@@ -383,7 +562,7 @@ __global__ __launch_bounds__(256) void attn_mla_kernel(const MlaParams kp)
         scur = snext;
         int tl0 = 0;
         asm volatile("" : "+s"(tl0));        // (opaque: with a known zero the compiler turns the flag arithmetic of make_ctl back into comparisons)
-        Ctl ctl = make_ctl<false>(cur, kp, tl0, wave, lds0, k_off, ksel_off, v_off);
+        Ctl ctl = make_ctl(cur, kp, tl0, wave, lds0, k_off, ksel_off, v_off);
 
         for (int tl = 0; tl < cur.n_tiles; ++tl) {
             if (__builtin_expect((ctl.full == 0) | need_ref, 0)) {      // rare: boundary tiles, and the first tiles of an item
@@ -411,15 +590,15 @@ __global__ __launch_bounds__(256) void attn_mla_kernel(const MlaParams kp)
                 if (j >= 4 && j < 20) asm volatile("v_mov_b32 %0, %1" : "=v"(scur[j - 4]) : "v"(snext[j - 4]));
                 // the bookkeeping of iteration tl+1, a few instructions per MFMA
                 switch (j) {
-                case 1: ctl_step<0, false>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
-                case 3: ctl_step<1, false>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
-                case 5: ctl_step<2, false>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
-                case 7: ctl_step<3, false>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
-                case 9: ctl_step<4, false>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
-                case 11: ctl_step<5, false>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
-                case 13: ctl_step<6, false>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
-                case 15: ctl_step<7, false>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
-                case 21: ctl_step<8, false>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
+                case 1: ctl_step<0>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
+                case 3: ctl_step<1>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
+                case 5: ctl_step<2>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
+                case 7: ctl_step<3>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
+                case 9: ctl_step<4>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
+                case 11: ctl_step<5>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
+                case 13: ctl_step<6>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
+                case 15: ctl_step<7>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
+                case 21: ctl_step<8>(nx, tmp, cur, kp, tl + 1, wave, lds0, k_off, ksel_off, v_off); break;
                 default: break;
                 }
             });
