@@ -40,11 +40,12 @@ __global__ __launch_bounds__(WAVES *WAVE) void summary_query_kernel(const T *__r
 // ---------------------------------------------------------------------------------------------
 // wave helpers
 // ---------------------------------------------------------------------------------------------
-// Sum R <= 8 per-lane partial values across the wave so that lane l ends with the total of value
+// Sum R (1, 2, 4 or 8) per-lane partial values across the wave so that lane l ends with the total of value
 // (l >> (6 - log2 R)).  log2(R) halving exchanges, then an all-reduce over the remaining lane bits.
 template <int R>
 __device__ __forceinline__ float wave_reduce_scatter(float (&v)[R], int lane)
 {
+    static_assert(R == 1 || R == 2 || R == 4 || R == 8, "three halving exchanges are written out");
     // (the lanes whose bit is set keep the second half of the values: what a swap of one register's upper lanes against the other's lower ones leaves in place)
     if constexpr (R > 1) {
 #pragma unroll
