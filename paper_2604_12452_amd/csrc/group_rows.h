@@ -177,7 +177,11 @@ template <typename T, int N> struct Rows {
         }
         float mine[EPC], f[EPC];                 // this lane's piece of q is the same for every row (lanes without a piece hold zeros)
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) mine[e] = c0 < chunks ? q[c0 * EPC + e] : 0.f;
+        for (int e = 0; e < EPC; ++e) mine[e] = 0.f;
+        if (c0 < chunks) {                       // (one branch around all of them: a choice per element left 4-byte loads, eight for two; 128 + 32, eight sets, g = 4, L = 5634 20.9 / 12.7 us)
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) mine[e] = q[c0 * EPC + e];
+        }
         constexpr int BATCH = N < 4 ? N : 4;
 #pragma unroll
         for (int i0 = 0; i0 < N; i0 += BATCH) {
