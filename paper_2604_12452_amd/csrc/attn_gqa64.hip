@@ -81,11 +81,13 @@ constexpr float SUM_REF_LIMIT = 0x1p20f;  // a reference from row sums may be th
 // binades at the bottom.
 constexpr float REF_SHIFT_F16 = 4.f;
 constexpr int FEW_REPS = 16;            // fp16: with fewer visible representatives an item starts with its raw tokens (make_blk)
-// ... and a row's reference is the largest logit of this many tokens, evenly spread over those that every row of the item sees (a few neighbouring tokens, alike
-// as they are, made one item in a hundred repeat, and those are among the last of a call): fp16, neighbouring tokens alike, 28 heads over 4 KV heads, three times
-// L = 5003 first entries / sample 279 / 260 us, 32 over 8, L = 16000 424 / 403 (bf16, which repeats nothing: 246 and 383); where nothing is repeated either way
-// the sample's copy and 16 MFMAs cost an item 0.3 us (three times L = 1000, w = 512 46.8 / 47.3, L = 5003, g = 32 246.8 / 248.2).
+// ... and a row's reference is the largest logit of this many tokens, evenly spread over those that every row of the item sees: a few neighbouring tokens, alike
+// as they are, made one item in a hundred repeat, and those are among the last of a call.  fp16, three sequences of such tokens, mean of 40 inputs, first entries / sample:
+// 28 heads over 4 KV heads, L = 1600 74.7 / 72.2 us, 2400 117 / 114, w = 2048 153 / 140, L = 5003, g = 32 308 / 297; 32 over 8, L = 2400 174 / 126, L = 5003 304 / 304
+// (w = 1024, g = 16 where nothing else is said).  The sample's copy and its 16 MFMAs cost an item 0.6 us, so that items of the first SAMPLE_FROM tokens of a sequence
+// without representatives, which do not repeat, go without (L = 150 12.8 / 13.4 us, 700 23.0 / 23.7).
 constexpr int NSAMPLE = 32;
+constexpr int SAMPLE_FROM = 1024;
 constexpr int RSRC_WORD3 = 0x00020000;  // raw buffer of dwords, gfx9 layout
 
 struct G64Params {
@@ -425,8 +427,8 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
     floatx16 acc[2][NDV];
     RowState st;
     char *const qbuf = &stages[3][0] + wave * (32 * RB);
-    // How far apart the sampled tokens of an item are: over those that every row of it sees; 0: too few, or nothing to sample
-    auto sample_step = [&](const Blk &k) { return k.flip ? max(0, k.t0 + 1 - k.mt_blk_hi * kp.g) / NSAMPLE : 0; };
+    // How far apart the sampled tokens of an item are: over those that every row of it sees; 0: too few, or no sample
+    auto sample_step = [&](const Blk &k) { return k.flip && (k.mt_blk_hi > 0 || k.t0 >= SAMPLE_FROM) ? max(0, k.t0 + 1 - k.mt_blk_hi * kp.g) / NSAMPLE : 0; };
     auto issue_first_copies = [&](const Blk &k, bool with_sample) {
         if (F16 && with_sample && sample_step(k) > 0) {
             const unsigned step = sample_step(k) * k.raw_stride, first = (unsigned)(k.mt_blk_hi * kp.g) * k.raw_stride + 4 * wave * step;

@@ -115,3 +115,19 @@ def test_mla_first_group_above_a_window_of_tokens(oracle, B, H, L, w, above, val
     run.prefill()
     rows = np.arange(w + 15, L, 9, dtype=np.int32)
     print("  rel err %.3e %.3e" % hp.check_prefill(oracle, wl, run, rows, Qf[:, rows], POOLf, SELf, ref, differ))
+
+
+@pytest.mark.parametrize("L", [1024, 1025, 1130, 1300])               # items from row 1024 on take their references from a sample, also without representatives
+@pytest.mark.parametrize("rise", [10.0, 14.5, 30.0, 95.0])
+def test_gqa_references_around_the_first_sampled_item(oracle, L, rise):
+    wl = inputs.Workload("from", B=1, L=L, H=4, S=2, d_pool=128, d_sel=128, g=16, w=2048, dtype="f16", mode=inputs.MODE_GQA, seed=9)
+    print(f"[case] {wl} rise {rise}", flush=True)
+    Q, POOL, SEL = (inputs.to_f64(x, "f16") for x in inputs.gen_all(wl))
+    Q[..., -1] = 1.0
+    SEL[..., -1] = 0.0
+    SEL[0, (64, 517, L - 3), ..., -1] = rise                          # (64: one of the sample of the items from 1024 on; 517: of none)
+    Q, POOL, SEL = (inputs.to_storage(x.astype(np.float32), "f16") for x in (Q, POOL, SEL))
+    rows = np.arange(896, L, dtype=np.int32)
+    run = hp.GpuRun(wl, Q, POOL, SEL).dense()
+    Qf, POOLf, SELf = (inputs.to_f64(a, "f16") for a in (Q, POOL, SEL))
+    hp.check_dense(oracle, wl, run, rows, Qf[:, rows], POOLf, SELf)
