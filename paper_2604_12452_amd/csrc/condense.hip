@@ -459,14 +459,16 @@ hipError_t launch_summary_query(const Dims &d, const void *Q, int L, float *qbar
 // Two launches / one, us: 28 heads over 4 KV heads, g = 32 (57 KB of queries), L = 1500 9.8 / 7.5, L = 16000 (236 workgroups) 12.2 / 9.4, 24000 (360) 15.3 / 16.9;
 // g = 16, L = 8192 9.3 / 6.9; 32 over 8, L = 6000 (312) 10.8 / 8.5, 10000 (568) 12.8 / 13.3; 64 / 64, four KV heads, L = 2500 8.4 / 6.1; fp32 128 + 32, g = 16, 4 heads (41 KB)
 // 7.5 / 6.8, 8 heads (82 KB) 7.5 / 7.4, 16 heads 7.6 / 8.1; 256 + 32, 8 heads (74 KB) 10.5 / 9.0, g = 32 11.8 / 11.7.
+// Groups of one load per component leave a workgroup little beside the queries: one workgroup per CU (128 / 128, one KV head, g = 4, twice L = 4283, 268 workgroups 6.8 / 7.4;
+// 96 / 96, two, L = 6084, 350 workgroups 7.3 / 8.0; 128 / 128, one, L = 5452, 167 workgroups 7.1 / 5.8).
 // Rows of 64 pieces are at home in condense_reg_kernel (512 + 64, one set of 2 heads 6.9 / 10.0); with three sets or more the kernel before would be the
 // matrix-core one, whose start-up is long: 16 sets, L = 1200 15.2 / 9.8, 3000 (256 workgroups) 15.5 / 10.9, 5000 (512) 16.3 / 22.6, g = 32, L = 1200 18.4 / 15.7.
 // (One to three sets of narrow rows would gain as well; they are what the any-width kernel's forms are tested with, and stay.)
 static bool condense_in_one(const Dims &d)
 {
     const int epc = 16 / d.elt, pool = d.d_pool / epc, sel = d.d_sel / epc, hps = d.H / d.S;
-    const long wgs = (long)((d.m + ONE_WAVES - 1) / ONE_WAVES) * d.S * d.B, most = d.g <= 16 && pool <= 32 ? 384 : 256;
     const int pool_loads = Rows<float, 1>::loads(pool, d.g), sel_loads = Rows<float, 1>::loads(sel, d.g);
+    const long wgs = (long)((d.m + ONE_WAVES - 1) / ONE_WAVES) * d.S * d.B, most = d.g <= 16 && pool <= 32 && pool_loads + sel_loads > 2 ? 384 : 256;
     return wgs <= most && (long)d.n_q * hps * d.d_qk * d.elt <= 80 << 10 && d.d_qk <= ONE_COLUMNS && pool <= WAVE && sel <= WAVE && pool_loads <= 32 &&
            sel_loads <= (pool_loads <= 8 ? 8 : 4) && (pool <= 32 || d.S >= 3) && (pool + sel >= 24 || (long)d.B * d.S >= 4);
 }
