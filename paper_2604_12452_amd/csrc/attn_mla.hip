@@ -731,25 +731,31 @@ bool attn_mla_supported(const Dims &d)
 
 size_t attn_mla_up_workspace_bytes(const Dims &d) { return attn_mla_supported(d) ? (size_t)d.H * DU * DV * 2 : 0; }
 
-// Whether a call's items are few enough for attn_mla_halves.hip, which has two for each of them and half as long.  While there is a CU for each of
+// Whether a call's items are few enough for attn_mla_halves.hip, which has two for each of them and half as long.  While there is a CU of their XCD for each of
 // the two it is the faster form whatever their length (attention alone, 16 heads, bf16, this kernel / halves: L = 100 14.5 / 11.9 us, 300 21.2 / 16.1, 1000 47.1 /
-// 33.3; 8 heads, L = 2000 52.7 / 38.2).  In the second round of a workgroup its items are taken from the other end of the list (heaviest first), so the
-// call lasts as long as its longest item or the two in the middle of the list with an item change between them (ten tiles' worth), at 0.75 us a tile where the
+// 33.3; 8 heads, L = 2000 52.7 / 38.2; 64 heads, L = 140 17.1 / 14.9).  In the second round of a workgroup its items are taken from the other end of the list (heaviest
+// first), so the call lasts as long as its longest item or the two in the middle of the list with an item change between them (ten tiles' worth), at 0.75 us a tile where the
 // undivided item takes 1.1: 16 heads, L = 1250 52.4 / 39.1, 1500 54.3 / 45.2, 1600 55.3 / 49.8, 1750 58.4 / 57.1, two sequences of 1000 53.6 / 46.2, three of 400 27.3 /
 // 24.4, but L = 2000 63.1 / 69.4, 3000 110 / 126; 8 heads, L = 2500 55.2 / 45.7, 3000 59.1 / 66.8.  With every CU at work the clock falls, and the larger items, whose
-// tiles are copied half as often, win.
-static bool mla_halves(const Dims &d, int dense, const MlaParams &kp, long cus)
+// tiles are copied half as often, win.  A row block's heads stay on one XCD (its CUs hold 32 half items): of 64 heads and more a second round is another
+// whole row block, or the same one (128 heads, L = 40 16.7 / 21.4, L = 104 20.1 / 25.1; 64 heads, L = 308 23.3 / 25.0).  With the up-projection, of 64 heads and more one
+// XCD reads 8 MB of matrices for each row block, and nothing is won by twice the workgroups that do (64 heads, fp16, L = 30 25.9 / 27.9, 217 36.3 / 38.4; bf16, L = 102 31.5 / 31.5,
+// 288 40.8 / 48.4).
+static bool mla_halves(const Dims &d, int dense, const MlaParams &kp, bool up, long cus)
 {
-    const long units = (long)kp.n_qb * d.B, per_unit = 2l * (d.H >> kp.hw_log2);
-    if (units * per_unit <= cus) return true;
-    if (units * per_unit > 2 * cus) return false;
+    const long units = (long)kp.n_qb * d.B, per_unit = 2l * (d.H >> kp.hw_log2), slots = cus / 8;
+    const int run = kp.run_log2;
+    const long list = (((units - 1) >> (run + 3)) + 1) * (per_unit << run);          // half items of an XCD
+    if (up && d.H >= 64) return false;
+    if (list <= slots) return true;
+    if (list > 2 * slots || per_unit >= slots) return false;
     auto visible = [&](long t) { return dense || t + 1 <= d.w ? 0l : (t + 1 - d.w) / d.g; };
-    auto tiles = [&](long item) {                 // of the list's item
+    auto tiles = [&](long unit) {
         const int rows = BM >> kp.hw_log2;
-        const long t0 = (kp.n_qb - 1 - item / per_unit / d.B) * rows, t1 = t0 + rows < d.L ? t0 + rows : d.L;
+        const long t0 = (kp.n_qb - 1 - unit / d.B) * rows, t1 = t0 + rows < d.L ? t0 + rows : d.L;
         return (visible(t1 - 1) + BN - 1) / BN + (t1 - visible(t0) * d.g + BN - 1) / BN;
     };
-    return 2 * (2 * tiles(cus) + 10) <= 3 * tiles(0);
+    return 2 * (2 * tiles((slots / per_unit) << (run + 3)) + 10) <= 3 * tiles(0);     // (the first row block that some XCD has in its second round)
 }
 
 hipError_t launch_attn_mla(const AttnArgs &a, hipStream_t st)
@@ -791,7 +797,7 @@ hipError_t launch_attn_mla(const AttnArgs &a, hipStream_t st)
     const long cus = persistent_grid();
     long grid = items < cus ? items : cus;
     grid = (grid + 7) / 8 * 8;
-    const bool halves = mla_halves(d, a.dense, kp, cus);
+    const bool halves = mla_halves(d, a.dense, kp, a.W_up != nullptr, cus);
     kp.W_up = nullptr;
     if (a.W_up != nullptr) {
         // the matrices in fragment order, in the caller's workspace (2 MB for 16 heads; microseconds)

@@ -196,6 +196,17 @@ def test_mla_items_halved_while_they_are_few(desc, halves, up):
     assert run.grid == min(256, items) and run.block == 256
 
 
+@pytest.mark.parametrize("desc,halves", [
+    (_mla(H=64, L=1), True), (_mla(H=64, L=256), True), (_mla(H=64, L=257), False), (_mla(H=64, B=8, L=32), True), (_mla(H=64, B=9, L=32), False), (_mla(H=128, L=1), False),
+    (_mla(H=32, L=512), True), (_mla(H=32, L=900), True), (_mla(H=32, L=900, w=64), False), (_mla(H=6, S=2, B=2, L=1024), True), (_mla(H=6, S=2, B=2, L=1188, w=64, g=32), False), (_mla(H=66, L=50), False),
+])
+@pytest.mark.parametrize("up", [False, True])
+def test_mla_items_halved_while_an_xcd_has_cus_for_them(desc, halves, up):
+    """The heads of a row block are one XCD's; with the up-projection no more than 63 of them."""
+    run = t.prefill(desc, up=up)[-1]
+    assert run.kernel.startswith("attn_mla_kernel_halves" if halves and not (up and desc.H >= 64) else "attn_mla_kernel<"), run
+
+
 def test_mla_batches_are_where_they_claim_to_be():
     from tests.test_gpu_item_rounds import MANY
     for B, L, H, S, g, w, _, up in MANY:
