@@ -85,9 +85,10 @@ constexpr int FEW_REPS = 16;            // fp16: with fewer visible representati
 // as they are, made one item in a hundred repeat, and those are among the last of a call.  fp16, three sequences of such tokens, mean of 40 inputs, first entries / sample:
 // 28 heads over 4 KV heads, L = 1600 74.7 / 72.2 us, 2400 117 / 114, w = 2048 153 / 140, L = 5003, g = 32 308 / 297; 32 over 8, L = 2400 174 / 126, L = 5003 304 / 304
 // (w = 1024, g = 16 where nothing else is said).  The sample's copy and its 16 MFMAs cost an item 0.6 us, so that items of the first SAMPLE_FROM tokens of a sequence
-// without representatives, which do not repeat, go without (L = 150 12.8 / 13.4 us, 700 23.0 / 23.7).
+// without representatives, which do not repeat, go without (L = 150 12.8 / 13.4 us, 700 23.0 / 23.7), and items of a short window, whose first tile is a good part of
+// it (w = 128, L = 377 14.8 / 15.2).
 constexpr int NSAMPLE = 32;
-constexpr int SAMPLE_FROM = 1024;
+constexpr int SAMPLE_FROM = 1024, SAMPLE_SPAN = 256;
 constexpr int RSRC_WORD3 = 0x00020000;  // raw buffer of dwords, gfx9 layout
 
 struct G64Params {
@@ -416,8 +417,8 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
 
     // A slot's items: one of every n_slots neighbours of the list, every other time counted from the other end, so that whoever has the heaviest
     // of one round has the lightest of the next.  With the same end every time / so, one sequence, bf16: 32 heads over 8 KV heads, L = 2500 (320 items on 256
-    // CUs) 53.7 / 42.6 us, 28 over 4, L = 5003 93.8 / 83.1; three sequences, fp16: 32 over 8, L = 1000 47.9 / 37.8, 28 over 4, L = 5003, g = 32 251 / 241;
-    // one round or many (L = 65536, 32 items per CU) 2734 / 2730.
+    // CUs) 53.7 / 42.6 us, 28 over 4, L = 5003 93.8 / 83.1; three sequences, fp16: 32 over 8, L = 1000 46.5 / 36.3, 28 over 4, L = 5003, g = 32
+    // 256 / 243 on inputs without a repeated item, 303 / 295 on the mean of 40 inputs; one round or many (L = 65536, 32 items per CU) 2734 / 2730.
     auto in_round = [&](int r) { return r * n_slots + ((r & 1) ? n_slots - 1 - slot : slot); };
     int round = 0, kidx = slot, iu, iqb;
     if (!item(kidx, iu, iqb)) return;
@@ -428,7 +429,10 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
     RowState st;
     char *const qbuf = &stages[3][0] + wave * (32 * RB);
     // How far apart the sampled tokens of an item are: over those that every row of it sees; 0: too few, or no sample
-    auto sample_step = [&](const Blk &k) { return k.flip && (k.mt_blk_hi > 0 || k.t0 >= SAMPLE_FROM) ? max(0, k.t0 + 1 - k.mt_blk_hi * kp.g) / NSAMPLE : 0; };
+    auto sample_step = [&](const Blk &k) {
+        const int span = k.t0 + 1 - k.mt_blk_hi * kp.g;
+        return k.flip && span >= SAMPLE_SPAN && (k.mt_blk_hi > 0 || k.t0 >= SAMPLE_FROM) ? span / NSAMPLE : 0;
+    };
     auto issue_first_copies = [&](const Blk &k, bool with_sample) {
         if (F16 && with_sample && sample_step(k) > 0) {
             const unsigned step = sample_step(k) * k.raw_stride, first = (unsigned)(k.mt_blk_hi * kp.g) * k.raw_stride + 4 * wave * step;
