@@ -246,3 +246,14 @@ def test_cases_without_a_number_are_where_they_claim_to_be():
         d = lca.Desc(B=B, L=64, H=H, S=S, d_pool=d_pool, d_sel=d_sel, g=16, w=0, n_q=n_q, mode=mode, sel_reduce=sr, dtype={"bf16": lca.BF16, "f16": lca.F16, "f32": lca.F32}[dtype])
         names.append(t.condense(d)[-1].kernel.split("<")[0])
     assert names == ["condense_one_kernel"] * 3 + ["condense_any_kernel"] * 3 + ["condense_reg_kernel"]
+
+
+def test_cases_of_many_items_are_where_they_claim_to_be():
+    from tests.test_gpu_many_items import GROUPS, MLA
+    for B, L, H, S, g, w, dtype, scale, bias, ties, up in MLA:
+        d = _mla(B=B, L=L, H=H, S=S, g=g, w=w, dtype={"bf16": lca.BF16, "f16": lca.F16}[dtype])
+        for kw in (dict(up=True),) if up else (dict(), dict(dense=True)):
+            assert t.prefill(d, **kw)[-1].kernel.startswith("attn_mla_kernel<"), (B, L, H)
+    for kernel, dtype, mode, d_pool, d_sel, H, S, g, w, L, B, n_q, scale, ties in GROUPS:
+        d = lca.Desc(B=B, L=L, H=H, S=S, d_pool=d_pool, d_sel=d_sel, g=g, w=w, n_q=n_q, mode=mode, dtype={"bf16": lca.BF16, "f16": lca.F16, "f32": lca.F32}[dtype])
+        assert kernel in t.condense(d)[-1].kernel, (L, g, t.condense(d))
