@@ -463,14 +463,16 @@ hipError_t launch_summary_query(const Dims &d, const void *Q, int L, float *qbar
 // 96 / 96, two, L = 6084, 350 workgroups 7.3 / 8.0; 128 / 128, one, L = 5452, 167 workgroups 7.1 / 5.8).
 // Rows of 64 pieces are at home in condense_reg_kernel (512 + 64, one set of 2 heads 6.9 / 10.0); with three sets or more the kernel before would be the
 // matrix-core one, whose start-up is long: 16 sets, L = 1200 15.2 / 9.8, 3000 (256 workgroups) 15.5 / 10.9, 5000 (512) 16.3 / 22.6, g = 32, L = 1200 18.4 / 15.7.
-// (One to three sets of narrow rows would gain as well; they are what the any-width kernel's forms are tested with, and stay.)
+// One to three sets of narrow rows have few workgroups of little work: two launches / one over 340 random calls of groups of 8 and more 1.097 to 1.26 by the group size (64 / 64,
+// one KV head, g = 32, L = 2574 7.4 / 5.7), but smaller groups, whose summary query is short too, are even (g = 2 1.025, g = 4 1.065) and some slower (96 / 80, g = 4, L = 194
+// 5.9 / 6.2; g = 2, L = 108 5.9 / 6.3): two launches.
 static bool condense_in_one(const Dims &d)
 {
     const int epc = 16 / d.elt, pool = d.d_pool / epc, sel = d.d_sel / epc, hps = d.H / d.S;
     const int pool_loads = Rows<float, 1>::loads(pool, d.g), sel_loads = Rows<float, 1>::loads(sel, d.g);
     const long wgs = (long)((d.m + ONE_WAVES - 1) / ONE_WAVES) * d.S * d.B, most = d.g <= 16 && pool <= 32 && pool_loads + sel_loads > 2 ? 384 : 256;
     return wgs <= most && (long)d.n_q * hps * d.d_qk * d.elt <= 80 << 10 && d.d_qk <= ONE_COLUMNS && pool <= WAVE && sel <= WAVE && pool_loads <= 32 &&
-           sel_loads <= (pool_loads <= 8 ? 8 : 4) && (pool <= 32 || d.S >= 3) && (pool + sel >= 24 || (long)d.B * d.S >= 4);
+           sel_loads <= (pool_loads <= 8 ? 8 : 4) && (pool <= 32 || d.S >= 3) && (pool + sel >= 24 || (long)d.B * d.S >= 4 || d.g >= 8);
 }
 
 hipError_t launch_condense(const CondenseArgs &a, hipStream_t st)

@@ -64,7 +64,7 @@ GROUPS = [
     ("condense_mfma_kernel", "bf16", inputs.MODE_MLA, 512, 64, 32, 16, 16, 64, 900, 3, 0, 0.04, True),
     ("condense_any_kernel", "f16", inputs.MODE_GQA, 64, 64, 8, 4, 8, 5, 1620, 4, 0, 1.0, False), ("condense_any_kernel", "bf16", inputs.MODE_GQA, 128, 128, 8, 4, 5, 0, 1100, 4, 9, 3.0, False),
     ("condense_reg_kernel", "f32", inputs.MODE_MLA, 128, 32, 4, 1, 16, 128, 1024, 60, 0, 1.0, False), ("condense_any_kernel", "bf16", inputs.MODE_GQA, 96, 112, 6, 6, 24, 16, 1500, 6, 0, 1.0, True),
-    ("condense_any_kernel", "f16", inputs.MODE_GQA, 32, 64, 8, 8, 1, 3, 500, 1, 0, 0.04, False), ("condense_any_kernel", "bf16", inputs.MODE_MLA, 256, 32, 8, 2, 64, 7, 9000, 8, 0, 1.0, False),
+    ("condense_any_kernel", "f32", inputs.MODE_MLA, 8, 4, 6, 1, 64, 0, 200, 300, 50, 1.0, False), ("condense_any_kernel", "f16", inputs.MODE_GQA, 32, 64, 8, 8, 1, 3, 500, 1, 0, 0.04, False), ("condense_any_kernel", "bf16", inputs.MODE_MLA, 256, 32, 8, 2, 64, 7, 9000, 8, 0, 1.0, False),
     ("condense_reg_kernel", "bf16", inputs.MODE_GQA, 128, 128, 16, 8, 16, 0, 3300, 2, 0, 1.0, False), ("condense_reg_kernel", "f16", inputs.MODE_GQA, 128, 128, 14, 2, 32, 100, 9000, 4, 0, 3.0, True),
 ]
 

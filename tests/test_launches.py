@@ -81,8 +81,8 @@ def test_rows_that_see_few_entries_are_taken_one_by_one(kw, most):
     (dict(d_pool=1024, d_sel=1024, g=1, mode=lca.MODE_GQA, dtype=lca.F32), "1, 1"),      # (more pieces than lanes: nothing is held)
 ])
 def test_any_width_condensation_by_rows_held(kw, held):
-    """The form of the any-width kernel whose registers hold the group's rows, and no more."""
-    run = t.condense(_odd(L=1000, **kw))
+    """The form of the any-width kernel whose registers hold the group's rows, and no more (of a batch with too many groups for one launch)."""
+    run = t.condense(_odd(L=1000, B=400, **kw))
     assert run[1].kernel.startswith("condense_any_kernel") and run[1].kernel.endswith(held + ">")
 
 
@@ -218,7 +218,8 @@ def test_mla_batches_are_where_they_claim_to_be():
     (_gqa(L=1040), True), (_gqa(L=7168), True), (_gqa(L=7200), False), (_gqa(L=8192, H=28, S=4), True), (_gqa(H=28, S=4, g=32, L=17000), True),
     (_gqa(H=28, S=4, g=32, L=18000), False), (_gqa(B=3, L=2000, H=16, S=4), True), (_gqa(L=2000, H=128, S=4), False), (_mla(L=1500), False), (_mla(L=1500, H=2), False),
     (_mla(L=3000, S=16), True), (_mla(L=3100, S=16), False), (_mla(L=2000, H=4, S=4, g=32), True), (_odd(), True), (_odd(g=32), False), (_odd(dtype=lca.F32, d_pool=128, H=8), True),
-    (_odd(dtype=lca.F32, d_pool=128, H=9), False), (_odd(d_pool=64, d_sel=64, H=16, S=4, mode=lca.MODE_GQA), True), (_odd(d_pool=64, d_sel=64, S=2, mode=lca.MODE_GQA), False),
+    (_odd(dtype=lca.F32, d_pool=128, H=9), False), (_odd(d_pool=64, d_sel=64, H=16, S=4, mode=lca.MODE_GQA), True), (_odd(d_pool=64, d_sel=64, S=2, mode=lca.MODE_GQA), True),
+    (_odd(d_pool=64, d_sel=64, S=2, g=8, mode=lca.MODE_GQA), True), (_odd(d_pool=64, d_sel=64, S=2, g=7, mode=lca.MODE_GQA), False), (_odd(d_pool=64, d_sel=64, S=4, g=7, mode=lca.MODE_GQA), True),
     (_gqa(H=8, S=1, g=4, w=0, L=8192), True), (_gqa(H=8, S=1, g=4, w=0, L=8196), False), (_gqa(H=8, S=1, g=5, w=0, L=10240), True),
     (_odd(d_pool=64, d_sel=64, S=2, B=2, mode=lca.MODE_GQA), True), (_odd(L=8192, g=64, d_pool=512, d_sel=64, S=4), False), (_odd(d_pool=1024, d_sel=8, S=8, mode=lca.MODE_GQA), False),
 ])
