@@ -502,9 +502,10 @@ bool decode_mla_supported(const Dims &d)
 // Wavefronts per (sequence, set), a multiple of 4 (a workgroup's, which leave one partial result): four tiles for each, where
 // the cache is long enough to fill the chip that way, never more workgroups than CUs (a second round costs as much as the
 // first).  A short or lonely cache is bound by the chain of tiles a wavefront works through: two tiles for each while the
-// workgroups stay below 160, one while they stay below 200 and the merge has few results to add (16 of 33 KB), or up to 32 results where there are fewer than
-// 92 workgroups and eight heads or more (8 heads, B = 1, L = 4001 10.1 / 9.2 us, 8-bit 10.8 / 9.6; with fewer it would pay as well, H = 4 9.7 / 8.6, but those widths keep
-// the two-tile ranges that the tests of two steps are made of).  Measured with the wavefronts of a workgroup sharing its tiles (step with merge, 16 heads, 16 bits; four / two / one tile each): B = 1, L = 700 13.8 /
+// workgroups stay below 160, one while they stay below 200 and the merge has few results to add: 16 of a full set of heads (33 KB each), or 48 where there are
+// fewer than 92 workgroups or fewer than eight heads.  (Two / one tile each at 17 to 48 results: 1 to 7 heads, up to 200 workgroups, 91 random calls 1.01 to 1.16, H = 4, B = 1, 20 results
+// 9.8 / 8.7 us, B = 8, 20 9.4 / 8.9, B = 4, 48 10.3 / 9.9; beyond 48 the gain ends, 7 heads, B = 2, 64 1.01, B = 3 1.00.  8 to 12 heads up to 92 workgroups 1.02 to 1.11, beyond from
+// 1.07 to 0.95; 16 heads, B = 1, 36 1.08, 48 1.02, 56 1.00, B = 2, 40 (80 workgroups) 1.02, B = 4, 24 (96) 0.98, B = 8, 24 0.92.)  Measured with the wavefronts of a workgroup sharing its tiles (step with merge, 16 heads, 16 bits; four / two / one tile each): B = 1, L = 700 13.8 /
 // 10.7 / 9.7 us, L = 4001 14.3 / 11.1 / 10.4, L = 16000 14.1 / 11.5 / 11.1, L = 131072 16.1 / 14.9 / 17.1; two / one: B = 2, L = 8000 11.7 / 10.8 (46 workgroups), B = 4,
 // L = 4001 11.7 / 11.4 (76), L = 8000 11.8 / 11.7 (92), but B = 3, L = 16000 11.9 / 12.0 (93), B = 6, L = 4001 11.9 / 11.9 (114), B = 8, L = 4001 12.5 / 12.8 (152); B = 16,
 // L = 4001 15.9 / 14.1 / 15.7; B = 32, L = 700 15.9 / 14.4 / 18.1 (96, 192, 352 workgroups), L = 1500 17.3 / 20.7 / 20.6; B = 150, L = 20000 96 us with two workgroups
@@ -519,8 +520,7 @@ int decode_mla_parts(const Dims &d)
     auto wgs_for = [&](int per_wave) { return (tiles + 4 * per_wave - 1) / (4 * per_wave); };
     int wgs = wgs_for(4);
     if (wgs == 1) return 4;
-    const int most_results = d.H / d.S >= 8 ? 32 : 16;
-    if (wgs_for(1) <= most_results && pairs * wgs_for(1) <= (wgs_for(1) <= 16 ? 200 : 92)) wgs = wgs_for(1);
+    if (wgs_for(1) <= 48 && pairs * wgs_for(1) <= (wgs_for(1) <= 16 || d.H / d.S < 8 ? 200 : 92)) wgs = wgs_for(1);
     else if (pairs * wgs_for(2) <= 160) wgs = wgs_for(2);
     const long most = pairs >= 256 ? 1 : 256 / pairs;
     if (wgs > most) wgs = (int)most;

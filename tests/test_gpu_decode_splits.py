@@ -13,13 +13,15 @@ pytestmark = pytest.mark.gpu
 CASES = [
     ("bf16", inputs.MODE_MLA, 1, 37, 16, 1, 4, 20, 1),              # fewer tiles than wavefronts of one workgroup
     ("bf16", inputs.MODE_MLA, 1, 1024, 16, 1, 16, 1024, 16),        # one tile per wavefront, the merge's one-group form at its limit
-    ("f16", inputs.MODE_MLA, 2, 2200, 16, 1, 1, 100, 18),           # two tiles per wavefront, the last one ragged
+    ("f16", inputs.MODE_MLA, 2, 3100, 16, 1, 1, 100, 25),           # two tiles per wavefront, the last one ragged
+    ("f16", inputs.MODE_MLA, 2, 2200, 16, 1, 1, 100, 35),           # one, the last workgroup with tiles for three of its wavefronts
     ("bf16", inputs.MODE_MLA, 1, 16400, 16, 1, 2, 16, 65),          # one more than a wavefront has lanes: the merge for any number
     ("bf16", inputs.MODE_MLA, 20, 1500, 4, 1, 1, 30, 6),            # four tiles per wavefront
     ("bf16", inputs.MODE_MLA, 130, 300, 2, 1, 2, 30, 1),            # more than half as many sequences as CUs: one workgroup each
     ("bf16", inputs.MODE_MLA, 1, 512, 16, 1, 16, 512, 8),           # 8 and 9 partial results: on both sides of eight rows per thread
     ("f16", inputs.MODE_MLA, 1, 520, 7, 1, 16, 1024, 9),
-    ("bf16", inputs.MODE_MLA, 1, 2100, 16, 1, 16, 4096, 17),        # the first with four groups
+    ("bf16", inputs.MODE_MLA, 1, 2100, 16, 1, 16, 4096, 33),        # one more than 32
+    ("bf16", inputs.MODE_MLA, 3, 2060, 16, 1, 16, 4096, 17),        # the first with four groups, of two tiles per wavefront
     ("bf16", inputs.MODE_MLA, 1, 8300, 16, 1, 16, 9000, 65),
     ("bf16", inputs.MODE_GQA, 1, 6100, 28, 4, 1, 40, 48),
     ("f16", inputs.MODE_GQA, 3, 2900, 14, 2, 2, 33, 12),
@@ -34,6 +36,12 @@ CASES = [
     ("f16", inputs.MODE_MLA, 2, 2048, 16, 1, 16, 9000, 32),
     ("bf16", inputs.MODE_MLA, 4, 1460, 8, 1, 16, 9000, 23),
     ("bf16", inputs.MODE_MLA, 4, 1480, 16, 1, 16, 9000, 12),
+    ("f16", inputs.MODE_MLA, 1, 3072, 16, 1, 16, 9000, 48),         # the most results, of few workgroups and of few heads; one more workgroup, or one more head, than that
+    ("bf16", inputs.MODE_MLA, 1, 3073, 16, 1, 16, 9000, 25),
+    ("bf16", inputs.MODE_MLA, 4, 3072, 7, 1, 16, 9000, 48),
+    ("f16", inputs.MODE_MLA, 4, 1480, 7, 1, 16, 9000, 24),
+    ("bf16", inputs.MODE_MLA, 2, 2200, 14, 2, 16, 9000, 35),
+    ("f16", inputs.MODE_MLA, 4, 1480, 8, 1, 16, 9000, 12),
 ]
 
 
@@ -83,7 +91,7 @@ def test_gqa_output_is_the_sum_divided_once(dtype, ulp, k):
 
 # ..., tiles per wavefront: one and two (shared by the wavefronts of a workgroup), three and four in a workgroup that has the sequence to itself, four otherwise
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("B,L,H,g,w,steps", [(1, 30, 16, 4, 64, 1), (2, 150, 7, 4, 200, 3), (1, 250, 16, 4, 300, 4), (1, 600, 16, 4, 700, 1), (1, 2205, 5, 2, 90, 2), (20, 1500, 4, 1, 30, 4)])
+@pytest.mark.parametrize("B,L,H,g,w,steps", [(1, 30, 16, 4, 64, 1), (2, 150, 7, 4, 200, 3), (1, 250, 16, 4, 300, 4), (1, 600, 16, 4, 700, 1), (1, 2205, 5, 2, 90, 1), (1, 6300, 5, 2, 90, 2), (20, 1500, 4, 1, 30, 4)])
 @pytest.mark.parametrize("late", [0.0, 100.0])
 def test_mla_step_over_shared_tiles(oracle, dtype, B, L, H, g, w, steps, late):
     """Partial last tiles and steps, and (late) logits that rise past any fixed reference in the last third of the raw tail, so that a workgroup of two steps
@@ -112,8 +120,8 @@ def test_mla_step_over_shared_tiles(oracle, dtype, B, L, H, g, w, steps, late):
     assert hp.vec_rel_err(hp.from_dev(O, dtype), ref) <= hp.TOL[dtype]
 
 
-# B, L, H, g, w, steps of a workgroup: codes and tail in one workgroup, codes alone and then both in several, one step each, four unshared
-Q8_STEPS = [(1, 250, 16, 4, 100, 3), (2, 280, 7, 4, 230, 4), (1, 2205, 5, 2, 90, 2), (1, 600, 16, 2, 200, 1), (20, 1500, 4, 1, 30, 4)]
+# B, L, H, g, w, steps of a workgroup: codes and tail in one workgroup, codes alone and then both in several, one step each (twice), four unshared
+Q8_STEPS = [(1, 250, 16, 4, 100, 3), (2, 280, 7, 4, 230, 4), (1, 6300, 5, 2, 90, 2), (1, 600, 16, 2, 200, 1), (1, 2205, 5, 2, 90, 1), (20, 1500, 4, 1, 30, 4)]
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
