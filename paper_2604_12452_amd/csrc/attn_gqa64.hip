@@ -87,6 +87,8 @@ constexpr int FEW_REPS = 16;            // fp16: with fewer visible representati
 // (w = 1024, g = 16 where nothing else is said).  The sample's copy and its 16 MFMAs cost an item 0.6 us, so that items of the first SAMPLE_FROM tokens of a sequence
 // without representatives, which do not repeat, go without (L = 150 12.8 / 13.4 us, 700 23.0 / 23.7), and items of a short window, whose first tile is a good part of
 // it (w = 128, L = 377 14.8 / 15.2).
+// (The sample's and the repeat's code is told to be the rare one: in line, a short call fetched the instructions around it for nothing; 28 heads over 4 KV heads, L = 60
+// 9.2 / 9.0 us, 300 14.4 / 14.1, bf16 8.9 / 8.7, 14.0 / 13.7; three times L = 5003 252 / 248, bf16 243 / 239.)
 constexpr int NSAMPLE = 32;
 constexpr int SAMPLE_FROM = 1024, SAMPLE_SPAN = 256;
 constexpr int RSRC_WORD3 = 0x00020000;  // raw buffer of dwords, gfx9 layout
@@ -434,7 +436,7 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
         return k.flip && span >= SAMPLE_SPAN && (k.mt_blk_hi > 0 || k.t0 >= SAMPLE_FROM) ? span / NSAMPLE : 0;
     };
     auto issue_first_copies = [&](const Blk &k, bool with_sample) {
-        if (F16 && with_sample && sample_step(k) > 0) {
+        if (F16 && __builtin_expect(with_sample && sample_step(k) > 0, 0)) {
             const unsigned step = sample_step(k) * k.raw_stride, first = (unsigned)(k.mt_blk_hi * kp.g) * k.raw_stride + 4 * wave * step;
             const int4v rs = {(int)k.raw_k.lo, (int)k.raw_k.hi, (int)k.raw_k.bytes, RSRC_WORD3};
             const unsigned m0 = lds_address(sample) + 4 * wave * RB;
@@ -612,7 +614,7 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
             // ---- tile 0 has landed (tiles 1 and 2 may be on their way); S^T chain of half 0 ----
             asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * COPIES) : "memory");
             __syncthreads();
-            if (F16 && pass == 0 && sample_step(cur) > 0) {          // references from the sample (every row sees all of it)
+            if (F16 && __builtin_expect(pass == 0 && sample_step(cur) > 0, 0)) {          // references from the sample (every row sees all of it)
                 Addr ax = adr;
 #pragma unroll
                 for (int ks = 0; ks < NKS; ++ks) ax.k[ks] += lds_address(sample) - lds0;
@@ -694,7 +696,7 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_gqa64_kernel(const G64Params 
                 redo |= !(l_tot[rb] <= L_LIMIT) | (F16 && !(acc[rb][0][0] * 0.f == 0.f));
             }
             // every wavefront is done with the stages; repeat the item if a row sum ran out of range
-            if (!__syncthreads_or(pass == 0 && redo)) break;
+            if (__builtin_expect(!__syncthreads_or(pass == 0 && redo), 1)) break;
             // Where the row sums are finite they bound the maxima well enough: from the logarithm of its sum as reference (in fp16 15 binades below it) a row's exponentials
             // add up to 1 (2^15) and none can pass the type's limit, as long as the reference is not rounded by as much as the binade that is left (up to 2^20: by 2^-5).  Only a
             // sum that is not finite, or a larger reference, takes the exact maxima, a pass of its own whose tiles nothing
