@@ -208,7 +208,7 @@ template <typename T, int N> struct Rows {
     {
         constexpr int EPC = Elt<T>::EPC;
         auto finish = [&](float (&acc)[EPC], int c) {
-            lanes::over_strided(acc, shift, lanes::Sum());                     // (lanes without a row of the group add zeros)
+            if (g > 1) lanes::over_strided(acc, shift, lanes::Sum());          // (lanes without a row of the group add zeros)
             if (row0 == 0 && c < chunks) *reinterpret_cast<uintx4 *>(out + c * EPC) = pack4<T>(acc);
         };
         float f[EPC], acc[EPC];
