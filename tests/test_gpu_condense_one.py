@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 # dtype, mode, d_pool, d_sel, H, S, g, w, L, n_q, pool_reduce, sel_reduce, sequences of the batch
 CASES = [
     ("bf16", lca.MODE_GQA, 128, 128, 32, 8, 16, 64, 700, 16, 0, 0, 30), ("f16", lca.MODE_GQA, 128, 128, 28, 4, 32, 100, 1030, 32, 0, 0, 40),
-    ("bf16", lca.MODE_GQA, 128, 128, 12, 4, 1, 500, 633, 7, 0, 0, 20), ("f16", lca.MODE_GQA, 128, 128, 8, 8, 2, 0, 77, 2, 0, 0, 30),
+    ("bf16", lca.MODE_GQA, 128, 128, 12, 4, 1, 500, 633, 8, 0, 0, 20), ("f16", lca.MODE_GQA, 128, 128, 8, 8, 2, 0, 77, 24, 0, 0, 30),
     ("bf16", lca.MODE_GQA, 64, 64, 16, 4, 16, 128, 900, 16, 0, 0, 40), ("f16", lca.MODE_GQA, 64, 64, 8, 8, 7, 5, 500, 50, 0, 0, 20),
     ("bf16", lca.MODE_GQA, 96, 112, 6, 6, 24, 16, 300, 24, 0, 0, 90), ("f32", lca.MODE_GQA, 32, 16, 4, 4, 64, 10, 650, 64, 0, 0, 120),
     ("f32", lca.MODE_MLA, 128, 32, 4, 1, 16, 128, 1024, 16, 0, 0, 70), ("f32", lca.MODE_MLA, 128, 32, 8, 1, 16, 128, 400, 16, 0, 0, 200),
