@@ -60,7 +60,7 @@ def test_one_launch_agrees_with_two(dtype, mode, d_pool, d_sel, H, S, g, w, L, n
 # dtype, mode, d_pool, d_sel, H, S, n_q, sel_reduce, B: one launch twice (held rows fill the registers at g = 16, or not), rows held by the any-width kernel (queries
 # of more than 80 KB), rows that it reads again, the fixed-size kernel
 NAN_CASES = [
-    ("f16", lca.MODE_GQA, 128, 128, 8, 4, 4, 0, 1), ("f32", lca.MODE_MLA, 128, 32, 4, 1, 4, 0, 2), ("bf16", lca.MODE_GQA, 128, 128, 8, 4, 4, lca.REDUCE_MAXPOOL, 1),
+    ("f16", lca.MODE_GQA, 128, 128, 8, 4, 12, 0, 1), ("f32", lca.MODE_MLA, 128, 32, 4, 1, 6, 0, 2), ("bf16", lca.MODE_GQA, 128, 128, 8, 4, 4, lca.REDUCE_MAXPOOL, 1),
     ("bf16", lca.MODE_GQA, 64, 64, 64, 4, 50, 0, 1), ("f32", lca.MODE_GQA, 520, 32, 4, 2, 4, 0, 1), ("bf16", lca.MODE_GQA, 16, 1024, 4, 2, 4, lca.REDUCE_MAXPOOL, 1),
     ("bf16", lca.MODE_MLA, 512, 64, 2, 1, 4, 0, 1),
 ]
