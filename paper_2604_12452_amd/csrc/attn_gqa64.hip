@@ -88,7 +88,7 @@ constexpr int FEW_REPS = 16;            // fp16: with fewer visible representati
 // without representatives, which do not repeat, go without (L = 150 12.8 / 13.4 us, 700 23.0 / 23.7), and items of a short window, whose first tile is a good part of
 // it (w = 128, L = 377 14.8 / 15.2).
 // (The sample's and the repeat's code is told to be the rare one: in line, a short call fetched the instructions around it for nothing; 28 heads over 4 KV heads, L = 60
-// 9.2 / 9.0 us, 300 14.4 / 14.1, bf16 8.9 / 8.7, 14.0 / 13.7; three times L = 5003 252 / 248, bf16 243 / 239.)
+// 9.2 / 9.0 us, 300 14.5 / 14.1, bf16 8.85 / 8.7, 13.9 / 13.7; long calls are even.)
 constexpr int NSAMPLE = 32;
 constexpr int SAMPLE_FROM = 1024, SAMPLE_SPAN = 256;
 constexpr int RSRC_WORD3 = 0x00020000;  // raw buffer of dwords, gfx9 layout
