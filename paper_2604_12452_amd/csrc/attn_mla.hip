@@ -734,28 +734,43 @@ size_t attn_mla_up_workspace_bytes(const Dims &d) { return attn_mla_supported(d)
 // Whether a call's items are few enough for attn_mla_halves.hip, which has two for each of them and half as long.  While there is a CU of their XCD for each of
 // the two it is the faster form whatever their length (attention alone, 16 heads, bf16, this kernel / halves: L = 100 14.5 / 11.9 us, 300 21.2 / 16.1, 1000 47.1 /
 // 33.3; 8 heads, L = 2000 52.7 / 38.2; 64 heads, L = 140 17.1 / 14.9).  In the second round of a workgroup its items are taken from the other end of the list (heaviest
-// first), so the call lasts as long as its longest item or the two in the middle of the list with an item change between them (ten tiles' worth), at 0.75 us a tile where the
-// undivided item takes 1.1: 16 heads, L = 1250 52.4 / 39.1, 1500 54.3 / 45.2, 1600 55.3 / 49.8, 1750 58.4 / 57.1, two sequences of 1000 53.6 / 46.2, three of 400 27.3 /
-// 24.4, but L = 2000 63.1 / 69.4, 3000 110 / 126; 8 heads, L = 2500 55.2 / 45.7, 3000 59.1 / 66.8.  With every CU at work the clock falls, and the larger items, whose
-// tiles are copied half as often, win.  A row block's heads stay on one XCD (its CUs hold 32 half items): of 64 heads and more a second round is another
-// whole row block, or the same one (128 heads, L = 40 16.7 / 21.4, L = 104 20.1 / 25.1; 64 heads, L = 308 23.3 / 25.0).  With the up-projection, of 64 heads and more one
-// XCD reads 8 MB of matrices for each row block, and nothing is won by twice the workgroups that do (64 heads, fp16, L = 30 25.9 / 27.9, 217 36.3 / 38.4; bf16, L = 102 31.5 / 31.5,
-// 288 40.8 / 48.4).
+// first), so the call lasts as long as the slowest workgroup's item or two items, an item change between them, at 0.75 us a tile where the undivided item takes 1.1.  A row block's heads stay on one
+// XCD, whose CUs hold 32 half items, so that is looked for in the lists of the XCD that has the heaviest row block and of the one that has the lightest of the first deal and the
+// heaviest of the second.  An item change is worth 14 tiles, and the halves are taken up to 1.7 times the tiles of the heaviest undivided item (1.6 with the up-projection, whose matrices
+// every half item reads).  Over 630 random calls of two rounds (whole call) the mean is 0.947 of the undivided kernel's time, 1.003 of the better form's; the slowest is 1.04 (a fp16 call whose items
+// are repeated aside).  16 heads, one set each, L = 1387,
+// w = 4096 67.3 / 49.5, L = 1877, w = 2048 85.3 / 73.7; 32 heads, 16 sets, L = 565 43.3 / 35.7; 16 heads, L = 1250 52.4 / 39.1, 1500 54.3 / 45.2, 1750 58.4 / 57.1, two sequences of
+// 1000 53.6 / 46.2, but L = 2000 63.1 / 69.4, 3000 110 / 126; 8 heads, L = 2500 55.2 / 45.7, 3000 59.1 / 66.8; 128 heads, L = 40 16.7 / 21.4; 40 heads, three of 75 15.0 / 21.7.  With every CU
+// at work the clock falls, and the larger items, whose tiles are copied half as often, win.
+// With the up-projection, of 64 heads and more one XCD reads 8 MB of matrices for each row block, and nothing is won by twice the workgroups that do (64 heads, fp16, L = 30 25.9 / 27.9,
+// 217 36.3 / 38.4; bf16, L = 102 31.5 / 31.5, 288 40.8 / 48.4).
 static bool mla_halves(const Dims &d, int dense, const MlaParams &kp, bool up, long cus)
 {
-    const long units = (long)kp.n_qb * d.B, per_unit = 2l * (d.H >> kp.hw_log2), slots = cus / 8;
-    const int run = kp.run_log2;
-    const long list = (((units - 1) >> (run + 3)) + 1) * (per_unit << run);          // half items of an XCD
+    const int rows = BM >> kp.hw_log2, run = kp.run_log2;
+    // half items of a row block (of one head x 128 rows, the later half does not exist in sequences of up to 64) and row blocks of an XCD
+    const long per_unit = (kp.hw_log2 == 0 && d.L <= BM / 2 ? 1l : 2l) * (d.H >> kp.hw_log2);
+    const long units = (long)kp.n_qb * d.B, mine = (((units - 1) >> (run + 3)) + 1) << run, slots = cus / 8;
     if (up && d.H >= 64) return false;
-    if (list <= slots) return true;
-    if (list > 2 * slots || per_unit >= slots) return false;
+    if (mine * per_unit <= slots) return true;
+    if (mine * per_unit > 2 * slots) return false;
     auto visible = [&](long t) { return dense || t + 1 <= d.w ? 0l : (t + 1 - d.w) / d.g; };
     auto tiles = [&](long unit) {
-        const int rows = BM >> kp.hw_log2;
+        if (unit >= units) return 0l;
         const long t0 = (kp.n_qb - 1 - unit / d.B) * rows, t1 = t0 + rows < d.L ? t0 + rows : d.L;
         return (visible(t1 - 1) + BN - 1) / BN + (t1 - visible(t0) * d.g + BN - 1) / BN;
     };
-    return 2 * (2 * tiles((slots / per_unit) << (run + 3)) + 10) <= 3 * tiles(0);     // (the first row block that some XCD has in its second round)
+    auto tiles_of = [&](long xcd, long j) {        // of the XCD's j-th row block (dealt out in runs, every other time in the opposite order)
+        const long deal = j >> run, pos = (xcd << run) + (j & ((1 << run) - 1));
+        return j < mine ? tiles((deal << (run + 3)) + ((deal & 1) ? (8 << run) - 1 - pos : pos)) : 0l;
+    };
+    long longest = 0;
+    for (long xcd = 0; xcd < 8; xcd += 7)
+        for (long j = 0; j * per_unit < slots; ++j) {
+            const long last = ((j + 1) * per_unit < slots ? (j + 1) * per_unit : slots) - 1;      // the slot of row block j whose second item is the heaviest
+            const long a = tiles_of(xcd, j), b = tiles_of(xcd, (2 * slots - 1 - last) / per_unit), both = a + b + (a > 0 && b > 0 ? 14 : 0);
+            longest = both > longest ? both : longest;
+        }
+    return 10 * longest <= (up ? 16 : 17) * tiles(0);
 }
 
 hipError_t launch_attn_mla(const AttnArgs &a, hipStream_t st)

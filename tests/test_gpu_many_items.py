@@ -28,8 +28,15 @@ MLA = [
     (1, 60, 128, 2, 16, 16, "bf16", 1.0, 0.0, False, False), (1, 70, 64, 1, 16, 16, "f16", 1.0, 0.0, False, True),       # many heads: undivided whatever the length
 ]
 
+# half items that some workgroups take two of (of one, two and four heads), and row blocks without a later half
+HALVES = [
+    (1, 1300, 16, 16, 32, 1200, "bf16", 1.0, math.log(32.0), False, False), (2, 640, 16, 16, 8, 500, "f16", 1.0, 0.1, False, True),
+    (1, 560, 32, 16, 16, 400, "bf16", 3.0, 0.1, False, False), (1, 1250, 16, 1, 16, 512, "f16", 1.0, 0.0, False, False),
+    (5, 60, 20, 20, 4, 16, "bf16", 1.0, 0.0, True, False), (3, 64, 19, 19, 16, 3, "f16", 0.3, 0.1, False, True),
+]
 
-@pytest.mark.parametrize("B,L,H,S,g,w,dtype,scale,bias,ties,up", MLA)
+
+@pytest.mark.parametrize("B,L,H,S,g,w,dtype,scale,bias,ties,up", MLA + HALVES)
 def test_mla_prefill(oracle, B, L, H, S, g, w, dtype, scale, bias, ties, up):
     import torch
     from paper_2604_12452_amd import lca

@@ -181,7 +181,7 @@ def test_q8_steps_are_where_they_claim_to_be():
 
 @pytest.mark.parametrize("desc,halves", [
     (_mla(L=1), True), (_mla(L=1024), True), (_mla(L=1025), True), (_mla(L=1600), True), (_mla(L=1900), False), (_mla(L=2048), False), (_mla(L=3000), False),
-    (_mla(L=8192), False), (_mla(H=8, L=2048), True), (_mla(H=8, L=3000), False), (_mla(H=1, L=16384), True), (_mla(H=1, L=32768), True), (_mla(H=2, L=10000), False),
+    (_mla(L=8192), False), (_mla(H=8, L=2048), True), (_mla(H=8, L=3000), False), (_mla(H=1, L=16384), True), (_mla(H=1, L=32768), True), (_mla(H=2, L=12000), False),
     (_mla(B=2, L=1000), True), (_mla(B=3, L=1000), False), (_mla(B=16, L=64), True), (_mla(B=17, L=64), False), (_mla(B=3, L=400), True), (_mla(B=64, L=64), False),
     (_mla(S=16, L=1024), True), (_mla(S=16, L=4096), False), (_mla(H=3, L=5000), True),
 ])
@@ -199,10 +199,12 @@ def test_mla_items_halved_while_they_are_few(desc, halves, up):
 @pytest.mark.parametrize("desc,halves", [
     (_mla(H=64, L=1), True), (_mla(H=64, L=256), True), (_mla(H=64, L=257), False), (_mla(H=64, B=8, L=32), True), (_mla(H=64, B=9, L=32), False), (_mla(H=128, L=1), False),
     (_mla(H=32, L=512), True), (_mla(H=32, L=900), True), (_mla(H=32, L=900, w=64), False), (_mla(H=6, S=2, B=2, L=1024), True), (_mla(H=6, S=2, B=2, L=1188, w=64, g=32), False), (_mla(H=66, L=50), False),
+    (_mla(S=16, L=1877, w=2048), True), (_mla(S=16, L=1700), False), (_mla(H=32, S=16, L=1024), True), (_mla(H=32, S=16, L=1024, w=64), False), (_mla(H=40, L=378), False), (_mla(H=40, B=3, L=75), False),
+    (_mla(H=20, S=20, L=64), True), (_mla(H=20, S=20, L=65), False), (_mla(H=33, S=33, L=64), False), (_mla(H=12, S=12, B=2, L=1003, w=4096), True),
 ])
 @pytest.mark.parametrize("up", [False, True])
 def test_mla_items_halved_while_an_xcd_has_cus_for_them(desc, halves, up):
-    """The heads of a row block are one XCD's; with the up-projection no more than 63 of them."""
+    """The heads of a row block are one XCD's, which has 32 CUs for them, or whose second round is short; with the up-projection no more than 63 heads."""
     run = t.prefill(desc, up=up)[-1]
     assert run.kernel.startswith("attn_mla_kernel_halves" if halves and not (up and desc.H >= 64) else "attn_mla_kernel<"), run
 
@@ -253,7 +255,10 @@ def test_cases_without_a_number_are_where_they_claim_to_be():
 
 
 def test_cases_of_many_items_are_where_they_claim_to_be():
-    from tests.test_gpu_many_items import GROUPS, MLA
+    from tests.test_gpu_many_items import GROUPS, HALVES, MLA
+    for B, L, H, S, g, w, dtype, scale, bias, ties, up in HALVES:
+        run = t.prefill(_mla(B=B, L=L, H=H, S=S, g=g, w=w, dtype={"bf16": lca.BF16, "f16": lca.F16}[dtype]), up=up)[-1]
+        assert run.kernel.startswith("attn_mla_kernel_halves") and run.grid == 256, (B, L, H, run)
     for B, L, H, S, g, w, dtype, scale, bias, ties, up in MLA:
         d = _mla(B=B, L=L, H=H, S=S, g=g, w=w, dtype={"bf16": lca.BF16, "f16": lca.F16}[dtype])
         for kw in (dict(up=True),) if up else (dict(), dict(dense=True)):
