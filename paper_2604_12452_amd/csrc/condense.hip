@@ -467,19 +467,22 @@ hipError_t launch_summary_query(const Dims &d, const void *Q, int L, float *qbar
 // One to three sets of narrow rows have few workgroups of little work: two launches / one over 340 random calls of groups of 8 and more 1.097 to 1.26 by the group size (64 / 64,
 // one KV head, g = 32, L = 2574 7.4 / 5.7), but smaller groups, whose summary query is short too, are even (g = 2 1.025, g = 4 1.065) and some slower (96 / 80, g = 4, L = 194
 // 5.9 / 6.2; g = 2, L = 108 5.9 / 6.3): two launches.
-// condense_reg_kernel's own widths leave less to gain than the any-width kernel's, and with fewer than 24 queries per set (groups of up to four rows, mostly) the summary
-// query is short as well: 16 bits, 128 / 128, under 24 queries 1.037 times as long in one launch over 61 random calls (bf16, one KV head of four heads, g = 4, L = 88 5.0 / 5.8 us; from 28 on
-// 0.81 to 1.01 times, 13 calls); fp32 128 + 32, one set 1.02 over 15 (L = 202, g = 2, four heads 5.3 / 5.6), with more sets, which that kernel takes in turn, 0.60 to 1.00.
+// condense_reg_kernel's own widths leave less to gain than the any-width kernel's where groups are small and the summary query is short: 16 bits, 128 / 128, groups of up to four
+// rows and under 24 queries per set 1.04 times as long in one launch over 80 random calls (bf16, one KV head of four heads, g = 4, L = 88 5.0 / 5.8 us), from 28 queries on 0.90 to 1.01, g = 8 1.01 with 8 and 16
+// queries and 0.91 with 24, g = 16 0.89 with 16; fp32 128 + 32, one set 1.03 (L = 202, g = 2, four heads 5.3 / 5.6).  With three sets and more that kernel takes the sets of a group in turn, which takes
+// longer than a second workgroup on a CU: groups of one load, 264 workgroups, eight sets 12.8 / 7.2, four sets 0.80, two 1.04 (and 0.99 to 1.26 at the other widths).
 static bool condense_in_one(const Dims &d)
 {
     const int epc = 16 / d.elt, pool = d.d_pool / epc, sel = d.d_sel / epc, hps = d.H / d.S;
-    const bool widths = d.mode == LCA_MODE_MLA ? d.dtype == LCA_F32 && d.d_pool == 128 && d.d_sel == 32 && d.S == 1 : d.dtype != LCA_F32 && d.d_pool == 128 && d.d_sel == 128;
-    const bool reg = widths && d.g <= 32 && (d.g & (d.g - 1)) == 0 && d.pool_reduce == LCA_REDUCE_WEIGHTED && d.sel_reduce == LCA_REDUCE_MAXSEL;
+    // condense_reg_kernel would take the groups
+    const bool own = d.g <= 32 && (d.g & (d.g - 1)) == 0 && d.pool_reduce == LCA_REDUCE_WEIGHTED && d.sel_reduce == LCA_REDUCE_MAXSEL;
+    const bool gqa16 = own && d.mode == LCA_MODE_GQA && d.dtype != LCA_F32 && d.d_pool == 128 && d.d_sel == 128;
+    const bool mla32 = own && d.mode == LCA_MODE_MLA && d.dtype == LCA_F32 && d.d_pool == 128 && d.d_sel == 32;
     const int pool_loads = Rows<float, 1>::loads(pool, d.g), sel_loads = Rows<float, 1>::loads(sel, d.g);
-    const long wgs = (long)((d.m + ONE_WAVES - 1) / ONE_WAVES) * d.S * d.B, most = d.g <= 16 && pool <= 32 && pool_loads + sel_loads > 2 ? 384 : 256;
+    const long wgs = (long)((d.m + ONE_WAVES - 1) / ONE_WAVES) * d.S * d.B, most = d.g <= 16 && pool <= 32 && (pool_loads + sel_loads > 2 || (mla32 && d.S >= 3)) ? 384 : 256;
     return wgs <= most && (long)d.n_q * hps * d.d_qk * d.elt <= 80 << 10 && d.d_qk <= ONE_COLUMNS && pool <= WAVE && sel <= WAVE && pool_loads <= 32 &&
            sel_loads <= (pool_loads <= 8 ? 8 : 4) && (pool <= 32 || d.S >= 3) && (pool + sel >= 24 || (long)d.B * d.S >= 4 || d.g >= 8) &&
-           !(reg && d.n_q * hps < 24);
+           !((gqa16 || (mla32 && d.S == 1)) && d.g <= 4 && d.n_q * hps < 24);
 }
 
 hipError_t launch_condense(const CondenseArgs &a, hipStream_t st)

@@ -224,8 +224,9 @@ def test_mla_batches_are_where_they_claim_to_be():
     (_odd(d_pool=64, d_sel=64, S=2, g=8, mode=lca.MODE_GQA), True), (_odd(d_pool=64, d_sel=64, S=2, g=7, mode=lca.MODE_GQA), False), (_odd(d_pool=64, d_sel=64, S=4, g=7, mode=lca.MODE_GQA), True),
     (_gqa(H=8, S=1, g=4, w=0, L=8192), True), (_gqa(H=8, S=1, g=4, w=0, L=8196), False), (_gqa(H=8, S=1, g=5, w=0, L=10240), True),
     (_gqa(H=5, S=1, g=4, w=0, L=800), False), (_gqa(H=6, S=1, g=4, w=0, L=800), True), (_gqa(H=6, S=2, g=4, w=0, L=800, n_q=8), True), (_gqa(H=5, S=1, g=4, w=0, L=800, sel_reduce=1), True),
-    (_gqa(H=4, S=1, g=5, w=0, L=800), True), (_odd(d_pool=128, H=2, g=8, dtype=lca.F32), False), (_odd(d_pool=128, H=3, g=8, dtype=lca.F32), True),
-    (_odd(d_pool=128, H=4, S=2, g=8, dtype=lca.F32), True), (_odd(d_pool=128, H=2, g=8), True),
+    (_gqa(H=4, S=1, g=5, w=0, L=800), True), (_odd(d_pool=128, H=5, g=4, dtype=lca.F32), False), (_odd(d_pool=128, H=6, g=4, dtype=lca.F32), True), (_gqa(H=1, S=1, w=0, L=800), True), (_gqa(H=1, S=1, g=8, w=0, L=800), True),
+    (_odd(d_pool=128, H=4, S=2, g=4, dtype=lca.F32), True), (_odd(H=2, g=4), True), (_odd(d_pool=128, H=16, S=8, g=1, L=390, dtype=lca.F32), True),
+    (_odd(d_pool=128, H=16, S=8, g=1, L=513, dtype=lca.F32), False), (_odd(d_pool=128, H=4, S=2, g=1, L=1178, dtype=lca.F32), False),
     (_odd(d_pool=64, d_sel=64, S=2, B=2, mode=lca.MODE_GQA), True), (_odd(L=8192, g=64, d_pool=512, d_sel=64, S=4), False), (_odd(d_pool=1024, d_sel=8, S=8, mode=lca.MODE_GQA), False),
 ])
 def test_condensation_in_one_launch(desc, one):
