@@ -442,8 +442,8 @@ def main():
     ms_cond = time_kernel(rotating(lambda i: (lambda: lca.condense(d, run.Q, rot[i][0], rot[i][1], run.pool_rep, run.sel_rep, run.anchor,
                                                                     None, run.ws))), 21, 3, behind=f_attn)
     del rot
-    # the same call over a single group (without any group nothing is launched).  At 512 + 64 that is the fixed part of the call above: the same two launches.
-    # In the GQA configuration a call of few groups is one launch of another kernel, and the figure is that kernel's
+    # the same call over a single group (without any group nothing is launched).  At 512 + 64 with one or two sets that is the fixed part of the call above: the same
+    # two launches.  With more sets and in the GQA configuration a call of few groups is one launch of another kernel, and the figure is that kernel's
     d_one = hp.lca_desc(wl.with_(w=wl.L - wl.g))
     ws_one, (rep_one, srep_one, anchor_one, _) = lca.alloc_workspace(d_one), lca.alloc_condensed(d_one)
     ms_one = time_kernel(lambda: lca.condense(d_one, run.Q, run.POOL, run.SEL, rep_one, srep_one, anchor_one, None, ws_one), 21, 3, behind=f_attn)
