@@ -126,6 +126,17 @@ def test_decode_split_cases_are_where_they_claim_to_be():
         assert [k.kernel.split("<")[0] for k in run[1:]] == ([merge] if merge else [])
 
 
+@pytest.mark.parametrize("H,S", [(1, 1), (7, 1), (8, 1), (16, 1), (14, 2), (32, 4)])
+@pytest.mark.parametrize("B", [1, 2, 4, 11, 60])
+def test_decode_results_fit_in_the_workspace(H, S, B):
+    """One partial result per workgroup, for any length: around every change of the number of workgroups."""
+    for L in [*range(16, 5000, 61), 3072, 3073, 4096, 20000, 131072]:
+        d = _mla(B=B, L=L, H=H, S=S, w=1 << 20)
+        run = t.decode(d)
+        if len(run) > 1:
+            assert run[0].grid * (H // S) * (512 + 2) * 4 <= lca.workspace_size(d), (L, run)
+
+
 def test_tiled_attention_cases_cover_every_instantiation():
     from tests import test_gpu_attn_tile as cases
     (mark,) = [m for m in cases.test_every_instantiation_all_rows.pytestmark if m.name == "parametrize"]
